@@ -220,7 +220,35 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
     if (r.fp32_out && r.amax != nullptr) publish_absmax(m, r.amax);
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool VEC, int MODE>
+// 16 bytes at any address (global memory takes 16-byte accesses at byte alignment)
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t x, y, z, w;
+};
+__device__ inline uint4 load16(const int8_t* p) {
+    const Bytes16 b = *reinterpret_cast<const Bytes16*>(p);
+    return make_uint4(b.x, b.y, b.z, b.w);
+}
+
+// v with its first n bytes (1 <= n <= 15) set to zero
+__device__ inline uint4 clear_low_bytes(uint4 v, int n) {
+    uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int c = min(max(n - 4 * d, 0), 4);                  // bytes of this dword that go
+        w[d] = c == 4 ? 0u : w[d] >> (8 * c) << (8 * c);
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Products whose operands the direct-to-LDS kernels cannot take (rows that are not 16-byte aligned, or a contraction
+// that is no multiple of 16): tiles are staged through registers, two steps ahead of the multiplication, into two LDS
+// buffers.  A 16-byte piece is one load at whatever byte address its row starts (the ragged shapes pay in cache-line
+// crossings, not in instructions: with one byte per load the products of a 1379 x 768 x 1000 layer took 198 and 100 us,
+// now 13.1 and 8.6; the 96 products 197 x 64 x 197 of an attention block 22.2, now 6.5).  The last, partial piece of a row is read as the row's last 16 bytes on both operands - the
+// contraction index may be permuted as long as both sides agree - and A's copies of bytes an earlier piece already
+// brought are zeroed, so no load leaves the row.  Only contractions shorter than 16 are assembled byte by byte (WIDE =
+// false).
+template <int BM, int BN, int BK, int WM, int WN, bool WIDE, int MODE>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
     const int8_t* __restrict__ A, int64_t lda, const int8_t* __restrict__ B, int64_t ldb, void* __restrict__ Cv,
     int64_t ldc, int M, int N, int K, int k_per_split, const int32_t* __restrict__ eA, int bitsA,
@@ -265,41 +293,51 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
         const int id = tid + j * NT, row = id / CPR, c = id % CPR;
-        pa[j] = A + static_cast<int64_t>(min(m0 + row, M - 1)) * lda + c * 16;
+        pa[j] = A + static_cast<int64_t>(min(m0 + row, M - 1)) * lda;
         lds_a[j] = row * BK + ((c ^ swizzle_of_row<BK>(row)) * 16);
         kc_a[j] = c * 16;
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int id = tid + j * NT, row = id / CPR, c = id % CPR;
-        pb[j] = B + static_cast<int64_t>(min(n0 + row, N - 1)) * ldb + c * 16;
+        pb[j] = B + static_cast<int64_t>(min(n0 + row, N - 1)) * ldb;
         lds_b[j] = BM * BK + row * BK + ((c ^ swizzle_of_row<BK>(row)) * 16);
         kc_b[j] = c * 16;
     }
-    uint4 ra[NA], rb[NB];
+    uint4 ra[2][NA], rb[2][NB];
 
-    auto load_piece = [&](const int8_t* p, int k_first) -> uint4 {
-        // k_first: contraction index of the piece's first byte; bytes at or beyond ke read as 0
-        if (VEC) {
-            if (k_first < ke) return *reinterpret_cast<const uint4*>(p);
-            return make_uint4(0, 0, 0, 0);
+    // the piece of row p whose first contraction index is k, in a step that reaches the end of the slice
+    auto tail_piece = [&](const int8_t* p, int k, bool clear) -> uint4 {
+        if (WIDE) {
+            if (k >= ke) return make_uint4(0, 0, 0, 0);
+            const int from = min(k, ke - 16);
+            const uint4 v = load16(p + from);
+            return clear && from < k ? clear_low_bytes(v, k - from) : v;
         }
         uint32_t w[4] = {0, 0, 0, 0};
         for (int b = 0; b < 16; ++b)
-            if (k_first + b < ke) w[b >> 2] |= static_cast<uint32_t>(static_cast<uint8_t>(p[b])) << (8 * (b & 3));
+            if (k + b < ke) w[b >> 2] |= static_cast<uint32_t>(static_cast<uint8_t>(p[k + b])) << (8 * (b & 3));
         return make_uint4(w[0], w[1], w[2], w[3]);
     };
-    auto load_step = [&](int kk) {
+    auto load_step = [&](int it, uint4 (&va)[NA], uint4 (&vb)[NB]) {
+        const int kk = kb + it * BK;
+        if (WIDE && kk + BK <= ke) {                              // workgroup-uniform
 #pragma unroll
-        for (int j = 0; j < NA; ++j) ra[j] = load_piece(pa[j] + kk, kk + kc_a[j]);
+            for (int j = 0; j < NA; ++j) va[j] = load16(pa[j] + kk + kc_a[j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) rb[j] = load_piece(pb[j] + kk, kk + kc_b[j]);
+            for (int j = 0; j < NB; ++j) vb[j] = load16(pb[j] + kk + kc_b[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NA; ++j) va[j] = tail_piece(pa[j], kk + kc_a[j], true);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) vb[j] = tail_piece(pb[j], kk + kc_b[j], false);
+        }
     };
-    auto store_step = [&](int buf) {
+    auto store_step = [&](int buf, const uint4 (&va)[NA], const uint4 (&vb)[NB]) {
 #pragma unroll
-        for (int j = 0; j < NA; ++j) *reinterpret_cast<uint4*>(&lds[buf][lds_a[j]]) = ra[j];
+        for (int j = 0; j < NA; ++j) *reinterpret_cast<uint4*>(&lds[buf][lds_a[j]]) = va[j];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) *reinterpret_cast<uint4*>(&lds[buf][lds_b[j]]) = rb[j];
+        for (int j = 0; j < NB; ++j) *reinterpret_cast<uint4*>(&lds[buf][lds_b[j]]) = vb[j];
     };
 
     // ---- fragment addressing ---------------------------------------------------------
@@ -316,14 +354,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
-    if (nk > 0) {
-        load_step(kb);
-        store_step(0);
-    }
-    __syncthreads();
-    for (int it = 0; it < nk; ++it) {
-        const int buf = it & 1;
-        if (it + 1 < nk) load_step(kb + (it + 1) * BK);
+    // step it: request step it + 2 into the registers step it came from, multiply, park step it + 1 in the other buffer
+    auto step = [&](int it, auto buf_c) {
+        constexpr int buf = decltype(buf_c)::value;
+        if (it + 2 < nk) load_step(it + 2, ra[buf], rb[buf]);
 #pragma unroll
         for (int ks = 0; ks < BK / 32; ++ks) {
             const int piece = ((2 * ks + fhalf) ^ fswz) * 16;
@@ -338,8 +372,16 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
                 for (int j = 0; j < FN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
-        if (it + 1 < nk) store_step(buf ^ 1);
+        if (it + 1 < nk) store_step(buf ^ 1, ra[buf ^ 1], rb[buf ^ 1]);
         __syncthreads();
+    };
+    if (nk > 0) load_step(0, ra[0], rb[0]);
+    if (nk > 1) load_step(1, ra[1], rb[1]);
+    if (nk > 0) store_step(0, ra[0], rb[0]);
+    __syncthreads();
+    for (int it = 0; it < nk; it += 2) {
+        step(it, IC<0>{});
+        if (it + 1 < nk) step(it + 1, IC<1>{});
     }
 
     // ---- epilogue --------------------------------------------------------------------
@@ -859,7 +901,7 @@ int transpose_i8_launch(const int8_t* src, int64_t rows, int64_t cols, int64_t l
 
 template <int BM, int BN, int BK, int WM, int WN>
 static int launch_cfg(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, const int8_t* B, int64_t ldb,
-                      void* C, int64_t ldc, int mode, bool vec, int splits, const int32_t* eA, int bitsA,
+                      void* C, int64_t ldc, int mode, int splits, const int32_t* eA, int bitsA,
                       const int32_t* eB, int bitsB, hipStream_t s, int64_t split_stride = 0, int* slices = nullptr,
                       Batch bt = Batch(), uint32_t* amax = nullptr, ReduceRider* ride = nullptr) {
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
@@ -878,11 +920,11 @@ static int launch_cfg(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t 
     }
     const dim3 grid(static_cast<unsigned>(tiles_m) * tiles_n + rider.blocks, ny, bt.count), block(NT);
     const int group_m = 8;
-#define FXP_GEMM_LAUNCH(VEC, MODE)                                                                                 \
-    hipLaunchKernelGGL((k_gemm_nt<BM, BN, BK, WM, WN, VEC, MODE>), grid, block, 0, s, A, lda, B, ldb, C, ldc,       \
+#define FXP_GEMM_LAUNCH(WIDE, MODE)                                                                                \
+    hipLaunchKernelGGL((k_gemm_nt<BM, BN, BK, WM, WN, WIDE, MODE>), grid, block, 0, s, A, lda, B, ldb, C, ldc,       \
                        static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), k_per_split, eA, bitsA, eB,   \
                        bitsB, tiles_m, tiles_n, group_m, split_stride, bt.a, bt.b, bt.c, amax, rider)
-    if (vec) {
+    if (K >= 16) {
         if (mode == kStoreI32) FXP_GEMM_LAUNCH(true, kStoreI32);
         else if (mode == kStoreF32) FXP_GEMM_LAUNCH(true, kStoreF32);
         else FXP_GEMM_LAUNCH(true, kAtomicI32);
@@ -1028,6 +1070,13 @@ size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t K) {
     return p.splits > 1 ? round_up(static_cast<size_t>(p.splits) * slice_stride(M, N) * sizeof(int32_t), 256) : 0;
 }
 
+// Register-staged products with fewer than two 128 x 128 tiles per CU (count: slices or matrices) take 64 x 64 tiles:
+// they are bound by the latency of a step, and four times the workgroups hide it (1379 x 768 x 1000 has 66 large
+// tiles for 256 CUs, 264 small ones).
+static bool small_tiles(int64_t M, int64_t N, int64_t count) {
+    return ((M + 127) / 128) * ((N + 127) / 128) * count < 512;
+}
+
 // `batch` products of one shape in one launch (grid.z), never split along K.
 int gemm_nt_batched_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, int64_t strideA,
                            const int8_t* B, int64_t ldb, int64_t strideB, void* C, int64_t ldc, int64_t strideC,
@@ -1048,9 +1097,10 @@ int gemm_nt_batched_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int
 #define FXP_BATCHED_TAIL 1, eA, bitsA, eB, bitsB, s, 0, nullptr, bt
     if (!dma) {
         // narrow outputs (head width 64 of the attention context and of dQ, dK, dV) take a tile of their own width
-        if (N <= 64) return launch_cfg<128, 64, 64, 64, 32>(FXP_BATCHED_ARGS, vec, FXP_BATCHED_TAIL);
-        if (M <= 64) return launch_cfg<64, 128, 64, 32, 64>(FXP_BATCHED_ARGS, vec, FXP_BATCHED_TAIL);
-        return launch_cfg<128, 128, 64, 64, 64>(FXP_BATCHED_ARGS, vec, FXP_BATCHED_TAIL);
+        if (small_tiles(M, N, batch)) return launch_cfg<64, 64, 128, 32, 32>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
+        if (N <= 64) return launch_cfg<128, 64, 64, 64, 32>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
+        if (M <= 64) return launch_cfg<64, 128, 64, 32, 64>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
+        return launch_cfg<128, 128, 64, 64, 64>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
     }
     if (use256 && K % 128 == 0) return launch_ring<64, 128>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
     if (use256) return launch_dma<256, 256, 64, 64, 128, 4>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
@@ -1120,8 +1170,10 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         hipLaunchKernelGGL(k_zero_rows, hgrid, dim3(256), 0, s, static_cast<int32_t*>(C), ldc, hr, hc);
         if ((rc = launch_status())) return rc;
     }
-    if (!dma)
-        rc = launch_cfg<128, 128, 64, 64, 64>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, vec, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
+    if (!dma && small_tiles(M, N, splits))
+        rc = launch_cfg<64, 64, 128, 32, 32>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
+    else if (!dma)
+        rc = launch_cfg<128, 128, 64, 64, 64>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
     else if (use256 && splits == 1 && stream_out && K % 128 == 0 && (K <= 256 || 4.0 * M * N < 128.0 * 1024 * 1024))
         // 64 KiB of LDS per workgroup keeps two resident per CU: one stores its tile while the other multiplies
         // (ResNet dX 25088 x 1152 x 128: 22.5 us against 27.3 with the 128 x 256 tile and 24.4 with the ring kernel;
