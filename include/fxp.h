@@ -93,8 +93,8 @@ int fxp_scale(const float* x, size_t n, int32_t* e_max, void* ws, size_t ws_byte
  * of word (i mod 4) of Philox-4x32-10 with key = seed and counter =
  * (i / 4, stream_id), i = row * cols + col: the result does not depend on the
  * launch geometry or on which copies are requested.
- * Fast path: x, q, qT 16-byte aligned and cols a multiple of 4; anything else
- * takes a slower element-wise kernel with identical results. */
+ * Fastest with x, q, qT 16-byte aligned and cols a multiple of 4 (or with q alone, whatever the shape);
+ * other alignments and widths are tiled in the same way with unaligned accesses, results are identical. */
 int fxp_map(const float* x, int64_t rows, int64_t cols, const int32_t* e_max, int8_t* q, int8_t* qT, uint64_t seed,
             uint64_t stream_id, int rounding, int bits, void* stream);
 

@@ -14,6 +14,11 @@
 //     so both copies carry the same rounding decisions and both stores coalesce;
 //   * the final step of the scale reduction (max over <= 1024 block maxima) can be
 //     folded in, which saves a launch per tensor.
+// Rows that are not whole quads, and bases off the 16-byte grid, take the same tiles with unaligned accesses (ANY);
+// a tensor that is wanted row-major only is one flat run of quads (map_flat_body); the one-element-per-thread
+// kernel is left for what neither reaches.  (18912 x 197, both copies: 25.9 us one element per thread - a Philox call
+// and a scattered byte per element - 14.2 as tiles; 1.6 M x 3, row-major only, with a small weight: 24.1 in two
+// launches, 11.1 flat in one.)
 // The random word of element i is word (i mod 4) of Philox-4x32-10 with key = seed
 // and counter = (i / 4, stream_id): nothing depends on the launch geometry.
 #include <algorithm>
@@ -23,6 +28,21 @@
 namespace fxp {
 
 constexpr int kMapThreads = 256;
+
+// 16 bytes at 4-byte alignment, 16 and 4 bytes at any alignment
+struct __attribute__((packed, aligned(4))) Quad {
+    uint32_t x, y, z, w;
+};
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t x, y, z, w;
+};
+struct __attribute__((packed, aligned(1))) Bytes4 {
+    uint32_t x;
+};
+__device__ inline uint4 load_quad(const uint32_t* p) {
+    const Quad v = *reinterpret_cast<const Quad*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
 
 struct MapCfg {
     int e_max;
@@ -78,6 +98,34 @@ __device__ inline uint32_t pack4(uint32_t q0, uint32_t q1, uint32_t q2, uint32_t
 }
 
 
+// the four mapped bytes of a quad: fast form (q_or and bad as above) and complete form
+template <bool STOCH>
+__device__ inline uint32_t map_quad_fast(const uint4 v, const uint4 w, const MapCfg& c, uint32_t& q_or, uint64_t& bad) {
+    const uint32_t m0 = magnitude_fast<STOCH>(v.x, w.x, c, bad), m1 = magnitude_fast<STOCH>(v.y, w.y, c, bad);
+    const uint32_t m2 = magnitude_fast<STOCH>(v.z, w.z, c, bad), m3 = magnitude_fast<STOCH>(v.w, w.w, c, bad);
+    q_or |= m0 | m1 | m2 | m3;
+    return pack4(m0, m1, m2, m3, v);
+}
+
+template <bool STOCH>
+__device__ inline uint32_t map_quad_full(const uint4 v, const uint4 w, const MapCfg& c) {
+    return pack4(magnitude_full<STOCH>(v.x, w.x, c), magnitude_full<STOCH>(v.y, w.y, c), magnitude_full<STOCH>(v.z, w.z, c),
+                 magnitude_full<STOCH>(v.w, w.w, c), v);
+}
+
+template <int V>
+using IC = std::integral_constant<int, V>;
+
+// the value of the next lane (of lane l + 1 in lane l), and of the lane N to the left within a row of 16 lanes
+__device__ inline uint32_t from_right(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x130, 0xf, 0xf, false));    // wave_shl:1
+}
+template <int N>
+__device__ inline uint32_t from_left(uint32_t v) {
+    if (N == 0) return v;
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x110 + N, 0xf, 0xf, false));  // row_shr:N
+}
+
 __device__ inline MapCfg make_cfg(int e_max, int bits) {
     MapCfg c;
     c.e_max = e_max;
@@ -105,6 +153,7 @@ struct MapJob {
     int8_t* qT;
     uint32_t sid0, sid1;
     int tiles_c;
+    int flat;               // row-major copy only: rows and columns do not matter (map_flat_body)
     unsigned blocks;
     unsigned xcd_blocks;    // leading workgroups whose tiles are numbered per XCD (see tile_of_workgroup)
     // scale taken as a guess (see k_map_tile_guess): where the guess comes from, where the workgroup maxima of
@@ -158,7 +207,8 @@ __device__ inline int resolve_scale(const int32_t* e_in, const uint32_t* partial
 // GUESS: the scale is not resolved from block maxima but given (e_given; do_map = false: there is none, only the
 // maximum is wanted), and the largest magnitude bits of the tile are accumulated into tile_max (clamped loads
 // of an edge tile repeat elements of the tensor, which a maximum does not mind).
-template <bool STOCH, bool EDGE, int PASSES, int TC, bool GUESS = false>
+// ANY: columns not a multiple of 4, or pointers off the 16-byte grid.
+template <bool STOCH, bool EDGE, int PASSES, int TC, bool GUESS = false, bool ANY = false>
 __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t rows, int64_t cols, const MapJob& J, int bits,
                                      bool publish, uint32_t* red, int8_t* __restrict__ q, int8_t* __restrict__ qT,
                                      uint32_t key0, uint32_t key1, uint32_t sid0, uint32_t sid1, int64_t r0, int64_t c0,
@@ -178,6 +228,7 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     const int rows_here = EDGE ? static_cast<int>(min<int64_t>(TR, rows - r0)) : TR;
     const int cols_here = EDGE ? static_cast<int>(min<int64_t>(TC, cols - c0)) : TC;
     const bool col_ok = !EDGE || 4 * cg < cols_here;
+    const bool quads = (ucols & 3u) == 0;         // whole quads per row (always, unless ANY)
     const uint32_t col_ld = EDGE ? static_cast<uint32_t>(min(4 * cg, cols_here - 4)) : 4 * cg;
 
     // PASSES passes of 4 * RGP rows.  The loads of pass p+1 are issued before the arithmetic of pass
@@ -187,7 +238,16 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int rr = EDGE ? min(lrow + k, rows_here - 1) : lrow + k;
-            v[k] = *reinterpret_cast<const uint4*>(xt + static_cast<uint32_t>(rr) * ucols + col_ld);
+            const uint32_t* row = xt + static_cast<uint32_t>(rr) * ucols;
+            if (ANY && EDGE) {
+                const int last = cols_here - 1;
+                v[k] = make_uint4(row[min(4 * cg, last)], row[min(4 * cg + 1, last)], row[min(4 * cg + 2, last)],
+                                  row[min(4 * cg + 3, last)]);
+            } else if (ANY) {
+                v[k] = load_quad(row + col_ld);
+            } else {
+                v[k] = *reinterpret_cast<const uint4*>(row + col_ld);
+            }
         }
     };
     uint4 cur[4], nxt[4];
@@ -211,39 +271,71 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
                 continue;
             }
         }
-        auto words_of = [&](int k) {
+        auto block_at = [&](uint64_t blk) {
+            return philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), sid0, sid1, key0, key1);
+        };
+        // ANY, rows that are not whole quads: a thread's four elements straddle two blocks of random words.  The
+        // second one is the first one of the lane to the right, except for the last column group of the tile, whose
+        // second blocks (one per row) are worked out by the last four lanes, one each: five blocks per 16 elements.
+        uint4 beyond = make_uint4(0, 0, 0, 0);
+        if (ANY && STOCH && !quads) {
+            const uint64_t i = static_cast<uint64_t>(origin) + static_cast<uint32_t>(lrow + (cg & 3)) * ucols + TC;
+            beyond = block_at(i >> 2);
+        }
+        auto words_of = [&](auto k_c) {
+            constexpr int k = decltype(k_c)::value;
             const uint32_t off = static_cast<uint32_t>(lrow + k) * ucols + 4 * cg;   // element offset in the tile
-            const uint64_t blk = blk0 + (off >> 2);
-            return STOCH ? philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), sid0, sid1, key0, key1)
-                         : make_uint4(0, 0, 0, 0);
+            if (!STOCH) return make_uint4(0, 0, 0, 0);
+            if (!ANY || quads) return block_at(blk0 + (off >> 2));
+            const uint64_t i = static_cast<uint64_t>(origin) + off;
+            const uint4 w = block_at(i >> 2);
+            // (moved in every lane before one is chosen: a lane must be active to be read)
+            const uint32_t rx = from_right(w.x), ry = from_right(w.y), rz = from_right(w.z);
+            const uint32_t bx = from_left<3 - k>(beyond.x), by = from_left<3 - k>(beyond.y), bz = from_left<3 - k>(beyond.z);
+            const bool last = cg == CG - 1;
+            const uint32_t n0 = last ? bx : rx, n1 = last ? by : ry, n2 = last ? bz : rz;
+            const bool odd = i & 1u, two = i & 2u;                   // words i % 4 .. i % 4 + 3 of the eight
+            const uint32_t a0 = odd ? w.y : w.x, a1 = odd ? w.z : w.y, a2 = odd ? w.w : w.z, a3 = odd ? n0 : w.w;
+            const uint32_t a4 = odd ? n1 : n0, a5 = odd ? n2 : n1;
+            return make_uint4(two ? a2 : a0, two ? a3 : a1, two ? a4 : a2, two ? a5 : a3);
         };
         uint32_t o[4];
         uint32_t q_or = 0;
         uint64_t bad = 0;                          // wave-uniform: any lane with an uncovered element
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint4 w = words_of(k);
-            const uint32_t m0 = magnitude_fast<STOCH>(cur[k].x, w.x, cfg, bad);
-            const uint32_t m1 = magnitude_fast<STOCH>(cur[k].y, w.y, cfg, bad);
-            const uint32_t m2 = magnitude_fast<STOCH>(cur[k].z, w.z, cfg, bad);
-            const uint32_t m3 = magnitude_fast<STOCH>(cur[k].w, w.w, cfg, bad);
-            q_or |= m0 | m1 | m2 | m3;
-            o[k] = pack4(m0, m1, m2, m3, cur[k]);
-        }
-        if (!scale_ok || bad != 0 || (q_or & over_bits)) {
+        auto fast_row = [&](auto k_c) {
+            constexpr int k = decltype(k_c)::value;
+            o[k] = map_quad_fast<STOCH>(cur[k], words_of(k_c), cfg, q_or, bad);
+        };
+        fast_row(IC<0>{});
+        fast_row(IC<1>{});
+        fast_row(IC<2>{});
+        fast_row(IC<3>{});
+        bool redo = !scale_ok || bad != 0 || (q_or & over_bits);
+        if (ANY) redo = __builtin_amdgcn_ballot_w64(redo) != 0;      // words come from other lanes: all of the wave or none
+        if (redo) {
             // rare: an element above the scale, a saturating result, a non-finite input or a tiny
             // scale somewhere in this 4 x 4 block: redo it with the complete per-element path
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint4 w = words_of(k);
-                o[k] = pack4(magnitude_full<STOCH>(cur[k].x, w.x, cfg), magnitude_full<STOCH>(cur[k].y, w.y, cfg),
-                             magnitude_full<STOCH>(cur[k].z, w.z, cfg), magnitude_full<STOCH>(cur[k].w, w.w, cfg), cur[k]);
-            }
+            auto full_row = [&](auto k_c) {
+                constexpr int k = decltype(k_c)::value;
+                o[k] = map_quad_full<STOCH>(cur[k], words_of(k_c), cfg);
+            };
+            full_row(IC<0>{});
+            full_row(IC<1>{});
+            full_row(IC<2>{});
+            full_row(IC<3>{});
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (qt != nullptr && col_ok && (!EDGE || lrow + k < rows_here))
-                *reinterpret_cast<uint32_t*>(qt + static_cast<uint32_t>(lrow + k) * ucols + 4 * cg) = o[k];
+            if (qt != nullptr && col_ok && (!EDGE || lrow + k < rows_here)) {
+                int8_t* dst = qt + static_cast<uint32_t>(lrow + k) * ucols + 4 * cg;
+                if (ANY && EDGE && 4 * cg + 4 > cols_here) {
+                    for (int j = 0; 4 * cg + j < cols_here; ++j) dst[j] = static_cast<int8_t>(o[k] >> (8 * j));
+                } else if (ANY) {
+                    reinterpret_cast<Bytes4*>(dst)->x = o[k];
+                } else {
+                    *reinterpret_cast<uint32_t*>(dst) = o[k];
+                }
+            }
         if (qT != nullptr) {
             uint32_t t[4];                          // t[c] = column c of the block, rows in ascending byte order
             transpose4x4(o, t);
@@ -258,30 +350,83 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     __syncthreads();
     int8_t* qTt = qT + c0 * rows + r0;             // element [c0][r0] of the transposed copy
     const uint32_t urows = static_cast<uint32_t>(rows);
-    if ((rows & 15) == 0) {
-        // 16 rows of one column = 16 contiguous bytes of qT
-        constexpr int PIECES = TR / 16;                     // per column
+    // 16 rows of one column = 16 contiguous bytes of qT, at any alignment when the rows are not whole 16-byte pieces
+    constexpr int PIECES = TR / 16;                     // per column
 #pragma unroll
-        for (int it = 0; it < (TC * PIECES + kMapThreads - 1) / kMapThreads; ++it) {
-            const int id = it * kMapThreads + tid;
-            const int c = id / PIECES, ch = id % PIECES;
-            if (c < TC && (!EDGE || (c < cols_here && 16 * ch < rows_here))) {
-                const uint32_t* src = stage + c * TS + 4 * ch;
-                *reinterpret_cast<uint4*>(qTt + static_cast<uint64_t>(c) * urows + 16 * ch) =
-                    make_uint4(src[0], src[1], src[2], src[3]);
+    for (int it = 0; it < (TC * PIECES + kMapThreads - 1) / kMapThreads; ++it) {
+        const int id = it * kMapThreads + tid;
+        const int c = id / PIECES, ch = id % PIECES;
+        if (c < TC && (!EDGE || (c < cols_here && 16 * ch < rows_here))) {
+            const uint32_t* src = stage + c * TS + 4 * ch;
+            int8_t* dst = qTt + static_cast<uint64_t>(c) * urows + 16 * ch;
+            if (!EDGE || 16 * ch + 16 <= rows_here) {
+                *reinterpret_cast<Bytes16*>(dst) = Bytes16{src[0], src[1], src[2], src[3]};
+            } else {
+                for (int r = 0; 16 * ch + r < rows_here; ++r) dst[r] = static_cast<int8_t>(src[r >> 2] >> (8 * (r & 3)));
             }
-        }
-    } else {
-        const uint8_t* bytes = reinterpret_cast<const uint8_t*>(stage);
-        for (int id = tid; id < TC * TR; id += kMapThreads) {
-            const int c = id / TR, r = id % TR;
-            if (c < cols_here && r < rows_here)
-                qTt[static_cast<uint64_t>(c) * urows + r] = static_cast<int8_t>(bytes[c * TS * 4 + r]);
         }
     }
 }
 
-template <bool STOCH, int PASSES, int TC>
+// A tensor wanted row-major only: quads of consecutive elements, 1024 * PASSES per workgroup from quad `first` on,
+// whatever its rows are and wherever x and q start.  The last quad may be short.
+template <bool STOCH, int PASSES>
+__device__ inline void map_flat_body(const MapJob& J, int bits, bool publish, uint32_t* red, uint32_t key0, uint32_t key1,
+                                     uint64_t first) {
+    const uint64_t n = static_cast<uint64_t>(J.rows) * static_cast<uint64_t>(J.cols);
+    const uint32_t quads = static_cast<uint32_t>(min<uint64_t>((n >> 2) - first, 4 * kMapThreads * PASSES));   // whole ones here
+    const uint32_t tail = static_cast<uint32_t>(n & 3u);         // elements of the short quad behind them, if it is this workgroup's
+    const uint32_t* __restrict__ x = J.x + 4 * first;
+    int8_t* __restrict__ q = J.q + 4 * first;
+    auto load_pass = [&](uint32_t i0, uint4 (&v)[4]) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t i = i0 + k * kMapThreads;
+            v[k] = make_uint4(0, 0, 0, 0);
+            if (i < quads) {
+                v[k] = load_quad(x + 4 * i);
+            } else if (i == quads && i < 4 * kMapThreads * PASSES) {
+                if (tail > 0) v[k].x = x[4 * i];
+                if (tail > 1) v[k].y = x[4 * i + 1];
+                if (tail > 2) v[k].z = x[4 * i + 2];
+            }
+        }
+    };
+    uint4 cur[4], nxt[4];
+    load_pass(threadIdx.x, cur);
+    const MapCfg cfg = make_cfg(resolve_scale(J.e_in, J.partials, J.n_partials, J.e_out, red, publish), bits);
+    const bool scale_ok = cfg.e_max >= 25 && cfg.e_max < 255;
+#pragma unroll 1
+    for (uint32_t i0 = threadIdx.x; i0 < 4 * kMapThreads * PASSES; i0 += 4 * kMapThreads) {
+        load_pass(i0 + 4 * kMapThreads, nxt);                     // (past the last pass: nothing is loaded)
+        uint32_t o[4], q_or = 0;
+        uint64_t bad = 0;
+        auto words_of = [&](uint32_t k) {
+            const uint64_t blk = first + (i0 + k * kMapThreads);
+            return STOCH ? philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), J.sid0, J.sid1, key0, key1)
+                         : make_uint4(0, 0, 0, 0);
+        };
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) o[k] = map_quad_fast<STOCH>(cur[k], words_of(k), cfg, q_or, bad);
+        if (!scale_ok || bad != 0 || (q_or & ~cfg.sat)) {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) o[k] = map_quad_full<STOCH>(cur[k], words_of(k), cfg);
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t i = i0 + k * kMapThreads;
+            if (i < quads) {
+                reinterpret_cast<Bytes4*>(q + 4 * i)->x = o[k];
+            } else if (i == quads) {
+                for (uint32_t j = 0; j < tail; ++j) q[4 * i + j] = static_cast<int8_t>(o[k] >> (8 * j));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) cur[k] = nxt[k];
+    }
+}
+
+template <bool STOCH, int PASSES, int TC, bool ANY>
 __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, uint32_t key0, uint32_t key1, int bits) {
     constexpr int RGP = kMapThreads / (TC / 4);
     constexpr int TR = 4 * RGP * PASSES;
@@ -296,6 +441,10 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
         const int e = resolve_scale(nullptr, J.partials, J.n_partials, J.e_out, red, bid == 0);
         if (J.guess_used[0] == e) return;
     }
+    if (J.flat) {
+        map_flat_body<STOCH, PASSES>(J, bits, bid == 0, red, key0, key1, static_cast<uint64_t>(bid) * (4 * kMapThreads * PASSES));
+        return;
+    }
     const uint32_t* __restrict__ x = J.x;
     int8_t* __restrict__ q = J.q;
     int8_t* __restrict__ qT = J.qT;
@@ -305,9 +454,9 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
     const int64_t r0 = static_cast<int64_t>(rb) * TR;
     const int64_t c0 = static_cast<int64_t>(cb) * TC;
     if (r0 + TR <= rows && c0 + TC <= cols)
-        map_tile_body<STOCH, false, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
+        map_tile_body<STOCH, false, PASSES, TC, false, ANY>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
     else
-        map_tile_body<STOCH, true, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
+        map_tile_body<STOCH, true, PASSES, TC, false, ANY>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
 }
 
 // Scale and map in ONE pass over the tensor, for a caller that has a guess of the scale (the tensor's scale of
@@ -394,25 +543,36 @@ struct MapPlan {
     int tc;          // tile columns
     int passes;      // 4, 2 or 1
     bool tile_path;  // false: the one-element-per-thread kernel
+    bool any;        // rows that are not whole quads, or pointers off the 16-byte grid
+    bool flat;       // no transposed copy: one run of quads
 };
+
+constexpr int64_t kFlatTileElements = 4096;     // of one pass
 
 static MapPlan plan_map(const MapTensor& t) {
     MapPlan p;
     // tile width: 64 when that pads the rows less than 128 does (cols = 64, 192, ...)
     p.tc = ((t.cols + 63) / 64) * 64 < ((t.cols + 127) / 128) * 128 ? 64 : 128;
+    p.flat = t.qT == nullptr;
     const int64_t tall = p.tc == 128 ? 128 : 256;   // rows of a 4-pass tile
     const int64_t tiles_c = (t.cols + p.tc - 1) / p.tc;
     // four passes per tile when that still gives a thousand workgroups (four per CU), else two, else single-pass
     // tiles (a sweep of the threshold from 512 to 8192 moved whole-step times by under 3 %)
-    auto count = [&](int64_t tile_rows) { return ((t.rows + tile_rows - 1) / tile_rows) * tiles_c; };
-    p.passes = count(tall) >= 1024 ? 4 : (count(tall / 2) >= 1024 ? 2 : 1);
-    p.tile_path = (t.cols % 4 == 0) && aligned(t.x, 16) && (!t.q || aligned(t.q, 16)) && (!t.qT || aligned(t.qT, 16)) &&
-                  t.rows > 0 && count(tall / 4) < (int64_t{1} << 30) && t.cols < (int64_t{1} << 22) &&   // 32-bit offsets inside a tile
-                  t.rows < (int64_t{1} << 32);                        // and a 32-bit row count in the transposed copy's addressing
+    auto count = [&](int64_t passes) {
+        if (p.flat) return (t.rows * t.cols + kFlatTileElements * passes - 1) / (kFlatTileElements * passes);
+        return (t.rows + tall / 4 * passes - 1) / (tall / 4 * passes) * tiles_c;
+    };
+    p.passes = count(4) >= 1024 ? 4 : (count(2) >= 1024 ? 2 : 1);
+    p.any = t.cols % 4 != 0 || !aligned(t.x, 16) || !aligned(t.q, 16) || !aligned(t.qT, 16);
+    p.tile_path = t.rows > 0 && t.cols > 0 && count(1) < (int64_t{1} << 30) &&
+                  (p.flat || (t.cols < (int64_t{1} << 22) &&          // 32-bit offsets inside a tile
+                              t.rows < (int64_t{1} << 32) &&          // and a 32-bit row count in the transposed copy's addressing
+                              // of a row shorter than a quarter of a tile most lanes would map nothing
+                              (!p.any || t.cols >= 16)));
     return p;
 }
 
-static MapJob make_job(const MapTensor& t, int tc, int passes) {
+static MapJob make_job(const MapTensor& t, int tc, int passes, bool flat) {
     MapJob j;
     const int64_t tr = (tc == 128 ? 128 : 256) / 4 * passes;
     j.x = reinterpret_cast<const uint32_t*>(t.x);
@@ -426,8 +586,10 @@ static MapJob make_job(const MapTensor& t, int tc, int passes) {
     j.qT = t.qT;
     j.sid0 = static_cast<uint32_t>(t.stream_id);
     j.sid1 = static_cast<uint32_t>(t.stream_id >> 32);
-    j.tiles_c = static_cast<int>((t.cols + tc - 1) / tc);
-    j.blocks = static_cast<unsigned>(((t.rows + tr - 1) / tr) * j.tiles_c);
+    j.flat = flat ? 1 : 0;
+    j.tiles_c = flat ? 1 : static_cast<int>((t.cols + tc - 1) / tc);
+    j.blocks = static_cast<unsigned>(flat ? (t.rows * t.cols + kFlatTileElements * passes - 1) / (kFlatTileElements * passes)
+                                          : ((t.rows + tr - 1) / tr) * j.tiles_c);
     const bool shared_lines = j.tiles_c > 1 && t.cols % 128 != 0;
     j.xcd_blocks = shared_lines ? static_cast<unsigned>((t.rows + tr - 1) / tr / 8 * 8 * j.tiles_c) : 0u;
     j.e_guess = nullptr;
@@ -436,11 +598,14 @@ static MapJob make_job(const MapTensor& t, int tc, int passes) {
     return j;
 }
 
-static void launch_tiles(const MapJobs& jobs, int tc, int passes, bool stoch, uint32_t k0, uint32_t k1, int bits,
+static void launch_tiles(const MapJobs& jobs, int tc, int passes, bool any, bool stoch, uint32_t k0, uint32_t k1, int bits,
                          hipStream_t s) {
     const dim3 grid(jobs.j[0].blocks + jobs.j[1].blocks), block(kMapThreads);
-#define FXP_MAP_LAUNCH(STOCH, PASSES, TC) \
-    hipLaunchKernelGGL((k_map_tile<STOCH, PASSES, TC>), grid, block, 0, s, jobs, k0, k1, bits)
+#define FXP_MAP_LAUNCH(STOCH, PASSES, TC)                                                                          \
+    do {                                                                                                           \
+        if (any) hipLaunchKernelGGL((k_map_tile<STOCH, PASSES, TC, true>), grid, block, 0, s, jobs, k0, k1, bits);  \
+        else hipLaunchKernelGGL((k_map_tile<STOCH, PASSES, TC, false>), grid, block, 0, s, jobs, k0, k1, bits);     \
+    } while (0)
 #define FXP_MAP_PICK(TC)                                   \
     if (stoch) {                                           \
         if (passes == 4) FXP_MAP_LAUNCH(true, 4, TC);      \
@@ -489,12 +654,12 @@ int scale_map_guess_launch(const MapTensor& a, const MapTensor* b, uint32_t* are
     const int64_t na = a.rows * a.cols, nb = b ? b->rows * b->cols : 0;
     // below a few million elements a scale reduction costs what the verifying launch costs
     if (std::max(na, nb) < kGuessMinElements) return kNoGuessPath;
-    if (!pa.tile_path || !pb.tile_path) return kNoGuessPath;
+    if (!pa.tile_path || !pb.tile_path || pa.any || pb.any) return kNoGuessPath;
     if (pa.tc != pb.tc) return kGuessOneByOne;        // different tile widths: no common launch, but each may guess alone
     const int passes = na >= nb ? pa.passes : pb.passes;
     MapJobs jobs;
-    jobs.j[0] = make_job(a, pa.tc, passes);
-    if (b) jobs.j[1] = make_job(*b, pa.tc, passes);
+    jobs.j[0] = make_job(a, pa.tc, passes, false);
+    if (b) jobs.j[1] = make_job(*b, pa.tc, passes, false);
     else { jobs.j[1] = jobs.j[0]; jobs.j[1].blocks = 0; }
     const uint64_t total = static_cast<uint64_t>(jobs.j[0].blocks) + jobs.j[1].blocks;
     if (total >= (uint64_t{1} << 31)) return kNoGuessPath;
@@ -520,7 +685,7 @@ int scale_map_guess_launch(const MapTensor& a, const MapTensor* b, uint32_t* are
         jobs.j[j].partials = areas[j];
         jobs.j[j].n_partials = static_cast<int>(grid);
     }
-    launch_tiles(jobs, pa.tc, passes, stoch, k0, k1, bits, s);
+    launch_tiles(jobs, pa.tc, passes, false, stoch, k0, k1, bits, s);
     return launch_status();
 }
 
@@ -530,10 +695,10 @@ int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStr
     const MapPlan p = plan_map(t);
     if (p.tile_path) {
         MapJobs jobs;
-        jobs.j[0] = make_job(t, p.tc, p.passes);
+        jobs.j[0] = make_job(t, p.tc, p.passes, p.flat);
         jobs.j[1] = jobs.j[0];
         jobs.j[1].blocks = 0;
-        launch_tiles(jobs, p.tc, p.passes, stoch, k0, k1, bits, s);
+        launch_tiles(jobs, p.tc, p.passes, p.any && !p.flat, stoch, k0, k1, bits, s);
     } else {
         const uint32_t s0 = static_cast<uint32_t>(t.stream_id), s1 = static_cast<uint32_t>(t.stream_id >> 32);
         const uint32_t* xb = reinterpret_cast<const uint32_t*>(t.x);
@@ -550,23 +715,25 @@ int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStr
     return launch_status();
 }
 
-// Two tensors in one launch when both take the tiled kernel with the same tile width; the tile height is the
+// Two tensors in one launch when both take the tiled kernel with the same tile width, or one of them is flat; the tile height is the
 // one the larger tensor would pick.  Otherwise one launch each.
 int map_launch2(const MapTensor& a, const MapTensor& b, uint64_t seed, int rounding, int bits, hipStream_t s) {
     const MapPlan pa = plan_map(a), pb = plan_map(b);
-    if (!pa.tile_path || !pb.tile_path || pa.tc != pb.tc) {
+    if (!pa.tile_path || !pb.tile_path || (pa.tc != pb.tc && !pa.flat && !pb.flat)) {
         const int rc = map_launch(a, seed, rounding, bits, s);
         return rc ? rc : map_launch(b, seed, rounding, bits, s);
     }
     const int passes = a.rows * a.cols >= b.rows * b.cols ? pa.passes : pb.passes;
+    const int tc = pa.flat ? pb.tc : pa.tc;          // a flat tensor has no tile width of its own
+    const bool any = (pa.any && !pa.flat) || (pb.any && !pb.flat);
     MapJobs jobs;
-    jobs.j[0] = make_job(a, pa.tc, passes);
-    jobs.j[1] = make_job(b, pa.tc, passes);
+    jobs.j[0] = make_job(a, tc, passes, pa.flat);
+    jobs.j[1] = make_job(b, tc, passes, pb.flat);
     if (static_cast<uint64_t>(jobs.j[0].blocks) + jobs.j[1].blocks >= (uint64_t{1} << 31)) {
         const int rc = map_launch(a, seed, rounding, bits, s);
         return rc ? rc : map_launch(b, seed, rounding, bits, s);
     }
-    launch_tiles(jobs, pa.tc, passes, rounding == FXP_ROUND_STOCHASTIC, static_cast<uint32_t>(seed),
+    launch_tiles(jobs, tc, passes, any, rounding == FXP_ROUND_STOCHASTIC, static_cast<uint32_t>(seed),
                  static_cast<uint32_t>(seed >> 32), bits, s);
     return launch_status();
 }

@@ -59,3 +59,36 @@ def test_gemm_batched_off_the_16_byte_grid(fxp, batch, M, N, K):
     rng = np.random.default_rng(batch + M + K)
     A, B = rand_i8(rng, (batch, M, K)), rand_i8(rng, (batch, N, K))
     assert np.array_equal(host(fxp.gemm_batched(dev(A), dev(B))), oracle.gemm_batched(A, B, transB=True))
+
+
+# columns: the narrowest the tiles take, around 64 and 128 at every residue of 4, two column tiles; rows: one, around the
+# 16-byte pieces of the transposed copy and the tile heights; the last reaches the four-pass tiles
+@pytest.mark.parametrize("rows,cols", [(1, 17), (15, 63), (17, 65), (33, 66), (64, 127), (130, 129), (257, 131), (40, 190), (300, 197),
+                                       (70, 15), (128, 256), (129, 260), (5000, 3), (66000, 65), (17000, 1001)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_map_rows_off_the_quad_grid(fxp, rows, cols, offset):
+    """Both copies from x and q that start on or off the 16-byte grid, a value that saturates, one above the scale, Inf
+    and NaN among them; then the row-major copy alone (the flat path)."""
+    say("ragged map", (rows, cols), "offset", offset)
+    rng = np.random.default_rng(rows * 131 + cols)
+    x = rng.standard_normal((rows, cols)).astype(np.float32)
+    e = oracle.scale(x)
+    x.flat[rng.integers(0, x.size, 6)] = np.array([np.inf, -np.inf, np.nan, 1e30, 1.9999999 * 2.0 ** (e - 127), 1e-42], np.float32)
+    want = oracle.map(x, e, seed=5, stream_id=77)
+    n = rows * cols
+    xd = torch.zeros(n + offset, dtype=torch.float32, device="cuda")
+    xd[offset:] = dev(x).flatten()
+    q = torch.zeros(n + 3 * offset, dtype=torch.int8, device="cuda")
+    qT = torch.zeros(n + 5 * offset, dtype=torch.int8, device="cuda")
+    ed = dev(np.array([e], np.int32))
+    p = lambda t: t.data_ptr()
+    args = (p(ed), p(q) + 3 * offset, p(qT) + 5 * offset)
+    assert fxp.lib().fxp_map(p(xd) + 4 * offset, rows, cols, *args, 5, 77, 0, 8, None) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(host(q)[3 * offset:].reshape(rows, cols), want)
+    assert np.array_equal(host(qT)[5 * offset:].reshape(cols, rows), want.T)
+    q.zero_()
+    assert fxp.lib().fxp_map(p(xd) + 4 * offset, rows, cols, p(ed), p(q) + 3 * offset, None, 5, 77, 0, 8, None) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(host(q)[3 * offset:].reshape(rows, cols), want)
+    assert not host(q)[:3 * offset].any()
