@@ -376,6 +376,8 @@ extern "C" int fxp_conv2d_fwd(const float* X, const float* W, const fxp_conv2d_s
     if ((rc = scale_and_map2(tX, tW, seed, rounding, bits, s))) return rc;
     // patches read straight from the int8 image by the GEMM loader where the shape allows, else stored first
     rc = conv_gemm_launch(taps_of(g), g.KH, M, g.Cout, saved->Xq, saved->Wq, Y, saved->eX, bits, saved->eW, bits, s);
+    if (rc == kNotApplicable)
+        rc = conv_thin_fwd_launch(taps_of(g), g.KH, g.N, M, g.Cout, saved->Xq, saved->Wq, Y, saved->eX, bits, saved->eW, bits, s);
     if (rc != kNotApplicable) return rc;
     if (g.C % 16 == 0)
         hipLaunchKernelGGL(k_im2col_i8<16>, dim3(static_cast<unsigned>((M + 31) / 32)), dim3(256), 0, s, saved->Xq, g, col);
@@ -409,10 +411,12 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     uint8_t* area = w8 + round_up(kScaleWsBytes, 256);
     const size_t area_bytes = ws_bytes - round_up(kScaleWsBytes, 256);
     const int64_t M = g.M(), K = g.K();
-    // With a weight gradient to compute, the block maxima of dY are reduced by the launch that writes the
-    // transposed patches (below) and the map of dY follows it; otherwise the usual pair of launches.
+    // a thin image's weight gradient reads the image itself; any other writes transposed patches first
+    const bool thin = dW && conv_thin_wgrad_fits(taps_of(g), g.KH, g.N, g.Cout, area_bytes);
+    // With transposed patches to write, the block maxima of dY are reduced by that launch (below) and the map of dY
+    // follows it; otherwise the usual pair of launches.
     SideScale side;
-    if (dW) {
+    if (dW && !thin) {
         side.x = reinterpret_cast<const uint32_t*>(dY);
         side.n = static_cast<size_t>(M) * static_cast<size_t>(g.Cout);
         side.partials = reinterpret_cast<uint32_t*>(w8);
@@ -423,12 +427,20 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     }
     const bool need_flip = dX && dx_as_conv(g);
     ReduceRider pending;                 // the weight gradient's split-K reduction while it waits for a launch to ride in
-    if (need_flip && !dW) {
+    if (need_flip && (!dW || thin)) {
         hipLaunchKernelGGL(k_flip_weights_i8, dim3(grid_for(static_cast<int64_t>(g.Cout) * K)), dim3(256), 0, s, saved->Wq, g,
                            saved->WqF);
         if ((rc = launch_status())) return rc;
     }
-    if (dW) {
+    if (thin) {
+        ReduceRider sum;
+        if ((rc = conv_thin_wgrad_launch(taps_of(g), g.KH, g.N, M, g.Cout, saved->Xq, dYqT, area, area_bytes, &sum, s))) return rc;
+        sum.C = dW;
+        sum.fp32_out = 1;
+        sum.eA = e_dY; sum.bitsA = bits;
+        sum.eB = saved->eX; sum.bitsB = bits;
+        if ((rc = splitk_reduce_launch(sum, s))) return rc;
+    } else if (dW) {
         int8_t* colT = reinterpret_cast<int8_t*>(area);
         const bool quads = g.C % 4 == 0;                        // the dword kernel takes 128 output pixels per tile
         const int tch = 64;                                     // channels per tile

@@ -1,0 +1,381 @@
+// Convolutions of thin images (a few channels: the stem of an image model) read straight from the int8 image.
+//
+// The patch matrix of such a layer is many times its image (7 x 7, stride 2: twelve times), and with 3 bytes per pixel it
+// can neither be written nor read in whole 16-byte pieces: stored patches cost the stem of a ResNet-18 (32 x 224 x 224 x 3
+// -> 64) 67 us forward and 2.2 ms transposed.  Here the patches exist in registers only.
+//   forward : a lane's MFMA operand is 16 consecutive bytes of one filter row of its output pixel - one unaligned load;
+//             every filter row is padded to 32 contraction bytes, the padding multiplied by zero weights.
+//   weight gradient : the contraction runs over output pixels, so the operand is 16 neighbouring pixels of one tap.  A
+//             workgroup holds its image rows in LDS split into planes (one per channel and column phase of the
+//             stride), where those 16 bytes are neighbours: five dwords and four byte alignments.
+#include <algorithm>
+
+#include "fxp_internal.h"
+
+namespace fxp {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+struct __attribute__((packed, aligned(1))) AnyBytes16 {
+    uint32_t x, y, z, w;
+};
+__device__ inline v4i load_any16(const int8_t* p) {
+    const AnyBytes16 b = *reinterpret_cast<const AnyBytes16*>(p);
+    v4i v;
+    v[0] = static_cast<int>(b.x); v[1] = static_cast<int>(b.y); v[2] = static_cast<int>(b.z); v[3] = static_cast<int>(b.w);
+    return v;
+}
+
+// the mask of bytes lo .. hi - 1 of a dword (clamped to 0 .. 4)
+__device__ inline uint32_t byte_mask(int lo, int hi) {
+    lo = min(max(lo, 0), 4);
+    hi = min(max(hi, 0), 4);
+    const uint32_t below_hi = hi == 4 ? 0xffffffffu : (1u << (8 * hi)) - 1u;
+    const uint32_t below_lo = lo == 4 ? 0xffffffffu : (1u << (8 * lo)) - 1u;
+    return below_hi & ~below_lo;
+}
+
+// 16 bytes from p with only bytes lo .. hi - 1 wanted, the others zero; whole: all 16 lie inside the tensor.  Otherwise
+// (its first and last bytes) the wanted ones are fetched one by one.
+__device__ inline v4i load_part16(const int8_t* p, int lo, int hi, bool whole, const uint32_t (&mask)[4]) {
+    v4i v = {0, 0, 0, 0};
+    if (hi <= lo) return v;
+    if (whole) {
+        v = load_any16(p);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = static_cast<int>(static_cast<uint32_t>(v[d]) & mask[d]);
+    } else {
+#pragma unroll
+        for (int b = 0; b < 16; ++b)
+            if (b >= lo && b < hi) v[b >> 2] |= static_cast<int>(static_cast<uint32_t>(static_cast<uint8_t>(p[b])) << (8 * (b & 3)));
+    }
+    return v;
+}
+
+// Y[m][co] = unmap(sum over filter rows kh of patch bytes * weights).  A wave owns tiles of 32 output pixels and all
+// 32 * FN output channels; the weights, laid out as MFMA operands, are shared through LDS.  Bound by the output: 103 MB
+// of a 139 MB stem go out in 128-byte runs.
+template <int FN>
+__global__ __launch_bounds__(256) void k_conv_thin_fwd(const int8_t* __restrict__ Xq, const int8_t* __restrict__ Wq,
+                                                       float* __restrict__ Y, ConvTaps ct, int KH, uint32_t M, int Cout,
+                                                       int64_t x_bytes, const int32_t* __restrict__ eA, int bitsA,
+                                                       const int32_t* __restrict__ eB, int bitsB, uint32_t tiles) {
+    extern __shared__ __attribute__((aligned(16))) int8_t lds[];   // [kh][fragment][lane] x 16 bytes
+    constexpr int kRows = 8;                                       // filter rows in flight
+    const int row_bytes = ct.KW * ct.C;                            // <= 32
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    for (int id = threadIdx.x; id < KH * FN * 64; id += 256) {
+        const int l = id & 63, f = (id >> 6) % FN, kh = (id >> 6) / FN;
+        const int co = 32 * f + (l & 31), k0 = 16 * (l >> 5), n = min(16, row_bytes - k0);
+        const uint32_t none[4] = {0, 0, 0, 0};
+        v4i w = {0, 0, 0, 0};
+        if (co < Cout) w = load_part16(Wq + (static_cast<int64_t>(co) * KH + kh) * row_bytes + k0, 0, n, false, none);
+        *reinterpret_cast<v4i*>(lds + id * 16) = w;
+    }
+    __syncthreads();
+    const int E = lsb_exponent(eA[0], bitsA) + lsb_exponent(eB[0], bitsB);
+    const bool plain = E >= -126 && E <= 127;
+    const float unit = __uint_as_float(static_cast<uint32_t>(plain ? E + 127 : 127) << 23);
+    const int image_row = ct.W * ct.C;
+    for (uint32_t tile = blockIdx.x * 4 + (threadIdx.x >> 6); tile < tiles; tile += gridDim.x * 4) {
+        const uint32_t m0 = tile * 32, m = min(m0 + col, M - 1);
+        const uint32_t t = m / static_cast<uint32_t>(ct.Wo), n = t / static_cast<uint32_t>(ct.Ho);
+        const int h0 = static_cast<int>(t - n * ct.Ho) * ct.stride - ct.pad;
+        const int off = (static_cast<int>(m - t * ct.Wo) * ct.stride - ct.padw) * ct.C + 16 * half;   // in the image row
+        // bytes of the piece inside the image row and inside the filter row
+        const int lo = max(0, -off), hi = min(min(16, image_row - off), row_bytes - 16 * half);
+        uint32_t mask[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) mask[d] = byte_mask(lo - 4 * d, hi - 4 * d);
+        const int64_t first = static_cast<int64_t>(n) * ct.H * image_row + off;
+        v16i acc[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][r] = 0;
+        for (int kb = 0; kb < KH; kb += kRows) {
+            v4i a[kRows];
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const int h = h0 + kb + k;
+                const int64_t at = first + static_cast<int64_t>(h) * image_row;
+                const bool inside = kb + k < KH && static_cast<unsigned>(h) < static_cast<unsigned>(ct.H);
+                a[k] = load_part16(Xq + at, inside ? lo : 16, hi, at >= 0 && at + 16 <= x_bytes, mask);
+            }
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                if (kb + k >= KH) break;
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const v4i w = *reinterpret_cast<const v4i*>(lds + (((kb + k) * FN + j) * 64 + lane) * 16);
+                    acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[k], w, acc[j], 0, 0, 0);
+                }
+            }
+        }
+        // accumulator register r of lane l is pixel 8 * (r / 4) + 4 * (l / 32) + r % 4 of the tile, channel l % 32
+        float* out = Y + static_cast<int64_t>(m0 + 4 * half) * Cout + col;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int dr = 8 * (r >> 2) + (r & 3);
+            if (m0 + 4 * half + dr >= M) continue;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if (32 * j + col >= Cout) continue;
+                const float v = plain ? static_cast<float>(acc[j][r]) * unit : unmap_value(acc[j][r], E);
+                __builtin_nontemporal_store(v, out + static_cast<int64_t>(dr) * Cout + 32 * j);
+            }
+        }
+    }
+}
+
+int conv_thin_fwd_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq,
+                         float* Y, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s) {
+    const int fn = static_cast<int>((Cout + 31) / 32);
+    // a filter row is one 32-byte step, all output channels of a pixel belong to one wave, the weights fit the LDS
+    if (ct.C > 4 || ct.KW * ct.C > 32 || fn > 4 || KH * fn > 64) return kNotApplicable;
+    if (static_cast<int64_t>(ct.W) * ct.C >= (int64_t{1} << 28)) return kNotApplicable;          // 32-bit offsets in an image row
+    const int64_t x_bytes = images * ct.H * ct.W * ct.C;
+    const uint32_t tiles = static_cast<uint32_t>((M + 31) / 32);
+    // eight workgroups per CU: the weights are laid out once per workgroup, not once per tile
+    const dim3 grid(std::min<uint32_t>((tiles + 3) / 4, 2048)), block(256);
+    const size_t lds = static_cast<size_t>(KH) * fn * 1024;
+#define FXP_THIN(FN)                                                                                                        \
+    hipLaunchKernelGGL((k_conv_thin_fwd<FN>), grid, block, lds, s, Xq, Wq, Y, ct, KH, static_cast<uint32_t>(M),               \
+                       static_cast<int>(Cout), x_bytes, eA, bitsA, eB, bitsB, tiles)
+    if (fn == 1) FXP_THIN(1);
+    else if (fn == 2) FXP_THIN(2);
+    else if (fn == 3) FXP_THIN(3);
+    else FXP_THIN(4);
+#undef FXP_THIN
+    return launch_status();
+}
+
+// How a weight gradient is cut up: a unit is `rows` output rows of one image, its image rows lie in LDS as planes.
+struct WgradGeo {
+    ConvTaps ct;
+    int KH, Cout, K;
+    int rows;             // output rows of a unit
+    int groups;           // units per image
+    int units;
+    int lds_rows;         // image rows of a unit
+    int shift;            // columns the planes start left of the image (a multiple of the stride, padding or more)
+    int planes;           // stride * C
+    int q;                // dwords of a plane row (odd: the planes of one pixel start in different banks)
+    int chunks;           // 16-pixel pieces per output row
+};
+
+// parts[slice][co][k] = sum over the slice's output pixels of dYqT[co][m] * patch[m][k].  A lane's A operand is 16
+// neighbouring pixels of one output channel of dYqT, its B operand the same pixels of one tap and channel; pixels beyond
+// the end of an output row are zero in A.  The four waves take the pixel pairs of a unit in turn, each with all FM * FK
+// fragments (blockIdx.y: the next FK * 32 columns k), and add up through LDS at the end.
+template <int FM, int FK>
+__global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __restrict__ Xq, const int8_t* __restrict__ dYqT,
+                                                            int32_t* __restrict__ parts, int64_t part_stride, int64_t M,
+                                                            WgradGeo g) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t planes[];
+    const ConvTaps& ct = g.ct;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
+    const int row_dw = g.planes * g.q;                             // dwords of one image row
+    const int k_first = static_cast<int>(blockIdx.y) * FK * 32;
+    int k_at[FK], k_align[FK];
+#pragma unroll
+    for (int j = 0; j < FK; ++j) {
+        const int k = min(k_first + 32 * j + col, g.K - 1);        // columns beyond K are not stored
+        const int tap = k / ct.C, c = k - tap * ct.C, kh = tap / ct.KW, kw = tap - kh * ct.KW;
+        const int x = kw - ct.padw + g.shift, i = x / ct.stride, phase = x - i * ct.stride;
+        k_at[j] = kh * row_dw + (phase * ct.C + c) * g.q + (i >> 2);
+        k_align[j] = i & 3;
+    }
+    const int8_t* a_row[FM];
+    bool last_row[FM];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        const int co = min(32 * i + col, g.Cout - 1);
+        a_row[i] = dYqT + static_cast<int64_t>(co) * M;
+        last_row[i] = co == g.Cout - 1;
+    }
+    v16i acc[FM][FK];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FK; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+
+    for (int unit = static_cast<int>(blockIdx.x); unit < g.units; unit += static_cast<int>(gridDim.x)) {
+        const int n = unit / g.groups, ho0 = (unit - n * g.groups) * g.rows, rows_here = min(g.rows, ct.Ho - ho0);
+        const int total = rows_here * g.chunks;                    // 16-pixel pieces of the unit
+        const int64_t m_unit = (static_cast<int64_t>(n) * ct.Ho + ho0) * ct.Wo;
+        auto piece_of = [&](int step, int& r, int& j) {            // piece of this half-wave in a step; r < 0: none
+            const int p = 2 * (4 * step + wave) + half;
+            r = p / g.chunks;
+            j = p - r * g.chunks;
+            if (p >= total) { r = -1; j = 0; }
+        };
+        auto load_a = [&](int r, int j, v4i (&a)[FM]) {
+            const int64_t m = m_unit + static_cast<int64_t>(r) * ct.Wo + 16 * j;
+            const int n_bytes = r < 0 ? 0 : min(16, ct.Wo - 16 * j);
+            uint32_t mask[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) mask[d] = byte_mask(0, n_bytes - 4 * d);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) a[i] = load_part16(a_row[i] + m, 0, n_bytes, m + 16 <= M || !last_row[i], mask);
+        };
+        const int steps = (total + 7) / 8;
+        int r, j;
+        v4i a[FM], a_next[FM];
+        piece_of(0, r, j);
+        load_a(r, j, a);
+        // image rows -> planes: dword q of plane (phase, c) holds columns w = (4 q + e) * stride + phase - shift
+        __syncthreads();                                           // the last unit's planes are read no more
+        const int h_first = ho0 * ct.stride - ct.pad;
+        for (int item = lane; item < row_dw; item += 64) {
+            const int p = item / g.q, q = item - p * g.q, phase = p / ct.C, c = p - phase * ct.C;
+            const int w0 = 4 * q * ct.stride + phase - g.shift;
+            for (int lr = wave; lr < g.lds_rows; lr += 4) {
+                const int h = h_first + lr;
+                uint32_t v = 0;
+                if (static_cast<unsigned>(h) < static_cast<unsigned>(ct.H)) {
+                    const int8_t* row = Xq + (static_cast<int64_t>(n) * ct.H + h) * ct.W * ct.C + c;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int w = w0 + e * ct.stride;
+                        if (static_cast<unsigned>(w) < static_cast<unsigned>(ct.W))
+                            v |= static_cast<uint32_t>(static_cast<uint8_t>(row[static_cast<int64_t>(w) * ct.C])) << (8 * e);
+                    }
+                }
+                planes[lr * row_dw + item] = v;
+            }
+        }
+        __syncthreads();
+        for (int step = 0; step < steps; ++step) {
+            const uint32_t* at = planes + max(r, 0) * ct.stride * row_dw + 4 * j;
+            if (step + 1 < steps) {
+                piece_of(step + 1, r, j);
+                load_a(r, j, a_next);
+            }
+#pragma unroll
+            for (int f = 0; f < FK; ++f) {
+                uint32_t d[5];
+#pragma unroll
+                for (int e = 0; e < 5; ++e) d[e] = at[k_at[f] + e];
+                v4i b;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    b[e] = static_cast<int>(__builtin_amdgcn_alignbyte(d[e + 1], d[e], static_cast<uint32_t>(k_align[f])));
+#pragma unroll
+                for (int i = 0; i < FM; ++i) acc[i][f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b, acc[i][f], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < FM; ++i) a[i] = a_next[i];
+        }
+    }
+    // the four waves' sums meet in LDS, [co][k] with FK * 32 columns
+    __syncthreads();
+    int32_t* sum = reinterpret_cast<int32_t*>(planes);
+    for (int i = threadIdx.x; i < FM * 32 * FK * 32; i += 256) sum[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FK; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                atomicAdd(sum + (32 * i + 8 * (r >> 2) + 4 * half + (r & 3)) * (FK * 32) + 32 * j + col, acc[i][j][r]);
+    __syncthreads();
+    int32_t* dst = parts + static_cast<int64_t>(blockIdx.x) * part_stride + k_first;
+    const int cols_here = min(FK * 32, g.K - k_first);
+    for (int co = wave; co < g.Cout; co += 4)
+        for (int k = lane; k < cols_here; k += 64) dst[static_cast<int64_t>(co) * g.K + k] = sum[co * (FK * 32) + k];
+}
+
+struct WgradPlan {
+    WgradGeo g;
+    int fm, fk, k_groups;      // fragments of output channels and of k per wave, groups of k fragments
+    int slices;
+    int64_t slice_stride;
+    size_t lds;
+};
+
+static bool plan_thin_wgrad(const ConvTaps& ct, int KH, int64_t images, int64_t Cout, size_t part_bytes, WgradPlan* p) {
+    if (ct.C > 4 || ct.KW * ct.C > 32 || Cout > 128 || ct.stride > 4) return false;
+    WgradGeo& g = p->g;
+    g.ct = ct;
+    g.KH = KH;
+    g.Cout = static_cast<int>(Cout);
+    g.K = KH * ct.KW * ct.C;
+    g.chunks = (ct.Wo + 15) / 16;
+    g.shift = (ct.padw + ct.stride - 1) / ct.stride * ct.stride;
+    g.planes = ct.stride * ct.C;
+    const int i_max = (ct.KW - 1 - ct.padw + g.shift) / ct.stride;
+    const int64_t q = (i_max / 4 + 4 * (static_cast<int64_t>(g.chunks) - 1) + 5) | 1;
+    const int k_frags = (g.K + 31) / 32;
+    p->fm = static_cast<int>((Cout + 31) / 32);
+    // fragments of k per wave: all of them where 160 accumulator registers hold them
+    const int fk_max = p->fm <= 2 ? 5 : (p->fm == 3 ? 3 : 2);
+    p->fk = k_frags == 1 ? 1 : (k_frags == 2 || fk_max == 2 ? 2 : fk_max);
+    p->k_groups = (k_frags + p->fk - 1) / p->fk;
+    // output rows per unit: as many as still give three workgroups for every two CUs (the image rows of neighbouring
+    // units overlap by the filter), within 32 KiB of LDS
+    auto image_bytes = [&](int64_t rows) { return ((rows - 1) * ct.stride + KH) * g.planes * q * 4; };
+    int rows = 16;
+    while (rows > 1 && (image_bytes(rows) > 32768 || images * ((ct.Ho + rows - 1) / rows) * p->k_groups < 384)) rows /= 2;
+    if (image_bytes(rows) > 32768) return false;
+    g.rows = rows;
+    g.q = static_cast<int>(q);
+    g.lds_rows = (rows - 1) * ct.stride + KH;
+    g.groups = (ct.Ho + rows - 1) / rows;
+    const int64_t units = images * g.groups;
+    if (units >= (int64_t{1} << 31)) return false;
+    g.units = static_cast<int>(units);
+    p->slice_stride = (Cout * g.K + 3) / 4 * 4;
+    const int64_t fit = static_cast<int64_t>(part_bytes / (static_cast<size_t>(p->slice_stride) * sizeof(int32_t)));
+    const int64_t slices = std::min<int64_t>({units, int64_t{std::max(1, 512 / p->k_groups)}, fit});
+    // every slice is exact in int32
+    if (slices < 1 || (units + slices - 1) / slices * rows * ct.Wo > kMaxSlice) return false;
+    p->slices = static_cast<int>(slices);
+    p->lds = std::max<size_t>(static_cast<size_t>(image_bytes(rows)), static_cast<size_t>(p->fm) * p->fk * 4096);
+    return true;
+}
+
+bool conv_thin_wgrad_fits(const ConvTaps& ct, int KH, int64_t images, int64_t Cout, size_t part_bytes) {
+    WgradPlan p;
+    return plan_thin_wgrad(ct, KH, images, Cout, part_bytes, &p);
+}
+
+// Leaves the slices in `parts` (16-byte aligned, part_bytes available) and describes in *sum the slices, to be completed
+// by the caller with the output and the scales.
+int conv_thin_wgrad_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* dYqT,
+                           void* parts, size_t part_bytes, ReduceRider* sum, hipStream_t s) {
+    WgradPlan p;
+    if (!plan_thin_wgrad(ct, KH, images, Cout, part_bytes, &p)) return kNotApplicable;
+    const dim3 grid(static_cast<unsigned>(p.slices), static_cast<unsigned>(p.k_groups)), block(256);
+#define FXP_THIN(FM, FK)                                                                                                     \
+    hipLaunchKernelGGL((k_conv_thin_wgrad<FM, FK>), grid, block, p.lds, s, Xq, dYqT, static_cast<int32_t*>(parts), p.slice_stride, \
+                       M, p.g)
+#define FXP_THIN_FK(FM, MAX)                 \
+    do {                                     \
+        if (p.fk == 1) FXP_THIN(FM, 1);      \
+        else if (p.fk == 2) FXP_THIN(FM, 2); \
+        else FXP_THIN(FM, MAX);              \
+    } while (0)
+    if (p.fm == 1) FXP_THIN_FK(1, 5);
+    else if (p.fm == 2) FXP_THIN_FK(2, 5);
+    else if (p.fm == 3) FXP_THIN_FK(3, 3);
+    else FXP_THIN_FK(4, 2);
+#undef FXP_THIN_FK
+#undef FXP_THIN
+    *sum = ReduceRider();
+    sum->parts = static_cast<const int32_t*>(parts);
+    sum->splits = p.slices;
+    sum->stride = p.slice_stride;
+    sum->M = static_cast<int>(Cout);
+    sum->N = p.g.K;
+    sum->ldc = p.g.K;
+    sum->wide = M > kMaxContraction ? 1 : 0;
+    plan_reduce(sum);
+    return launch_status();
+}
+
+}  // namespace fxp

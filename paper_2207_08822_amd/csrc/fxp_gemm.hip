@@ -150,7 +150,7 @@ __device__ inline float store_fragments(const v16i (&acc)[FM][FN], void* __restr
     return store_loop<FM, FN, MODE, AMAX, true, false>(acc, Cv, ldc, M, N, row0, col0, fhalf, frow, E);
 }
 
-// Sum of the split-K slices of a product (int32, exact in any order) -> int32 or inverse-mapped fp32, by workgroup
+// Sum of the split-K slices of a product (exact in any order) -> int32 or inverse-mapped fp32, by workgroup
 // `b` of `nb`.  The slices are dense M x N matrices `stride` elements apart.  A dense, 16-byte aligned output is
 // walked as one flat run of 16-byte pieces, anything else row by row.
 __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsigned nb) {
@@ -172,9 +172,48 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
     };
     const int64_t total = static_cast<int64_t>(r.M) * r.N;
     const bool flat = r.ldc == r.N && (reinterpret_cast<uintptr_t>(r.C) & 15u) == 0;
+    // 16-byte pieces of a flat output: `group` lanes of a wave share a piece, each sums every group-th slice, and the
+    // lanes add up by exchange (no LDS: a host product's own tiles may fill it)
+    auto pieces = [&](auto wide_c) {
+        constexpr bool WIDE = decltype(wide_c)::value != 0;
+        using Sum = typename std::conditional<WIDE, int64_t, int>::type;
+        const int lane = threadIdx.x & 63, per_wave = 64 / r.group, sub = lane / per_wave;
+        const int64_t nvec = total >> 2, waves = static_cast<int64_t>(nb) * (nt >> 6);
+        int64_t i = (static_cast<int64_t>(b) * (nt >> 6) + (threadIdx.x >> 6)) * per_wave + lane % per_wave;
+        for (; i < nvec; i += waves * per_wave) {                  // the lanes of one piece leave together
+            Sum s[4] = {0, 0, 0, 0};
+#pragma unroll 8
+            for (int sidx = sub; sidx < splits; sidx += r.group) {
+                const int4 v = reinterpret_cast<const int4*>(parts + sidx * stride)[i];
+                s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
+            }
+            for (int d = per_wave; d < 64; d *= 2)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[k] += __shfl_xor(s[k], d);
+            if (sub != 0) continue;
+            if (r.fp32_out) {
+                float o[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if constexpr (WIDE) o[k] = unmap_value64(s[k], E);
+                    else o[k] = unmap_value(s[k], E);
+                    m = fmaxf(m, fabsf(o[k]));
+                }
+                reinterpret_cast<float4*>(r.C)[i] = make_float4(o[0], o[1], o[2], o[3]);
+            } else {
+                reinterpret_cast<int4*>(r.C)[i] =
+                    make_int4(static_cast<int>(s[0]), static_cast<int>(s[1]), static_cast<int>(s[2]), static_cast<int>(s[3]));
+            }
+        }
+    };
     if (r.wide) {
-        // contraction beyond what one int32 sum holds: 64-bit sum of the slices, one element per thread and round
-        for (int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x; i < total; i += static_cast<int64_t>(nb) * nt) {
+        // contraction beyond what one int32 sum holds: 64-bit sums of the slices
+        int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x;
+        if (flat) {
+            pieces(IC<1>{});
+            i += total & ~int64_t{3};                               // the tail, one element per thread
+        }
+        for (; i < total; i += static_cast<int64_t>(nb) * nt) {
             int64_t acc = 0;
             for (int sidx = 0; sidx < splits; ++sidx) acc += parts[sidx * stride + i];
             const float o = unmap_value64(acc, E);
@@ -182,24 +221,8 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
             m = fmaxf(m, fabsf(o));
         }
     } else if (flat) {
+        pieces(IC<0>{});
         const int64_t nvec = total >> 2;
-        for (int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x; i < nvec; i += static_cast<int64_t>(nb) * nt) {
-            int4 acc = make_int4(0, 0, 0, 0);
-#pragma unroll 8
-            for (int sidx = 0; sidx < splits; ++sidx) {
-                const int4 v = reinterpret_cast<const int4*>(parts + sidx * stride)[i];
-                acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-            }
-            if (r.fp32_out) {
-                float4 o;
-                o.x = unmap_value(acc.x, E); o.y = unmap_value(acc.y, E);
-                o.z = unmap_value(acc.z, E); o.w = unmap_value(acc.w, E);
-                reinterpret_cast<float4*>(r.C)[i] = o;
-                m = fmaxf(fmaxf(m, fmaxf(fabsf(o.x), fabsf(o.y))), fmaxf(fabsf(o.z), fabsf(o.w)));
-            } else {
-                reinterpret_cast<int4*>(r.C)[i] = acc;
-            }
-        }
         if (b == 0 && threadIdx.x < (total & 3)) {                 // the slices are 16-byte aligned, the tail is not a piece
             const int64_t i = (nvec << 2) + threadIdx.x;
             int acc = 0;
@@ -1002,10 +1025,14 @@ static int launch_dma(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t 
 
 __global__ __launch_bounds__(256) void k_splitk_reduce(ReduceRider r) { splitk_reduce_body(r, blockIdx.x, gridDim.x); }
 
-// workgroups a reduction wants: one 16-byte piece of the output per thread (its loads over the slices are
-// independent of each other), 256 threads per workgroup, at most 2048 workgroups
-static unsigned reduce_blocks(int64_t M, int64_t N) {
-    return static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (M * N / 4 + 255) / 256)));
+// Lanes per 16-byte piece of the output and workgroups of a reduction.  One lane a piece while the pieces alone fill the
+// chip or the slices are few; else up to sixteen lanes, each with eight slices or more (a 64 x 147 output of 126 slices:
+// ten workgroups walked all slices in turn, 123 us).  256 threads per workgroup, at most 2048 workgroups.
+void plan_reduce(ReduceRider* r) {
+    const int64_t pieces = std::max<int64_t>(1, static_cast<int64_t>(r->M) * r->N / 4);
+    r->group = 1;
+    while (r->group < 16 && r->splits >= 16 * r->group && pieces * r->group < 65536) r->group *= 2;
+    r->blocks = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (pieces * r->group + 255) / 256)));
 }
 
 int splitk_reduce_launch(const ReduceRider& r, hipStream_t s) {
@@ -1210,7 +1237,7 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         r.eA = eA; r.bitsA = bitsA; r.eB = eB; r.bitsB = bitsB;
         r.amax = amax;
         r.wide = K > kMaxContraction ? 1 : 0;
-        r.blocks = reduce_blocks(M, N);
+        plan_reduce(&r);
         if (defer != nullptr) {
             *defer = r;
             return FXP_OK;
