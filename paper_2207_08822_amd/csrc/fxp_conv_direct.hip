@@ -36,28 +36,34 @@ __device__ inline uint32_t byte_mask(int lo, int hi) {
     return below_hi & ~below_lo;
 }
 
-// 16 bytes from p with only bytes lo .. hi - 1 wanted, the others zero; whole: all 16 lie inside the tensor.  Otherwise
-// (its first and last bytes) the wanted ones are fetched one by one.
-__device__ inline v4i load_part16(const int8_t* p, int lo, int hi, bool whole, const uint32_t (&mask)[4]) {
-    v4i v = {0, 0, 0, 0};
-    if (hi <= lo) return v;
-    if (whole) {
-        v = load_any16(p);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) v[d] = static_cast<int>(static_cast<uint32_t>(v[d]) & mask[d]);
-    } else {
+// Bytes at .. at + 15 of a tensor of `size` >= 16 bytes for operands whose unwanted bytes are zero: the load itself is
+// unconditional (from the nearest 16 bytes that lie inside), so that a wave's loads are all in flight before one is
+// waited for; keep() then picks the bytes.
+__device__ inline v4i load_near16(const int8_t* base, int64_t at, int64_t size) {
+    return load_any16(base + min(max(at, int64_t{0}), size - 16));
+}
+// The 16 bytes at `at` with only those of the mask kept (the wanted ones: lo .. hi - 1).  A lane at one of the tensor's
+// ends, whose load was moved, fetches its bytes one by one.
+__device__ inline v4i keep(v4i v, const int8_t* base, int64_t at, int64_t size, int lo, int hi, const uint32_t (&mask)[4]) {
+    const bool moved = lo < hi && (at < 0 || at > size - 16);
+    if (__builtin_amdgcn_ballot_w64(moved) != 0 && moved) {
+        v = v4i{0, 0, 0, 0};
 #pragma unroll
         for (int b = 0; b < 16; ++b)
-            if (b >= lo && b < hi) v[b >> 2] |= static_cast<int>(static_cast<uint32_t>(static_cast<uint8_t>(p[b])) << (8 * (b & 3)));
+            if (b >= lo && b < hi) v[b >> 2] |= static_cast<int>(static_cast<uint32_t>(static_cast<uint8_t>(base[at + b])) << (8 * (b & 3)));
+        return v;
     }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) v[d] = lo < hi ? static_cast<int>(static_cast<uint32_t>(v[d]) & mask[d]) : 0;
     return v;
 }
 
 // Y[m][co] = unmap(sum over filter rows kh of patch bytes * weights).  A wave owns tiles of 32 output pixels and all
-// 32 * FN output channels; the weights, laid out as MFMA operands, are shared through LDS.  Bound by the output: 103 MB
-// of a 139 MB stem go out in 128-byte runs.
+// 32 * FN output channels; the weights, laid out as MFMA operands, are shared through LDS.  Bound by the output, 103 MB
+// of the 113 MB that the 32 x 224 x 224 x 3 -> 64 stem moves: 32 us (3.5 TB/s; 118 with the patch matrix stored and read
+// back, 57 with every load waited for before the next).
 template <int FN>
-__global__ __launch_bounds__(256) void k_conv_thin_fwd(const int8_t* __restrict__ Xq, const int8_t* __restrict__ Wq,
+__global__ __launch_bounds__(256, FN <= 2 ? 4 : 2) void k_conv_thin_fwd(const int8_t* __restrict__ Xq, const int8_t* __restrict__ Wq,
                                                        float* __restrict__ Y, ConvTaps ct, int KH, uint32_t M, int Cout,
                                                        int64_t x_bytes, const int32_t* __restrict__ eA, int bitsA,
                                                        const int32_t* __restrict__ eB, int bitsB, uint32_t tiles) {
@@ -68,9 +74,12 @@ __global__ __launch_bounds__(256) void k_conv_thin_fwd(const int8_t* __restrict_
     for (int id = threadIdx.x; id < KH * FN * 64; id += 256) {
         const int l = id & 63, f = (id >> 6) % FN, kh = (id >> 6) / FN;
         const int co = 32 * f + (l & 31), k0 = 16 * (l >> 5), n = min(16, row_bytes - k0);
-        const uint32_t none[4] = {0, 0, 0, 0};
-        v4i w = {0, 0, 0, 0};
-        if (co < Cout) w = load_part16(Wq + (static_cast<int64_t>(co) * KH + kh) * row_bytes + k0, 0, n, false, none);
+        const int64_t w_bytes = static_cast<int64_t>(Cout) * KH * row_bytes;
+        const int64_t at = (static_cast<int64_t>(min(co, Cout - 1)) * KH + kh) * row_bytes + k0;
+        uint32_t mask[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) mask[d] = byte_mask(0, n - 4 * d);
+        const v4i w = keep(load_near16(Wq, at, w_bytes), Wq, at, w_bytes, 0, co < Cout ? n : 0, mask);
         *reinterpret_cast<v4i*>(lds + id * 16) = w;
     }
     __syncthreads();
@@ -97,15 +106,14 @@ __global__ __launch_bounds__(256) void k_conv_thin_fwd(const int8_t* __restrict_
         for (int kb = 0; kb < KH; kb += kRows) {
             v4i a[kRows];
 #pragma unroll
-            for (int k = 0; k < kRows; ++k) {
-                const int h = h0 + kb + k;
-                const int64_t at = first + static_cast<int64_t>(h) * image_row;
-                const bool inside = kb + k < KH && static_cast<unsigned>(h) < static_cast<unsigned>(ct.H);
-                a[k] = load_part16(Xq + at, inside ? lo : 16, hi, at >= 0 && at + 16 <= x_bytes, mask);
-            }
+            for (int k = 0; k < kRows; ++k)
+                if (kb + k < KH) a[k] = load_near16(Xq, first + static_cast<int64_t>(h0 + kb + k) * image_row, x_bytes);
 #pragma unroll
             for (int k = 0; k < kRows; ++k) {
                 if (kb + k >= KH) break;
+                const int h = h0 + kb + k;
+                const bool inside = static_cast<unsigned>(h) < static_cast<unsigned>(ct.H);
+                a[k] = keep(a[k], Xq, first + static_cast<int64_t>(h) * image_row, x_bytes, inside ? lo : 16, hi, mask);
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
                     const v4i w = *reinterpret_cast<const v4i*>(lds + (((kb + k) * FN + j) * 64 + lane) * 16);
@@ -136,8 +144,9 @@ int conv_thin_fwd_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, 
     if (ct.C > 4 || ct.KW * ct.C > 32 || fn > 4 || KH * fn > 64) return kNotApplicable;
     if (static_cast<int64_t>(ct.W) * ct.C >= (int64_t{1} << 28)) return kNotApplicable;          // 32-bit offsets in an image row
     const int64_t x_bytes = images * ct.H * ct.W * ct.C;
+    if (x_bytes < 16 || Cout * KH * ct.KW * ct.C < 16) return kNotApplicable;
     const uint32_t tiles = static_cast<uint32_t>((M + 31) / 32);
-    // eight workgroups per CU: the weights are laid out once per workgroup, not once per tile
+    // up to eight workgroups per CU: the weights are laid out once per workgroup, not once per tile
     const dim3 grid(std::min<uint32_t>((tiles + 3) / 4, 2048)), block(256);
     const size_t lds = static_cast<size_t>(KH) * fn * 1024;
 #define FXP_THIN(FN)                                                                                                        \
@@ -151,14 +160,16 @@ int conv_thin_fwd_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, 
     return launch_status();
 }
 
-// How a weight gradient is cut up: a unit is `rows` output rows of one image, its image rows lie in LDS as planes.
+constexpr int kWgradThreads = 512, kWgradWaves = kWgradThreads / 64;
+
+// how a weight gradient is cut up
 struct WgradGeo {
     ConvTaps ct;
     int KH, Cout, K;
-    int rows;             // output rows of a unit
-    int groups;           // units per image
-    int units;
-    int lds_rows;         // image rows of a unit
+    int all_rows;         // output rows of the batch
+    int wg_rows;          // output rows of a workgroup, a run over the batch
+    int rows;             // those of them, at most, whose image rows are in LDS together (never of two images)
+    int lds_rows;         // image rows of such a unit
     int shift;            // columns the planes start left of the image (a multiple of the stride, padding or more)
     int planes;           // stride * C
     int q;                // dwords of a plane row (odd: the planes of one pixel start in different banks)
@@ -167,16 +178,19 @@ struct WgradGeo {
 
 // parts[slice][co][k] = sum over the slice's output pixels of dYqT[co][m] * patch[m][k].  A lane's A operand is 16
 // neighbouring pixels of one output channel of dYqT, its B operand the same pixels of one tap and channel; pixels beyond
-// the end of an output row are zero in A.  The four waves take the pixel pairs of a unit in turn, each with all FM * FK
-// fragments (blockIdx.y: the next FK * 32 columns k), and add up through LDS at the end.
+// the end of an output row are zero in A.  The eight waves take the pairs of pieces of a unit in turn, each with all
+// FM * FK fragments (blockIdx.y: the next FK * 32 columns k), and add up through LDS at the end.  One workgroup per CU:
+// with two of half the waves there are twice the slices to write and to sum (30 and 13 us against 22 and 9; 2205, 20
+// and 123 through stored transposed patches).
 template <int FM, int FK>
-__global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __restrict__ Xq, const int8_t* __restrict__ dYqT,
+__global__ __launch_bounds__(kWgradThreads, 2) void k_conv_thin_wgrad(const int8_t* __restrict__ Xq, const int8_t* __restrict__ dYqT,
                                                             int32_t* __restrict__ parts, int64_t part_stride, int64_t M,
                                                             WgradGeo g) {
     extern __shared__ __attribute__((aligned(16))) uint32_t planes[];
     const ConvTaps& ct = g.ct;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
     const int row_dw = g.planes * g.q;                             // dwords of one image row
+    const int image_row = ct.W * ct.C;
     const int k_first = static_cast<int>(blockIdx.y) * FK * 32;
     int k_at[FK], k_align[FK];
 #pragma unroll
@@ -187,14 +201,10 @@ __global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __rest
         k_at[j] = kh * row_dw + (phase * ct.C + c) * g.q + (i >> 2);
         k_align[j] = i & 3;
     }
-    const int8_t* a_row[FM];
-    bool last_row[FM];
+    const int64_t a_bytes = static_cast<int64_t>(g.Cout) * M;
+    int64_t a_row[FM];
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-        const int co = min(32 * i + col, g.Cout - 1);
-        a_row[i] = dYqT + static_cast<int64_t>(co) * M;
-        last_row[i] = co == g.Cout - 1;
-    }
+    for (int i = 0; i < FM; ++i) a_row[i] = static_cast<int64_t>(min(32 * i + col, g.Cout - 1)) * M;
     v16i acc[FM][FK];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -203,26 +213,34 @@ __global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __rest
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
-    for (int unit = static_cast<int>(blockIdx.x); unit < g.units; unit += static_cast<int>(gridDim.x)) {
-        const int n = unit / g.groups, ho0 = (unit - n * g.groups) * g.rows, rows_here = min(g.rows, ct.Ho - ho0);
+    int row_first = static_cast<int>(blockIdx.x) * g.wg_rows;
+    const int row_end = min(row_first + g.wg_rows, g.all_rows);
+    while (row_first < row_end) {
+        const int n = row_first / ct.Ho, ho0 = row_first - n * ct.Ho;
+        const int rows_here = min(min(g.rows, ct.Ho - ho0), row_end - row_first);
         const int total = rows_here * g.chunks;                    // 16-pixel pieces of the unit
-        const int64_t m_unit = (static_cast<int64_t>(n) * ct.Ho + ho0) * ct.Wo;
+        const int64_t m_unit = static_cast<int64_t>(row_first) * ct.Wo;
+        row_first += rows_here;
         auto piece_of = [&](int step, int& r, int& j) {            // piece of this half-wave in a step; r < 0: none
-            const int p = 2 * (4 * step + wave) + half;
+            const int p = 2 * (kWgradWaves * step + wave) + half;
             r = p / g.chunks;
             j = p - r * g.chunks;
             if (p >= total) { r = -1; j = 0; }
         };
+        auto m_of = [&](int r, int j) { return m_unit + static_cast<int64_t>(max(r, 0)) * ct.Wo + 16 * j; };
         auto load_a = [&](int r, int j, v4i (&a)[FM]) {
-            const int64_t m = m_unit + static_cast<int64_t>(r) * ct.Wo + 16 * j;
+#pragma unroll
+            for (int i = 0; i < FM; ++i) a[i] = load_near16(dYqT, a_row[i] + m_of(r, j), a_bytes);
+        };
+        auto keep_a = [&](int r, int j, v4i (&a)[FM]) {
             const int n_bytes = r < 0 ? 0 : min(16, ct.Wo - 16 * j);
             uint32_t mask[4];
 #pragma unroll
             for (int d = 0; d < 4; ++d) mask[d] = byte_mask(0, n_bytes - 4 * d);
 #pragma unroll
-            for (int i = 0; i < FM; ++i) a[i] = load_part16(a_row[i] + m, 0, n_bytes, m + 16 <= M || !last_row[i], mask);
+            for (int i = 0; i < FM; ++i) a[i] = keep(a[i], dYqT, a_row[i] + m_of(r, j), a_bytes, 0, n_bytes, mask);
         };
-        const int steps = (total + 7) / 8;
+        const int steps = (total + 2 * kWgradWaves - 1) / (2 * kWgradWaves);
         int r, j;
         v4i a[FM], a_next[FM];
         piece_of(0, r, j);
@@ -232,29 +250,30 @@ __global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __rest
         const int h_first = ho0 * ct.stride - ct.pad;
         for (int item = lane; item < row_dw; item += 64) {
             const int p = item / g.q, q = item - p * g.q, phase = p / ct.C, c = p - phase * ct.C;
-            const int w0 = 4 * q * ct.stride + phase - g.shift;
-            for (int lr = wave; lr < g.lds_rows; lr += 4) {
-                const int h = h_first + lr;
-                uint32_t v = 0;
-                if (static_cast<unsigned>(h) < static_cast<unsigned>(ct.H)) {
-                    const int8_t* row = Xq + (static_cast<int64_t>(n) * ct.H + h) * ct.W * ct.C + c;
+            const int8_t* at[4];                                   // of image row 0; columns outside are masked
+            uint32_t mask = 0;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int w = w0 + e * ct.stride;
-                        if (static_cast<unsigned>(w) < static_cast<unsigned>(ct.W))
-                            v |= static_cast<uint32_t>(static_cast<uint8_t>(row[static_cast<int64_t>(w) * ct.C])) << (8 * e);
-                    }
-                }
-                planes[lr * row_dw + item] = v;
+            for (int e = 0; e < 4; ++e) {
+                const int w = (4 * q + e) * ct.stride + phase - g.shift;
+                if (static_cast<unsigned>(w) < static_cast<unsigned>(ct.W)) mask |= 0xffu << (8 * e);
+                at[e] = Xq + (static_cast<int64_t>(n) * ct.H * ct.W + min(max(w, 0), ct.W - 1)) * ct.C + c;
+            }
+#pragma unroll 4
+            for (int lr = wave; lr < g.lds_rows; lr += kWgradWaves) {
+                const int h = h_first + lr;
+                const int64_t row = static_cast<int64_t>(min(max(h, 0), ct.H - 1)) * image_row;
+                uint32_t v = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v |= static_cast<uint32_t>(static_cast<uint8_t>(at[e][row])) << (8 * e);
+                planes[lr * row_dw + item] = static_cast<unsigned>(h) < static_cast<unsigned>(ct.H) ? v & mask : 0u;
             }
         }
         __syncthreads();
         for (int step = 0; step < steps; ++step) {
             const uint32_t* at = planes + max(r, 0) * ct.stride * row_dw + 4 * j;
-            if (step + 1 < steps) {
-                piece_of(step + 1, r, j);
-                load_a(r, j, a_next);
-            }
+            keep_a(r, j, a);
+            piece_of(step + 1, r, j);                              // none behind the last step: a load that is not used
+            load_a(r, j, a_next);
 #pragma unroll
             for (int f = 0; f < FK; ++f) {
                 uint32_t d[5];
@@ -271,10 +290,10 @@ __global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __rest
             for (int i = 0; i < FM; ++i) a[i] = a_next[i];
         }
     }
-    // the four waves' sums meet in LDS, [co][k] with FK * 32 columns
+    // the waves' sums meet in LDS, [co][k] with FK * 32 columns
     __syncthreads();
     int32_t* sum = reinterpret_cast<int32_t*>(planes);
-    for (int i = threadIdx.x; i < FM * 32 * FK * 32; i += 256) sum[i] = 0;
+    for (int i = threadIdx.x; i < FM * 32 * FK * 32; i += kWgradThreads) sum[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -286,7 +305,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_thin_wgrad(const int8_t* __rest
     __syncthreads();
     int32_t* dst = parts + static_cast<int64_t>(blockIdx.x) * part_stride + k_first;
     const int cols_here = min(FK * 32, g.K - k_first);
-    for (int co = wave; co < g.Cout; co += 4)
+    for (int co = wave; co < g.Cout; co += kWgradWaves)
         for (int k = lane; k < cols_here; k += 64) dst[static_cast<int64_t>(co) * g.K + k] = sum[co * (FK * 32) + k];
 }
 
@@ -316,25 +335,26 @@ static bool plan_thin_wgrad(const ConvTaps& ct, int KH, int64_t images, int64_t 
     const int fk_max = p->fm <= 2 ? 5 : (p->fm == 3 ? 3 : 2);
     p->fk = k_frags == 1 ? 1 : (k_frags == 2 || fk_max == 2 ? 2 : fk_max);
     p->k_groups = (k_frags + p->fk - 1) / p->fk;
-    // output rows per unit: as many as still give three workgroups for every two CUs (the image rows of neighbouring
-    // units overlap by the filter), within 32 KiB of LDS
+    // One workgroup per CU with an equal run of output rows.  Image rows in LDS at a time: 48 KiB at most, for a run of up
+    // to 16 output rows (rows of the filter that reach into the neighbouring unit are fetched by both).
     auto image_bytes = [&](int64_t rows) { return ((rows - 1) * ct.stride + KH) * g.planes * q * 4; };
-    int rows = 16;
-    while (rows > 1 && (image_bytes(rows) > 32768 || images * ((ct.Ho + rows - 1) / rows) * p->k_groups < 384)) rows /= 2;
-    if (image_bytes(rows) > 32768) return false;
-    g.rows = rows;
-    g.q = static_cast<int>(q);
-    g.lds_rows = (rows - 1) * ct.stride + KH;
-    g.groups = (ct.Ho + rows - 1) / rows;
-    const int64_t units = images * g.groups;
-    if (units >= (int64_t{1} << 31)) return false;
-    g.units = static_cast<int>(units);
     p->slice_stride = (Cout * g.K + 3) / 4 * 4;
+    const int64_t all_rows = images * ct.Ho;
     const int64_t fit = static_cast<int64_t>(part_bytes / (static_cast<size_t>(p->slice_stride) * sizeof(int32_t)));
-    const int64_t slices = std::min<int64_t>({units, int64_t{std::max(1, 512 / p->k_groups)}, fit});
-    // every slice is exact in int32
-    if (slices < 1 || (units + slices - 1) / slices * rows * ct.Wo > kMaxSlice) return false;
-    p->slices = static_cast<int>(slices);
+    const int64_t want = std::min<int64_t>({all_rows, int64_t{std::max(1, 256 / p->k_groups)}, fit});
+    if (want < 1 || all_rows >= (int64_t{1} << 30)) return false;
+    const int64_t wg_rows = (all_rows + want - 1) / want;
+    int64_t rows = std::min<int64_t>({wg_rows, 16, ct.Ho});
+    while (rows > 1 && image_bytes(rows) > 49152) --rows;
+    // ... and every slice exact in int32
+    if (image_bytes(rows) > 49152 || wg_rows * ct.Wo > kMaxSlice || images * ct.H * ct.W * ct.C < 16 || Cout * all_rows * ct.Wo < 16)
+        return false;
+    g.all_rows = static_cast<int>(all_rows);
+    g.wg_rows = static_cast<int>(wg_rows);
+    g.rows = static_cast<int>(rows);
+    g.q = static_cast<int>(q);
+    g.lds_rows = static_cast<int>((rows - 1) * ct.stride + KH);
+    p->slices = static_cast<int>((all_rows + wg_rows - 1) / wg_rows);
     p->lds = std::max<size_t>(static_cast<size_t>(image_bytes(rows)), static_cast<size_t>(p->fm) * p->fk * 4096);
     return true;
 }
@@ -350,7 +370,7 @@ int conv_thin_wgrad_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M
                            void* parts, size_t part_bytes, ReduceRider* sum, hipStream_t s) {
     WgradPlan p;
     if (!plan_thin_wgrad(ct, KH, images, Cout, part_bytes, &p)) return kNotApplicable;
-    const dim3 grid(static_cast<unsigned>(p.slices), static_cast<unsigned>(p.k_groups)), block(256);
+    const dim3 grid(static_cast<unsigned>(p.slices), static_cast<unsigned>(p.k_groups)), block(kWgradThreads);
 #define FXP_THIN(FM, FK)                                                                                                     \
     hipLaunchKernelGGL((k_conv_thin_wgrad<FM, FK>), grid, block, p.lds, s, Xq, dYqT, static_cast<int32_t*>(parts), p.slice_stride, \
                        M, p.g)
