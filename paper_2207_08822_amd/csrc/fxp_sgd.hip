@@ -11,6 +11,9 @@
 // One kernel per line: 8 B read + 4 B written per element, two Philox blocks per four elements.  The
 // scales of x and y arrive as block maxima (the kernel finishes the reduction, like the map kernel does), and
 // the kernel leaves the block maxima of z behind, so a chain of lines needs no scale pass for intermediates.
+// Bound by VALU issue, just above what the memory takes: per wave and quad 36 64-bit multiply-adds of 16 cycles for
+// the random words and about 160 instructions of 4 cycles.  A line over 11.7 M parameters: 29.4 us with the elements
+// handled as signed integers that are tested against their scale, 26.1 on magnitudes (5.4 TB/s).
 #include "fxp_internal.h"
 
 namespace fxp {
@@ -59,6 +62,13 @@ __device__ inline int map16_fast(uint32_t b, uint32_t r9, int to_units, float li
     const uint32_t ms = static_cast<uint32_t>(ldexpf(ax, to_units));
     const uint32_t q = min((ms + (STOCH ? (r9 ^ 511u) : 256u)) >> 9, 32767u);
     return (b >> 31) ? -static_cast<int>(q) : static_cast<int>(q);
+}
+
+// magnitude of a finite element at or below the scale, scale in [25, 254]: to_units = 2^(150 - e_max)
+template <bool STOCH>
+__device__ inline uint32_t magnitude16(uint32_t b, uint32_t r9, float to_units) {
+    const uint32_t ms = static_cast<uint32_t>(fabsf(__uint_as_float(b)) * to_units);
+    return min((ms + (STOCH ? (r9 ^ 511u) : 256u)) >> 9, 32767u);
 }
 
 // How the int32 product (unit 2^(Ea+Ey)) reaches the unit of x_hat, s = Ex - (Ea + Ey); all wave-uniform.
@@ -146,8 +156,19 @@ __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t
             ru = philox4x32_10(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), sid_u, sid_hi, key0, key1);
         }
     };
+    // the same for tensors of fewer than 2^32 quads: the counter's upper word is the constant zero, so the first round's
+    // product of the stream id and the second round's of what it leads to are worked out once per wave (two of twenty)
+    const bool low_counters = n < (uint64_t{1} << 34);
+    auto blocks_of_low = [&](uint32_t q, uint4& rxy, uint4& ru) {
+        rxy = ru = make_uint4(0, 0, 0, 0);
+        if (STOCH) {
+            rxy = philox4x32_10(q, 0u, sid_xy, sid_hi, key0, key1);
+            ru = philox4x32_10(q, 0u, sid_u, sid_hi, key0, key1);
+        }
+    };
 
     uint32_t zmax = 0;
+    float fmax = 0.0f;
     const uint64_t stride = static_cast<uint64_t>(nblocks) * kAxpyThreads;
     const uint64_t first = static_cast<uint64_t>(bid) * kAxpyThreads + threadIdx.x;
     if (VEC) {
@@ -155,13 +176,19 @@ __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t
         const uint4* xv = reinterpret_cast<const uint4*>(x);
         const uint4* yv = reinterpret_cast<const uint4*>(y);
         float4* zv = reinterpret_cast<float4*>(z);
-        // The loop over whole quads, once for the usual alignment (the product sits 1..31 bits below the unit
-        // of x_hat and 2^Ex is a normal float: straight-line 32-bit code) and once for every other case; the
-        // choice is made here, outside the loop.
+        // The loop over whole quads, once for the usual case (finite tensors that are not tiny throughout, the product
+        // 1..31 bits below the unit of x_hat and 2^Ex a normal float: straight-line 32-bit code) and once for every
+        // other; the choice is made here, outside the loop.
         auto quad_loop = [&](auto usual_c) __attribute__((always_inline)) {
             constexpr bool USUAL = decltype(usual_c)::value;
             const int sh = al.right;                                   // USUAL: 1..31
             const float unit = __uint_as_float(static_cast<uint32_t>(Ex + 127) << 23);
+            // USUAL: |x| * 2^(150 - ex) is the mantissa on the scale (ex in [25, 254]: the factor is a normal float); the
+            // size and the sign of the scalar
+            const float to_x = __uint_as_float(static_cast<uint32_t>(277 - (USUAL ? ex : 150)) << 23);
+            const float to_y = __uint_as_float(static_cast<uint32_t>(277 - (USUAL ? ey : 150)) << 23);
+            const uint32_t a_mag = static_cast<uint32_t>(a_hat < 0 ? -a_hat : a_hat);
+            const float a_sign = a_hat < 0 ? -1.0f : 1.0f;
             // scale 255 (a non-finite element somewhere): the limit becomes -0 and every quad takes the full path
             const int ux = 150 - ex, uy = 150 - ey;
             const float limx = __uint_as_float(static_cast<uint32_t>(ex + 1) << 23);
@@ -176,38 +203,48 @@ __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t
                 xn = xv[qn];
                 yn = yv[qn];
                 uint4 rxy, ru;
-                blocks_of(q, rxy, ru);
+                if constexpr (USUAL) blocks_of_low(static_cast<uint32_t>(q), rxy, ru);
+                else blocks_of(q, rxy, ru);
                 const uint32_t xb[4] = {xc.x, xc.y, xc.z, xc.w}, yb[4] = {yc.x, yc.y, yc.z, yc.w};
                 const uint32_t wxy[4] = {rxy.x, rxy.y, rxy.z, rxy.w}, wu[4] = {ru.x, ru.y, ru.z, ru.w};
-                uint64_t bad = 0;                                      // wave-uniform lane mask
                 float zf[4];
+                if constexpr (USUAL) {
+                    // Every element is finite and at or below its scale (the scales are those of these tensors), so all is
+                    // done on magnitudes: the signs join with the conversion back, whose sum is exact (below 2^24) and
+                    // whose last addition turns a negative zero into the integer's zero.
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int xh = map16_fast<STOCH>(xb[k], wxy[k] >> 23, ux, limx, bad);
-                    const int yh = map16_fast<STOCH>(yb[k], (wxy[k] >> 14) & 511u, uy, limy, bad);
-                    const int p = a_hat * yh;
-                    if (USUAL) {
-                        const uint32_t m = static_cast<uint32_t>(p < 0 ? -p : p);
-                        const uint32_t up = STOCH ? (wu[k] < ((m & al.mask) << al.thr_left) ? 1u : 0u) : (m >> al.half) & 1u;
-                        const int u = static_cast<int>(min((m >> sh) + up, kUpdateSat));
-                        zf[k] = static_cast<float>(xh + (p < 0 ? -u : u)) * unit;
-                    } else {
-                        zf[k] = unmap_value(xh + update_on_grid<STOCH>(p, al, wu[k]), Ex);
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t xq = magnitude16<STOCH>(xb[k], wxy[k] >> 23, to_x);
+                        const uint32_t yq = magnitude16<STOCH>(yb[k], (wxy[k] >> 14) & 511u, to_y);
+                        const uint32_t m = __umul24(a_mag, yq);        // 15 bits each
+                        // the dropped bits, at the top of a word, against a whole random word
+                        const uint32_t up = STOCH ? (wu[k] < (m << al.thr_left) ? 1u : 0u) : (m >> al.half) & 1u;
+                        const uint32_t u = min((m >> sh) + up, kUpdateSat);
+                        const float fx = copysignf(static_cast<float>(xq), __uint_as_float(xb[k]));
+                        const float fu = copysignf(static_cast<float>(u), __uint_as_float(yb[k]));
+                        zf[k] = fmaf(fmaf(fu, a_sign, fx), unit, 0.0f);
+                    }
+                } else {
+                    uint64_t bad = 0;                                  // wave-uniform lane mask
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int xh = map16_fast<STOCH>(xb[k], wxy[k] >> 23, ux, limx, bad);
+                        const int yh = map16_fast<STOCH>(yb[k], (wxy[k] >> 14) & 511u, uy, limy, bad);
+                        zf[k] = unmap_value(xh + update_on_grid<STOCH>(a_hat * yh, al, wu[k]), Ex);
+                    }
+                    if (bad != 0) {           // rare: a non-finite element (or one above a scale) in this wave's quads
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) zf[k] = axpy_one<STOCH>(xb[k], yb[k], wxy[k], wu[k], ex, ey, a_hat, al, Ex);
                     }
                 }
-                if (bad != 0) {               // rare: a non-finite element (or one above a scale) in this wave's quads
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) zf[k] = axpy_one<STOCH>(xb[k], yb[k], wxy[k], wu[k], ex, ey, a_hat, al, Ex);
-                }
                 zv[q] = make_float4(zf[0], zf[1], zf[2], zf[3]);
-                zmax = max(max(zmax, __float_as_uint(zf[0]) & 0x7fffffffu),
-                           max(max(__float_as_uint(zf[1]) & 0x7fffffffu, __float_as_uint(zf[2]) & 0x7fffffffu),
-                               __float_as_uint(zf[3]) & 0x7fffffffu));
+                // (never NaN: the inverse mapping of integers)
+                fmax = fmaxf(fmaxf(fmax, fmaxf(fabsf(zf[0]), fabsf(zf[1]))), fmaxf(fabsf(zf[2]), fabsf(zf[3])));
                 xc = xn;
                 yc = yn;
             }
         };
-        if (al.left < 0 && al.right < 32 && Ex >= -126 && Ex <= 127) quad_loop(IC<true>{});
+        if (low_counters && al.left < 0 && al.right < 32 && Ex >= -126 && Ex <= 127 && ex >= 25 && ex < 255 && ey >= 25 && ey < 255) quad_loop(IC<true>{});
         else quad_loop(IC<false>{});
         const uint32_t tail = static_cast<uint32_t>(n & 3u);
         if (bid == 0 && threadIdx.x < tail) {
@@ -228,7 +265,7 @@ __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t
             zmax = max(zmax, __float_as_uint(zf) & 0x7fffffffu);
         }
     }
-    zmax = block_max(zmax, red);
+    zmax = block_max(max(zmax, __float_as_uint(fmax)), red);
     if (pz != nullptr && threadIdx.x == 0) pz[bid] = zmax;
 }
 
