@@ -263,6 +263,22 @@ __device__ inline uint4 clear_low_bytes(uint4 v, int n) {
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// one product of a launch that may hold two
+struct Product {
+    const int8_t* A = nullptr;
+    const int8_t* B = nullptr;
+    void* C = nullptr;
+    int64_t lda = 0, ldb = 0, ldc = 0;
+    int M = 0, N = 0, K = 0;
+    const int32_t* eA = nullptr;
+    const int32_t* eB = nullptr;
+    int bitsA = 8, bitsB = 8;
+    uint32_t* amax = nullptr;
+    int64_t batch_a = 0, batch_b = 0, batch_c = 0;
+    int tiles_m = 0, tiles_n = 0;
+    unsigned tiles = 0;      // 0: no product
+};
+
 // Products whose operands the direct-to-LDS kernels cannot take (rows that are not 16-byte aligned, or a contraction
 // that is no multiple of 16): tiles are staged through registers, two steps ahead of the multiplication, into two LDS
 // buffers.  A 16-byte piece is one load at whatever byte address its row starts (the ragged shapes pay in cache-line
@@ -276,7 +292,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
     const int8_t* __restrict__ A, int64_t lda, const int8_t* __restrict__ B, int64_t ldb, void* __restrict__ Cv,
     int64_t ldc, int M, int N, int K, int k_per_split, const int32_t* __restrict__ eA, int bitsA,
     const int32_t* __restrict__ eB, int bitsB, int tiles_m, int tiles_n, int group_m, int64_t split_stride,
-    int64_t batch_a, int64_t batch_b, int64_t batch_c, uint32_t* __restrict__ amax, ReduceRider rider) {
+    int64_t batch_a, int64_t batch_b, int64_t batch_c, uint32_t* __restrict__ amax, ReduceRider rider, Product two) {
     int tile_block = static_cast<int>(blockIdx.x);
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
@@ -285,6 +301,18 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
+    }
+    if (two.tiles != 0 && tile_block >= tiles_m * tiles_n) {      // workgroup-uniform: a tile of the second product
+        tile_block -= tiles_m * tiles_n;
+        A = two.A; B = two.B; Cv = two.C;
+        lda = two.lda; ldb = two.ldb; ldc = two.ldc;
+        M = two.M; N = two.N; K = two.K;
+        k_per_split = two.K;
+        eA = two.eA; eB = two.eB;
+        bitsA = two.bitsA; bitsB = two.bitsB;
+        amax = two.amax;
+        batch_a = two.batch_a; batch_b = two.batch_b; batch_c = two.batch_c;
+        tiles_m = two.tiles_m; tiles_n = two.tiles_n;
     }
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
     constexpr int CPR = BK / 16;
@@ -415,6 +443,93 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
         publish_absmax(store_fragments<FM, FN, MODE, true>(acc, Cv, ldc, M, N, m0 + wm0, n0 + wn0, fhalf, frow, E), amax);
     else
         store_fragments<FM, FN, MODE, false>(acc, Cv, ldc, M, N, m0 + wm0, n0 + wn0, fhalf, frow, E);
+}
+
+// Products too small to fill the chip with LDS-staged tiles, up to two of them per launch.  What bounds those is the
+// latency of one workgroup: launch, first loads, a barrier per K step.  Here a wave loads its MFMA operands straight
+// from memory - 16 bytes of 32 rows, any alignment - with 8 steps of 32 in flight and no barrier; the four waves of a
+// workgroup share one 32 x 32 tile and take every fourth step (together whole 128-byte lines), and their sums meet in LDS
+// once.  The last, partial piece of a row is read as the row's last 16 bytes, as in k_gemm_nt: K >= 16.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_gemm_nt_direct(Product p0, Product p1, ReduceRider rider) {
+    if (rider.blocks != 0 && blockIdx.x >= rider.tiles) {          // workgroup-uniform: the last workgroups
+        splitk_reduce_body(rider, blockIdx.x - rider.tiles, rider.blocks);
+        return;
+    }
+    const bool second = blockIdx.x >= p0.tiles;
+    const Product& p = second ? p1 : p0;
+    constexpr int U = 8;                                           // steps in flight
+    __shared__ int32_t sums[3][4][4][64];                          // [source][destination wave][register][lane]
+    int tm, tn;
+    tile_of_block(static_cast<int>(blockIdx.x - (second ? p0.tiles : 0u)), p.tiles_m, p.tiles_n, 8, &tm, &tn);
+    const int m0 = tm * 32, n0 = tn * 32, K = p.K;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int frow = lane & 31, fhalf = lane >> 5;
+    const int8_t* pa = p.A + static_cast<int64_t>(min(m0 + frow, p.M - 1)) * p.lda;
+    const int8_t* pb = p.B + static_cast<int64_t>(min(n0 + frow, p.N - 1)) * p.ldb;
+    v16i acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0;
+    auto as_frag = [](const uint4& v) {
+        v4i f;
+        f[0] = static_cast<int>(v.x); f[1] = static_cast<int>(v.y); f[2] = static_cast<int>(v.z); f[3] = static_cast<int>(v.w);
+        return f;
+    };
+    const int whole = K / 32;                                      // steps that lie inside every row
+    for (int s0 = wave; s0 < whole; s0 += 4 * U) {
+        uint4 a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + 4 * u >= whole) break;                        // wave-uniform
+            const int k = 32 * (s0 + 4 * u) + 16 * fhalf;
+            a[u] = load16(pa + k);
+            b[u] = load16(pb + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + 4 * u >= whole) break;
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_frag(a[u]), as_frag(b[u]), acc, 0, 0, 0);
+        }
+    }
+    if (32 * whole < K && wave == (whole & 3)) {                   // the last, partial step
+        const int k = 32 * whole + 16 * fhalf, from = min(k, K - 16);
+        uint4 a = load16(pa + from);
+        const uint4 b = load16(pb + from);
+        if (k >= K) a = make_uint4(0, 0, 0, 0);
+        else if (from < k) a = clear_low_bytes(a, k - from);
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_frag(a), as_frag(b), acc, 0, 0, 0);
+    }
+    // wave w finishes registers 4 w .. 4 w + 3: rows 8 w + 4 * (l / 32) + 0 .. 3
+    int own[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int src = wave < w ? wave : wave - 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (w == wave) own[r] = acc[4 * w + r];                // wave-uniform
+            else sums[src][w][r][lane] = acc[4 * w + r];
+        }
+    }
+    __syncthreads();
+    int E = 0;
+    if (MODE == kStoreF32) E = lsb_exponent(p.eA[0], p.bitsA) + (p.eB ? lsb_exponent(p.eB[0], p.bitsB) : 0);
+    float m = 0.0f;
+    const int col = n0 + frow;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int sum = own[r] + sums[0][wave][r][lane] + sums[1][wave][r][lane] + sums[2][wave][r][lane];
+        const int row = m0 + 8 * wave + 4 * fhalf + r;
+        if (row >= p.M || col >= p.N) continue;
+        const int64_t off = static_cast<int64_t>(row) * p.ldc + col;
+        if (MODE == kStoreF32) {
+            const float v = unmap_value(sum, E);
+            static_cast<float*>(p.C)[off] = v;
+            m = fmaxf(m, fabsf(v));
+        } else {
+            static_cast<int32_t*>(p.C)[off] = sum;
+        }
+    }
+    if (MODE == kStoreF32 && p.amax != nullptr) publish_absmax(m, p.amax);
 }
 
 // s_waitcnt immediate (gfx9 encoding): wait until at most `vm` vector-memory operations
@@ -926,7 +1041,7 @@ template <int BM, int BN, int BK, int WM, int WN>
 static int launch_cfg(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, const int8_t* B, int64_t ldb,
                       void* C, int64_t ldc, int mode, int splits, const int32_t* eA, int bitsA,
                       const int32_t* eB, int bitsB, hipStream_t s, int64_t split_stride = 0, int* slices = nullptr,
-                      Batch bt = Batch(), uint32_t* amax = nullptr, ReduceRider* ride = nullptr) {
+                      Batch bt = Batch(), uint32_t* amax = nullptr, ReduceRider* ride = nullptr, const Product& two = Product()) {
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
     const int tiles_m = static_cast<int>((M + BM - 1) / BM), tiles_n = static_cast<int>((N + BN - 1) / BN);
     int k_per_split = static_cast<int>((K + splits - 1) / splits);
@@ -941,12 +1056,12 @@ static int launch_cfg(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t 
         rider.front = rider.tiles >= 512;                       // several rounds of tiles: ride in the first one
         ride->blocks = 0;                                       // taken
     }
-    const dim3 grid(static_cast<unsigned>(tiles_m) * tiles_n + rider.blocks, ny, bt.count), block(NT);
+    const dim3 grid(static_cast<unsigned>(tiles_m) * tiles_n + two.tiles + rider.blocks, ny, bt.count), block(NT);
     const int group_m = 8;
 #define FXP_GEMM_LAUNCH(WIDE, MODE)                                                                                \
     hipLaunchKernelGGL((k_gemm_nt<BM, BN, BK, WM, WN, WIDE, MODE>), grid, block, 0, s, A, lda, B, ldb, C, ldc,       \
                        static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), k_per_split, eA, bitsA, eB,   \
-                       bitsB, tiles_m, tiles_n, group_m, split_stride, bt.a, bt.b, bt.c, amax, rider)
+                       bitsB, tiles_m, tiles_n, group_m, split_stride, bt.a, bt.b, bt.c, amax, rider, two)
     if (K >= 16) {
         if (mode == kStoreI32) FXP_GEMM_LAUNCH(true, kStoreI32);
         else if (mode == kStoreF32) FXP_GEMM_LAUNCH(true, kStoreF32);
@@ -1104,6 +1219,68 @@ static bool small_tiles(int64_t M, int64_t N, int64_t count) {
     return ((M + 127) / 128) * ((N + 127) / 128) * count < 512;
 }
 
+// Products that k_gemm_nt_direct takes: at most one 32 x 32 tile per CU, at most one round of loads per wave.  Measured
+// with a launch behind a launch against the LDS-staged kernels: 197 x 768 x 768 5.1 us for 6.5, 1 x 3072 x 768 4.6 for
+// 6.5, 512 x 512 x 512 5.2 for 5.6; but 197 x 3072 x 768 7.8 for 6.8 and 197 x 768 x 3072 (four rounds) 11.5 for 11.1:
+// every load instruction touches 32 rows.
+static bool direct_fits(int64_t M, int64_t N, int64_t K) {
+    return K >= 16 && K <= 1024 && ((M + 63) / 64) * ((N + 63) / 64) <= 64;
+}
+
+static Product make_product(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, const int8_t* B, int64_t ldb, void* C,
+                            int64_t ldc, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, uint32_t* amax, int tile) {
+    Product p;
+    p.A = A; p.B = B; p.C = C;
+    p.lda = lda; p.ldb = ldb; p.ldc = ldc;
+    p.M = static_cast<int>(M); p.N = static_cast<int>(N); p.K = static_cast<int>(K);
+    p.eA = eA; p.eB = eB; p.bitsA = bitsA; p.bitsB = bitsB;
+    p.amax = amax;
+    p.tiles_m = static_cast<int>((M + tile - 1) / tile);
+    p.tiles_n = static_cast<int>((N + tile - 1) / tile);
+    p.tiles = static_cast<unsigned>(p.tiles_m) * p.tiles_n;
+    return p;
+}
+
+static int launch_direct(const Product& p0, const Product& p1, bool fp32_out, hipStream_t s, ReduceRider* ride = nullptr) {
+    ReduceRider rider;
+    if (ride != nullptr && ride->blocks != 0) {
+        rider = *ride;
+        rider.tiles = p0.tiles + p1.tiles;
+        ride->blocks = 0;                                       // taken
+    }
+    const dim3 grid(p0.tiles + p1.tiles + rider.blocks), block(256);
+    if (fp32_out) hipLaunchKernelGGL((k_gemm_nt_direct<kStoreF32>), grid, block, 0, s, p0, p1, rider);
+    else hipLaunchKernelGGL((k_gemm_nt_direct<kStoreI32>), grid, block, 0, s, p0, p1, rider);
+    return launch_status();
+}
+
+// Two independent products with fp32 outputs (the gradients of one layer, or of `batch` matrices each) in one launch, where
+// both take the same small-product kernel; kNotApplicable: one launch each.  Such launches wait for each other longer
+// than they run (a launch behind a launch takes 4.5 us), and neither fills the chip: the gradients of a 1379 x 768 x 1000
+// layer 13.7 + 8.7 -> 13.4 us, of 256 x 256 x 256 4.7 + 4.6 -> 4.9, the second pair of 96 x (197 x 64 x 197) 6.5 + 6.9 -> 7.9.
+int gemm_nt_pair_launch(const GemmArgs& a, const GemmArgs& b, int64_t batch, hipStream_t s) {
+    auto product = [](const GemmArgs& g, int tile) {
+        Product p = make_product(g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.eA, g.bitsA, g.eB, g.bitsB, nullptr, tile);
+        p.batch_a = g.strideA; p.batch_b = g.strideB; p.batch_c = g.strideC;
+        return p;
+    };
+    if (batch == 1 && direct_fits(a.M, a.N, a.K) && direct_fits(b.M, b.N, b.K))
+        return launch_direct(product(a, 32), product(b, 32), true, s);
+    auto staged = [&](const GemmArgs& g) {
+        const bool vec = aligned(g.A, 16) && aligned(g.B, 16) && g.lda % 16 == 0 && g.ldb % 16 == 0 && g.K % 16 == 0 &&
+                         (batch == 1 || (g.strideA % 16 == 0 && g.strideB % 16 == 0));
+        return !(vec && g.K >= 64) && g.K >= 16 && g.K <= kMaxContraction && small_tiles(g.M, g.N, batch) &&
+               (batch > 1 || (plan_gemm(g.M, g.N, g.K).splits == 1 && !direct_fits(g.M, g.N, g.K)));
+    };
+    if (!staged(a) || !staged(b)) return kNotApplicable;
+    const Product two = product(b, 64);
+    Batch bt;
+    bt.count = static_cast<unsigned>(batch);
+    bt.a = a.strideA; bt.b = a.strideB; bt.c = a.strideC;
+    return launch_cfg<64, 64, 128, 32, 32>(a.M, a.N, a.K, a.A, a.lda, a.B, a.ldb, a.C, a.ldc, kStoreF32, 1, a.eA, a.bitsA, a.eB,
+                                           a.bitsB, s, 0, nullptr, bt, nullptr, nullptr, two);
+}
+
 // `batch` products of one shape in one launch (grid.z), never split along K.
 int gemm_nt_batched_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, int64_t strideA,
                            const int8_t* B, int64_t ldb, int64_t strideB, void* C, int64_t ldc, int64_t strideC,
@@ -1169,6 +1346,8 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
                    void* ws, size_t ws_bytes, hipStream_t s, uint32_t* amax, ReduceRider* ride, ReduceRider* defer) {
     if (M == 0 || N == 0) return FXP_OK;
     if (!fp32_out) amax = nullptr;
+    if (direct_fits(M, N, K))
+        return launch_direct(make_product(M, N, K, A, lda, B, ldb, C, ldc, eA, bitsA, eB, bitsB, amax, 32), Product(), fp32_out, s, ride);
     uint32_t* amax1 = nullptr;      // the product kernel publishes the maximum itself only when it writes the final fp32
     const bool vec = aligned(A, 16) && aligned(B, 16) && lda % 16 == 0 && ldb % 16 == 0 && K % 16 == 0;
     const bool dma = vec && K >= 64;   // K % 16 == 0: the direct-to-LDS kernels pad a partial last step with zeros

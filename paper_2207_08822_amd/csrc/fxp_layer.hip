@@ -230,6 +230,14 @@ static int linear_bwd_impl(const float* dY, const fxp_saved* saved, int64_t M, i
     }
     uint8_t* rest = static_cast<uint8_t*>(ws) + round_up(kScaleWsBytes, 256);
     const size_t rest_bytes = ws_bytes - round_up(kScaleWsBytes, 256);
+    if (dX && dW) {                                    // both gradients in one launch where they are small
+        const GemmArgs gW{K, N, M, saved->XqT, M, 0, dYqT, M, 0, dW, N, 0, saved->eX, bits, e_dY, bits};
+        const GemmArgs gX{M, K, N, dYq, N, 0, saved->Wq, N, 0, dX, K, 0, e_dY, bits, saved->eW, bits};
+        if ((rc = gemm_nt_pair_launch(gW, gX, 1, s)) != kNotApplicable) {
+            timeline_mark(s, FXP_TL_GEMM_DX);
+            return rc;
+        }
+    }
     // The weight gradient first: when it is split along K, the sum of its slices does not get a launch of its own
     // but rides in the launch of the input-gradient product (whose last workgroups do it) - unless that product
     // is split too and needs the slice area for itself.
@@ -393,23 +401,17 @@ static int bmm_bwd_impl(const float* dY, const fxp_bmm_saved* saved, int64_t bat
                                static_cast<uint32_t*>(ws), s);
         if (rc) return rc;
     }
-    if (dA) {
-        const int8_t* Bop = transB ? saved->BqT : saved->Bq;      // [K,N] per matrix, N contiguous
-        const int64_t ldb = transB ? batch * N : N, strideB = transB ? N : K * N;
-        if ((rc = gemm_nt_batched_launch(M, K, N, dYq, N, M * N, Bop, ldb, strideB, dA, K, M * K, batch, true, e_dY, bits,
-                                         saved->eB, bits, s)))
+    // dA: B as [K,N] per matrix, N contiguous; dBm: both operands are column blocks of a transposed copy
+    const int64_t ld = batch * M;
+    const GemmArgs gA{M, K, N, dYq, N, M * N, transB ? saved->BqT : saved->Bq, transB ? batch * N : N, transB ? N : K * N,
+                      dA, K, M * K, e_dY, bits, saved->eB, bits};
+    const GemmArgs gB = transB ? GemmArgs{N, K, M, dYqT, ld, M, saved->AqT, ld, M, dBm, K, N * K, e_dY, bits, saved->eA, bits}
+                               : GemmArgs{K, N, M, saved->AqT, ld, M, dYqT, ld, M, dBm, N, K * N, saved->eA, bits, e_dY, bits};
+    if (dA && dBm && (rc = gemm_nt_pair_launch(gA, gB, batch, s)) != kNotApplicable) return rc;
+    for (const GemmArgs* g : {dA ? &gA : nullptr, dBm ? &gB : nullptr})
+        if (g && (rc = gemm_nt_batched_launch(g->M, g->N, g->K, g->A, g->lda, g->strideA, g->B, g->ldb, g->strideB, g->C, g->ldc,
+                                              g->strideC, batch, true, g->eA, g->bitsA, g->eB, g->bitsB, s)))
             return rc;
-    }
-    if (dBm) {
-        const int64_t ld = batch * M;                              // both operands are column blocks of a transposed copy
-        if (transB)
-            rc = gemm_nt_batched_launch(N, K, M, dYqT, ld, M, saved->AqT, ld, M, dBm, K, N * K, batch, true, e_dY, bits,
-                                        saved->eA, bits, s);
-        else
-            rc = gemm_nt_batched_launch(K, N, M, saved->AqT, ld, M, dYqT, ld, M, dBm, N, K * N, batch, true, saved->eA, bits,
-                                        e_dY, bits, s);
-        if (rc) return rc;
-    }
     return FXP_OK;
 }
 }  // namespace fxp

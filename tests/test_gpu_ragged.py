@@ -92,3 +92,50 @@ def test_map_rows_off_the_quad_grid(fxp, rows, cols, offset):
     torch.cuda.synchronize()
     assert np.array_equal(host(q)[3 * offset:].reshape(rows, cols), want)
     assert not host(q)[:3 * offset].any()
+
+
+# products of at most one 32 x 32 tile per CU and at most 1024 terms: tile edges, contractions of one piece up to the
+# longest, every residue of the 32-byte steps over the four waves; and the sizes just beyond
+@pytest.mark.parametrize("M,N,K", [(1, 1, 16), (31, 33, 17), (32, 32, 32), (64, 64, 128), (33, 65, 159), (256, 256, 256), (512, 512, 1024),
+                                   (511, 513, 96), (1, 4096, 1023), (70, 31, 1024), (70, 31, 1025), (520, 520, 64)])
+def test_small_gemm(fxp, M, N, K):
+    say("small gemm", (M, N, K))
+    rng = np.random.default_rng(M * 31 + N * 7 + K)
+    A, B = rand_i8(rng, (M, K)), rand_i8(rng, (N, K))
+    want = oracle.gemm(A, B, transB=True)
+    assert np.array_equal(host(fxp.gemm(dev(A), dev(B), transB=True)), want)
+    e = dev(np.array([3, 5], np.int32))                               # a sub-normal unit
+    assert same_bits(host(fxp.gemm_unmap(dev(A), dev(B), e[0:1], e[1:2], transB=True)), oracle.unmap(want, 3, 5))
+    absmax = torch.zeros(fxp.ABSMAX_WORDS, dtype=torch.int32, device="cuda")
+    C = host(fxp.gemm_unmap_absmax(dev(A), dev(B), dev(np.array([121], np.int32)), dev(np.array([130], np.int32)), absmax, transB=True))
+    assert same_bits(C, oracle.unmap(want, 121, 130))
+    assert int(host(absmax).max()) == int(np.abs(C).max().view(np.uint32))
+
+
+# both gradients of a layer in one launch: small products, register-staged ones (odd rows), one of each kind (two launches)
+@pytest.mark.parametrize("M,K,N", [(32, 64, 64), (256, 256, 256), (100, 96, 64), (1379, 768, 1000), (200, 130, 514), (17, 16, 19), (300, 768, 33),
+                                   (16, 16, 15)])
+def test_layer_gradients_in_one_launch(fxp, M, K, N):
+    say("layer gradients", (M, K, N))
+    rng = np.random.default_rng(M + K + N)
+    X, W, dY = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N), (M, N)))
+    buf = fxp.LayerBuffers(M, K, N)
+    Y = fxp.linear_fwd(dev(X), dev(W), buf, seed=2, step=3)
+    dX, dW = fxp.linear_bwd(dev(dY), buf, seed=2, step=3)
+    Yo, saved = oracle.linear_fwd(X, W, seed=2, step=3)
+    dXo, dWo, _ = oracle.linear_bwd(dY, saved, seed=2, step=3)
+    assert same_bits(host(Y), Yo) and same_bits(host(dX), dXo) and same_bits(host(dW), dWo)
+
+
+@pytest.mark.parametrize("batch,M,K,N,transB", [(96, 197, 64, 197, True), (3, 50, 33, 70, False), (7, 65, 80, 97, True), (2, 16, 16, 16, False)])
+def test_bmm_gradients_in_one_launch(fxp, batch, M, K, N, transB):
+    say("bmm gradients", (batch, M, K, N, transB))
+    rng = np.random.default_rng(batch + M + K + N)
+    A, dY = rng.standard_normal((batch, M, K)).astype(np.float32), rng.standard_normal((batch, M, N)).astype(np.float32)
+    B = rng.standard_normal((batch, N, K) if transB else (batch, K, N)).astype(np.float32)
+    buf = fxp.BmmBuffers(batch, M, K, N, transB=transB)
+    Y = fxp.bmm_fwd(dev(A), dev(B), buf, seed=2, step=3)
+    dA, dB = fxp.bmm_bwd(dev(dY), buf, seed=2, step=3)
+    Yo, saved = oracle.bmm_fwd(A, B, transB=transB, seed=2, step=3)
+    dAo, dBo, _ = oracle.bmm_bwd(dY, saved, seed=2, step=3)
+    assert same_bits(host(Y), Yo) and same_bits(host(dA), dAo) and same_bits(host(dB), dBo)
