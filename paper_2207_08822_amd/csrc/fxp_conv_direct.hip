@@ -394,7 +394,6 @@ int conv_thin_wgrad_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M
     sum->N = p.g.K;
     sum->ldc = p.g.K;
     sum->wide = M > kMaxContraction ? 1 : 0;
-    plan_reduce(sum);
     return launch_status();
 }
 

@@ -152,7 +152,10 @@ __device__ inline float store_fragments(const v16i (&acc)[FM][FN], void* __restr
 
 // Sum of the split-K slices of a product (exact in any order) -> int32 or inverse-mapped fp32, by workgroup
 // `b` of `nb`.  The slices are dense M x N matrices `stride` elements apart.  A dense, 16-byte aligned output is
-// walked as one flat run of 16-byte pieces, anything else row by row.
+// walked as one flat run of 16-byte pieces, anything else row by row.  ALONE: a launch of its own, which may also add in
+// 64 bits and share a piece among lanes; a rider in a product's launch keeps the one plain loop (with all three inside
+// every product kernel, and twice the riders, the input gradient of a 32 x 28 x 28 x 128 3x3 layer took 14.0 us for 11.3).
+template <bool ALONE>
 __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsigned nb) {
     const unsigned nt = blockDim.x;                  // 256 stand-alone; the host product's workgroup size when riding
     float m = 0.0f;
@@ -173,7 +176,7 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
     const int64_t total = static_cast<int64_t>(r.M) * r.N;
     const bool flat = r.ldc == r.N && (reinterpret_cast<uintptr_t>(r.C) & 15u) == 0;
     // 16-byte pieces of a flat output: `group` lanes of a wave share a piece, each sums every group-th slice, and the
-    // lanes add up by exchange (no LDS: a host product's own tiles may fill it)
+    // lanes add up by exchange
     auto pieces = [&](auto wide_c) {
         constexpr bool WIDE = decltype(wide_c)::value != 0;
         using Sum = typename std::conditional<WIDE, int64_t, int>::type;
@@ -206,7 +209,7 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
             }
         }
     };
-    if (r.wide) {
+    if (ALONE && r.wide) {
         // contraction beyond what one int32 sum holds: 64-bit sums of the slices
         int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x;
         if (flat) {
@@ -221,8 +224,28 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
             m = fmaxf(m, fabsf(o));
         }
     } else if (flat) {
-        pieces(IC<0>{});
         const int64_t nvec = total >> 2;
+        if (ALONE && r.group > 1) {
+            pieces(IC<0>{});
+        } else {
+            for (int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x; i < nvec; i += static_cast<int64_t>(nb) * nt) {
+                int4 acc = make_int4(0, 0, 0, 0);
+#pragma unroll 8
+                for (int sidx = 0; sidx < splits; ++sidx) {
+                    const int4 v = reinterpret_cast<const int4*>(parts + sidx * stride)[i];
+                    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+                }
+                if (r.fp32_out) {
+                    float4 o;
+                    o.x = unmap_value(acc.x, E); o.y = unmap_value(acc.y, E);
+                    o.z = unmap_value(acc.z, E); o.w = unmap_value(acc.w, E);
+                    reinterpret_cast<float4*>(r.C)[i] = o;
+                    m = fmaxf(fmaxf(m, fmaxf(fabsf(o.x), fabsf(o.y))), fmaxf(fabsf(o.z), fabsf(o.w)));
+                } else {
+                    reinterpret_cast<int4*>(r.C)[i] = acc;
+                }
+            }
+        }
         if (b == 0 && threadIdx.x < (total & 3)) {                 // the slices are 16-byte aligned, the tail is not a piece
             const int64_t i = (nvec << 2) + threadIdx.x;
             int acc = 0;
@@ -297,7 +320,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
         if (blockIdx.x >= first && blockIdx.x < first + rider.blocks) {
-            splitk_reduce_body(rider, blockIdx.x - first, rider.blocks);
+            splitk_reduce_body<false>(rider, blockIdx.x - first, rider.blocks);
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
@@ -453,7 +476,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
 template <int MODE>
 __global__ __launch_bounds__(256) void k_gemm_nt_direct(Product p0, Product p1, ReduceRider rider) {
     if (rider.blocks != 0 && blockIdx.x >= rider.tiles) {          // workgroup-uniform: the last workgroups
-        splitk_reduce_body(rider, blockIdx.x - rider.tiles, rider.blocks);
+        splitk_reduce_body<false>(rider, blockIdx.x - rider.tiles, rider.blocks);
         return;
     }
     const bool second = blockIdx.x >= p0.tiles;
@@ -569,7 +592,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt_dma(
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
         if (blockIdx.x >= first && blockIdx.x < first + rider.blocks) {
-            splitk_reduce_body(rider, blockIdx.x - first, rider.blocks);
+            splitk_reduce_body<false>(rider, blockIdx.x - first, rider.blocks);
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
@@ -799,7 +822,7 @@ __global__ __launch_bounds__((256 / WM) * (256 / WN) * 64) void k_gemm_nt_ring(
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
         if (blockIdx.x >= first && blockIdx.x < first + rider.blocks) {
-            splitk_reduce_body(rider, blockIdx.x - first, rider.blocks);
+            splitk_reduce_body<false>(rider, blockIdx.x - first, rider.blocks);
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
@@ -1138,19 +1161,21 @@ static int launch_dma(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t 
     return launch_status();
 }
 
-__global__ __launch_bounds__(256) void k_splitk_reduce(ReduceRider r) { splitk_reduce_body(r, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void k_splitk_reduce(ReduceRider r) { splitk_reduce_body<true>(r, blockIdx.x, gridDim.x); }
 
-// Lanes per 16-byte piece of the output and workgroups of a reduction.  One lane a piece while the pieces alone fill the
-// chip or the slices are few; else up to sixteen lanes, each with eight slices or more (a 64 x 147 output of 126 slices:
-// ten workgroups walked all slices in turn, 123 us; 256 slices now 9 us).  256 threads per workgroup, at most 2048 workgroups.
-void plan_reduce(ReduceRider* r) {
-    const int64_t pieces = std::max<int64_t>(1, static_cast<int64_t>(r->M) * r->N / 4);
-    r->group = 1;
-    while (r->group < 16 && r->splits >= 16 * r->group && pieces * r->group < 65536) r->group *= 2;
-    r->blocks = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (pieces * r->group + 255) / 256)));
+// workgroups of a reduction with `lanes` lanes per 16-byte piece of the output: 256 threads each, at most 2048
+static unsigned reduce_blocks(const ReduceRider& r, int lanes) {
+    const int64_t pieces = static_cast<int64_t>(r.M) * r.N / 4;
+    return static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (pieces * lanes + 255) / 256)));
 }
 
-int splitk_reduce_launch(const ReduceRider& r, hipStream_t s) {
+// One lane a piece while the pieces alone fill the chip or the slices are few; else up to sixteen lanes, each with eight
+// slices or more (a 64 x 147 output of 126 slices: ten workgroups walked all slices in turn, 123 us; 256 slices now 9 us).
+int splitk_reduce_launch(ReduceRider r, hipStream_t s) {
+    const int64_t pieces = static_cast<int64_t>(r.M) * r.N / 4;
+    r.group = 1;
+    while (r.group < 16 && r.splits >= 16 * r.group && pieces * r.group < 65536) r.group *= 2;
+    r.blocks = reduce_blocks(r, r.group);
     hipLaunchKernelGGL(k_splitk_reduce, dim3(r.blocks), dim3(256), 0, s, r);
     return launch_status();
 }
@@ -1416,8 +1441,8 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         r.eA = eA; r.bitsA = bitsA; r.eB = eB; r.bitsB = bitsB;
         r.amax = amax;
         r.wide = K > kMaxContraction ? 1 : 0;
-        plan_reduce(&r);
-        if (defer != nullptr) {
+        if (defer != nullptr && !r.wide) {                      // riders add in 32 bits
+            r.blocks = reduce_blocks(r, 1);
             *defer = r;
             return FXP_OK;
         }

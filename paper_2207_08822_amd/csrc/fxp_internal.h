@@ -85,7 +85,7 @@ struct ReduceRider {
     int bitsB = 8;
     uint32_t* amax = nullptr;
     int wide = 0;            // the contraction is longer than kMaxContraction: the slices are added in 64 bits
-    int group = 1;           // lanes that share a 16-byte piece of the output (a power of two, see plan_reduce)
+    int group = 1;           // lanes that share a 16-byte piece of the output (a power of two; a rider's is 1)
     unsigned blocks = 0;
     unsigned tiles = 0;      // set by the launcher: workgroups of the host product
     bool front = false;      // set by the launcher: riders before the tiles
@@ -125,8 +125,7 @@ int conv_thin_fwd_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, 
 bool conv_thin_wgrad_fits(const ConvTaps& ct, int KH, int64_t images, int64_t Cout, size_t part_bytes);
 int conv_thin_wgrad_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, int64_t Cout, const int8_t* Xq,
                            const int8_t* dYqT, void* parts, size_t part_bytes, ReduceRider* sum, hipStream_t s);
-void plan_reduce(ReduceRider* r);      // fills group and blocks from the output's size and the number of slices
-int splitk_reduce_launch(const ReduceRider& r, hipStream_t s);
+int splitk_reduce_launch(ReduceRider r, hipStream_t s);      // chooses group and blocks itself
 size_t gemm_ws_worst(int64_t M, int64_t N, int64_t K);
 int transpose_i8_launch(const int8_t* src, int64_t rows, int64_t cols, int64_t ld, int8_t* dst, hipStream_t s);
 
