@@ -7,6 +7,7 @@
 //             dW[Cout,K] = unmap(dYqT * colT^T) with colT[K,M] rebuilt from the saved int8 X,
 //             dX: for stride 1 it is itself a convolution - im2col of dYq (padded by K-1-pad) times the
 //             flipped weights WqF, inverse mapping fused in the GEMM; for other strides
+//             the same per class of input pixels (StrideClasses: stride 2), or
 //             dcol[M,K] = dYq * Wq (int32) and dX = unmap(col2im(dcol)) as a gather: every input
 //             pixel sums the <= KH*KW patch entries that read it, so no atomics are needed.
 // The saved state of a layer is the int8 activation itself (1 byte per element), not its patches.
@@ -79,11 +80,32 @@ __global__ __launch_bounds__(256) void k_im2col_i8(const int8_t* __restrict__ Xq
 }
 
 // WqF[c][(kh', kw', co)] = Wq[co][(KH-1-kh', KW-1-kw', c)]: the weights of the stride-1 input-gradient
-// convolution (the upstream gradient correlated with the flipped kernel), contraction-contiguous
+// convolution (the upstream gradient correlated with the flipped kernel), contraction-contiguous.
+// Strides > 1: one such array per class of input pixels, [C][TH][TW][Cout] of the taps kh = rh + stride * (TH - 1 - i),
+// kw = rw + stride * (TW - 1 - j), class (rh, rw) after class.
+__host__ __device__ inline int class_taps(int k, int r, int stride) { return (k - r + stride - 1) / stride; }   // r < stride
+
 __device__ inline void flip_weights_body(const int8_t* __restrict__ Wq, const ConvGeo& g, int8_t* __restrict__ WqF, unsigned bid,
                                          unsigned nblocks) {
     const int64_t K = g.K(), Kf = static_cast<int64_t>(g.KH) * g.KW * g.Cout, total = static_cast<int64_t>(g.C) * Kf;
     for (int64_t id = static_cast<int64_t>(bid) * 256 + threadIdx.x; id < total; id += static_cast<int64_t>(nblocks) * 256) {
+        if (g.stride > 1) {
+            int64_t at = id;
+            for (int cls = 0; cls < g.stride * g.stride; ++cls) {
+                const int rh = cls / g.stride, rw = cls - rh * g.stride;
+                const int th = class_taps(g.KH, rh, g.stride), tw = class_taps(g.KW, rw, g.stride), kc = th * tw * g.Cout;
+                if (at >= static_cast<int64_t>(g.C) * kc) {
+                    at -= static_cast<int64_t>(g.C) * kc;
+                    continue;
+                }
+                const int c = static_cast<int>(at / kc), rem = static_cast<int>(at - static_cast<int64_t>(c) * kc);
+                const int tap = rem / g.Cout, co = rem - tap * g.Cout, i = tap / tw, j = tap - i * tw;
+                const int kh = rh + g.stride * (th - 1 - i), kw = rw + g.stride * (tw - 1 - j);
+                WqF[id] = Wq[co * K + static_cast<int64_t>(kh * g.KW + kw) * g.C + c];
+                break;
+            }
+            continue;
+        }
         const int c = static_cast<int>(id / Kf);
         const int rem = static_cast<int>(id - c * Kf);
         const int tap = rem / g.Cout, co = rem - tap * g.Cout;
@@ -293,6 +315,43 @@ static ConvGeo dx_geo(const ConvGeo& g) {
     return d;
 }
 
+// the classes of input pixels of a strided convolution: pixel h meets taps kh = (h + pad) mod stride + stride * k at
+// gradient row (h + pad - kh) / stride
+static StrideClasses classes_of(const ConvGeo& g) {
+    StrideClasses sc;
+    sc.H = g.Ho; sc.W = g.Wo; sc.C = g.Cout;
+    sc.outH = g.H; sc.outW = g.W; sc.stride = g.stride;
+    int64_t first = 0;
+    // remainder r along one axis of `size` pixels: first pixel and count of the class, and its padding
+    auto axis = [&](int size, int k, int pad, int r, int* p0, int* count, int* taps, int* cpad) {
+        const int q = pad > r ? (pad - r + g.stride - 1) / g.stride : 0;       // (pixel + pad) / stride at the first pixel
+        *p0 = g.stride * q + r - pad;
+        *count = *p0 < size ? (size - 1 - *p0) / g.stride + 1 : 0;
+        *taps = class_taps(k, r, g.stride);
+        *cpad = *taps - 1 - q;
+    };
+    for (int c = 0; c < g.stride * g.stride; ++c) {
+        StrideClass& k = sc.cls[c];
+        axis(g.H, g.KH, g.pad, c / g.stride, &k.h0, &k.Ho, &k.TH, &k.pad);
+        axis(g.W, g.KW, g.padw, c % g.stride, &k.w0, &k.Wo, &k.TW, &k.padw);
+        k.w_first = first;
+        first += static_cast<int64_t>(g.C) * k.TH * k.TW * g.Cout;
+    }
+    return sc;
+}
+
+// Strided input gradients without the patch-gradient matrix, the class weights in the last bytes of the workspace behind
+// whatever the weight gradient keeps there.  Fewer than 32 channels leave most of a 128-column tile empty and the matrix
+// of a thin image is small.
+static bool dx_strided(const ConvGeo& g, bool with_dw, size_t area_bytes, size_t* wc_at) {
+    if (g.stride == 1 || g.stride > kMaxStride || g.C < 32 || !conv_strided_dx_fits(classes_of(g), g.N)) return false;
+    const size_t wc = round_up(static_cast<size_t>(g.C) * g.KH * g.KW * g.Cout, 256);
+    const size_t dw = with_dw ? round_up(static_cast<size_t>(g.K()) * g.M(), 256) + gemm_split_ws_bytes(g.Cout, g.K(), g.M()) : 0;
+    if (area_bytes < dw + wc + 256) return false;
+    *wc_at = (area_bytes - wc) / 256 * 256;
+    return true;
+}
+
 static ConvTaps taps_of(const ConvGeo& g) {
     ConvTaps t;
     t.H = g.H; t.W = g.W; t.C = g.C; t.KW = g.KW; t.stride = g.stride; t.pad = g.pad; t.padw = g.padw; t.Ho = g.Ho; t.Wo = g.Wo;
@@ -425,11 +484,14 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
                                    reinterpret_cast<uint32_t*>(w8), s))) {
         return rc;
     }
-    const bool need_flip = dX && dx_as_conv(g);
+    size_t wc_at = 0;
+    const bool strided = dX && !thin && dx_strided(g, dW != nullptr, area_bytes, &wc_at);
+    const bool need_flip = dX && (dx_as_conv(g) || strided);
+    int8_t* flipped = strided ? reinterpret_cast<int8_t*>(area + wc_at) : saved->WqF;
     ReduceRider pending;                 // the weight gradient's split-K reduction while it waits for a launch to ride in
     if (need_flip && (!dW || thin)) {
         hipLaunchKernelGGL(k_flip_weights_i8, dim3(grid_for(static_cast<int64_t>(g.Cout) * K)), dim3(256), 0, s, saved->Wq, g,
-                           saved->WqF);
+                           flipped);
         if ((rc = launch_status())) return rc;
     }
     if (thin) {
@@ -454,10 +516,10 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
         const dim3 tgrid(side.blocks + static_cast<unsigned>(blocks) + flip_blocks);
         if (quads)
             hipLaunchKernelGGL(k_im2col_t_i8<64>, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c,
-                               static_cast<unsigned>(blocks), saved->Wq, saved->WqF, side);
+                               static_cast<unsigned>(blocks), saved->Wq, flipped, side);
         else
             hipLaunchKernelGGL(k_im2col_t_i8_bytes, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c,
-                               static_cast<unsigned>(blocks), saved->Wq, saved->WqF, side);
+                               static_cast<unsigned>(blocks), saved->Wq, flipped, side);
         if ((rc = launch_status())) return rc;
         // dY: the map kernel finishes the reduction from the block maxima just written
         const MapTensor tdY{dY, M, g.Cout, nullptr, side.partials, static_cast<int>(side.blocks), e_dY, dYq, dYqT,
@@ -468,10 +530,14 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
         // (split along K: the sum of its slices rides in the launch of the input-gradient convolution when that
         // one reads its patches in the loader and leaves the workspace alone)
         if ((rc = gemm_nt_launch(g.Cout, K, M, dYqT, M, colT, M, dW, K, true, e_dY, bits, saved->eX, bits, area + used,
-                                 area_bytes - used, s, nullptr, nullptr, dX && dx_as_conv(g) ? &pending : nullptr)))
+                                 (strided ? wc_at : area_bytes) - used, s, nullptr, nullptr, need_flip ? &pending : nullptr)))
             return rc;
     }
-    if (dX && dx_as_conv(g)) {
+    if (strided) {
+        rc = conv_strided_dx_launch(classes_of(g), g.N, g.C, dYq, flipped, dX, e_dY, bits, saved->eW, bits, s, &pending);
+        if (rc == FXP_OK && pending.blocks != 0) rc = splitk_reduce_launch(pending, s);
+        if (rc) return rc;
+    } else if (dX && dx_as_conv(g)) {
         // stride 1: dX[N*H*W, C] = unmap( im2col(dYq, pad K-1-pad) * WqF^T ), the inverse mapping fused as usual
         const ConvGeo d = dx_geo(g);
         int8_t* colg = reinterpret_cast<int8_t*>(area);

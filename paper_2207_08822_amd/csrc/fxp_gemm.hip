@@ -582,12 +582,16 @@ __device__ __attribute__((aligned(256))) const uint8_t g_zero_page[256] = {0};
 // works out, per K step, which input pixel a row reads (one tap of the filter, since C % BK == 0) and takes
 // the bytes straight from the image, or from a page of zeros where the tap falls into the padding.  Nothing
 // else differs from the plain product.
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, int MODE, bool SCHED, bool CONV = false>
+//
+// Taps = StrideClasses: the input gradient of a strided convolution, all classes in one launch.  The row tiles of the
+// classes alternate (an XCD's run of tiles then holds every class of the same pixels, which read the same gradient
+// pixels, and the classes' different contraction lengths spread evenly); the epilogue scatters rows to their pixels.
+template <int BM, int BN, int BK, int WM, int WN, int STAGES, int MODE, bool SCHED, bool CONV = false, typename Taps = ConvTaps>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt_dma(
     const int8_t* __restrict__ A, int64_t lda, const int8_t* __restrict__ B, int64_t ldb, void* __restrict__ Cv,
     int64_t ldc, int M, int N, int K, int k_per_split, const int32_t* __restrict__ eA, int bitsA,
     const int32_t* __restrict__ eB, int bitsB, int tiles_m, int tiles_n, int group_m, int64_t split_stride,
-    int64_t batch_a, int64_t batch_b, int64_t batch_c, ConvTaps ct, uint32_t* __restrict__ amax, ReduceRider rider) {
+    int64_t batch_a, int64_t batch_b, int64_t batch_c, Taps taps, uint32_t* __restrict__ amax, ReduceRider rider) {
     int tile_block = static_cast<int>(blockIdx.x);
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
@@ -630,6 +634,24 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt_dma(
         else matrix = o;
         tm = t % tiles_m;
         tn = t / tiles_m;
+    }
+    constexpr bool STRIDED = std::is_same<Taps, StrideClasses>::value;
+    ConvTaps ct;
+    [[maybe_unused]] StrideClass cl{};
+    if constexpr (STRIDED) {
+        const int classes = taps.stride * taps.stride, c = tm % classes;
+        tm /= classes;
+        cl = taps.cls[c];
+        M = M * cl.Ho * cl.Wo;                                       // M: images
+        if (tm * BM >= M) return;                                    // workgroup-uniform: a class of fewer tiles
+        K = cl.TH * cl.TW * taps.C;
+        k_per_split = K;
+        B += cl.w_first;
+        ldb = K;
+        ct.H = taps.H; ct.W = taps.W; ct.C = taps.C; ct.KW = cl.TW;
+        ct.pad = cl.pad; ct.padw = cl.padw; ct.Ho = cl.Ho; ct.Wo = cl.Wo;
+    } else {
+        ct = taps;
     }
     const int m0 = tm * BM, n0 = tn * BN;
     const int kb = slice * k_per_split;
@@ -797,6 +819,30 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt_dma(
 
     int E = 0;
     if (MODE == kStoreF32) E = lsb_exponent(eA[0], bitsA) + (eB ? lsb_exponent(eB[0], bitsB) : 0);
+    if constexpr (STRIDED) {
+        // where the tile's rows go: one division chain per row, shared through LDS
+        int64_t* row_at = reinterpret_cast<int64_t*>(lds);
+        __syncthreads();                                             // every wave is past its last read of a stage
+        if (tid < BM) {
+            const uint32_t m = static_cast<uint32_t>(min(m0 + tid, M - 1));
+            const uint32_t t = m / static_cast<uint32_t>(cl.Wo), n = t / static_cast<uint32_t>(cl.Ho);
+            const int h = cl.h0 + taps.stride * static_cast<int>(t - n * cl.Ho), w = cl.w0 + taps.stride * static_cast<int>(m - t * cl.Wo);
+            row_at[tid] = ((static_cast<int64_t>(n) * taps.outH + h) * taps.outW + w) * ldc;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = wm0 + 32 * i + 8 * (r >> 2) + 4 * fhalf + (r & 3);
+                if (m0 + row >= M) continue;
+                float* out = static_cast<float*>(Cv) + row_at[row] + n0 + wn0 + frow;
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    if (n0 + wn0 + 32 * j + frow < N) __builtin_nontemporal_store(unmap_value(acc[i][j][r], E), out + 32 * j);
+            }
+        return;
+    }
     if (MODE == kStoreF32 && amax != nullptr)
         publish_absmax(store_fragments<FM, FN, MODE, true>(acc, Cv, ldc, M, N, m0 + wm0, n0 + wn0, fhalf, frow, E), amax);
     else
@@ -1486,6 +1532,45 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     // one K step = one run of channels of one filter tap: 128 channels (8 waves) where C allows, else 64 (4 waves)
     if (ct.C % 128 == 0) return conv_gemm_launch_cfg<128, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
     return conv_gemm_launch_cfg<64, 64>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+}
+
+// dX[N, H, W, C] of a strided convolution from dYq[N, Ho, Wo, Cout] and the weights in class order (StrideClasses): the
+// channels of the gradient must fill whole K steps.
+bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images) {
+    int64_t tiles = 0;
+    for (int c = 0; c < sc.stride * sc.stride; ++c) {
+        const int64_t rows = images * sc.cls[c].Ho * sc.cls[c].Wo;
+        tiles = std::max(tiles, (rows + 127) / 128 * sc.stride * sc.stride);
+    }
+    return sc.stride > 1 && sc.stride <= kMaxStride && sc.C % 64 == 0 && tiles < (int64_t{1} << 24);
+}
+
+template <int BK, int WN>
+static int conv_strided_dx_cfg(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
+                               const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
+    constexpr int BM = 128, BN = 128, WM = 64, STAGES = 4;
+    int64_t rows = 0;
+    for (int c = 0; c < sc.stride * sc.stride; ++c) rows = std::max(rows, images * sc.cls[c].Ho * sc.cls[c].Wo);
+    const int tiles_m = static_cast<int>((rows + BM - 1) / BM) * sc.stride * sc.stride, tiles_n = static_cast<int>((C + BN - 1) / BN);
+    ReduceRider rider;
+    if (ride != nullptr && ride->blocks != 0) {
+        rider = *ride;
+        rider.tiles = static_cast<unsigned>(tiles_m) * tiles_n;
+        rider.front = rider.tiles >= 512;                       // several rounds of tiles: ride in the first one
+        ride->blocks = 0;                                       // taken
+    }
+    const dim3 grid(static_cast<unsigned>(tiles_m) * tiles_n + rider.blocks), block((BM / WM) * (BN / WN) * 64);
+    hipLaunchKernelGGL((k_gemm_nt_dma<BM, BN, BK, WM, WN, STAGES, kStoreF32, true, true, StrideClasses>), grid, block, 0, s, dYq,
+                       int64_t{0}, Wc, int64_t{0}, static_cast<void*>(dX), C, static_cast<int>(images), static_cast<int>(C), 0, 0, eA,
+                       bitsA, eB, bitsB, tiles_m, tiles_n, 8, int64_t{0}, int64_t{0}, int64_t{0}, int64_t{0}, sc,
+                       static_cast<uint32_t*>(nullptr), rider);
+    return launch_status();
+}
+
+int conv_strided_dx_launch(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
+                           const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
+    if (sc.C % 128 == 0) return conv_strided_dx_cfg<128, 32>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
+    return conv_strided_dx_cfg<64, 64>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
 }
 
 // long_k: the caller can take a contraction beyond kMaxContraction (fp32 output through workspace slices)

@@ -117,6 +117,23 @@ size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t K);
 struct ConvTaps {
     int H = 0, W = 0, C = 1, KW = 1, stride = 1, pad = 0, padw = 0, Ho = 1, Wo = 1;
 };
+// Input gradient of a strided convolution: input pixels whose coordinates share their remainders modulo the stride
+// ("class") read the same filter taps, so each class is a stride-1 convolution of the gradient with its own part of
+// the filter.  Class c covers pixels (h0 + s i, w0 + s j), i < Ho, j < Wo; its patches start at gradient pixel
+// (i - pad, j - padw) and have TH x TW taps; its weights [C][TH][TW][Cout] begin at element w_first.
+constexpr int kMaxStride = 2;
+struct StrideClass {
+    int h0, w0, Ho, Wo, TH, TW, pad, padw;
+    int64_t w_first;
+};
+struct StrideClasses {
+    int H = 0, W = 0, C = 1;             // the gradient: H x W x C
+    int outH = 0, outW = 0, stride = 1;  // the input image
+    StrideClass cls[kMaxStride * kMaxStride];
+};
+int conv_strided_dx_launch(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
+                           const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride);
+bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images);
 int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq, float* Y,
                      const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride = nullptr);
 // convolutions of thin images (fxp_conv_direct.hip); kNotApplicable / false: the shape takes the general path

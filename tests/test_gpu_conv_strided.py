@@ -1,0 +1,37 @@
+"""Input gradients of stride-2 convolutions, computed per class of input pixels: odd and even sizes, filters smaller than
+the stride (classes without taps), paddings beyond the filter, rows and columns that no output reads, one image row per
+class, several tiles per class, both K steps, and the weight gradient's sum riding along.  Bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import say
+from tests.test_gpu_conv import check_conv, fxp  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # N, H, W, C, Cout, KH, KW, pad
+    (2, 8, 8, 32, 64, 3, 3, 1), (2, 9, 7, 32, 64, 3, 3, 1), (1, 11, 12, 33, 128, 3, 3, 0), (3, 8, 9, 64, 128, 1, 1, 0),
+    (2, 7, 8, 40, 64, 1, 1, 1), (1, 6, 5, 48, 192, 1, 3, 2), (2, 10, 10, 36, 64, 2, 2, 0), (1, 13, 9, 64, 64, 5, 4, 3),
+    (1, 12, 15, 32, 64, 7, 7, 3), (1, 1, 9, 64, 128, 1, 3, 1), (1, 3, 2, 130, 128, 3, 2, 0),
+    (3, 29, 27, 129, 128, 3, 3, 1), (12, 28, 28, 128, 256, 3, 3, 1), (17, 33, 32, 64, 128, 3, 3, 1)]
+
+
+def _tensors(N, H, W, C, Cout, KH, KW, pad):
+    rng = np.random.default_rng(N * 1000 + H * 10 + C)
+    X = rng.standard_normal((N, H, W, C)).astype(np.float32)
+    Wt = rng.standard_normal((Cout, KH, KW, C)).astype(np.float32)
+    Ho, Wo = oracle.conv_out_hw(H, W, KH, KW, 2, pad)
+    return X, Wt, rng.laplace(0, 1e-3, (N, Ho, Wo, Cout)).astype(np.float32)
+
+
+@pytest.mark.parametrize("N,H,W,C,Cout,KH,KW,pad", CASES)
+def test_strided_input_gradient(fxp, N, H, W, C, Cout, KH, KW, pad):  # noqa: F811
+    say("strided conv", (N, H, W, C, Cout, KH, KW, pad))
+    check_conv(fxp, *_tensors(N, H, W, C, Cout, KH, KW, pad), 2, pad)
+
+
+@pytest.mark.parametrize("case", [CASES[1], CASES[4], CASES[11]])
+def test_strided_input_gradient_alone(fxp, case):  # noqa: F811
+    say("strided conv, dX alone", case)
+    check_conv(fxp, *_tensors(*case), 2, case[-1], bits=5, need_dW=False)
