@@ -1502,11 +1502,11 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
 // Y[M, Cout] = unmap(patches(Xq) * Wq^T) with the patch matrix never stored (see k_gemm_nt_dma, CONV): M output
 // pixels, K = KH*KW*C.  Returns kNotApplicable when the shape needs the explicit patch matrix: channels not a
 // multiple of 64 (the smallest K step), a product that plan_gemm would split along K or give 256 x 256 tiles.
-template <int BK, int WN>
+template <int BN, int BK, int WN>
 static int conv_gemm_launch_cfg(const ConvTaps& ct, int64_t K, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq,
                                 float* Y, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s,
                                 ReduceRider* ride) {
-    constexpr int BM = 128, BN = 128, WM = 64, STAGES = 4;
+    constexpr int BM = 128, WM = 64, STAGES = 4;
     const int tiles_m = static_cast<int>((M + BM - 1) / BM), tiles_n = static_cast<int>((Cout + BN - 1) / BN);
     ReduceRider rider;
     if (ride != nullptr && ride->blocks != 0) {
@@ -1529,9 +1529,12 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     if (ct.C % 64 != 0 || !aligned(Xq, 16) || !aligned(Wq, 16) || M <= 0 || Cout <= 0) return kNotApplicable;
     const GemmPlan plan = plan_gemm(M, Cout, K);
     if (plan.splits != 1 || plan.use256) return kNotApplicable;
+    // up to 64 output channels: a tile of their own width and three workgroups per CU (32 x 56 x 56 x 64 -> 64 3x3 layer step
+    // 102.2 -> 88.7 us, 1x1 66.9 -> 61.8).
     // one K step = one run of channels of one filter tap: 128 channels (8 waves) where C allows, else 64 (4 waves)
-    if (ct.C % 128 == 0) return conv_gemm_launch_cfg<128, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
-    return conv_gemm_launch_cfg<64, 64>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    if (Cout <= 64) return conv_gemm_launch_cfg<64, 64, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    if (ct.C % 128 == 0) return conv_gemm_launch_cfg<128, 128, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    return conv_gemm_launch_cfg<128, 64, 64>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
 }
 
 // dX[N, H, W, C] of a strided convolution from dYq[N, Ho, Wo, Cout] and the weights in class order (StrideClasses): the
@@ -1545,10 +1548,10 @@ bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images) {
     return sc.stride > 1 && sc.stride <= kMaxStride && sc.C % 64 == 0 && tiles < (int64_t{1} << 24);
 }
 
-template <int BK, int WN>
+template <int BN, int BK, int WN>
 static int conv_strided_dx_cfg(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
                                const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
-    constexpr int BM = 128, BN = 128, WM = 64, STAGES = 4;
+    constexpr int BM = 128, WM = 64, STAGES = 4;
     int64_t rows = 0;
     for (int c = 0; c < sc.stride * sc.stride; ++c) rows = std::max(rows, images * sc.cls[c].Ho * sc.cls[c].Wo);
     const int tiles_m = static_cast<int>((rows + BM - 1) / BM) * sc.stride * sc.stride, tiles_n = static_cast<int>((C + BN - 1) / BN);
@@ -1569,8 +1572,10 @@ static int conv_strided_dx_cfg(const StrideClasses& sc, int64_t images, int64_t 
 
 int conv_strided_dx_launch(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
                            const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
-    if (sc.C % 128 == 0) return conv_strided_dx_cfg<128, 32>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
-    return conv_strided_dx_cfg<64, 64>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
+    // as in conv_gemm_launch (48 x 56 x 56 x 64 -> 128 3x3 layer step 100.6 -> 83.6 us, 1x1 80.7 -> 66.5)
+    if (C <= 64) return conv_strided_dx_cfg<64, 64, 32>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
+    if (sc.C % 128 == 0) return conv_strided_dx_cfg<128, 128, 32>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
+    return conv_strided_dx_cfg<128, 64, 64>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
 }
 
 // long_k: the caller can take a contraction beyond kMaxContraction (fp32 output through workspace slices)
