@@ -352,6 +352,8 @@ static bool dx_strided(const ConvGeo& g, bool with_dw, size_t area_bytes, size_t
     return true;
 }
 
+static bool patches_are_image(const ConvGeo& g) { return g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.padw == 0; }
+
 static ConvTaps taps_of(const ConvGeo& g) {
     ConvTaps t;
     t.H = g.H; t.W = g.W; t.C = g.C; t.KW = g.KW; t.stride = g.stride; t.pad = g.pad; t.padw = g.padw; t.Ho = g.Ho; t.Wo = g.Wo;
@@ -428,7 +430,7 @@ extern "C" int fxp_conv2d_fwd(const float* X, const float* W, const fxp_conv2d_s
     uint32_t* pX = reinterpret_cast<uint32_t*>(w8);
     uint32_t* pW = reinterpret_cast<uint32_t*>(w8 + round_up(kScaleWsBytes, 256));
     int8_t* col = reinterpret_cast<int8_t*>(w8 + 2 * round_up(kScaleWsBytes, 256));
-    uint8_t* rest = reinterpret_cast<uint8_t*>(col) + round_up(static_cast<size_t>(g.M()) * g.K(), 256);
+    uint8_t* const rest = reinterpret_cast<uint8_t*>(col) + round_up(static_cast<size_t>(g.M()) * g.K(), 256);
     const int64_t M = g.M(), K = g.K(), pixels = static_cast<int64_t>(g.N) * g.H * g.W;
     const MapTensor tX{X, pixels, g.C, nullptr, pX, 0, saved->eX, saved->Xq, nullptr, (step << 8) | FXP_TAG_X};
     const MapTensor tW{W, g.Cout, K, nullptr, pW, 0, saved->eW, saved->Wq, saved->WqT, (step << 8) | FXP_TAG_W};
@@ -438,7 +440,9 @@ extern "C" int fxp_conv2d_fwd(const float* X, const float* W, const fxp_conv2d_s
     if (rc == kNotApplicable)
         rc = conv_thin_fwd_launch(taps_of(g), g.KH, g.N, M, g.Cout, saved->Xq, saved->Wq, Y, saved->eX, bits, saved->eW, bits, s);
     if (rc != kNotApplicable) return rc;
-    if (g.C % 16 == 0)
+    // (the patches of a 1x1 layer are the image: a copy of 3.2 MB and its launch cost 4 us)
+    if (patches_are_image(g)) col = saved->Xq;
+    else if (g.C % 16 == 0)
         hipLaunchKernelGGL(k_im2col_i8<16>, dim3(static_cast<unsigned>((M + 31) / 32)), dim3(256), 0, s, saved->Xq, g, col);
     else
         hipLaunchKernelGGL(k_im2col_i8<1>, dim3(static_cast<unsigned>((M + 31) / 32)), dim3(256), 0, s, saved->Xq, g, col);
@@ -552,7 +556,8 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
             if ((rc = splitk_reduce_launch(pending, s))) return rc;
             pending.blocks = 0;
         }
-        if (d.C % 16 == 0)
+        if (patches_are_image(d)) colg = dYq;
+        else if (d.C % 16 == 0)
             hipLaunchKernelGGL(k_im2col_i8<16>, dim3(static_cast<unsigned>((Md + 31) / 32)), dim3(256), 0, s, dYq, d, colg);
         else
             hipLaunchKernelGGL(k_im2col_i8<1>, dim3(static_cast<unsigned>((Md + 31) / 32)), dim3(256), 0, s, dYq, d, colg);

@@ -1501,12 +1501,12 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
 
 // Y[M, Cout] = unmap(patches(Xq) * Wq^T) with the patch matrix never stored (see k_gemm_nt_dma, CONV): M output
 // pixels, K = KH*KW*C.  Returns kNotApplicable when the shape needs the explicit patch matrix: channels not a
-// multiple of 64 (the smallest K step), a product that plan_gemm would split along K or give 256 x 256 tiles.
-template <int BN, int BK, int WN>
+// multiple of 64 (the smallest K step), or a product that plan_gemm would give 256 x 256 tiles.
+template <int BM, int BN, int BK, int WM, int WN>
 static int conv_gemm_launch_cfg(const ConvTaps& ct, int64_t K, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq,
                                 float* Y, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s,
                                 ReduceRider* ride) {
-    constexpr int BM = 128, WM = 64, STAGES = 4;
+    constexpr int STAGES = 4;
     const int tiles_m = static_cast<int>((M + BM - 1) / BM), tiles_n = static_cast<int>((Cout + BN - 1) / BN);
     ReduceRider rider;
     if (ride != nullptr && ride->blocks != 0) {
@@ -1528,13 +1528,21 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     const int64_t K = static_cast<int64_t>(KH) * ct.KW * ct.C;
     if (ct.C % 64 != 0 || !aligned(Xq, 16) || !aligned(Wq, 16) || M <= 0 || Cout <= 0) return kNotApplicable;
     const GemmPlan plan = plan_gemm(M, Cout, K);
-    if (plan.splits != 1 || plan.use256) return kNotApplicable;
+    if (plan.use256) return kNotApplicable;
+    // few tiles: a product of stored patches would be split along K (or leave CUs idle); here tiles a quarter the size
+    // fill the chip, no patches are stored and no slices summed.  Layer steps against stored patches: 32 x 14 x 14 x 256 -> 256
+    // 3x3 110 -> 64 us (98 large tiles; unsplit large tiles: 68), 32 x 7 x 7 x 512 -> 512 113 -> 80 (52; 95), batch 64 140 -> 96
+    // (100; 102); with 196 large tiles (batch 64 of 14 x 14) 131 -> 104, large ones 86.
+    if (((M + 127) / 128) * ((Cout + 127) / 128) <= 128) {
+        if (ct.C % 128 == 0) return conv_gemm_launch_cfg<64, 64, 128, 32, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+        return conv_gemm_launch_cfg<64, 64, 64, 32, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    }
     // up to 64 output channels: a tile of their own width and three workgroups per CU (32 x 56 x 56 x 64 -> 64 3x3 layer step
     // 102.2 -> 88.7 us, 1x1 66.9 -> 61.8).
     // one K step = one run of channels of one filter tap: 128 channels (8 waves) where C allows, else 64 (4 waves)
-    if (Cout <= 64) return conv_gemm_launch_cfg<64, 64, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
-    if (ct.C % 128 == 0) return conv_gemm_launch_cfg<128, 128, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
-    return conv_gemm_launch_cfg<128, 64, 64>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    if (Cout <= 64) return conv_gemm_launch_cfg<128, 64, 64, 64, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    if (ct.C % 128 == 0) return conv_gemm_launch_cfg<128, 128, 128, 64, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    return conv_gemm_launch_cfg<128, 128, 64, 64, 64>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
 }
 
 // dX[N, H, W, C] of a strided convolution from dYq[N, Ho, Wo, Cout] and the weights in class order (StrideClasses): the

@@ -1,4 +1,4 @@
-"""Input gradients of stride-2 convolutions, computed per class of input pixels: odd and even sizes, filters smaller than
+"""Tiles of implicit convolutions.  Input gradients of stride-2 convolutions, computed per class of input pixels: odd and even sizes, filters smaller than
 the stride (classes without taps), paddings beyond the filter, rows and columns that no output reads, one image row per
 class, several tiles per class, both K steps, and the weight gradient's sum riding along.  Bit for bit."""
 import numpy as np
@@ -29,6 +29,20 @@ def _tensors(N, H, W, C, Cout, KH, KW, pad):
 def test_strided_input_gradient(fxp, N, H, W, C, Cout, KH, KW, pad):  # noqa: F811
     say("strided conv", (N, H, W, C, Cout, KH, KW, pad))
     check_conv(fxp, *_tensors(N, H, W, C, Cout, KH, KW, pad), 2, pad)
+
+
+@pytest.mark.parametrize("N,H,W,C,Cout,KH,pad", [
+    (3, 14, 14, 128, 256, 3, 1), (2, 7, 7, 512, 512, 3, 1), (5, 9, 11, 192, 320, 3, 0), (70, 14, 13, 64, 256, 3, 1),
+    (1, 5, 5, 128, 65, 1, 0), (90, 14, 14, 256, 256, 3, 1), (2, 9, 8, 24, 40, 1, 0), (64, 28, 14, 128, 256, 1, 0)])
+def test_few_tiles(fxp, N, H, W, C, Cout, KH, pad):  # noqa: F811
+    """Stride 1: the quarter-size tiles of small outputs (at most 128 large ones), either K step, and both sides of the
+    rule; 1x1 layers whose patches are the image itself."""
+    say("conv, few tiles", (N, H, W, C, Cout, KH, pad))
+    rng = np.random.default_rng(N * 1000 + H * 10 + C)
+    X = rng.standard_normal((N, H, W, C)).astype(np.float32)
+    Wt = rng.standard_normal((Cout, KH, KH, C)).astype(np.float32)
+    Ho, Wo = oracle.conv_out_hw(H, W, KH, KH, 1, pad)
+    check_conv(fxp, X, Wt, rng.laplace(0, 1e-3, (N, Ho, Wo, Cout)).astype(np.float32), 1, pad)
 
 
 @pytest.mark.parametrize("case", [CASES[1], CASES[4], CASES[11]])
