@@ -1501,7 +1501,9 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
 
 // Y[M, Cout] = unmap(patches(Xq) * Wq^T) with the patch matrix never stored (see k_gemm_nt_dma, CONV): M output
 // pixels, K = KH*KW*C.  Returns kNotApplicable when the shape needs the explicit patch matrix: channels not a
-// multiple of 64 (the smallest K step), or a product that plan_gemm would give 256 x 256 tiles.
+// multiple of 64 (the smallest K step), or a 1x1 layer that plan_gemm gives 256 x 256 tiles (64 x 28 x 28 x 128 -> 256 81.3 us
+// with them, 84.3 here; of a 3x3 layer the stored patches cost more than the larger tiles gain: 64 x 14 x 14 x 256 -> 512
+// 135 us with them, 125 here).
 template <int BM, int BN, int BK, int WM, int WN>
 static int conv_gemm_launch_cfg(const ConvTaps& ct, int64_t K, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq,
                                 float* Y, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s,
@@ -1528,7 +1530,7 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     const int64_t K = static_cast<int64_t>(KH) * ct.KW * ct.C;
     if (ct.C % 64 != 0 || !aligned(Xq, 16) || !aligned(Wq, 16) || M <= 0 || Cout <= 0) return kNotApplicable;
     const GemmPlan plan = plan_gemm(M, Cout, K);
-    if (plan.use256) return kNotApplicable;
+    if (plan.use256 && K == ct.C) return kNotApplicable;
     // few tiles: a product of stored patches would be split along K (or leave CUs idle); here tiles a quarter the size
     // fill the chip, no patches are stored and no slices summed.  Layer steps against stored patches: 32 x 14 x 14 x 256 -> 256
     // 3x3 110 -> 64 us (98 large tiles; unsplit large tiles: 68), 32 x 7 x 7 x 512 -> 512 113 -> 80 (52; 95), batch 64 140 -> 96
