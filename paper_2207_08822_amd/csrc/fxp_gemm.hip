@@ -1504,11 +1504,10 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
 // multiple of 64 (the smallest K step), or a 1x1 layer that plan_gemm gives 256 x 256 tiles (64 x 28 x 28 x 128 -> 256 81.3 us
 // with them, 84.3 here; of a 3x3 layer the stored patches cost more than the larger tiles gain: 64 x 14 x 14 x 256 -> 512
 // 135 us with them, 125 here).
-template <int BM, int BN, int BK, int WM, int WN>
+template <int BM, int BN, int BK, int WM, int WN, int STAGES = 4>
 static int conv_gemm_launch_cfg(const ConvTaps& ct, int64_t K, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq,
                                 float* Y, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s,
                                 ReduceRider* ride) {
-    constexpr int STAGES = 4;
     const int tiles_m = static_cast<int>((M + BM - 1) / BM), tiles_n = static_cast<int>((Cout + BN - 1) / BN);
     ReduceRider rider;
     if (ride != nullptr && ride->blocks != 0) {
@@ -1535,7 +1534,8 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     // fill the chip, no patches are stored and no slices summed.  Layer steps against stored patches: 32 x 14 x 14 x 256 -> 256
     // 3x3 110 -> 64 us (98 large tiles; unsplit large tiles: 68), 32 x 7 x 7 x 512 -> 512 113 -> 80 (52; 95), batch 64 140 -> 96
     // (100; 102); with 196 large tiles (batch 64 of 14 x 14) 131 -> 104, large ones 86.
-    if (((M + 127) / 128) * ((Cout + 127) / 128) <= 128) {
+    const int64_t t128 = ((M + 127) / 128) * ((Cout + 127) / 128);
+    if (t128 <= 128) {
         if (ct.C % 128 == 0) return conv_gemm_launch_cfg<64, 64, 128, 32, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
         return conv_gemm_launch_cfg<64, 64, 64, 32, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
     }
@@ -1543,6 +1543,11 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     // 102.2 -> 88.7 us, 1x1 66.9 -> 61.8).
     // one K step = one run of channels of one filter tap: 128 channels (8 waves) where C allows, else 64 (4 waves)
     if (Cout <= 64) return conv_gemm_launch_cfg<128, 64, 64, 64, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
+    // more tiles than CUs: two stages leave room for two workgroups per CU, one stores while the other multiplies, and the last
+    // round is fuller (layer steps 64 x 28 x 28 x 128 3x3 100.7 -> 91.5 us, 64 x 28 x 28 x 256 -> 512 415 -> 370, 64 x 14 x 14 x 512
+    // 192 -> 172; 128 x 64 tiles of two stages 101, 391, 210)
+    if (ct.C % 128 == 0 && t128 > 256)
+        return conv_gemm_launch_cfg<128, 128, 128, 64, 32, 2>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
     if (ct.C % 128 == 0) return conv_gemm_launch_cfg<128, 128, 128, 64, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
     return conv_gemm_launch_cfg<128, 128, 64, 64, 64>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
 }
@@ -1558,10 +1563,10 @@ bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images) {
     return sc.stride > 1 && sc.stride <= kMaxStride && sc.C % 64 == 0 && tiles < (int64_t{1} << 24);
 }
 
-template <int BN, int BK, int WN>
+template <int BN, int BK, int WN, int STAGES = 4>
 static int conv_strided_dx_cfg(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
                                const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
-    constexpr int BM = 128, WM = 64, STAGES = 4;
+    constexpr int BM = 128, WM = 64;
     int64_t rows = 0;
     for (int c = 0; c < sc.stride * sc.stride; ++c) rows = std::max(rows, images * sc.cls[c].Ho * sc.cls[c].Wo);
     const int tiles_m = static_cast<int>((rows + BM - 1) / BM) * sc.stride * sc.stride, tiles_n = static_cast<int>((C + BN - 1) / BN);
@@ -1584,6 +1589,9 @@ int conv_strided_dx_launch(const StrideClasses& sc, int64_t images, int64_t C, c
                            const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
     // as in conv_gemm_launch (48 x 56 x 56 x 64 -> 128 3x3 layer step 100.6 -> 83.6 us, 1x1 80.7 -> 66.5)
     if (C <= 64) return conv_strided_dx_cfg<64, 64, 32>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
+    int64_t tiles = 0;
+    for (int c = 0; c < sc.stride * sc.stride; ++c) tiles += (images * sc.cls[c].Ho * sc.cls[c].Wo + 127) / 128 * ((C + 127) / 128);
+    if (sc.C % 128 == 0 && tiles > 256) return conv_strided_dx_cfg<128, 128, 32, 2>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
     if (sc.C % 128 == 0) return conv_strided_dx_cfg<128, 128, 32>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
     return conv_strided_dx_cfg<128, 64, 64>(sc, images, C, dYq, Wc, dX, eA, bitsA, eB, bitsB, s, ride);
 }

@@ -14,7 +14,7 @@ CASES = [  # N, H, W, C, Cout, KH, KW, pad
     (2, 8, 8, 32, 64, 3, 3, 1), (2, 9, 7, 32, 64, 3, 3, 1), (1, 11, 12, 33, 128, 3, 3, 0), (3, 8, 9, 64, 128, 1, 1, 0),
     (2, 7, 8, 40, 64, 1, 1, 1), (1, 6, 5, 48, 192, 1, 3, 2), (2, 10, 10, 36, 64, 2, 2, 0), (1, 13, 9, 64, 64, 5, 4, 3),
     (1, 12, 15, 32, 64, 7, 7, 3), (1, 1, 9, 64, 128, 1, 3, 1), (1, 3, 2, 130, 128, 3, 2, 0),
-    (3, 29, 27, 129, 128, 3, 3, 1), (12, 28, 28, 128, 256, 3, 3, 1), (17, 33, 32, 64, 128, 3, 3, 1)]
+    (3, 29, 27, 129, 128, 3, 3, 1), (12, 28, 28, 128, 256, 3, 3, 1), (44, 28, 28, 128, 128, 3, 3, 1), (17, 33, 32, 64, 128, 3, 3, 1)]
 
 
 def _tensors(N, H, W, C, Cout, KH, KW, pad):
@@ -33,10 +33,10 @@ def test_strided_input_gradient(fxp, N, H, W, C, Cout, KH, KW, pad):  # noqa: F8
 
 @pytest.mark.parametrize("N,H,W,C,Cout,KH,pad", [
     (3, 14, 14, 128, 256, 3, 1), (2, 7, 7, 512, 512, 3, 1), (5, 9, 11, 192, 320, 3, 0), (70, 14, 13, 64, 256, 3, 1),
-    (1, 5, 5, 128, 65, 1, 0), (90, 14, 14, 256, 256, 3, 1), (2, 9, 8, 24, 40, 1, 0), (64, 28, 14, 128, 256, 1, 0)])
+    (1, 5, 5, 128, 65, 1, 0), (90, 14, 14, 256, 256, 3, 1), (2, 9, 8, 24, 40, 1, 0), (64, 28, 14, 128, 256, 1, 0), (43, 28, 28, 128, 128, 3, 1)])
 def test_few_tiles(fxp, N, H, W, C, Cout, KH, pad):  # noqa: F811
     """Stride 1: the quarter-size tiles of small outputs (at most 128 large ones), either K step, and both sides of the
-    rule; 1x1 layers whose patches are the image itself."""
+    rule; more tiles than CUs; 1x1 layers whose patches are the image itself."""
     say("conv, few tiles", (N, H, W, C, Cout, KH, pad))
     rng = np.random.default_rng(N * 1000 + H * 10 + C)
     X = rng.standard_normal((N, H, W, C)).astype(np.float32)
