@@ -97,6 +97,56 @@ def read_step_traffic(name):
     return None
 
 
+# timeline tags of include/fxp.h -> rows of the line (a stand-alone slice sum belongs to dW)
+TIMELINE_ROWS = {1: "scale", 2: "map", 3: "gemm_fwd", 4: "gemm_dW", 5: "gemm_dX", 6: "gemm_dW", 7: "gemm_dW+dX"}
+
+
+def join_paired_gradients(rows, gemm_rows, layers, in_step):
+    """The layers whose two gradient products go out in one launch (in_step holds one interval for both): their two
+    entries of `gemm_rows` and their shares of the rows gemm_dW and gemm_dX become one, with the sums of both."""
+    for li, layer in enumerate(layers):
+        if (li, "gemm_dW+dX") not in in_step:
+            continue
+        # dX and dW of layer li, in the order the rows were made in
+        pair = [g for g in gemm_rows if g["layer_index"] == li and g["gemm"] in ("dX", "dW")]
+        joint = dict(pair[0], gemm="dW+dX", launches=1, bound=None, products=[[g["M"], g["N"], g["K"]] for g in pair])
+        for k in ("M", "N", "K"):
+            del joint[k]
+        for k in ("ops", "bytes", "us", "us_loop_min"):
+            joint[k] = sum(g[k] for g in pair)
+        clocks = [g["core_clock_mhz"] for g in pair if g["core_clock_mhz"]]
+        joint["bound"] = "mfma" if joint["ops"] / joint["bytes"] > RIDGE_OPS_PER_BYTE else "hbm"
+        joint["core_clock_mhz"] = sum(clocks) / len(clocks) if clocks else None
+        to = rows.setdefault("gemm_dW+dX", dict(kernel=rows["gemm_dW"]["kernel"], t=0.0, tmin=0.0, launches=0, bytes=0.0, ops=0.0))
+        to["launches"] += 1
+        for g in pair:
+            row = rows["gemm_" + g["gemm"]]
+            for r, sign in ((row, -1.0), (to, 1.0)):
+                r["bytes"] += sign * g["bytes"]
+                r["ops"] += sign * g["ops"]
+                r["t"] += sign * g["us"] * 1e-6
+                r["tmin"] += sign * g["us_loop_min"] * 1e-6
+            row["launches"] -= 1
+            if row["launches"] == 0:
+                del rows["gemm_" + g["gemm"]]
+        at = gemm_rows.index(pair[0])
+        gemm_rows[at] = joint
+        gemm_rows.remove(pair[1])
+
+
+def set_in_step_times(rows, gemm_rows, in_step, steps):
+    """Durations inside the step (in_step: (layer index, row) -> microseconds over `steps` steps) in place of those of a
+    loop of its own, which are kept beside them."""
+    for row in rows:
+        t = sum(v for (li, c), v in in_step.items() if c == row) / steps * 1e-6
+        rows[row]["t_loop"], rows[row]["t"] = rows[row]["t"], t
+    for g in gemm_rows:
+        t = in_step[(g["layer_index"], "gemm_" + g["gemm"])] / steps
+        g["us_loop"], g["us"] = round(g["us"], 2), round(t, 2)
+        g["tops"], g["gbs"] = round(g["ops"] / t / 1e6, 1), round(g["bytes"] / t / 1e3, 1)
+        g["frac_of_roofline"] = round(max(g["ops"] / (PEAK_INT8_TOPS * 1e6), g["bytes"] / (PEAK_HBM_GBS * 1e3)) / t, 3)
+
+
 def repeat_to_target(run_once, target_seconds, most=64):
     """Run the (whole-workload) CPU sample once; when that is far below the target time, repeat it.  Returns
     (repetitions, total seconds)."""
@@ -525,7 +575,7 @@ def main():
         torch.cuda.synchronize()
         ticks, cycles = probe_out.cpu().tolist()
         return 100.0 * cycles / ticks if ticks > 0 else None
-    for layer, (X, W, dY), buf in zip(layers, dev_inputs, bufs):
+    for li, (layer, (X, W, dY), buf) in enumerate(zip(layers, dev_inputs, bufs)):
         M, K, N = layer.M, layer.K, layer.N
         # map: 4 B read + 1 B written per copy (both orientations) per element; launched as the step launches it:
         # activation and weight in one launch, the gradient in one of its own
@@ -579,12 +629,9 @@ def main():
             mhz = clock_during(lambda: lib.fxp_gemm_unmap(0, 1, gm, gn, gk, p(A), gk, p(B), gk, p(eA), args.bits, p(eB), args.bits,
                                                           p(C), gn, p(gws), gws.numel(), st), dt) if mfma_bound else None
             del gws
-            t_roof = max(ops / (PEAK_INT8_TOPS * 1e12), nbytes / (PEAK_HBM_GBS * 1e9))
-            gemm_rows.append(dict(layer=layer.name, gemm=name, M=gm, N=gn, K=gk, us=round(dt * 1e6, 2),
-                                  us_loop_min=round(timed.last_min * 1e6, 2),
-                                  tops=round(ops / dt / 1e12, 1), gbs=round(nbytes / dt / 1e9, 1),
+            gemm_rows.append(dict(layer=layer.name, layer_index=li, gemm=name, M=gm, N=gn, K=gk, ops=ops, bytes=nbytes,
+                                  us=dt * 1e6, us_loop_min=round(timed.last_min * 1e6, 2),
                                   bound="mfma" if mfma_bound else "hbm",
-                                  frac_of_roofline=round(t_roof / dt, 3),
                                   core_clock_mhz=round(mhz, 0) if mhz else None))
             add("gemm_" + name, "k_gemm_nt*", dt, nbytes, ops)
 
@@ -594,7 +641,6 @@ def main():
     # runs - behind the kernel that precedes it in the step and with what that kernel left in the caches (the
     # reduction walks a tensor back to front so that the map, walking front to back, finds its head in the
     # Infinity Cache; a loop of map launches alone never sees that).  These are the durations the rows use.
-    TL = {1: "scale", 2: "map", 3: "gemm_fwd", 4: "gemm_dW", 5: "gemm_dX", 6: "gemm_dW"}     # a stand-alone slice sum belongs to dW
     tl_steps = max(3, min(args.steps, 20))
     cap = tl_steps * len(layers) * 12 + 8
     us_buf, tag_buf, cnt = (ctypes.c_float * cap)(), (ctypes.c_int * cap)(), ctypes.c_int(0)
@@ -613,17 +659,10 @@ def main():
             idle_us += us
         else:
             li = (entries // 2) % len(layers)
-            in_step[(li, TL[tag])] = in_step.get((li, TL[tag]), 0.0) + us
-    launches = dict(scale=2, map=2, gemm_fwd=1, gemm_dW=1, gemm_dX=1)
-    for row in rows:
-        t = sum(v for (li, c), v in in_step.items() if c == row) / tl_steps * 1e-6
-        rows[row]["t_loop"], rows[row]["t"] = rows[row]["t"], t
-    for g, li in zip(gemm_rows, [i for i in range(len(layers)) for _ in range(3)]):
-        t = in_step.get((li, "gemm_" + g["gemm"]), 0.0) / tl_steps
-        ops, nbytes = 2.0 * g["M"] * g["N"] * g["K"], float(g["M"] * g["K"] + g["N"] * g["K"] + 4 * g["M"] * g["N"])
-        g["us_loop"], g["us"] = g["us"], round(t, 2)
-        g["tops"], g["gbs"] = round(ops / t / 1e6, 1), round(nbytes / t / 1e3, 1)
-        g["frac_of_roofline"] = round(max(ops / (PEAK_INT8_TOPS * 1e6), nbytes / (PEAK_HBM_GBS * 1e3)) / t, 3)
+            key = (li, TIMELINE_ROWS[tag])
+            in_step[key] = in_step.get(key, 0.0) + us
+    join_paired_gradients(rows, gemm_rows, layers, in_step)
+    set_in_step_times(rows, gemm_rows, in_step, tl_steps)
     # core clock over whole steps (the probe runs beside about 5 ms of steps)
     n_probe = max(2, int(5.0 / max(ms_per_step, 1e-3)))
     for i in range(2):
@@ -675,7 +714,7 @@ def main():
     if mfma_rows:
         t_all = sum(g["us"] for g in mfma_rows) * 1e-6
         t_loop = sum(g["us_loop"] for g in mfma_rows) * 1e-6
-        ops_all = sum(2.0 * g["M"] * g["N"] * g["K"] for g in mfma_rows)
+        ops_all = sum(g["ops"] for g in mfma_rows)
         clocks = [g["core_clock_mhz"] for g in mfma_rows if g["core_clock_mhz"]]
         mhz = sum(clocks) / len(clocks) if clocks else None
         tops_all, tops_loop = ops_all / t_all / 1e12, ops_all / t_loop / 1e12

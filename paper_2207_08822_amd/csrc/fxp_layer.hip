@@ -234,7 +234,7 @@ static int linear_bwd_impl(const float* dY, const fxp_saved* saved, int64_t M, i
         const GemmArgs gW{K, N, M, saved->XqT, M, 0, dYqT, M, 0, dW, N, 0, saved->eX, bits, e_dY, bits};
         const GemmArgs gX{M, K, N, dYq, N, 0, saved->Wq, N, 0, dX, K, 0, e_dY, bits, saved->eW, bits};
         if ((rc = gemm_nt_pair_launch(gW, gX, 1, s)) != kNotApplicable) {
-            timeline_mark(s, FXP_TL_GEMM_DX);
+            timeline_mark(s, FXP_TL_GEMM_GRADS);
             return rc;
         }
     }

@@ -578,6 +578,26 @@ def test_empty_operands_are_no_ops(fxp):
     assert bool((guard == 7).all()) and bool((x == 0).all())
 
 
+@pytest.mark.parametrize("M,K,N,grads", [(256, 256, 256, [7]), (197, 96, 70, [7]), (1379, 768, 1000, [7])])
+def test_timeline_tags_both_gradients_of_one_launch(fxp, M, K, N, grads):
+    """One interval per launch, each with the tag of what the launch was: both gradients together where they go out
+    together, under a tag of their own."""
+    import ctypes
+    say("timeline of a small layer", (M, K, N))
+    L = fxp.lib()
+    X, W, dY = (torch.randn(s, device="cuda") for s in ((M, K), (K, N), (M, N)))
+    buf = fxp.LayerBuffers(M, K, N)
+    assert L.fxp_timeline_begin(64) == 0
+    for _ in range(2):
+        fxp.linear_fwd(X, W, buf, 5, 2)
+        fxp.linear_bwd(dY, buf, 5, 2)
+    us, tags, n = (ctypes.c_float * 64)(), (ctypes.c_int * 64)(), ctypes.c_int(0)
+    assert L.fxp_timeline_end(us, tags, 64, ctypes.byref(n)) == 0
+    one = [1, 2, 3, 0, 1, 2] + grads
+    assert [tags[i] for i in range(n.value)] == one + [0] + one
+    assert all(us[i] > 0.0 for i in range(n.value))
+
+
 def test_timeline_and_clock_probe_measure_without_changing_results(fxp):
     """The measurement helpers: the events recorded inside the layer calls come back as one interval per launch,
     in launch order, and the outputs are the ones an undisturbed call gives; the clock probe reports a plausible
