@@ -85,11 +85,16 @@ __global__ __launch_bounds__(256) void k_im2col_i8(const int8_t* __restrict__ Xq
 // kw = rw + stride * (TW - 1 - j), class (rh, rw) after class.
 __host__ __device__ inline int class_taps(int k, int r, int stride) { return (k - r + stride - 1) / stride; }   // r < stride
 
+//
+// CLASSES: which of the two, a parameter of every kernel that flips: with both forms in it, the launch the flip rides
+// in was compiled differently (34 VGPRs for 53) and took 12.95 us, with the stride-1 form alone 12.64 (k_im2col_t_i8 of
+// 32 x 28 x 28 x 128, 3x3; means of three traces).
+template <bool CLASSES>
 __device__ inline void flip_weights_body(const int8_t* __restrict__ Wq, const ConvGeo& g, int8_t* __restrict__ WqF, unsigned bid,
                                          unsigned nblocks) {
     const int64_t K = g.K(), Kf = static_cast<int64_t>(g.KH) * g.KW * g.Cout, total = static_cast<int64_t>(g.C) * Kf;
     for (int64_t id = static_cast<int64_t>(bid) * 256 + threadIdx.x; id < total; id += static_cast<int64_t>(nblocks) * 256) {
-        if (g.stride > 1) {
+        if constexpr (CLASSES) {
             int64_t at = id;
             for (int cls = 0; cls < g.stride * g.stride; ++cls) {
                 const int rh = cls / g.stride, rw = cls - rh * g.stride;
@@ -114,8 +119,9 @@ __device__ inline void flip_weights_body(const int8_t* __restrict__ Wq, const Co
     }
 }
 
+template <bool CLASSES>
 __global__ __launch_bounds__(256) void k_flip_weights_i8(const int8_t* __restrict__ Wq, ConvGeo g, int8_t* __restrict__ WqF) {
-    flip_weights_body(Wq, g, WqF, blockIdx.x, gridDim.x);
+    flip_weights_body<CLASSES>(Wq, g, WqF, blockIdx.x, gridDim.x);
 }
 
 // The launch that writes the transposed patches carries two more pieces of the backward pass that depend on
@@ -130,6 +136,7 @@ struct SideScale {
 };
 
 // true: this workgroup had one of the side roles and is done
+template <bool CLASSES>
 __device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, const int8_t* __restrict__ Wq, const ConvGeo& g,
                                   int8_t* __restrict__ WqF) {
     if (blockIdx.x < side.blocks) {
@@ -139,7 +146,7 @@ __device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, c
     }
     const unsigned b = blockIdx.x - side.blocks;
     if (b >= tile_blocks) {
-        flip_weights_body(Wq, g, WqF, b - tile_blocks, gridDim.x - side.blocks - tile_blocks);
+        flip_weights_body<CLASSES>(Wq, g, WqF, b - tile_blocks, gridDim.x - side.blocks - tile_blocks);
         return true;
     }
     return false;
@@ -156,11 +163,11 @@ __device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, c
 // Workgroups beyond the tile_blocks tiles flip the weights for the input-gradient convolution (Wq -> WqF;
 // flip_blocks of them, possibly 0): two independent pieces of the backward pass in one launch.
 constexpr int kColTileM = 128;
-template <int TCH>
+template <int TCH, bool CLASSES>
 __global__ __launch_bounds__(256) void k_im2col_t_i8(const int8_t* __restrict__ Xq, ConvGeo g, int8_t* __restrict__ colT,
                                                      int tiles_m, int tiles_c, unsigned tile_blocks,
                                                      const int8_t* __restrict__ Wq, int8_t* __restrict__ WqF, SideScale side) {
-    if (side_roles(side, tile_blocks, Wq, g, WqF)) return;
+    if (side_roles<CLASSES>(side, tile_blocks, Wq, g, WqF)) return;
     constexpr int TS = kColTileM / 4 + 1;                        // dwords per staged channel (+ 1 pad)
     constexpr int CG = TCH / 4, MG = 256 / CG;                   // channel groups x row groups per round
     constexpr int ROUNDS = kColTileM / 4 / MG;                   // groups of 4 rows per thread
@@ -224,10 +231,11 @@ __global__ __launch_bounds__(256) void k_im2col_t_i8(const int8_t* __restrict__ 
 }
 
 // same, one byte at a time, for C % 4 != 0
+template <bool CLASSES>
 __global__ __launch_bounds__(256) void k_im2col_t_i8_bytes(const int8_t* __restrict__ Xq, ConvGeo g, int8_t* __restrict__ colT,
                                                            int tiles_m, int tiles_c, unsigned tile_blocks,
                                                            const int8_t* __restrict__ Wq, int8_t* __restrict__ WqF, SideScale side) {
-    if (side_roles(side, tile_blocks, Wq, g, WqF)) return;
+    if (side_roles<CLASSES>(side, tile_blocks, Wq, g, WqF)) return;
     __shared__ int8_t t[64][65];
     int b = static_cast<int>(blockIdx.x - side.blocks);
     const int tc = b % tiles_c; b /= tiles_c;
@@ -494,8 +502,8 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     int8_t* flipped = strided ? reinterpret_cast<int8_t*>(area + wc_at) : saved->WqF;
     ReduceRider pending;                 // the weight gradient's split-K reduction while it waits for a launch to ride in
     if (need_flip && (!dW || thin)) {
-        hipLaunchKernelGGL(k_flip_weights_i8, dim3(grid_for(static_cast<int64_t>(g.Cout) * K)), dim3(256), 0, s, saved->Wq, g,
-                           flipped);
+        hipLaunchKernelGGL(strided ? k_flip_weights_i8<true> : k_flip_weights_i8<false>, dim3(grid_for(static_cast<int64_t>(g.Cout) * K)),
+                           dim3(256), 0, s, saved->Wq, g, flipped);
         if ((rc = launch_status())) return rc;
     }
     if (thin) {
@@ -518,12 +526,10 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
         const unsigned flip_blocks = need_flip ? grid_for(static_cast<int64_t>(g.Cout) * K) : 0u;
         if (blocks + flip_blocks + side.blocks >= (int64_t{1} << 31)) return FXP_ERR_DIMS;
         const dim3 tgrid(side.blocks + static_cast<unsigned>(blocks) + flip_blocks);
-        if (quads)
-            hipLaunchKernelGGL(k_im2col_t_i8<64>, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c,
-                               static_cast<unsigned>(blocks), saved->Wq, flipped, side);
-        else
-            hipLaunchKernelGGL(k_im2col_t_i8_bytes, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c,
-                               static_cast<unsigned>(blocks), saved->Wq, flipped, side);
+        const auto transpose = quads ? (strided ? k_im2col_t_i8<64, true> : k_im2col_t_i8<64, false>)
+                                     : (strided ? k_im2col_t_i8_bytes<true> : k_im2col_t_i8_bytes<false>);
+        hipLaunchKernelGGL(transpose, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c, static_cast<unsigned>(blocks),
+                           saved->Wq, flipped, side);
         if ((rc = launch_status())) return rc;
         // dY: the map kernel finishes the reduction from the block maxima just written
         const MapTensor tdY{dY, M, g.Cout, nullptr, side.partials, static_cast<int>(side.blocks), e_dY, dYq, dYqT,
