@@ -15,7 +15,7 @@
 //   * the final step of the scale reduction (max over <= 1024 block maxima) can be
 //     folded in, which saves a launch per tensor.
 // Rows that are not whole quads, and bases off the 16-byte grid, take the same tiles with unaligned accesses (ANY);
-// a tensor that is wanted row-major only is one flat run of quads (map_flat_body); the one-element-per-thread
+// a tensor that is wanted row-major only is one flat run of quads (map_flat_body) up to a size; the one-element-per-thread
 // kernel is left for what neither reaches.  (18912 x 197, both copies: 25.9 us one element per thread - a Philox call
 // and a scattered byte per element - 14.2 as tiles; 1.6 M x 3, row-major only, with a small weight: 24.1 in two
 // launches, 11.1 flat in one.)
@@ -369,40 +369,43 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
 }
 
 // A tensor wanted row-major only: quads of consecutive elements, 1024 * PASSES per workgroup from quad `first` on,
-// whatever its rows are and wherever x and q start.  The last quad may be short.
-template <bool STOCH, int PASSES>
+// whatever its rows are and wherever x and q start.  SHORT: the workgroup has fewer quads, and a last one that may be
+// short; the others carry no bounds code (with it around every load, 12608 x 768 took 13.2 us where tiles take 10.6).
+template <bool STOCH, int PASSES, bool SHORT>
 __device__ inline void map_flat_body(const MapJob& J, int bits, bool publish, uint32_t* red, uint32_t key0, uint32_t key1,
                                      uint64_t first) {
     const uint64_t n = static_cast<uint64_t>(J.rows) * static_cast<uint64_t>(J.cols);
-    const uint32_t quads = static_cast<uint32_t>(min<uint64_t>((n >> 2) - first, 4 * kMapThreads * PASSES));   // whole ones here
-    const uint32_t tail = static_cast<uint32_t>(n & 3u);         // elements of the short quad behind them, if it is this workgroup's
+    const uint32_t quads = SHORT ? static_cast<uint32_t>((n >> 2) - first) : 4 * kMapThreads * PASSES;    // whole ones here
+    const uint32_t tail = static_cast<uint32_t>(n & 3u);         // SHORT: elements of the quad behind them
     const uint32_t* __restrict__ x = J.x + 4 * first;
     int8_t* __restrict__ q = J.q + 4 * first;
-    auto load_pass = [&](uint32_t i0, uint4 (&v)[4]) {
+    auto load_pass = [&](int p, uint4 (&v)[4]) {
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t i = i0 + k * kMapThreads;
-            v[k] = make_uint4(0, 0, 0, 0);
-            if (i < quads) {
+            const uint32_t i = (4 * p + k) * kMapThreads + threadIdx.x;
+            if (!SHORT || i < quads) {
                 v[k] = load_quad(x + 4 * i);
-            } else if (i == quads && i < 4 * kMapThreads * PASSES) {
-                if (tail > 0) v[k].x = x[4 * i];
-                if (tail > 1) v[k].y = x[4 * i + 1];
-                if (tail > 2) v[k].z = x[4 * i + 2];
+            } else {
+                v[k] = make_uint4(0, 0, 0, 0);
+                if (i == quads) {
+                    if (tail > 0) v[k].x = x[4 * i];
+                    if (tail > 1) v[k].y = x[4 * i + 1];
+                    if (tail > 2) v[k].z = x[4 * i + 2];
+                }
             }
         }
     };
     uint4 cur[4], nxt[4];
-    load_pass(threadIdx.x, cur);
+    load_pass(0, cur);
     const MapCfg cfg = make_cfg(resolve_scale(J.e_in, J.partials, J.n_partials, J.e_out, red, publish), bits);
     const bool scale_ok = cfg.e_max >= 25 && cfg.e_max < 255;
-#pragma unroll 1
-    for (uint32_t i0 = threadIdx.x; i0 < 4 * kMapThreads * PASSES; i0 += 4 * kMapThreads) {
-        load_pass(i0 + 4 * kMapThreads, nxt);                     // (past the last pass: nothing is loaded)
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        if (p + 1 < PASSES) load_pass(p + 1, nxt);
         uint32_t o[4], q_or = 0;
         uint64_t bad = 0;
         auto words_of = [&](uint32_t k) {
-            const uint64_t blk = first + (i0 + k * kMapThreads);
+            const uint64_t blk = first + ((4 * p + k) * kMapThreads + threadIdx.x);
             return STOCH ? philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), J.sid0, J.sid1, key0, key1)
                          : make_uint4(0, 0, 0, 0);
         };
@@ -414,8 +417,8 @@ __device__ inline void map_flat_body(const MapJob& J, int bits, bool publish, ui
         }
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t i = i0 + k * kMapThreads;
-            if (i < quads) {
+            const uint32_t i = (4 * p + k) * kMapThreads + threadIdx.x;
+            if (!SHORT || i < quads) {
                 reinterpret_cast<Bytes4*>(q + 4 * i)->x = o[k];
             } else if (i == quads) {
                 for (uint32_t j = 0; j < tail; ++j) q[4 * i + j] = static_cast<int8_t>(o[k] >> (8 * j));
@@ -426,7 +429,9 @@ __device__ inline void map_flat_body(const MapJob& J, int bits, bool publish, ui
     }
 }
 
-template <bool STOCH, int PASSES, int TC, bool ANY>
+// FLAT: a launch with a flat tensor in it.  (A parameter: with the flat body in every instantiation the tiles of an aligned
+// tensor ran at lower occupancy or spilled, 159744 x 208 both copies 39.1 -> 40.0 us.)
+template <bool STOCH, int PASSES, int TC, bool ANY, bool FLAT>
 __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, uint32_t key0, uint32_t key1, int bits) {
     constexpr int RGP = kMapThreads / (TC / 4);
     constexpr int TR = 4 * RGP * PASSES;
@@ -441,8 +446,11 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
         const int e = resolve_scale(nullptr, J.partials, J.n_partials, J.e_out, red, bid == 0);
         if (J.guess_used[0] == e) return;
     }
-    if (J.flat) {
-        map_flat_body<STOCH, PASSES>(J, bits, bid == 0, red, key0, key1, static_cast<uint64_t>(bid) * (4 * kMapThreads * PASSES));
+    if (FLAT && J.flat) {
+        const uint64_t first = static_cast<uint64_t>(bid) * (4 * kMapThreads * PASSES);
+        const uint64_t whole = static_cast<uint64_t>(J.rows) * static_cast<uint64_t>(J.cols) >> 2;
+        if (first + 4 * kMapThreads * PASSES <= whole) map_flat_body<STOCH, PASSES, false>(J, bits, bid == 0, red, key0, key1, first);
+        else map_flat_body<STOCH, PASSES, true>(J, bits, bid == 0, red, key0, key1, first);
         return;
     }
     const uint32_t* __restrict__ x = J.x;
@@ -544,31 +552,36 @@ struct MapPlan {
     int passes;      // 4, 2 or 1
     bool tile_path;  // false: the one-element-per-thread kernel
     bool any;        // rows that are not whole quads, or pointers off the 16-byte grid
-    bool flat;       // no transposed copy: one run of quads
+    bool flat;       // one run of quads (no transposed copy)
 };
 
-constexpr int64_t kFlatTileElements = 4096;     // of one pass
+constexpr int64_t kFlatTileElements = 4096;                 // of one pass
+constexpr int64_t kFlatMaxElements = int64_t{1} << 26;      // of a tensor of long rows
 
 static MapPlan plan_map(const MapTensor& t) {
     MapPlan p;
     // tile width: 64 when that pads the rows less than 128 does (cols = 64, 192, ...)
     p.tc = ((t.cols + 63) / 64) * 64 < ((t.cols + 127) / 128) * 128 ? 64 : 128;
-    p.flat = t.qT == nullptr;
+    p.any = t.cols % 4 != 0 || !aligned(t.x, 16) || !aligned(t.q, 16) || !aligned(t.qT, 16);
     const int64_t tall = p.tc == 128 ? 128 : 256;   // rows of a 4-pass tile
     const int64_t tiles_c = (t.cols + p.tc - 1) / p.tc;
+    auto tile_count = [&](int64_t passes) { return (t.rows + tall / 4 * passes - 1) / (tall / 4 * passes) * tiles_c; };
+    const bool tiles = t.rows > 0 && t.cols > 0 && t.cols < (int64_t{1} << 22) &&     // 32-bit offsets inside a tile
+                       t.rows < (int64_t{1} << 32) &&       // and a 32-bit row count in the transposed copy's addressing
+                       // of a row shorter than a quarter of a tile most lanes would map nothing
+                       (!p.any || t.cols >= 16) && tile_count(1) < (int64_t{1} << 30);
+    // Row-major only: flat, but tiles where a tensor of long rows is so large that it comes from HBM alone - their short
+    // runs in many rows spread better (stochastic rounding, flat / tiles in us: 8192 x 2048 15.0 / 18.9, 8192 x 4096
+    // 26.7 / 27.0, 12288 x 4096 39.7 / 39.4, 16384 x 4096 62.6 / 61.1, 16384 x 8192 129 / 120, 50000 x 2048 99.6 / 94.0; of
+    // shorter rows 262144 x 256 62.3 / 63.5, 4194304 x 16 62.6 / 162).
+    p.flat = t.qT == nullptr && (!tiles || p.any || t.cols < 1024 || t.rows * t.cols < kFlatMaxElements);
     // four passes per tile when that still gives a thousand workgroups (four per CU), else two, else single-pass
     // tiles (a sweep of the threshold from 512 to 8192 moved whole-step times by under 3 %)
     auto count = [&](int64_t passes) {
-        if (p.flat) return (t.rows * t.cols + kFlatTileElements * passes - 1) / (kFlatTileElements * passes);
-        return (t.rows + tall / 4 * passes - 1) / (tall / 4 * passes) * tiles_c;
+        return p.flat ? (t.rows * t.cols + kFlatTileElements * passes - 1) / (kFlatTileElements * passes) : tile_count(passes);
     };
     p.passes = count(4) >= 1024 ? 4 : (count(2) >= 1024 ? 2 : 1);
-    p.any = t.cols % 4 != 0 || !aligned(t.x, 16) || !aligned(t.q, 16) || !aligned(t.qT, 16);
-    p.tile_path = t.rows > 0 && t.cols > 0 && count(1) < (int64_t{1} << 30) &&
-                  (p.flat || (t.cols < (int64_t{1} << 22) &&          // 32-bit offsets inside a tile
-                              t.rows < (int64_t{1} << 32) &&          // and a 32-bit row count in the transposed copy's addressing
-                              // of a row shorter than a quarter of a tile most lanes would map nothing
-                              (!p.any || t.cols >= 16)));
+    p.tile_path = p.flat ? t.rows > 0 && t.cols > 0 && count(1) < (int64_t{1} << 30) : tiles;
     return p;
 }
 
@@ -601,10 +614,12 @@ static MapJob make_job(const MapTensor& t, int tc, int passes, bool flat) {
 static void launch_tiles(const MapJobs& jobs, int tc, int passes, bool any, bool stoch, uint32_t k0, uint32_t k1, int bits,
                          hipStream_t s) {
     const dim3 grid(jobs.j[0].blocks + jobs.j[1].blocks), block(kMapThreads);
+    const bool flat = jobs.j[0].flat || (jobs.j[1].blocks != 0 && jobs.j[1].flat);
 #define FXP_MAP_LAUNCH(STOCH, PASSES, TC)                                                                          \
     do {                                                                                                           \
-        if (any) hipLaunchKernelGGL((k_map_tile<STOCH, PASSES, TC, true>), grid, block, 0, s, jobs, k0, k1, bits);  \
-        else hipLaunchKernelGGL((k_map_tile<STOCH, PASSES, TC, false>), grid, block, 0, s, jobs, k0, k1, bits);     \
+        auto kernel = any ? (flat ? k_map_tile<STOCH, PASSES, TC, true, true> : k_map_tile<STOCH, PASSES, TC, true, false>)     \
+                          : (flat ? k_map_tile<STOCH, PASSES, TC, false, true> : k_map_tile<STOCH, PASSES, TC, false, false>);  \
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, jobs, k0, k1, bits);                                          \
     } while (0)
 #define FXP_MAP_PICK(TC)                                   \
     if (stoch) {                                           \

@@ -139,3 +139,24 @@ def test_bmm_gradients_in_one_launch(fxp, batch, M, K, N, transB):
     Yo, saved = oracle.bmm_fwd(A, B, transB=transB, seed=2, step=3)
     dAo, dBo, _ = oracle.bmm_bwd(dY, saved, seed=2, step=3)
     assert same_bits(host(Y), Yo) and same_bits(host(dA), dAo) and same_bits(host(dB), dBo)
+
+
+# a whole number of workgroups, one element and one quad more and less, in one, two and four passes; both sides of the
+# size beyond which tensors of long rows are tiled
+@pytest.mark.parametrize("rows,cols", [(1, 4096), (1, 4097), (1, 4095), (4, 1025), (1, 4100), (1024, 8192), (1024 * 8192 + 3, 1), (4096, 4096),
+                                       (16777213, 1), (65535, 1024), (65536, 1024), (65536, 1020)])
+def test_map_row_major_alone(fxp, rows, cols):
+    """The row-major copy alone is the one that is written beside a transposed copy."""
+    say("map, row-major alone", (rows, cols))
+    x = torch.randn((rows, cols), device="cuda")
+    x[rows // 2, cols // 3] = float("inf")
+    x[rows - 1, cols - 1] = 7.9999999
+    e = torch.full((1,), 129, dtype=torch.int32, device="cuda")
+    q, qT, alone = (torch.zeros(rows * cols, dtype=torch.int8, device="cuda") for _ in range(3))
+    for out, outT in ((q, qT.data_ptr()), (alone, None)):
+        assert fxp.lib().fxp_map(x.data_ptr(), rows, cols, e.data_ptr(), out.data_ptr(), outT, 5, 77, 0, 8, None) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(q, alone)
+    n = min(rows * cols, 200000)
+    want = oracle.map(host(x).reshape(1, -1)[:, :n], 129, seed=5, stream_id=77)
+    assert np.array_equal(host(alone)[:n], want[0])
