@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "fxp_internal.h"
+#include "fxp_map_plan.h"
 
 namespace fxp {
 
@@ -546,43 +547,8 @@ __global__ __launch_bounds__(kMapThreads) void k_map_generic(const uint32_t* __r
     }
 }
 
-// how one tensor would be tiled
-struct MapPlan {
-    int tc;          // tile columns
-    int passes;      // 4, 2 or 1
-    bool tile_path;  // false: the one-element-per-thread kernel
-    bool any;        // rows that are not whole quads, or pointers off the 16-byte grid
-    bool flat;       // one run of quads (no transposed copy)
-};
-
-constexpr int64_t kFlatTileElements = 4096;                 // of one pass
-constexpr int64_t kFlatMaxElements = int64_t{1} << 26;      // of a tensor of long rows
-
 static MapPlan plan_map(const MapTensor& t) {
-    MapPlan p;
-    // tile width: 64 when that pads the rows less than 128 does (cols = 64, 192, ...)
-    p.tc = ((t.cols + 63) / 64) * 64 < ((t.cols + 127) / 128) * 128 ? 64 : 128;
-    p.any = t.cols % 4 != 0 || !aligned(t.x, 16) || !aligned(t.q, 16) || !aligned(t.qT, 16);
-    const int64_t tall = p.tc == 128 ? 128 : 256;   // rows of a 4-pass tile
-    const int64_t tiles_c = (t.cols + p.tc - 1) / p.tc;
-    auto tile_count = [&](int64_t passes) { return (t.rows + tall / 4 * passes - 1) / (tall / 4 * passes) * tiles_c; };
-    const bool tiles = t.rows > 0 && t.cols > 0 && t.cols < (int64_t{1} << 22) &&     // 32-bit offsets inside a tile
-                       t.rows < (int64_t{1} << 32) &&       // and a 32-bit row count in the transposed copy's addressing
-                       // of a row shorter than a quarter of a tile most lanes would map nothing
-                       (!p.any || t.cols >= 16) && tile_count(1) < (int64_t{1} << 30);
-    // Row-major only: flat, but tiles where a tensor of long rows is so large that it comes from HBM alone - their short
-    // runs in many rows spread better (stochastic rounding, flat / tiles in us: 8192 x 2048 15.0 / 18.9, 8192 x 4096
-    // 26.7 / 27.0, 12288 x 4096 39.7 / 39.4, 16384 x 4096 62.6 / 61.1, 16384 x 8192 129 / 120, 50000 x 2048 99.6 / 94.0; of
-    // shorter rows 262144 x 256 62.3 / 63.5, 4194304 x 16 62.6 / 162).
-    p.flat = t.qT == nullptr && (!tiles || p.any || t.cols < 1024 || t.rows * t.cols < kFlatMaxElements);
-    // four passes per tile when that still gives a thousand workgroups (four per CU), else two, else single-pass
-    // tiles (a sweep of the threshold from 512 to 8192 moved whole-step times by under 3 %)
-    auto count = [&](int64_t passes) {
-        return p.flat ? (t.rows * t.cols + kFlatTileElements * passes - 1) / (kFlatTileElements * passes) : tile_count(passes);
-    };
-    p.passes = count(4) >= 1024 ? 4 : (count(2) >= 1024 ? 2 : 1);
-    p.tile_path = p.flat ? t.rows > 0 && t.cols > 0 && count(1) < (int64_t{1} << 30) : tiles;
-    return p;
+    return plan_map(t.rows, t.cols, aligned(t.x, 16) && aligned(t.q, 16) && aligned(t.qT, 16), t.qT != nullptr);
 }
 
 static MapJob make_job(const MapTensor& t, int tc, int passes, bool flat) {
@@ -669,7 +635,8 @@ int scale_map_guess_launch(const MapTensor& a, const MapTensor* b, uint32_t* are
     const int64_t na = a.rows * a.cols, nb = b ? b->rows * b->cols : 0;
     // below a few million elements a scale reduction costs what the verifying launch costs
     if (std::max(na, nb) < kGuessMinElements) return kNoGuessPath;
-    if (!pa.tile_path || !pb.tile_path || pa.any || pb.any) return kNoGuessPath;
+    // (tiles, whether or not an ordinary map would take the tensor flat)
+    if (!pa.tiles || !pb.tiles || pa.any || pb.any) return kNoGuessPath;
     if (pa.tc != pb.tc) return kGuessOneByOne;        // different tile widths: no common launch, but each may guess alone
     const int passes = na >= nb ? pa.passes : pb.passes;
     MapJobs jobs;

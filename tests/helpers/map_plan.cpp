@@ -1,0 +1,13 @@
+// map_plan: prints what plan_map answers for "rows cols aligned16 transposed" lines on standard input
+#include <cstdio>
+
+#include "fxp_map_plan.h"
+
+int main() {
+    long long rows, cols;
+    int aligned16, transposed;
+    while (std::scanf("%lld %lld %d %d", &rows, &cols, &aligned16, &transposed) == 4) {
+        const fxp::MapPlan p = fxp::plan_map(rows, cols, aligned16 != 0, transposed != 0);
+        std::printf("%d %d %d %d %d %d\n", p.tc, p.passes, p.tiles, p.any, p.flat, p.tile_path);
+    }
+}
