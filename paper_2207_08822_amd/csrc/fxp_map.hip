@@ -351,10 +351,26 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     __syncthreads();
     int8_t* qTt = qT + c0 * rows + r0;             // element [c0][r0] of the transposed copy
     const uint32_t urows = static_cast<uint32_t>(rows);
-    // 16 rows of one column = 16 contiguous bytes of qT, at any alignment when the rows are not whole 16-byte pieces
-    constexpr int PIECES = TR / 16;                     // per column
+    constexpr int PIECES = TR / 16;                // 16 rows of one column = 16 contiguous bytes of qT
+    constexpr int ROUNDS = (TC * PIECES + kMapThreads - 1) / kMapThreads;
+    // Rows that are whole pieces have a loop of their own, and that of edge tiles is not unrolled: every map kernel holds them all
+    // (with one unrolled loop for either, k_map_tile_guess lost 2 % of a step: 12608 x 768 x 2304 164.0 -> 167.1 us).
+    if (!ANY && (rows & 15) == 0) {
 #pragma unroll
-    for (int it = 0; it < (TC * PIECES + kMapThreads - 1) / kMapThreads; ++it) {
+        for (int it = 0; it < ROUNDS; ++it) {
+            const int id = it * kMapThreads + tid;
+            const int c = id / PIECES, ch = id % PIECES;
+            if (c < TC && (!EDGE || (c < cols_here && 16 * ch < rows_here))) {
+                const uint32_t* src = stage + c * TS + 4 * ch;
+                *reinterpret_cast<uint4*>(qTt + static_cast<uint64_t>(c) * urows + 16 * ch) =
+                    make_uint4(src[0], src[1], src[2], src[3]);
+            }
+        }
+        return;
+    }
+    // ... any others take 16 bytes at any alignment, and their last bytes one by one
+#pragma unroll (EDGE ? 1 : ROUNDS)
+    for (int it = 0; it < ROUNDS; ++it) {
         const int id = it * kMapThreads + tid;
         const int c = id / PIECES, ch = id % PIECES;
         if (c < TC && (!EDGE || (c < cols_here && 16 * ch < rows_here))) {
