@@ -152,9 +152,11 @@ __device__ inline float store_fragments(const v16i (&acc)[FM][FN], void* __restr
 
 // Sum of the split-K slices of a product (exact in any order) -> int32 or inverse-mapped fp32, by workgroup
 // `b` of `nb`.  The slices are dense M x N matrices `stride` elements apart.  A dense, 16-byte aligned output is
-// walked as one flat run of 16-byte pieces, anything else row by row.  ALONE: a launch of its own, which may also add in
-// 64 bits and share a piece among lanes; a rider in a product's launch keeps the one plain loop (with all three inside
-// every product kernel, and twice the riders, the input gradient of a 32 x 28 x 28 x 128 3x3 layer took 14.0 us for 11.3).
+// walked as one flat run of 16-byte pieces, anything else row by row.  ALONE: a launch of its own, which may share a piece
+// among lanes; a rider in a product's launch takes a lane a piece (with the shared pieces in every product kernel, and twice
+// the riders, the input gradient of a 32 x 28 x 28 x 128 3x3 layer took 14.0 us for 11.3).  64-bit sums ride like any other:
+// layer steps of 64 x 56 x 56 x 64 -> 64 3x3 145 us, with a launch of their own 151, one element a thread 176;
+// 262144 x 128 x 512 521 / 528 / 525; 200000 x 256 x 64 230 / 241 / 264.
 template <bool ALONE>
 __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsigned nb) {
     const unsigned nt = blockDim.x;                  // 256 stand-alone; the host product's workgroup size when riding
@@ -209,11 +211,30 @@ __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsi
             }
         }
     };
-    if (ALONE && r.wide) {
+    // the same with a lane a piece
+    auto wide_pieces = [&]() {
+        for (int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x; i < total >> 2; i += static_cast<int64_t>(nb) * nt) {
+            int64_t s[4] = {0, 0, 0, 0};
+#pragma unroll 8
+            for (int sidx = 0; sidx < splits; ++sidx) {
+                const int4 v = reinterpret_cast<const int4*>(parts + sidx * stride)[i];
+                s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
+            }
+            float o[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                o[k] = unmap_value64(s[k], E);
+                m = fmaxf(m, fabsf(o[k]));
+            }
+            reinterpret_cast<float4*>(r.C)[i] = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    };
+    if (r.wide) {
         // contraction beyond what one int32 sum holds: 64-bit sums of the slices
         int64_t i = static_cast<int64_t>(b) * nt + threadIdx.x;
         if (flat) {
-            pieces(IC<1>{});
+            if constexpr (ALONE) pieces(IC<1>{});
+            else wide_pieces();
             i += total & ~int64_t{3};                               // the tail, one element per thread
         }
         for (; i < total; i += static_cast<int64_t>(nb) * nt) {
@@ -1487,7 +1508,7 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         r.eA = eA; r.bitsA = bitsA; r.eB = eB; r.bitsB = bitsB;
         r.amax = amax;
         r.wide = K > kMaxContraction ? 1 : 0;
-        if (defer != nullptr && !r.wide) {                      // riders add in 32 bits
+        if (defer != nullptr) {
             r.blocks = reduce_blocks(r, 1);
             *defer = r;
             return FXP_OK;
