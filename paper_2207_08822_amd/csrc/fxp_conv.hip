@@ -89,28 +89,35 @@ __host__ __device__ inline int class_taps(int k, int r, int stride) { return (k 
 // CLASSES: which of the two, a parameter of every kernel that flips: with both forms in it, the launch the flip rides
 // in was compiled differently (34 VGPRs for 53) and took 12.95 us, with the stride-1 form alone 12.64 (k_im2col_t_i8 of
 // 32 x 28 x 28 x 128, 3x3; means of three traces).
+// The class form reads WqT (in the place of Wq) and is a permutation of its rows (Cout contiguous bytes, whole 16-byte pieces: Cout % 64 == 0), one
+// piece per thread and round: from the rows of Wq, byte by byte, 4096 x 4608 weights took 92 us of the launch, now 11.
 template <bool CLASSES>
 __device__ inline void flip_weights_body(const int8_t* __restrict__ Wq, const ConvGeo& g, int8_t* __restrict__ WqF, unsigned bid,
                                          unsigned nblocks) {
-    const int64_t K = g.K(), Kf = static_cast<int64_t>(g.KH) * g.KW * g.Cout, total = static_cast<int64_t>(g.C) * Kf;
-    for (int64_t id = static_cast<int64_t>(bid) * 256 + threadIdx.x; id < total; id += static_cast<int64_t>(nblocks) * 256) {
-        if constexpr (CLASSES) {
-            int64_t at = id;
+    if constexpr (CLASSES) {
+        // (below 2^31 rows and pieces: both contractions are at most kMaxContraction long)
+        const uint32_t per_row = static_cast<uint32_t>(g.Cout) / 16, pieces = static_cast<uint32_t>(g.K()) * per_row;
+        for (uint32_t id = bid * 256 + threadIdx.x; id < pieces; id += nblocks * 256) {
+            uint32_t at = id / per_row;                                // row of WqF, then of its class
+            const uint32_t piece = id - at * per_row;
             for (int cls = 0; cls < g.stride * g.stride; ++cls) {
                 const int rh = cls / g.stride, rw = cls - rh * g.stride;
-                const int th = class_taps(g.KH, rh, g.stride), tw = class_taps(g.KW, rw, g.stride), kc = th * tw * g.Cout;
-                if (at >= static_cast<int64_t>(g.C) * kc) {
-                    at -= static_cast<int64_t>(g.C) * kc;
+                const uint32_t tw = class_taps(g.KW, rw, g.stride), taps = class_taps(g.KH, rh, g.stride) * tw;
+                if (at >= g.C * taps) {
+                    at -= g.C * taps;
                     continue;
                 }
-                const int c = static_cast<int>(at / kc), rem = static_cast<int>(at - static_cast<int64_t>(c) * kc);
-                const int tap = rem / g.Cout, co = rem - tap * g.Cout, i = tap / tw, j = tap - i * tw;
-                const int kh = rh + g.stride * (th - 1 - i), kw = rw + g.stride * (tw - 1 - j);
-                WqF[id] = Wq[co * K + static_cast<int64_t>(kh * g.KW + kw) * g.C + c];
+                const uint32_t c = at / taps, tap = at - c * taps, i = tap / tw, j = tap - i * tw, th = taps / tw;
+                const uint32_t kh = rh + g.stride * (th - 1 - i), kw = rw + g.stride * (tw - 1 - j);
+                reinterpret_cast<uint4*>(WqF)[id] =
+                    reinterpret_cast<const uint4*>(Wq)[static_cast<uint64_t>((kh * g.KW + kw) * g.C + c) * per_row + piece];
                 break;
             }
-            continue;
         }
+        return;
+    }
+    const int64_t K = g.K(), Kf = static_cast<int64_t>(g.KH) * g.KW * g.Cout, total = static_cast<int64_t>(g.C) * Kf;
+    for (int64_t id = static_cast<int64_t>(bid) * 256 + threadIdx.x; id < total; id += static_cast<int64_t>(nblocks) * 256) {
         const int c = static_cast<int>(id / Kf);
         const int rem = static_cast<int>(id - c * Kf);
         const int tap = rem / g.Cout, co = rem - tap * g.Cout;
@@ -501,9 +508,11 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     const bool need_flip = dX && (dx_as_conv(g) || strided);
     int8_t* flipped = strided ? reinterpret_cast<int8_t*>(area + wc_at) : saved->WqF;
     ReduceRider pending;                 // the weight gradient's split-K reduction while it waits for a launch to ride in
+    const int8_t* to_flip = strided ? saved->WqT : saved->Wq;
+    const unsigned flip_blocks = need_flip ? grid_for(static_cast<int64_t>(g.Cout) * K / (strided ? 16 : 1)) : 0u;
     if (need_flip && (!dW || thin)) {
-        hipLaunchKernelGGL(strided ? k_flip_weights_i8<true> : k_flip_weights_i8<false>, dim3(grid_for(static_cast<int64_t>(g.Cout) * K)),
-                           dim3(256), 0, s, saved->Wq, g, flipped);
+        hipLaunchKernelGGL(strided ? k_flip_weights_i8<true> : k_flip_weights_i8<false>, dim3(flip_blocks), dim3(256), 0, s, to_flip, g,
+                           flipped);
         if ((rc = launch_status())) return rc;
     }
     if (thin) {
@@ -523,13 +532,12 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
         const int64_t blocks = static_cast<int64_t>(g.KH) * (quads ? 1 : g.KW) * tiles_m * tiles_c;
         if (blocks >= (int64_t{1} << 31)) return FXP_ERR_DIMS;
         // the flipped weights of the input-gradient convolution ride along in the same launch
-        const unsigned flip_blocks = need_flip ? grid_for(static_cast<int64_t>(g.Cout) * K) : 0u;
         if (blocks + flip_blocks + side.blocks >= (int64_t{1} << 31)) return FXP_ERR_DIMS;
         const dim3 tgrid(side.blocks + static_cast<unsigned>(blocks) + flip_blocks);
         const auto transpose = quads ? (strided ? k_im2col_t_i8<64, true> : k_im2col_t_i8<64, false>)
                                      : (strided ? k_im2col_t_i8_bytes<true> : k_im2col_t_i8_bytes<false>);
         hipLaunchKernelGGL(transpose, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c, static_cast<unsigned>(blocks),
-                           saved->Wq, flipped, side);
+                           to_flip, flipped, side);
         if ((rc = launch_status())) return rc;
         // dY: the map kernel finishes the reduction from the block maxima just written
         const MapTensor tdY{dY, M, g.Cout, nullptr, side.partials, static_cast<int>(side.blocks), e_dY, dYq, dYqT,
