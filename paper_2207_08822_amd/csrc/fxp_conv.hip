@@ -359,7 +359,7 @@ static StrideClasses classes_of(const ConvGeo& g) {
 // whatever the weight gradient keeps there.  Fewer than 32 channels leave most of a 128-column tile empty and the matrix
 // of a thin image is small.
 static bool dx_strided(const ConvGeo& g, bool with_dw, size_t area_bytes, size_t* wc_at) {
-    if (g.stride == 1 || g.stride > kMaxStride || g.C < 32 || !conv_strided_dx_fits(classes_of(g), g.N)) return false;
+    if (g.stride == 1 || g.stride > kMaxStride || g.C < 32 || !conv_strided_dx_fits(classes_of(g), g.N, g.C)) return false;
     const size_t wc = round_up(static_cast<size_t>(g.C) * g.KH * g.KW * g.Cout, 256);
     const size_t dw = with_dw ? round_up(static_cast<size_t>(g.K()) * g.M(), 256) + gemm_split_ws_bytes(g.Cout, g.K(), g.M()) : 0;
     if (area_bytes < dw + wc + 256) return false;

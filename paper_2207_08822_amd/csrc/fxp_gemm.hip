@@ -1545,6 +1545,16 @@ static int conv_gemm_launch_cfg(const ConvTaps& ct, int64_t K, int64_t M, int64_
     return launch_status();
 }
 
+// Contractions that few tiles walk as one chain of steps for longer than it takes to store the patches and split the product.
+// The chain grows with K, the stored patches with K and M.  Layer steps in us, stored and split / implicit: K = 9216, M = 16
+// 122 / 142, 49 148 / 143, 98 151 / 146; 13824, 49 267 / 271, 98 272 / 277, 196 298 / 280; 18432, 98 377 / 382, 392 445 / 414,
+// 784 104 / 106 (64 output channels); 36864, 128 240 / 275, 392 153 / 190 (64).  Of a 1x1 layer, whose patches are the image,
+// K = 2048, M = 49 64.7 / 61.1, 4096, 49 143 / 154, 196 159 / 160.
+static bool deep_chain(const ConvTaps& ct, int64_t M, int64_t K) {
+    if (K == ct.C && ct.stride == 1 && ct.pad == 0 && ct.padw == 0) return K > 2048;
+    return K > 4608 && (K > 18432 || K > 128 * M);
+}
+
 int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq, float* Y,
                      const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride) {
     const int64_t K = static_cast<int64_t>(KH) * ct.KW * ct.C;
@@ -1555,8 +1565,11 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     // fill the chip, no patches are stored and no slices summed.  Layer steps against stored patches: 32 x 14 x 14 x 256 -> 256
     // 3x3 110 -> 64 us (98 large tiles; unsplit large tiles: 68), 32 x 7 x 7 x 512 -> 512 113 -> 80 (52; 95), batch 64 140 -> 96
     // (100; 102); with 196 large tiles (batch 64 of 14 x 14) 131 -> 104, large ones 86.
+    // (Of contractions up to 4608 every size down to one image of 4 x 4 gains: 1 x 7 x 7 x 512 95.6 -> 70.9, 1 x 4 x 4 x 256
+    // 60.2 -> 45.1.)
     const int64_t t128 = ((M + 127) / 128) * ((Cout + 127) / 128);
     if (t128 <= 128) {
+        if (plan.splits > 1 && deep_chain(ct, M, K)) return kNotApplicable;
         if (ct.C % 128 == 0) return conv_gemm_launch_cfg<64, 64, 128, 32, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
         return conv_gemm_launch_cfg<64, 64, 64, 32, 32>(ct, K, M, Cout, Xq, Wq, Y, eA, bitsA, eB, bitsB, s, ride);
     }
@@ -1575,13 +1588,22 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
 
 // dX[N, H, W, C] of a strided convolution from dYq[N, Ho, Wo, Cout] and the weights in class order (StrideClasses): the
 // channels of the gradient must fill whole K steps.
-bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images) {
-    int64_t tiles = 0;
+//
+// Against the stored patch gradient (which may be split along its contraction) the longest class must not be a long
+// serial chain in few tiles.  Layer steps in us, patch gradient / classes, at contraction length (tiles): 512 (196) 69 / 53;
+// 1024 (16) 50.1 / 48.7, (196) 87 / 67; 2048 (32) 56.8 / 59.8, (56) 57.4 / 59.8, (152) 84 / 72; 4096 (28) 78.7 / 83.5,
+// (112) 80.2 / 87.6, (196) 103 / 94, (296) 126 / 121; 8192 (224) 169 / 180, (608) 315 / 339; 9216 (32) 68 / 105.
+bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images, int64_t C) {
+    if (sc.stride <= 1 || sc.stride > kMaxStride || sc.C % 64 != 0) return false;
+    int64_t row_tiles = 0, tiles = 0, longest = 0;
     for (int c = 0; c < sc.stride * sc.stride; ++c) {
-        const int64_t rows = images * sc.cls[c].Ho * sc.cls[c].Wo;
-        tiles = std::max(tiles, (rows + 127) / 128 * sc.stride * sc.stride);
+        const StrideClass& k = sc.cls[c];
+        const int64_t t = (images * k.Ho * k.Wo + 127) / 128;
+        row_tiles = std::max(row_tiles, t * sc.stride * sc.stride);
+        tiles += t * ((C + 127) / 128);
+        longest = std::max(longest, static_cast<int64_t>(k.TH) * k.TW * sc.C);
     }
-    return sc.stride > 1 && sc.stride <= kMaxStride && sc.C % 64 == 0 && tiles < (int64_t{1} << 24);
+    return row_tiles < (int64_t{1} << 24) && (longest <= 1024 || (longest <= 4096 && longest <= 32 * tiles));
 }
 
 template <int BN, int BK, int WN, int STAGES = 4>

@@ -133,7 +133,7 @@ struct StrideClasses {
 };
 int conv_strided_dx_launch(const StrideClasses& sc, int64_t images, int64_t C, const int8_t* dYq, const int8_t* Wc, float* dX,
                            const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride);
-bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images);
+bool conv_strided_dx_fits(const StrideClasses& sc, int64_t images, int64_t C);
 int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq, float* Y,
                      const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s, ReduceRider* ride = nullptr);
 // convolutions of thin images (fxp_conv_direct.hip); kNotApplicable / false: the shape takes the general path

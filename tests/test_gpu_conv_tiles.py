@@ -49,3 +49,36 @@ def test_few_tiles(fxp, N, H, W, C, Cout, KH, pad):  # noqa: F811
 def test_strided_input_gradient_alone(fxp, case):  # noqa: F811
     say("strided conv, dX alone", case)
     check_conv(fxp, *_tensors(*case), 2, case[-1], bits=5, need_dW=False)
+
+
+# more than 128 large tiles and at most 64 output channels: 128 x 64 tiles, ragged in the last row tile and in the columns
+@pytest.mark.parametrize("N,H,W,C,Cout,KH", [(6, 53, 53, 64, 64, 3), (6, 53, 53, 64, 64, 1), (6, 53, 53, 64, 40, 3), (5, 59, 57, 192, 8, 3)])
+def test_many_tiles_of_few_channels(fxp, N, H, W, C, Cout, KH):  # noqa: F811
+    say("conv, 128 x 64 tiles", (N, H, W, C, Cout, KH))
+    rng = np.random.default_rng(H + C + Cout)
+    X = np.maximum(rng.standard_normal((N, H, W, C)), 0).astype(np.float32)
+    Wt = rng.standard_normal((Cout, KH, KH, C)).astype(np.float32)
+    assert N * H * W > 128 * 128
+    check_conv(fxp, X, Wt, rng.laplace(0, 1e-3, (N, H, W, Cout)).astype(np.float32), 1, KH // 2)
+
+
+# both sides of the rule on long contractions in few tiles: 5184 terms over 16 and 49 pixels, 9216 over 64 and 98, beyond
+# 18432; 1x1 layers around 2048 channels
+@pytest.mark.parametrize("N,H,C,Cout,KH", [(1, 4, 576, 64, 3), (1, 7, 576, 64, 3), (1, 8, 1024, 70, 3), (2, 7, 1024, 64, 3), (3, 8, 2112, 64, 3),
+                                           (2, 7, 2048, 100, 1), (2, 7, 2112, 128, 1), (2, 7, 128, 2112, 1)])
+def test_long_contractions_in_few_tiles(fxp, N, H, C, Cout, KH):  # noqa: F811
+    say("conv, long contraction, few tiles", (N, H, C, Cout, KH))
+    rng = np.random.default_rng(H + C + Cout)
+    X = np.maximum(rng.standard_normal((N, H, H, C)), 0).astype(np.float32)
+    Wt = rng.standard_normal((Cout, KH, KH, C)).astype(np.float32)
+    check_conv(fxp, X, Wt, rng.laplace(0, 1e-3, (N, H, H, Cout)).astype(np.float32), 1, KH // 2)
+
+
+# both sides of the rule on the longest class of a strided input gradient: 512 and 1024 channels (2048 and 4096 terms), few
+# tiles (patch gradient) and enough of them (classes); beyond 4096 terms
+@pytest.mark.parametrize("N,H,C,Cout,KH", [(2, 14, 64, 512, 3), (19, 14, 129, 512, 3), (2, 9, 33, 1024, 3), (37, 14, 257, 1024, 3), (3, 9, 32, 1088, 3),
+                                           (2, 12, 64, 2112, 1)])
+def test_strided_input_gradient_long_classes(fxp, N, H, C, Cout, KH):  # noqa: F811
+    say("strided conv, long classes", (N, H, C, Cout, KH))
+    pad = KH // 2
+    check_conv(fxp, *_tensors(N, H, H, C, Cout, KH, KH, pad), 2, pad)
