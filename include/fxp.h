@@ -347,7 +347,7 @@ typedef struct fxp_conv_saved {
     int8_t* Wq;   /* [Cout, KH*KW*C] */
     int8_t* WqT;  /* [KH*KW*C, Cout] */
     int8_t* WqF;  /* [C, KH*KW*Cout]: kernel flipped in both spatial axes; scratch of the backward call, which
-                     fills it from Wq when it computes the input gradient of a stride-1 convolution */
+                     fills it from WqT when it computes the input gradient of a stride-1 convolution */
     int32_t* eX;  /* 1 */
     int32_t* eW;  /* 1 */
 } fxp_conv_saved;

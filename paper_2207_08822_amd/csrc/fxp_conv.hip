@@ -83,58 +83,60 @@ __global__ __launch_bounds__(256) void k_im2col_i8(const int8_t* __restrict__ Xq
 // convolution (the upstream gradient correlated with the flipped kernel), contraction-contiguous.
 // Strides > 1: one such array per class of input pixels, [C][TH][TW][Cout] of the taps kh = rh + stride * (TH - 1 - i),
 // kw = rw + stride * (TW - 1 - j), class (rh, rw) after class.
+// Either is a permutation of the rows of WqT[(kh, kw, c)][co], copied 16 bytes a thread and round (from the rows of Wq, byte
+// by byte, 4096 x 4608 weights in class order took 92 us of their launch, 2048 x 2048 flipped 19).
+// CLASSES: which of the two, a parameter of every kernel that flips: with both forms in it, the launch the flip rides
+// in took 12.95 us, with the stride-1 form alone 12.64 (k_im2col_t_i8 of 32 x 28 x 28 x 128, 3x3; means of three traces).
 __host__ __device__ inline int class_taps(int k, int r, int stride) { return (k - r + stride - 1) / stride; }   // r < stride
 
-//
-// CLASSES: which of the two, a parameter of every kernel that flips: with both forms in it, the launch the flip rides
-// in was compiled differently (34 VGPRs for 53) and took 12.95 us, with the stride-1 form alone 12.64 (k_im2col_t_i8 of
-// 32 x 28 x 28 x 128, 3x3; means of three traces).
-// The class form reads WqT (in the place of Wq) and is a permutation of its rows (Cout contiguous bytes, whole 16-byte pieces: Cout % 64 == 0), one
-// piece per thread and round: from the rows of Wq, byte by byte, 4096 x 4608 weights took 92 us of the launch, now 11.
+__host__ __device__ inline int flip_pieces(const ConvGeo& g) { return (g.Cout + 15) / 16; }       // per row
+
 template <bool CLASSES>
-__device__ inline void flip_weights_body(const int8_t* __restrict__ Wq, const ConvGeo& g, int8_t* __restrict__ WqF, unsigned bid,
+__device__ inline void flip_weights_body(const int8_t* __restrict__ WqT, const ConvGeo& g, int8_t* __restrict__ WqF, unsigned bid,
                                          unsigned nblocks) {
-    if constexpr (CLASSES) {
-        // (below 2^31 rows and pieces: both contractions are at most kMaxContraction long)
-        const uint32_t per_row = static_cast<uint32_t>(g.Cout) / 16, pieces = static_cast<uint32_t>(g.K()) * per_row;
-        for (uint32_t id = bid * 256 + threadIdx.x; id < pieces; id += nblocks * 256) {
-            uint32_t at = id / per_row;                                // row of WqF, then of its class
-            const uint32_t piece = id - at * per_row;
+    // (below 2^31 rows and pieces: both contractions are at most kMaxContraction long)
+    const uint32_t per_row = flip_pieces(g), pieces = static_cast<uint32_t>(g.K()) * per_row, Cout = g.Cout, C = g.C;
+    for (uint32_t id = bid * 256 + threadIdx.x; id < pieces; id += nblocks * 256) {
+        const uint32_t row = id / per_row, piece = id - row * per_row;
+        uint32_t from = 0;                                             // row of WqT
+        if constexpr (CLASSES) {
+            uint32_t at = row;                                         // in its class
             for (int cls = 0; cls < g.stride * g.stride; ++cls) {
                 const int rh = cls / g.stride, rw = cls - rh * g.stride;
                 const uint32_t tw = class_taps(g.KW, rw, g.stride), taps = class_taps(g.KH, rh, g.stride) * tw;
-                if (at >= g.C * taps) {
-                    at -= g.C * taps;
+                if (at >= C * taps) {
+                    at -= C * taps;
                     continue;
                 }
                 const uint32_t c = at / taps, tap = at - c * taps, i = tap / tw, j = tap - i * tw, th = taps / tw;
                 const uint32_t kh = rh + g.stride * (th - 1 - i), kw = rw + g.stride * (tw - 1 - j);
-                reinterpret_cast<uint4*>(WqF)[id] =
-                    reinterpret_cast<const uint4*>(Wq)[static_cast<uint64_t>((kh * g.KW + kw) * g.C + c) * per_row + piece];
+                from = (kh * g.KW + kw) * C + c;
                 break;
             }
+        } else {
+            const uint32_t taps = static_cast<uint32_t>(g.KH) * g.KW, c = row / taps, tap = row - c * taps;
+            from = (taps - 1 - tap) * C + c;                           // both axes flipped: the taps in reverse
         }
-        return;
-    }
-    const int64_t K = g.K(), Kf = static_cast<int64_t>(g.KH) * g.KW * g.Cout, total = static_cast<int64_t>(g.C) * Kf;
-    for (int64_t id = static_cast<int64_t>(bid) * 256 + threadIdx.x; id < total; id += static_cast<int64_t>(nblocks) * 256) {
-        const int c = static_cast<int>(id / Kf);
-        const int rem = static_cast<int>(id - c * Kf);
-        const int tap = rem / g.Cout, co = rem - tap * g.Cout;
-        const int kh = tap / g.KW, kw = tap - kh * g.KW;
-        WqF[id] = Wq[co * K + static_cast<int64_t>((g.KH - 1 - kh) * g.KW + (g.KW - 1 - kw)) * g.C + c];
+        const int8_t* src = WqT + static_cast<uint64_t>(from) * Cout + 16 * piece;
+        int8_t* dst = WqF + static_cast<uint64_t>(row) * Cout + 16 * piece;
+        if (Cout % 16 == 0) {
+            *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+        } else {
+            const uint32_t n = min(16u, Cout - 16 * piece);
+            for (uint32_t b = 0; b < n; ++b) dst[b] = src[b];
+        }
     }
 }
 
 template <bool CLASSES>
-__global__ __launch_bounds__(256) void k_flip_weights_i8(const int8_t* __restrict__ Wq, ConvGeo g, int8_t* __restrict__ WqF) {
-    flip_weights_body<CLASSES>(Wq, g, WqF, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(256) void k_flip_weights_i8(const int8_t* __restrict__ WqT, ConvGeo g, int8_t* __restrict__ WqF) {
+    flip_weights_body<CLASSES>(WqT, g, WqF, blockIdx.x, gridDim.x);
 }
 
 // The launch that writes the transposed patches carries two more pieces of the backward pass that depend on
 // nothing it writes: its first side.blocks workgroups reduce the block maxima of the incoming gradient (the
 // scale reduction that would otherwise be a launch of its own, and the first one of the pass), and the workgroups
-// beyond the tile_blocks tiles flip the weights for the input-gradient convolution (Wq -> WqF; possibly none).
+// beyond the tile_blocks tiles flip the weights for the input-gradient convolution (WqT -> WqF; possibly none).
 struct SideScale {
     const uint32_t* x = nullptr;      // the gradient, as bit patterns
     size_t n = 0;
@@ -144,7 +146,7 @@ struct SideScale {
 
 // true: this workgroup had one of the side roles and is done
 template <bool CLASSES>
-__device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, const int8_t* __restrict__ Wq, const ConvGeo& g,
+__device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, const int8_t* __restrict__ WqT, const ConvGeo& g,
                                   int8_t* __restrict__ WqF) {
     if (blockIdx.x < side.blocks) {
         __shared__ uint32_t red[4];
@@ -153,7 +155,7 @@ __device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, c
     }
     const unsigned b = blockIdx.x - side.blocks;
     if (b >= tile_blocks) {
-        flip_weights_body<CLASSES>(Wq, g, WqF, b - tile_blocks, gridDim.x - side.blocks - tile_blocks);
+        flip_weights_body<CLASSES>(WqT, g, WqF, b - tile_blocks, gridDim.x - side.blocks - tile_blocks);
         return true;
     }
     return false;
@@ -167,14 +169,14 @@ __device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, c
 // A workgroup walks the KW taps of one filter row for its tile (the rows' patch coordinates are worked out once, and
 // the loads of the next tap are in flight while this one is written out: 0.0645 -> 0.0633 ms per layer step on the
 // ResNet layer; all KH * KW taps per workgroup leave too few workgroups: 0.071 ms).
-// Workgroups beyond the tile_blocks tiles flip the weights for the input-gradient convolution (Wq -> WqF;
+// Workgroups beyond the tile_blocks tiles flip the weights for the input-gradient convolution (WqT -> WqF;
 // flip_blocks of them, possibly 0): two independent pieces of the backward pass in one launch.
 constexpr int kColTileM = 128;
 template <int TCH, bool CLASSES>
 __global__ __launch_bounds__(256) void k_im2col_t_i8(const int8_t* __restrict__ Xq, ConvGeo g, int8_t* __restrict__ colT,
                                                      int tiles_m, int tiles_c, unsigned tile_blocks,
-                                                     const int8_t* __restrict__ Wq, int8_t* __restrict__ WqF, SideScale side) {
-    if (side_roles<CLASSES>(side, tile_blocks, Wq, g, WqF)) return;
+                                                     const int8_t* __restrict__ WqT, int8_t* __restrict__ WqF, SideScale side) {
+    if (side_roles<CLASSES>(side, tile_blocks, WqT, g, WqF)) return;
     constexpr int TS = kColTileM / 4 + 1;                        // dwords per staged channel (+ 1 pad)
     constexpr int CG = TCH / 4, MG = 256 / CG;                   // channel groups x row groups per round
     constexpr int ROUNDS = kColTileM / 4 / MG;                   // groups of 4 rows per thread
@@ -241,8 +243,8 @@ __global__ __launch_bounds__(256) void k_im2col_t_i8(const int8_t* __restrict__ 
 template <bool CLASSES>
 __global__ __launch_bounds__(256) void k_im2col_t_i8_bytes(const int8_t* __restrict__ Xq, ConvGeo g, int8_t* __restrict__ colT,
                                                            int tiles_m, int tiles_c, unsigned tile_blocks,
-                                                           const int8_t* __restrict__ Wq, int8_t* __restrict__ WqF, SideScale side) {
-    if (side_roles<CLASSES>(side, tile_blocks, Wq, g, WqF)) return;
+                                                           const int8_t* __restrict__ WqT, int8_t* __restrict__ WqF, SideScale side) {
+    if (side_roles<CLASSES>(side, tile_blocks, WqT, g, WqF)) return;
     __shared__ int8_t t[64][65];
     int b = static_cast<int>(blockIdx.x - side.blocks);
     const int tc = b % tiles_c; b /= tiles_c;
@@ -508,10 +510,9 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     const bool need_flip = dX && (dx_as_conv(g) || strided);
     int8_t* flipped = strided ? reinterpret_cast<int8_t*>(area + wc_at) : saved->WqF;
     ReduceRider pending;                 // the weight gradient's split-K reduction while it waits for a launch to ride in
-    const int8_t* to_flip = strided ? saved->WqT : saved->Wq;
-    const unsigned flip_blocks = need_flip ? grid_for(static_cast<int64_t>(g.Cout) * K / (strided ? 16 : 1)) : 0u;
+    const unsigned flip_blocks = need_flip ? grid_for(K * flip_pieces(g)) : 0u;
     if (need_flip && (!dW || thin)) {
-        hipLaunchKernelGGL(strided ? k_flip_weights_i8<true> : k_flip_weights_i8<false>, dim3(flip_blocks), dim3(256), 0, s, to_flip, g,
+        hipLaunchKernelGGL(strided ? k_flip_weights_i8<true> : k_flip_weights_i8<false>, dim3(flip_blocks), dim3(256), 0, s, saved->WqT, g,
                            flipped);
         if ((rc = launch_status())) return rc;
     }
@@ -537,7 +538,7 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
         const auto transpose = quads ? (strided ? k_im2col_t_i8<64, true> : k_im2col_t_i8<64, false>)
                                      : (strided ? k_im2col_t_i8_bytes<true> : k_im2col_t_i8_bytes<false>);
         hipLaunchKernelGGL(transpose, tgrid, dim3(256), 0, s, saved->Xq, g, colT, tiles_m, tiles_c, static_cast<unsigned>(blocks),
-                           to_flip, flipped, side);
+                           saved->WqT, flipped, side);
         if ((rc = launch_status())) return rc;
         // dY: the map kernel finishes the reduction from the block maxima just written
         const MapTensor tdY{dY, M, g.Cout, nullptr, side.partials, static_cast<int>(side.blocks), e_dY, dYq, dYqT,
