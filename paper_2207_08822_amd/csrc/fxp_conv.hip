@@ -358,10 +358,11 @@ static StrideClasses classes_of(const ConvGeo& g) {
 }
 
 // Strided input gradients without the patch-gradient matrix, the class weights in the last bytes of the workspace behind
-// whatever the weight gradient keeps there.  Fewer than 32 channels leave most of a 128-column tile empty and the matrix
-// of a thin image is small.
+// whatever the weight gradient keeps there.  Down to 8 channels, in tiles of 64 columns (layer steps, patch gradient /
+// classes in us: 48 x 56 x 56 x 24 -> 64 3x3 93 / 76, 4 x 57 x 57 x 16 -> 128 57 / 50, 48 x 28 x 28 x 8 -> 64 58 / 49, 48 x 56 x 56 x 8
+// -> 64 5x5 97 / 83).
 static bool dx_strided(const ConvGeo& g, bool with_dw, size_t area_bytes, size_t* wc_at) {
-    if (g.stride == 1 || g.stride > kMaxStride || g.C < 32 || !conv_strided_dx_fits(classes_of(g), g.N, g.C)) return false;
+    if (g.stride == 1 || g.stride > kMaxStride || g.C < 8 || !conv_strided_dx_fits(classes_of(g), g.N, g.C)) return false;
     const size_t wc = round_up(static_cast<size_t>(g.C) * g.KH * g.KW * g.Cout, 256);
     const size_t dw = with_dw ? round_up(static_cast<size_t>(g.K()) * g.M(), 256) + gemm_split_ws_bytes(g.Cout, g.K(), g.M()) : 0;
     if (area_bytes < dw + wc + 256) return false;

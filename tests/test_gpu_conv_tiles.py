@@ -45,6 +45,14 @@ def test_few_tiles(fxp, N, H, W, C, Cout, KH, pad):  # noqa: F811
     check_conv(fxp, X, Wt, rng.laplace(0, 1e-3, (N, Ho, Wo, Cout)).astype(np.float32), 1, pad)
 
 
+# down to 8 channels, and the 7 below
+@pytest.mark.parametrize("N,H,W,C,Cout,KH,KW,pad", [(3, 15, 14, 8, 64, 3, 3, 1), (2, 14, 17, 7, 64, 3, 3, 1), (40, 28, 27, 9, 64, 5, 5, 2),
+                                                    (5, 31, 30, 24, 128, 3, 3, 0), (2, 20, 20, 31, 192, 2, 3, 1), (6, 28, 28, 16, 64, 1, 1, 0)])
+def test_strided_input_gradient_of_few_channels(fxp, N, H, W, C, Cout, KH, KW, pad):  # noqa: F811
+    say("strided conv, few channels", (N, H, W, C, Cout, KH, KW, pad))
+    check_conv(fxp, *_tensors(N, H, W, C, Cout, KH, KW, pad), 2, pad)
+
+
 @pytest.mark.parametrize("case", [CASES[1], CASES[4], CASES[11]])
 def test_strided_input_gradient_alone(fxp, case):  # noqa: F811
     say("strided conv, dX alone", case)
