@@ -107,7 +107,8 @@ int fxp_scale_map(const float* x, int64_t rows, int64_t cols, int32_t* e_max, in
  * (and one reduction launch) instead of two each - the layer calls use this for the activation and the
  * weight of a forward pass, where the second tensor is often too small to fill the chip by itself.  Results
  * are identical to two separate calls.  One launch needs both tensors on the fast path of fxp_map and of the
- * same tile width (cols <= 64 or cols % 128 in 1..64 selects the narrow tile); otherwise two launches are made. */
+ * same tile width (cols <= 64 or cols % 128 in 1..64 selects the narrow tile), or one of them wanted row-major only (which
+ * needs no tiles, whatever its width); otherwise two launches are made. */
 typedef struct fxp_map_desc {
     const float* x;      /* [rows, cols] fp32, device */
     int64_t rows, cols;
@@ -142,7 +143,7 @@ int fxp_map_absmax(const float* x, int64_t rows, int64_t cols, const uint32_t* a
  * contraction; other forms first transpose the operand into ws.  K <= 133144 (127^2 * K < 2^31: the int32
  * sums cannot wrap).
  * Fast loads need A, B 16-byte aligned and lda, ldb, K multiples of 16; other
- * shapes take a slower loader with identical results.  C 4-byte aligned. */
+ * shapes are loaded 16 bytes at a time at any address, results are identical.  C 4-byte aligned. */
 int fxp_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, const int8_t* B,
              int64_t ldb, int32_t* C, int64_t ldc, void* ws, size_t ws_bytes, void* stream);
 
@@ -269,7 +270,7 @@ typedef struct fxp_bmm_saved {
  * b < batch <= 65535.  A[batch,M,K] fp32; Bm[batch,K,N], or [batch,N,K] with transB != 0 (keys: scores =
  * Q K^T); Y[batch,M,N] fp32.  One scale per tensor; random streams FXP_TAG_X for A, FXP_TAG_W for Bm, element
  * index = row-major index in the whole tensor.  Fills every member of *saved.  Full speed needs M, K, N
- * multiples of 16 (pad the sequence length); other sizes take the slower general loads, same results.
+ * multiples of 16 (pad the sequence length); other sizes take 16-byte loads at any address, same results.
  * ws: fxp_workspace_bytes(FXP_OP_BMM_FWD, ...) bytes, 256-byte aligned. */
 int fxp_bmm_fwd(const float* A, const float* Bm, int64_t batch, int64_t M, int64_t K, int64_t N, int transB, float* Y,
                 const fxp_bmm_saved* saved, uint64_t seed, uint64_t step, int rounding, int bits, void* ws,
@@ -357,8 +358,9 @@ size_t fxp_conv2d_workspace_bytes(const fxp_conv2d_shape* shape, int backward);
 
 /* Forward: the activation tensor is mapped once as a whole (element index = its channels-last flat index,
  * FXP_TAG_X), the weights likewise (FXP_TAG_W); the int8 patches are multiplied on the matrix cores - read
- * straight from the int8 activation by the GEMM loader when C is a multiple of 64, gathered into scratch
- * first otherwise - and Y receives the inverse-mapped fp32 result.  Contractions KH*KW*C and KH*KW*Cout <= 133144. */
+ * straight from the int8 activation when C is a multiple of 64 (by the GEMM loader, save for a few long contractions) or
+ * at most 4 (filter rows of up to 32 bytes, up to 128 output channels), gathered into scratch first otherwise (a 1x1 layer's
+ * patches are the activation itself) - and Y receives the inverse-mapped fp32 result.  Contractions KH*KW*C and KH*KW*Cout <= 133144. */
 int fxp_conv2d_fwd(const float* X, const float* W, const fxp_conv2d_shape* shape, float* Y, const fxp_conv_saved* saved,
                    uint64_t seed, uint64_t step, int rounding, int bits, void* ws, size_t ws_bytes, void* stream);
 

@@ -1313,7 +1313,7 @@ static bool small_tiles(int64_t M, int64_t N, int64_t count) {
 
 // Products that k_gemm_nt_direct takes: at most one 32 x 32 tile per CU, at most one round of loads per wave.  Measured
 // with a launch behind a launch against the LDS-staged kernels: 197 x 768 x 768 5.1 us for 6.5, 1 x 3072 x 768 4.6 for
-// 6.5, 512 x 512 x 512 5.2 for 5.6; but 197 x 3072 x 768 7.8 for 6.8 and 197 x 768 x 3072 (four rounds) 11.5 for 11.1:
+// 6.5, 512 x 512 x 512 5.2 for 5.6; but 197 x 3072 x 768 7.8 for 6.8 and 197 x 768 x 3072 (three rounds) 11.5 for 11.1:
 // every load instruction touches 32 rows.
 static bool direct_fits(int64_t M, int64_t N, int64_t K) {
     return K >= 16 && K <= 1024 && ((M + 63) / 64) * ((N + 63) / 64) <= 64;
@@ -1414,8 +1414,10 @@ int gemm_nt_batched_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int
 // the device), else the int32 sums.  C is overwritten in both cases.
 //
 // Kernel choice (measured on MI355X with mapped Gaussian operands):
-//   * operands 16-byte aligned and K a multiple of 64 -> direct-to-LDS kernels, else the
-//     register-staged 128 x 128 x 64 kernel with its element-wise loader;
+//   * small outputs of at most 1024 terms, whatever the alignment -> k_gemm_nt_direct (direct_fits);
+//   * operands 16-byte aligned, K a multiple of 16 and 64 or more -> direct-to-LDS kernels, else the register-staged
+//     kernel (k_gemm_nt: whole 16-byte loads at any byte address), 64 x 64 x 128 tiles below 512 large ones
+//     (small_tiles), else 128 x 128 x 64;
 //   * enough 256 x 256 tiles to fill the chip -> the ring kernel (K % 128 == 0) or the
 //     four-stage 256 x 256 x 64 kernel; otherwise 128 x 128 tiles;
 //   * output-bound products (below the ridge, wide and large output or a very short contraction) -> 128-row tiles
@@ -1522,9 +1524,11 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
 
 // Y[M, Cout] = unmap(patches(Xq) * Wq^T) with the patch matrix never stored (see k_gemm_nt_dma, CONV): M output
 // pixels, K = KH*KW*C.  Returns kNotApplicable when the shape needs the explicit patch matrix: channels not a
-// multiple of 64 (the smallest K step), or a 1x1 layer that plan_gemm gives 256 x 256 tiles (64 x 28 x 28 x 128 -> 256 81.3 us
-// with them, 84.3 here; of a 3x3 layer the stored patches cost more than the larger tiles gain: 64 x 14 x 14 x 256 -> 512
-// 135 us with them, 125 here).
+// multiple of 64 (the smallest K step), a long contraction in few tiles (deep_chain), or a 1x1 layer that plan_gemm gives
+// 256 x 256 tiles.  For these neither way is ahead throughout (layer steps in us, with those tiles / here: 64 x 14 x 14 x 1024
+// -> 1024 130.6 / 138.6, 64 x 28 x 28 x 128 -> 256 77.7 / 78.2, but 256 -> 512 141 / 135, 32 x 28 x 28 x 512 -> 256 90.7 / 84.2,
+// 32 x 56 x 56 x 256 181 / 172); of a 3x3 layer the stored patches cost more than the larger tiles gain (64 x 14 x 14 x 256 ->
+// 512 135 / 125).
 template <int BM, int BN, int BK, int WM, int WN, int STAGES = 4>
 static int conv_gemm_launch_cfg(const ConvTaps& ct, int64_t K, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* Wq,
                                 float* Y, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, hipStream_t s,
@@ -1562,9 +1566,9 @@ int conv_gemm_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const 
     const GemmPlan plan = plan_gemm(M, Cout, K);
     if (plan.use256 && K == ct.C) return kNotApplicable;
     // few tiles: a product of stored patches would be split along K (or leave CUs idle); here tiles a quarter the size
-    // fill the chip, no patches are stored and no slices summed.  Layer steps against stored patches: 32 x 14 x 14 x 256 -> 256
-    // 3x3 110 -> 64 us (98 large tiles; unsplit large tiles: 68), 32 x 7 x 7 x 512 -> 512 113 -> 80 (52; 95), batch 64 140 -> 96
-    // (100; 102); with 196 large tiles (batch 64 of 14 x 14) 131 -> 104, large ones 86.
+    // fill more of the chip, no patches are stored and no slices summed.  Layer steps against stored patches: 32 x 14 x 14 x
+    // 256 -> 256 3x3 110 -> 64 us (98 large tiles), 32 x 7 x 7 x 512 113 -> 80 (52).  The line, 64 x 64 / large tiles: 96
+    // (37 x 14 x 14 x 512) 120 / 126, 92 (29 x 14 x 14 x 256) 86 / 90, 112 (36) 68.5 / 70.3, 130 (42) 117.5 / 103.7, 192 140.7 / 128.5.
     // (Of contractions up to 4608 every size down to one image of 4 x 4 gains: 1 x 7 x 7 x 512 95.6 -> 70.9, 1 x 4 x 4 x 256
     // 60.2 -> 45.1.)
     const int64_t t128 = ((M + 127) / 128) * ((Cout + 127) / 128);
