@@ -327,11 +327,14 @@ struct Product {
 // that is no multiple of 16): tiles are staged through registers, two steps ahead of the multiplication, into two LDS
 // buffers.  A 16-byte piece is one load at whatever byte address its row starts (the ragged shapes pay in cache-line
 // crossings, not in instructions: with one byte per load the products of a 1379 x 768 x 1000 layer took 198 and 100 us,
-// now 13.1 and 8.6; the 96 products 197 x 64 x 197 of an attention block 22.2, now 6.5).  The last, partial piece of a row is read as the row's last 16 bytes on both operands - the
-// contraction index may be permuted as long as both sides agree - and A's copies of bytes an earlier piece already
-// brought are zeroed, so no load leaves the row.  Only contractions shorter than 16 are assembled byte by byte (WIDE =
-// false).
-template <int BM, int BN, int BK, int WM, int WN, bool WIDE, int MODE>
+// now 13.1 and 8.6; the 96 products 197 x 64 x 197 of an attention block 22.2, now 6.5).  The last, partial piece of a
+// row is read as the row's last 16 bytes on both operands - the contraction index may be permuted as long as both sides
+// agree - and A's copies of bytes an earlier piece already brought are zeroed, so no load leaves the row.
+// A contraction of one step (K <= BK) needs neither the second set of registers nor the second buffer: twice the workgroups
+// per CU (the attention step of 4096 x (32 x 32 x 32): 157 us before there was a second set, 202 with both, 164 without).  STEPS: kManySteps, kOneStep, or
+// kOneStepBytes, a contraction shorter than 16 whose pieces are assembled byte by byte.
+constexpr int kManySteps = 0, kOneStep = 1, kOneStepBytes = 2;
+template <int BM, int BN, int BK, int WM, int WN, int STEPS, int MODE>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
     const int8_t* __restrict__ A, int64_t lda, const int8_t* __restrict__ B, int64_t ldb, void* __restrict__ Cv,
     int64_t ldc, int M, int N, int K, int k_per_split, const int32_t* __restrict__ eA, int bitsA,
@@ -363,8 +366,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
     constexpr int NA = BM * CPR / NT, NB = BN * CPR / NT;   // 16-byte pieces per thread per step
     constexpr int FM = WM / 32, FN = WN / 32;               // 32x32 fragments per wave
     static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile does not divide over the threads");
+    constexpr bool WIDE = STEPS != kOneStepBytes;
+    constexpr int BUFS = STEPS == kManySteps ? 2 : 1;
 
-    __shared__ __attribute__((aligned(16))) int8_t lds[2][(BM + BN) * BK];
+    __shared__ __attribute__((aligned(16))) int8_t lds[BUFS][(BM + BN) * BK];
 
     int tm, tn;
     tile_of_block(tile_block, tiles_m, tiles_n, group_m, &tm, &tn);
@@ -399,7 +404,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
         lds_b[j] = BM * BK + row * BK + ((c ^ swizzle_of_row<BK>(row)) * 16);
         kc_b[j] = c * 16;
     }
-    uint4 ra[2][NA], rb[2][NB];
+    uint4 ra[BUFS][NA], rb[BUFS][NB];
 
     // the piece of row p whose first contraction index is k, in a step that reaches the end of the slice
     auto tail_piece = [&](const int8_t* p, int k, bool clear) -> uint4 {
@@ -449,10 +454,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
-    // step it: request step it + 2 into the registers step it came from, multiply, park step it + 1 in the other buffer
-    auto step = [&](int it, auto buf_c) {
-        constexpr int buf = decltype(buf_c)::value;
-        if (it + 2 < nk) load_step(it + 2, ra[buf], rb[buf]);
+    auto multiply = [&](int buf) {
 #pragma unroll
         for (int ks = 0; ks < BK / 32; ++ks) {
             const int piece = ((2 * ks + fhalf) ^ fswz) * 16;
@@ -467,16 +469,29 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
                 for (int j = 0; j < FN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
-        if (it + 1 < nk) store_step(buf ^ 1, ra[buf ^ 1], rb[buf ^ 1]);
-        __syncthreads();
     };
-    if (nk > 0) load_step(0, ra[0], rb[0]);
-    if (nk > 1) load_step(1, ra[1], rb[1]);
-    if (nk > 0) store_step(0, ra[0], rb[0]);
-    __syncthreads();
-    for (int it = 0; it < nk; it += 2) {
-        step(it, IC<0>{});
-        if (it + 1 < nk) step(it + 1, IC<1>{});
+    if constexpr (STEPS == kManySteps) {
+        // step it: request step it + 2 into the registers step it came from, multiply, park step it + 1 in the other buffer
+        auto step = [&](int it, auto buf_c) {
+            constexpr int buf = decltype(buf_c)::value;
+            if (it + 2 < nk) load_step(it + 2, ra[buf], rb[buf]);
+            multiply(buf);
+            if (it + 1 < nk) store_step(buf ^ 1, ra[buf ^ 1], rb[buf ^ 1]);
+            __syncthreads();
+        };
+        if (nk > 0) load_step(0, ra[0], rb[0]);
+        if (nk > 1) load_step(1, ra[1], rb[1]);
+        if (nk > 0) store_step(0, ra[0], rb[0]);
+        __syncthreads();
+        for (int it = 0; it < nk; it += 2) {
+            step(it, IC<0>{});
+            if (it + 1 < nk) step(it + 1, IC<1>{});
+        }
+    } else if (nk > 0) {                                          // workgroup-uniform
+        load_step(0, ra[0], rb[0]);
+        store_step(0, ra[0], rb[0]);
+        __syncthreads();
+        multiply(0);
     }
 
     // ---- epilogue --------------------------------------------------------------------
@@ -1148,19 +1163,21 @@ static int launch_cfg(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t 
     }
     const dim3 grid(static_cast<unsigned>(tiles_m) * tiles_n + two.tiles + rider.blocks, ny, bt.count), block(NT);
     const int group_m = 8;
-#define FXP_GEMM_LAUNCH(WIDE, MODE)                                                                                \
-    hipLaunchKernelGGL((k_gemm_nt<BM, BN, BK, WM, WN, WIDE, MODE>), grid, block, 0, s, A, lda, B, ldb, C, ldc,       \
+#define FXP_GEMM_LAUNCH(STEPS, MODE)                                                                               \
+    hipLaunchKernelGGL((k_gemm_nt<BM, BN, BK, WM, WN, STEPS, MODE>), grid, block, 0, s, A, lda, B, ldb, C, ldc,      \
                        static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), k_per_split, eA, bitsA, eB,   \
                        bitsB, tiles_m, tiles_n, group_m, split_stride, bt.a, bt.b, bt.c, amax, rider, two)
-    if (K >= 16) {
-        if (mode == kStoreI32) FXP_GEMM_LAUNCH(true, kStoreI32);
-        else if (mode == kStoreF32) FXP_GEMM_LAUNCH(true, kStoreF32);
-        else FXP_GEMM_LAUNCH(true, kAtomicI32);
-    } else {
-        if (mode == kStoreI32) FXP_GEMM_LAUNCH(false, kStoreI32);
-        else if (mode == kStoreF32) FXP_GEMM_LAUNCH(false, kStoreF32);
-        else FXP_GEMM_LAUNCH(false, kAtomicI32);
-    }
+#define FXP_GEMM_MODES(STEPS)                                            \
+    do {                                                                 \
+        if (mode == kStoreI32) FXP_GEMM_LAUNCH(STEPS, kStoreI32);        \
+        else if (mode == kStoreF32) FXP_GEMM_LAUNCH(STEPS, kStoreF32);   \
+        else FXP_GEMM_LAUNCH(STEPS, kAtomicI32);                         \
+    } while (0)
+    // (a second product has 16 terms or more)
+    if (K < 16) FXP_GEMM_MODES(kOneStepBytes);
+    else if (K <= BK && two.K <= BK) FXP_GEMM_MODES(kOneStep);
+    else FXP_GEMM_MODES(kManySteps);
+#undef FXP_GEMM_MODES
 #undef FXP_GEMM_LAUNCH
     return launch_status();
 }
@@ -1394,6 +1411,8 @@ int gemm_nt_batched_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int
     if (!dma) {
         // narrow outputs (head width 64 of the attention context and of dQ, dK, dV) take a tile of their own width
         if (small_tiles(M, N, batch)) return launch_cfg<64, 64, 128, 32, 32>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
+        // matrices of one tile and one step (4096 x (32 x 32 x 32) attention step 137 us, in tiles of 128 rows 164)
+        if (M <= 64 && N <= 64 && K <= 64) return launch_cfg<64, 64, 64, 32, 32>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
         if (N <= 64) return launch_cfg<128, 64, 64, 64, 32>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
         if (M <= 64) return launch_cfg<64, 128, 64, 32, 64>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);
         return launch_cfg<128, 128, 64, 64, 64>(FXP_BATCHED_ARGS, FXP_BATCHED_TAIL);

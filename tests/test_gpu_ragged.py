@@ -160,3 +160,17 @@ def test_map_row_major_alone(fxp, rows, cols):
     n = min(rows * cols, 200000)
     want = oracle.map(host(x).reshape(1, -1)[:, :n], 129, seed=5, stream_id=77)
     assert np.array_equal(host(alone)[:n], want[0])
+
+
+# contractions of one K step in many small matrices, aligned and ragged: below 16 terms, 16, up to one 64-byte step and a
+# byte beyond it; every tile (64 and 128 columns and rows), one matrix per tile and several
+@pytest.mark.parametrize("batch,M,N,K", [(600, 16, 16, 16), (513, 33, 40, 15), (700, 17, 70, 64), (600, 70, 17, 63), (520, 130, 129, 48),
+                                         (600, 16, 16, 65), (512, 130, 70, 13), (530, 40, 30, 33)])
+def test_gemm_batched_one_step(fxp, batch, M, N, K):
+    say("batched gemm of one step", (batch, M, N, K))
+    rng = np.random.default_rng(batch + M + K)
+    A, B = rand_i8(rng, (batch, M, K)), rand_i8(rng, (batch, N, K))
+    want = oracle.gemm_batched(A, B, transB=True)
+    assert np.array_equal(host(fxp.gemm_batched(dev(A), dev(B))), want)
+    e = dev(np.array([121, 130], np.int32))
+    assert same_bits(host(fxp.gemm_batched(dev(A), dev(B), e[0:1], e[1:2])).reshape(-1), oracle.unmap(want.reshape(-1), 121, 130))
