@@ -331,8 +331,8 @@ struct Product {
 // row is read as the row's last 16 bytes on both operands - the contraction index may be permuted as long as both sides
 // agree - and A's copies of bytes an earlier piece already brought are zeroed, so no load leaves the row.
 // A contraction of one step (K <= BK) needs neither the second set of registers nor the second buffer: twice the workgroups
-// per CU (the attention step of 4096 x (32 x 32 x 32): 157 us before there was a second set, 202 with both, 164 without).  STEPS: kManySteps, kOneStep, or
-// kOneStepBytes, a contraction shorter than 16 whose pieces are assembled byte by byte.
+// per CU (the attention step of 4096 x (32 x 32 x 32): 157 us before there was a second set, 202 with both, 164 without).
+// STEPS: kManySteps, kOneStep, or kOneStepBytes, a contraction shorter than 16 whose pieces are assembled byte by byte.
 constexpr int kManySteps = 0, kOneStep = 1, kOneStepBytes = 2;
 template <int BM, int BN, int BK, int WM, int WN, int STEPS, int MODE>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
