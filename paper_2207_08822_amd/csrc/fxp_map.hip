@@ -718,9 +718,7 @@ int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStr
 // one the larger tensor would pick.  Otherwise one launch each.
 int map_launch2(const MapTensor& a, const MapTensor& b, uint64_t seed, int rounding, int bits, hipStream_t s) {
     MapPlan pa = plan_map(a), pb = plan_map(b);
-    if (pa.tiles && pb.tiles && pa.tc == pb.tc && !pa.any && !pb.any) {
-        // tiles for both where they need no unaligned accesses: one body in the launch is less than two (layer steps of
-        // 32 x 28 x 28 x 128 -> 256 3x3 stride 2 57.5 us with a flat image, 56.2 with tiles, 32 x 7 x 7 x 512 3x3 82.9, 81.7)
+    if (tiles_for_both(pa, a.cols, pb, b.cols)) {
         pa = plan_map(a.rows, a.cols, true, true);
         pb = plan_map(b.rows, b.cols, true, true);
     }

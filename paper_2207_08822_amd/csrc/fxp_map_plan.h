@@ -44,4 +44,13 @@ inline MapPlan plan_map(int64_t rows, int64_t cols, bool aligned16, bool transpo
     return p;
 }
 
+// Two tensors of a launch, at least one of them planned flat: tiles for both where they are of one width, need no unaligned
+// accesses and a flat one would fill seven eighths of its tiles - one body in the launch is less than two (layer steps, image
+// flat / tiled in us: 32 x 28 x 28 x 128 -> 256 3x3 stride 2 57.5 / 56.2, 32 x 7 x 7 x 512 3x3 82.9 / 81.7), but a row of four
+// channels leaves most of a tile empty (64 x 56 x 56 x 4 -> 128 1x1 stride 2 63.4 / 70.4, 2 x 512 x 512 x 4 -> 128 3x3 300 / 318).
+inline bool tiles_for_both(const MapPlan& a, int64_t cols_a, const MapPlan& b, int64_t cols_b) {
+    auto full = [](const MapPlan& p, int64_t cols) { return 8 * cols >= 7 * ((cols + p.tc - 1) / p.tc * p.tc); };
+    return a.tiles && b.tiles && a.tc == b.tc && !a.any && !b.any && (!a.flat || full(a, cols_a)) && (!b.flat || full(b, cols_b));
+}
+
 }  // namespace fxp

@@ -20,7 +20,7 @@ def plan(tmp_path_factory):
     def ask(*cases):
         text = "".join("%d %d %d %d\n" % c for c in cases)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
-        return [dict(zip(("tc", "passes", "tiles", "any", "flat", "tile_path"), map(int, l.split()))) for l in out.splitlines()]
+        return [dict(zip(("tc", "passes", "tiles", "any", "flat", "tile_path", "both"), map(int, l.split()))) for l in out.splitlines()]
     return ask
 
 
@@ -56,3 +56,14 @@ def test_row_major_alone(plan):
     """Flat, but tiles for long rows from 2^26 elements on, unless they are off the grid."""
     got = plan((65535, 1024, 1, 0), (65536, 1024, 1, 0), (65536, 1024, 0, 0), (1 << 20, 1020, 1, 0), (65536, 1025, 1, 0))
     assert [p["flat"] for p in got] == [1, 0, 1, 1, 1]
+
+
+@pytest.mark.parametrize("image,weights,both", [((25088, 128, 1, 0), (128, 1152, 1, 1), 1), ((50176, 64, 1, 0), (64, 576, 1, 1), 1),
+                                                ((200704, 4, 1, 0), (128, 4, 1, 1), 0), ((524288, 4, 1, 0), (128, 36, 1, 1), 0),
+                                                ((25088, 128, 0, 0), (128, 1152, 1, 1), 0), ((25088, 48, 1, 0), (96, 432, 1, 1), 0),
+                                                ((25088, 56, 1, 0), (64, 576, 1, 1), 1), ((25088, 52, 1, 0), (64, 576, 1, 1), 0),
+                                                ((25088, 128, 1, 0), (64, 576, 1, 1), 0), ((25088, 3, 1, 0), (64, 147, 1, 1), 0)])
+def test_an_image_and_its_weights(plan, image, weights, both):
+    """Tiles for both: one tile width, aligned, and rows that fill the tiles."""
+    got = plan(image, weights)
+    assert got[0]["flat"] and got[1]["both"] == both
