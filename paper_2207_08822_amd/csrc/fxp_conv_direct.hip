@@ -349,6 +349,14 @@ static bool plan_thin_wgrad(const ConvTaps& ct, int KH, int64_t images, int64_t 
     // ... and every slice exact in int32
     if (image_bytes(rows) > 49152 || wg_rows * ct.Wo > kMaxSlice || images * ct.H * ct.W * ct.C < 16 || Cout * all_rows * ct.Wo < 16)
         return false;
+    // A unit costs 1.1 us for each 32 output channels, however few its pixels; a stored patch costs by its bytes, taps next to
+    // each other in a row more than one column of them, and little where a pixel's channels are one dword.  Many units of few
+    // pixels are stored patches' (layer steps, image here / stored in us: 20000 x 2 x 2 x 1 -> 128 2x2 420 / 52, 10000 x 4 x 4 x 1
+    // -> 16 1x1 92 / 66, 3000 x 7 x 7 x 3 -> 128 1x1 143 / 91, 64 x 4096 x 1 x 4 -> 64 3x1 270 / 79, 20000 x 4 x 4 x 4 -> 64 3x3
+    // 219 / 108; on the other side 3000 x 7 x 7 x 1 -> 128 3x3 121 / 131, 64 x 4096 x 1 x 2 -> 16 5x1 171 / 206, 64 x 256 x 8 x 1
+    // -> 16 1x1 43 / 58, 512 x 14 x 14 x 4 -> 64 3x3 52 / 59, 64 x 128 x 32 x 4 -> 64 3x1 equal).  One or two units save a launch.
+    const int64_t pixels = rows * ct.Wo, patch = pixels * g.K * ct.KW;
+    if (wg_rows > 2 * rows && (ct.C == 4 ? patch < 2048 * p->fm : pixels < 128 && patch < 156 * p->fm)) return false;
     g.all_rows = static_cast<int>(all_rows);
     g.wg_rows = static_cast<int>(wg_rows);
     g.rows = static_cast<int>(rows);

@@ -32,6 +32,20 @@ def test_thin_conv(fxp, N, H, W, C, Cout, KH, KW, stride, pad):  # noqa: F811
         check_conv(fxp, X, Wt, dY, stride, pad, rounding=1, bits=5)
 
 
+# many units of few pixels, on both sides of the line between transposed patches and the image itself
+@pytest.mark.parametrize("N,H,W,C,Cout,KH,KW", [(900, 2, 2, 1, 33, 2, 2), (700, 4, 4, 1, 16, 1, 1), (700, 4, 4, 3, 16, 3, 1),
+                                                (600, 5, 5, 3, 130, 3, 3), (600, 5, 5, 3, 128, 3, 3), (600, 5, 5, 3, 31, 3, 3),
+                                                (5, 4096, 1, 4, 64, 3, 1), (5, 4096, 1, 2, 16, 5, 1), (40, 300, 1, 1, 16, 3, 1),
+                                                (700, 3, 5, 4, 64, 3, 3), (20, 256, 16, 4, 32, 3, 3), (9, 512, 8, 1, 128, 1, 1)])
+def test_many_small_units(fxp, N, H, W, C, Cout, KH, KW):  # noqa: F811
+    say("thin conv, small units", (N, H, W, C, Cout, KH, KW))
+    rng = np.random.default_rng(N + H + W)
+    X = rng.standard_normal((N, H, W, C)).astype(np.float32)
+    Wt = (rng.standard_normal((Cout, KH, KW, C)) * 0.1).astype(np.float32)
+    dY = rng.laplace(0, 1e-3, (N, H - KH + 1, W - KW + 1, Cout)).astype(np.float32)
+    check_conv(fxp, X, Wt, dY, 1, 0)
+
+
 def test_thin_conv_beyond_one_int32_sum(fxp):  # noqa: F811
     """136 161 output pixels of one sign: the slices need 64 bits together."""
     say("thin conv, long contraction")
