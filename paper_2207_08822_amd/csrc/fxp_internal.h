@@ -27,6 +27,8 @@ inline int launch_status() { return hipGetLastError() == hipSuccess ? FXP_OK : F
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+constexpr int kNotApplicable = 1;      // a launcher's answer where the shape takes another path
+
 // Launchers used by the layer composition (all enqueue on `s`, arguments already validated).
 int scale_partials(const float* x, size_t n, uint32_t* partials, int* n_partials, hipStream_t s);
 // the same for two tensors in one launch
@@ -50,6 +52,9 @@ struct MapTensor {
     uint64_t stream_id;
 };
 int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStream_t s);
+int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s);
+// scale + map of small tensors in one launch (fxp_map_rows.hip); b may be null, partials are not used
+int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s);
 // scale + map in one pass with the previous scale as a guess (fxp_map.hip)
 constexpr unsigned kGuessBlocks = 1008;            // workgroups of a guessing launch: their maxima and the guess fit one scratch area
 constexpr int64_t kGuessMinElements = int64_t{1} << 22;
@@ -95,7 +100,6 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
                    void* C, int64_t ldc, bool fp32_out, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB,
                    void* ws, size_t ws_bytes, hipStream_t s, uint32_t* amax = nullptr, ReduceRider* ride = nullptr,
                    ReduceRider* defer = nullptr);
-constexpr int kNotApplicable = 1;
 // one of two products of a launch: C[M,N] = A[M,K] * B[N,K]^T with fp32 output; strides between the matrices of a batch
 struct GemmArgs {
     int64_t M, N, K;
@@ -165,13 +169,14 @@ __device__ inline uint32_t wave_max(uint32_t v) {
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
 }
 
-// max over a block of up to 1024 threads; lds holds blockDim.x / 64 words
+// max over a block of 256 threads; lds holds four words.  (The size is a constant: blockDim is a vector load from the dispatch's
+// arguments, waited for with all loads before it.)
 __device__ inline uint32_t block_max(uint32_t v, uint32_t* lds) {
     v = wave_max(v);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane == 0) lds[wave] = v;
     __syncthreads();
-    uint32_t r = (lane < nw) ? lds[lane] : 0u;
+    uint32_t r = lds[lane & 3];
     r = wave_max(r);
     __syncthreads();
     return r;

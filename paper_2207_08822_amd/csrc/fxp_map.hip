@@ -14,132 +14,21 @@
 //     so both copies carry the same rounding decisions and both stores coalesce;
 //   * the final step of the scale reduction (max over <= 1024 block maxima) can be
 //     folded in, which saves a launch per tensor.
-// Rows that are not whole quads, and bases off the 16-byte grid, take the same tiles with unaligned accesses (ANY);
-// a tensor that is wanted row-major only is one flat run of quads (map_flat_body) up to a size; the one-element-per-thread
-// kernel is left for what neither reaches.  (18912 x 197, both copies: 25.9 us one element per thread - a Philox call
-// and a scattered byte per element - 14.2 as tiles; 1.6 M x 3, row-major only, with a small weight: 24.1 in two
-// launches, 11.1 flat in one.)
+// Rows that are not whole quads, and bases off the 16-byte grid, take tiles of quads (fxp_map_rows.hip), as do small tensors,
+// whose scale is found in the same launch; a tensor that is wanted row-major only is one flat run of quads (map_flat_body) up to
+// a size; the one-element-per-thread kernel is left for what none of them reaches.
 // The random word of element i is word (i mod 4) of Philox-4x32-10 with key = seed
 // and counter = (i / 4, stream_id): nothing depends on the launch geometry.
 #include <algorithm>
 
 #include "fxp_internal.h"
+#include "fxp_map_device.h"
 #include "fxp_map_plan.h"
 
 namespace fxp {
 
-constexpr int kMapThreads = 256;
-
-// 16 bytes at 4-byte alignment, 16 and 4 bytes at any alignment
-struct __attribute__((packed, aligned(4))) Quad {
-    uint32_t x, y, z, w;
-};
-struct __attribute__((packed, aligned(1))) Bytes16 {
-    uint32_t x, y, z, w;
-};
-struct __attribute__((packed, aligned(1))) Bytes4 {
-    uint32_t x;
-};
-__device__ inline uint4 load_quad(const uint32_t* p) {
-    const Quad v = *reinterpret_cast<const Quad*>(p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-struct MapCfg {
-    int e_max;
-    int cut;        // low bits dropped: 24 - (bits - 1)
-    int rshift;     // 32 - cut: the random number is the top `cut` bits of the word
-    uint32_t sat;   // 2^(bits-1) - 1
-    uint32_t half;  // 2^(cut-1), the nearest-rounding increment
-    uint32_t low_mask;  // 2^cut - 1
-    float to_units;     // 2^(150 - e_max): |x| * to_units = the 24-bit mantissa shifted to the scale (e_max in [25, 254])
-    float limit;        // 2^(e_max - 126): magnitudes from here on are above the scale (+Inf for e_max = 254)
-};
-
-// Magnitude of one element, every case: non-finite input, scale below the element.
-template <bool STOCH>
-__device__ inline uint32_t magnitude_full(uint32_t b, uint32_t word, const MapCfg& c) {
-    const uint32_t e = (b >> 23) & 0xffu, f = b & 0x7fffffu;
-    if (e == 255u) return f == 0u ? c.sat : 0u;
-    const int d = c.e_max - static_cast<int>(max(e, 1u));
-    if (d < 0) return c.sat;
-    const uint32_t m = f | (e ? 0x800000u : 0u);
-    const uint32_t mp = m >> min(d, 31);
-    const uint32_t add = STOCH ? ((~word) >> c.rshift) : c.half;
-    return min((mp + add) >> c.cut, c.sat);
-}
-
-// Same for the common case: e_max in [25, 254], no element above the scale, no result above the largest
-// magnitude.  The shifted mantissa m >> (e_max - e) is the integer part of |x| * 2^(150 - e_max): the factor is a
-// power of two (a normal float for these scales), so the product is exact whenever it is 1 or more and below 1
-// otherwise, sub-normal inputs included, and the conversion truncates - two instructions for unpack, hidden
-// bit, clamp and shift.  r < low  <=>  low + (2^cut - 1 - r) carries out of the cut.  `bad` collects, as a lane
-// mask (one compare per element, accumulated on the scalar side), the lanes with an element the scale does not
-// cover (exponent above it, Inf, NaN); the caller also ORs the results (a bit above the magnitude bits = needs
-// the saturating path) and redoes the block with magnitude_full if either fires.
-template <bool STOCH>
-__device__ inline uint32_t magnitude_fast(uint32_t b, uint32_t word, const MapCfg& c, uint64_t& bad) {
-    const float ax = fabsf(__uint_as_float(b));
-    bad |= __builtin_amdgcn_ballot_w64(!(ax < c.limit));
-    const uint32_t mp = static_cast<uint32_t>(ax * c.to_units);
-    const uint32_t add = STOCH ? ((word >> c.rshift) ^ c.low_mask) : c.half;
-    return (mp + add) >> c.cut;
-}
-
-__device__ inline uint32_t with_sign(uint32_t mag, uint32_t b) {
-    const uint32_t sm = static_cast<uint32_t>(static_cast<int32_t>(b) >> 31);
-    return (mag ^ sm) - sm;
-}
-
-// the four signed results of a 16-byte load as one dword, low bytes in element order
-__device__ inline uint32_t pack4(uint32_t q0, uint32_t q1, uint32_t q2, uint32_t q3, const uint4 v) {
-    const uint32_t p01 = perm(with_sign(q1, v.y), with_sign(q0, v.x), 0x0c0c0400u);
-    const uint32_t p23 = perm(with_sign(q3, v.w), with_sign(q2, v.z), 0x0c0c0400u);
-    return perm(p23, p01, 0x05040100u);
-}
-
-
-// the four mapped bytes of a quad: fast form (q_or and bad as above) and complete form
-template <bool STOCH>
-__device__ inline uint32_t map_quad_fast(const uint4 v, const uint4 w, const MapCfg& c, uint32_t& q_or, uint64_t& bad) {
-    const uint32_t m0 = magnitude_fast<STOCH>(v.x, w.x, c, bad), m1 = magnitude_fast<STOCH>(v.y, w.y, c, bad);
-    const uint32_t m2 = magnitude_fast<STOCH>(v.z, w.z, c, bad), m3 = magnitude_fast<STOCH>(v.w, w.w, c, bad);
-    q_or |= m0 | m1 | m2 | m3;
-    return pack4(m0, m1, m2, m3, v);
-}
-
-template <bool STOCH>
-__device__ inline uint32_t map_quad_full(const uint4 v, const uint4 w, const MapCfg& c) {
-    return pack4(magnitude_full<STOCH>(v.x, w.x, c), magnitude_full<STOCH>(v.y, w.y, c), magnitude_full<STOCH>(v.z, w.z, c),
-                 magnitude_full<STOCH>(v.w, w.w, c), v);
-}
-
 template <int V>
 using IC = std::integral_constant<int, V>;
-
-// the value of the next lane (of lane l + 1 in lane l), and of the lane N to the left within a row of 16 lanes
-__device__ inline uint32_t from_right(uint32_t v) {
-    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x130, 0xf, 0xf, false));    // wave_shl:1
-}
-template <int N>
-__device__ inline uint32_t from_left(uint32_t v) {
-    if (N == 0) return v;
-    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x110 + N, 0xf, 0xf, false));  // row_shr:N
-}
-
-__device__ inline MapCfg make_cfg(int e_max, int bits) {
-    MapCfg c;
-    c.e_max = e_max;
-    c.cut = 24 - (bits - 1);
-    c.rshift = 32 - c.cut;
-    c.sat = (1u << (bits - 1)) - 1u;
-    c.half = 1u << (c.cut - 1);
-    c.low_mask = (1u << c.cut) - 1u;
-    const int e = min(max(e_max, 25), 254);                       // outside: the fast path is not taken
-    c.to_units = __uint_as_float(static_cast<uint32_t>(277 - e) << 23);
-    c.limit = __uint_as_float(static_cast<uint32_t>(e + 1) << 23);
-    return c;
-}
 
 // One tensor of a map launch.  A launch carries up to two (the activation and the weight of a forward pass):
 // the first `blocks` workgroups belong to job 0, the rest to job 1.
@@ -186,19 +75,6 @@ __device__ inline void tile_of_workgroup(const MapJob& J, unsigned bid, unsigned
     }
 }
 
-// scale of the tensor: either given, or the max of the per-block maxima (and then
-// block 0 publishes it)
-__device__ inline int resolve_scale(const int32_t* e_in, const uint32_t* partials, int n_partials, int32_t* e_out,
-                                    uint32_t* red, bool publish) {
-    if (partials == nullptr) return e_in[0];
-    uint32_t m = 0;
-    for (int i = threadIdx.x; i < n_partials; i += blockDim.x) m = max(m, partials[i]);
-    m = block_max(m, red);
-    const int e = max(1, static_cast<int>(m >> 23));
-    if (publish && threadIdx.x == 0) e_out[0] = e;
-    return e;
-}
-
 // One tile of TC columns (128, or 64 for tensors whose width pads less that way: head width 64 of the
 // attention operands) and TR = 1024 / TC * 4 * PASSES rows: every thread owns 4 x 4 elements per pass, the 256
 // threads of a pass cover 32 x 128 or 64 x 64.  PASSES = 4 for large tensors, 2 or 1 when the tensor is too small
@@ -208,8 +84,7 @@ __device__ inline int resolve_scale(const int32_t* e_in, const uint32_t* partial
 // GUESS: the scale is not resolved from block maxima but given (e_given; do_map = false: there is none, only the
 // maximum is wanted), and the largest magnitude bits of the tile are accumulated into tile_max (clamped loads
 // of an edge tile repeat elements of the tensor, which a maximum does not mind).
-// ANY: columns not a multiple of 4, or pointers off the 16-byte grid.
-template <bool STOCH, bool EDGE, int PASSES, int TC, bool GUESS = false, bool ANY = false>
+template <bool STOCH, bool EDGE, int PASSES, int TC, bool GUESS = false>
 __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t rows, int64_t cols, const MapJob& J, int bits,
                                      bool publish, uint32_t* red, int8_t* __restrict__ q, int8_t* __restrict__ qT,
                                      uint32_t key0, uint32_t key1, uint32_t sid0, uint32_t sid1, int64_t r0, int64_t c0,
@@ -229,7 +104,6 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     const int rows_here = EDGE ? static_cast<int>(min<int64_t>(TR, rows - r0)) : TR;
     const int cols_here = EDGE ? static_cast<int>(min<int64_t>(TC, cols - c0)) : TC;
     const bool col_ok = !EDGE || 4 * cg < cols_here;
-    const bool quads = (ucols & 3u) == 0;         // whole quads per row (always, unless ANY)
     const uint32_t col_ld = EDGE ? static_cast<uint32_t>(min(4 * cg, cols_here - 4)) : 4 * cg;
 
     // PASSES passes of 4 * RGP rows.  The loads of pass p+1 are issued before the arithmetic of pass
@@ -239,22 +113,14 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int rr = EDGE ? min(lrow + k, rows_here - 1) : lrow + k;
-            const uint32_t* row = xt + static_cast<uint32_t>(rr) * ucols;
-            if (ANY && EDGE) {
-                const int last = cols_here - 1;
-                v[k] = make_uint4(row[min(4 * cg, last)], row[min(4 * cg + 1, last)], row[min(4 * cg + 2, last)],
-                                  row[min(4 * cg + 3, last)]);
-            } else if (ANY) {
-                v[k] = load_quad(row + col_ld);
-            } else {
-                v[k] = *reinterpret_cast<const uint4*>(row + col_ld);
-            }
+            v[k] = *reinterpret_cast<const uint4*>(xt + static_cast<uint32_t>(rr) * ucols + col_ld);
         }
     };
     uint4 cur[4], nxt[4];
+    const uint32_t share = GUESS ? 0u : partials_share(J.partials, J.n_partials);
     load_pass(0, cur);
     // the scale is resolved (block maxima re-read and reduced) while the first loads are in flight
-    const MapCfg cfg = make_cfg(GUESS ? e_given : resolve_scale(J.e_in, J.partials, J.n_partials, J.e_out, red, publish), bits);
+    const MapCfg cfg = make_cfg(GUESS ? e_given : resolve_scale(J.e_in, J.partials, share, J.e_out, red, publish), bits);
     const bool scale_ok = cfg.e_max >= 25 && cfg.e_max < 255;
     const uint32_t over_bits = ~cfg.sat;          // a fast-path result with any of these set needs saturation
     uint32_t seen = 0;                             // GUESS: largest magnitude bits this thread has loaded
@@ -272,71 +138,26 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
                 continue;
             }
         }
-        auto block_at = [&](uint64_t blk) {
-            return philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), sid0, sid1, key0, key1);
-        };
-        // ANY, rows that are not whole quads: a thread's four elements straddle two blocks of random words.  The
-        // second one is the first one of the lane to the right, except for the last column group of the tile, whose
-        // second blocks (one per row) are worked out by the last four lanes, one each: five blocks per 16 elements.
-        uint4 beyond = make_uint4(0, 0, 0, 0);
-        if (ANY && STOCH && !quads) {
-            const uint64_t i = static_cast<uint64_t>(origin) + static_cast<uint32_t>(lrow + (cg & 3)) * ucols + TC;
-            beyond = block_at(i >> 2);
-        }
-        auto words_of = [&](auto k_c) {
-            constexpr int k = decltype(k_c)::value;
-            const uint32_t off = static_cast<uint32_t>(lrow + k) * ucols + 4 * cg;   // element offset in the tile
+        auto words_of = [&](int k) {
             if (!STOCH) return make_uint4(0, 0, 0, 0);
-            if (!ANY || quads) return block_at(blk0 + (off >> 2));
-            const uint64_t i = static_cast<uint64_t>(origin) + off;
-            const uint4 w = block_at(i >> 2);
-            // (moved in every lane before one is chosen: a lane must be active to be read)
-            const uint32_t rx = from_right(w.x), ry = from_right(w.y), rz = from_right(w.z);
-            const uint32_t bx = from_left<3 - k>(beyond.x), by = from_left<3 - k>(beyond.y), bz = from_left<3 - k>(beyond.z);
-            const bool last = cg == CG - 1;
-            const uint32_t n0 = last ? bx : rx, n1 = last ? by : ry, n2 = last ? bz : rz;
-            const bool odd = i & 1u, two = i & 2u;                   // words i % 4 .. i % 4 + 3 of the eight
-            const uint32_t a0 = odd ? w.y : w.x, a1 = odd ? w.z : w.y, a2 = odd ? w.w : w.z, a3 = odd ? n0 : w.w;
-            const uint32_t a4 = odd ? n1 : n0, a5 = odd ? n2 : n1;
-            return make_uint4(two ? a2 : a0, two ? a3 : a1, two ? a4 : a2, two ? a5 : a3);
+            const uint64_t blk = blk0 + ((static_cast<uint32_t>(lrow + k) * ucols + 4 * cg) >> 2);
+            return philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), sid0, sid1, key0, key1);
         };
         uint32_t o[4];
         uint32_t q_or = 0;
         uint64_t bad = 0;                          // wave-uniform: any lane with an uncovered element
-        auto fast_row = [&](auto k_c) {
-            constexpr int k = decltype(k_c)::value;
-            o[k] = map_quad_fast<STOCH>(cur[k], words_of(k_c), cfg, q_or, bad);
-        };
-        fast_row(IC<0>{});
-        fast_row(IC<1>{});
-        fast_row(IC<2>{});
-        fast_row(IC<3>{});
-        bool redo = !scale_ok || bad != 0 || (q_or & over_bits);
-        if (ANY) redo = __builtin_amdgcn_ballot_w64(redo) != 0;      // words come from other lanes: all of the wave or none
-        if (redo) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = map_quad_fast<STOCH>(cur[k], words_of(k), cfg, q_or, bad);
+        if (!scale_ok || bad != 0 || (q_or & over_bits)) {
             // rare: an element above the scale, a saturating result, a non-finite input or a tiny
             // scale somewhere in this 4 x 4 block: redo it with the complete per-element path
-            auto full_row = [&](auto k_c) {
-                constexpr int k = decltype(k_c)::value;
-                o[k] = map_quad_full<STOCH>(cur[k], words_of(k_c), cfg);
-            };
-            full_row(IC<0>{});
-            full_row(IC<1>{});
-            full_row(IC<2>{});
-            full_row(IC<3>{});
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = map_quad_full<STOCH>(cur[k], words_of(k), cfg);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (qt != nullptr && col_ok && (!EDGE || lrow + k < rows_here)) {
-                int8_t* dst = qt + static_cast<uint32_t>(lrow + k) * ucols + 4 * cg;
-                if (ANY && EDGE && 4 * cg + 4 > cols_here) {
-                    for (int j = 0; 4 * cg + j < cols_here; ++j) dst[j] = static_cast<int8_t>(o[k] >> (8 * j));
-                } else if (ANY) {
-                    reinterpret_cast<Bytes4*>(dst)->x = o[k];
-                } else {
-                    *reinterpret_cast<uint32_t*>(dst) = o[k];
-                }
-            }
+            if (qt != nullptr && col_ok && (!EDGE || lrow + k < rows_here))
+                *reinterpret_cast<uint32_t*>(qt + static_cast<uint32_t>(lrow + k) * ucols + 4 * cg) = o[k];
         if (qT != nullptr) {
             uint32_t t[4];                          // t[c] = column c of the block, rows in ascending byte order
             transpose4x4(o, t);
@@ -355,7 +176,7 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     constexpr int ROUNDS = (TC * PIECES + kMapThreads - 1) / kMapThreads;
     // Rows that are whole pieces have a loop of their own, and that of edge tiles is not unrolled: every map kernel holds them all
     // (with one unrolled loop for either, k_map_tile_guess lost 2 % of a step: 12608 x 768 x 2304 164.0 -> 167.1 us).
-    if (!ANY && (rows & 15) == 0) {
+    if ((rows & 15) == 0) {
 #pragma unroll
         for (int it = 0; it < ROUNDS; ++it) {
             const int id = it * kMapThreads + tid;
@@ -386,70 +207,9 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     }
 }
 
-// A tensor wanted row-major only: quads of consecutive elements, 1024 * PASSES per workgroup from quad `first` on,
-// whatever its rows are and wherever x and q start.  SHORT: the workgroup has fewer quads, and a last one that may be
-// short; the others carry no bounds code (with it around every load, 12608 x 768 took 13.2 us where tiles take 10.6).
-template <bool STOCH, int PASSES, bool SHORT>
-__device__ inline void map_flat_body(const MapJob& J, int bits, bool publish, uint32_t* red, uint32_t key0, uint32_t key1,
-                                     uint64_t first) {
-    const uint64_t n = static_cast<uint64_t>(J.rows) * static_cast<uint64_t>(J.cols);
-    const uint32_t quads = SHORT ? static_cast<uint32_t>((n >> 2) - first) : 4 * kMapThreads * PASSES;    // whole ones here
-    const uint32_t tail = static_cast<uint32_t>(n & 3u);         // SHORT: elements of the quad behind them
-    const uint32_t* __restrict__ x = J.x + 4 * first;
-    int8_t* __restrict__ q = J.q + 4 * first;
-    auto load_pass = [&](int p, uint4 (&v)[4]) {
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t i = (4 * p + k) * kMapThreads + threadIdx.x;
-            if (!SHORT || i < quads) {
-                v[k] = load_quad(x + 4 * i);
-            } else {
-                v[k] = make_uint4(0, 0, 0, 0);
-                if (i == quads) {
-                    if (tail > 0) v[k].x = x[4 * i];
-                    if (tail > 1) v[k].y = x[4 * i + 1];
-                    if (tail > 2) v[k].z = x[4 * i + 2];
-                }
-            }
-        }
-    };
-    uint4 cur[4], nxt[4];
-    load_pass(0, cur);
-    const MapCfg cfg = make_cfg(resolve_scale(J.e_in, J.partials, J.n_partials, J.e_out, red, publish), bits);
-    const bool scale_ok = cfg.e_max >= 25 && cfg.e_max < 255;
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        if (p + 1 < PASSES) load_pass(p + 1, nxt);
-        uint32_t o[4], q_or = 0;
-        uint64_t bad = 0;
-        auto words_of = [&](uint32_t k) {
-            const uint64_t blk = first + ((4 * p + k) * kMapThreads + threadIdx.x);
-            return STOCH ? philox4x32_10(static_cast<uint32_t>(blk), static_cast<uint32_t>(blk >> 32), J.sid0, J.sid1, key0, key1)
-                         : make_uint4(0, 0, 0, 0);
-        };
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) o[k] = map_quad_fast<STOCH>(cur[k], words_of(k), cfg, q_or, bad);
-        if (!scale_ok || bad != 0 || (q_or & ~cfg.sat)) {
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) o[k] = map_quad_full<STOCH>(cur[k], words_of(k), cfg);
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t i = (4 * p + k) * kMapThreads + threadIdx.x;
-            if (!SHORT || i < quads) {
-                reinterpret_cast<Bytes4*>(q + 4 * i)->x = o[k];
-            } else if (i == quads) {
-                for (uint32_t j = 0; j < tail; ++j) q[4 * i + j] = static_cast<int8_t>(o[k] >> (8 * j));
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) cur[k] = nxt[k];
-    }
-}
-
 // FLAT: a launch with a flat tensor in it.  (A parameter: with the flat body in every instantiation the tiles of an aligned
 // tensor ran at lower occupancy or spilled, 159744 x 208 both copies 39.1 -> 40.0 us.)
-template <bool STOCH, int PASSES, int TC, bool ANY, bool FLAT>
+template <bool STOCH, int PASSES, int TC, bool FLAT>
 __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, uint32_t key0, uint32_t key1, int bits) {
     constexpr int RGP = kMapThreads / (TC / 4);
     constexpr int TR = 4 * RGP * PASSES;
@@ -461,7 +221,7 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
     if (J.guess_used != nullptr) {
         // this launch follows k_map_tile_guess: the tensor is already mapped if the guess was its scale - then
         // the scale is published and nothing else is left to do; otherwise the tile is mapped now
-        const int e = resolve_scale(nullptr, J.partials, J.n_partials, J.e_out, red, bid == 0);
+        const int e = resolve_scale(nullptr, J.partials, partials_share(J.partials, J.n_partials), J.e_out, red, bid == 0);
         if (J.guess_used[0] == e) return;
     }
     if (FLAT && J.flat) {
@@ -480,9 +240,9 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
     const int64_t r0 = static_cast<int64_t>(rb) * TR;
     const int64_t c0 = static_cast<int64_t>(cb) * TC;
     if (r0 + TR <= rows && c0 + TC <= cols)
-        map_tile_body<STOCH, false, PASSES, TC, false, ANY>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
+        map_tile_body<STOCH, false, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
     else
-        map_tile_body<STOCH, true, PASSES, TC, false, ANY>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
+        map_tile_body<STOCH, true, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
 }
 
 // Scale and map in ONE pass over the tensor, for a caller that has a guess of the scale (the tensor's scale of
@@ -543,7 +303,7 @@ __global__ __launch_bounds__(kMapThreads) void k_map_generic(const uint32_t* __r
                                                              int8_t* __restrict__ qT, uint32_t key0, uint32_t key1,
                                                              uint32_t sid0, uint32_t sid1, int bits) {
     __shared__ uint32_t red[kMapThreads / 64];
-    const MapCfg cfg = make_cfg(resolve_scale(e_in, partials, n_partials, e_out, red, blockIdx.x == 0), bits);
+    const MapCfg cfg = make_cfg(resolve_scale(e_in, partials, partials_share(partials, n_partials), e_out, red, blockIdx.x == 0), bits);
     const uint64_t n = static_cast<uint64_t>(rows) * static_cast<uint64_t>(cols);
     for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kMapThreads + threadIdx.x; i < n;
          i += static_cast<uint64_t>(gridDim.x) * kMapThreads) {
@@ -594,14 +354,13 @@ static MapJob make_job(const MapTensor& t, int tc, int passes, bool flat) {
     return j;
 }
 
-static void launch_tiles(const MapJobs& jobs, int tc, int passes, bool any, bool stoch, uint32_t k0, uint32_t k1, int bits,
+static void launch_tiles(const MapJobs& jobs, int tc, int passes, bool stoch, uint32_t k0, uint32_t k1, int bits,
                          hipStream_t s) {
     const dim3 grid(jobs.j[0].blocks + jobs.j[1].blocks), block(kMapThreads);
     const bool flat = jobs.j[0].flat || (jobs.j[1].blocks != 0 && jobs.j[1].flat);
 #define FXP_MAP_LAUNCH(STOCH, PASSES, TC)                                                                          \
     do {                                                                                                           \
-        auto kernel = any ? (flat ? k_map_tile<STOCH, PASSES, TC, true, true> : k_map_tile<STOCH, PASSES, TC, true, false>)     \
-                          : (flat ? k_map_tile<STOCH, PASSES, TC, false, true> : k_map_tile<STOCH, PASSES, TC, false, false>);  \
+        auto kernel = flat ? k_map_tile<STOCH, PASSES, TC, true> : k_map_tile<STOCH, PASSES, TC, false>;            \
         hipLaunchKernelGGL(kernel, grid, block, 0, s, jobs, k0, k1, bits);                                          \
     } while (0)
 #define FXP_MAP_PICK(TC)                                   \
@@ -684,7 +443,7 @@ int scale_map_guess_launch(const MapTensor& a, const MapTensor* b, uint32_t* are
         jobs.j[j].partials = areas[j];
         jobs.j[j].n_partials = static_cast<int>(grid);
     }
-    launch_tiles(jobs, pa.tc, passes, false, stoch, k0, k1, bits, s);
+    launch_tiles(jobs, pa.tc, passes, stoch, k0, k1, bits, s);
     return launch_status();
 }
 
@@ -692,12 +451,13 @@ int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStr
     const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
     const bool stoch = rounding == FXP_ROUND_STOCHASTIC;
     const MapPlan p = plan_map(t);
+    if (p.tile_path && p.any && !p.flat) return map_rows_launch(t, nullptr, seed, rounding, bits, s);
     if (p.tile_path) {
         MapJobs jobs;
         jobs.j[0] = make_job(t, p.tc, p.passes, p.flat);
         jobs.j[1] = jobs.j[0];
         jobs.j[1].blocks = 0;
-        launch_tiles(jobs, p.tc, p.passes, p.any && !p.flat, stoch, k0, k1, bits, s);
+        launch_tiles(jobs, p.tc, p.passes, stoch, k0, k1, bits, s);
     } else {
         const uint32_t s0 = static_cast<uint32_t>(t.stream_id), s1 = static_cast<uint32_t>(t.stream_id >> 32);
         const uint32_t* xb = reinterpret_cast<const uint32_t*>(t.x);
@@ -722,13 +482,14 @@ int map_launch2(const MapTensor& a, const MapTensor& b, uint64_t seed, int round
         pa = plan_map(a.rows, a.cols, true, true);
         pb = plan_map(b.rows, b.cols, true, true);
     }
+    if (pa.tile_path && pb.tile_path && ((pa.any && !pa.flat) || (pb.any && !pb.flat)))
+        return map_rows_launch(a, &b, seed, rounding, bits, s);
     if (!pa.tile_path || !pb.tile_path || (pa.tc != pb.tc && !pa.flat && !pb.flat)) {
         const int rc = map_launch(a, seed, rounding, bits, s);
         return rc ? rc : map_launch(b, seed, rounding, bits, s);
     }
     const int passes = a.rows * a.cols >= b.rows * b.cols ? pa.passes : pb.passes;
     const int tc = pa.flat ? pb.tc : pa.tc;          // a flat tensor has no tile width of its own
-    const bool any = (pa.any && !pa.flat) || (pb.any && !pb.flat);
     MapJobs jobs;
     jobs.j[0] = make_job(a, tc, passes, pa.flat);
     jobs.j[1] = make_job(b, tc, passes, pb.flat);
@@ -736,7 +497,7 @@ int map_launch2(const MapTensor& a, const MapTensor& b, uint64_t seed, int round
         const int rc = map_launch(a, seed, rounding, bits, s);
         return rc ? rc : map_launch(b, seed, rounding, bits, s);
     }
-    launch_tiles(jobs, tc, passes, any, rounding == FXP_ROUND_STOCHASTIC, static_cast<uint32_t>(seed),
+    launch_tiles(jobs, tc, passes, rounding == FXP_ROUND_STOCHASTIC, static_cast<uint32_t>(seed),
                  static_cast<uint32_t>(seed >> 32), bits, s);
     return launch_status();
 }
@@ -785,12 +546,12 @@ extern "C" int fxp_scale_map(const float* x, int64_t rows, int64_t cols, int32_t
     if (!fxp::aligned(ws, 4)) return FXP_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* partials = static_cast<uint32_t*>(ws);
-    int np = 0;
-    rc = fxp::scale_partials(x, static_cast<size_t>(rows * cols), partials, &np, s);
-    if (rc) return rc;
-    if (rows * cols == 0) return fxp::scale_finish(partials, np, e_max, s);
-    fxp::MapTensor t{x, rows, cols, nullptr, partials, np, e_max, q, qT, stream_id};
-    return fxp::map_launch(t, seed, rounding, bits, s);
+    if (rows * cols == 0) {
+        int np = 0;
+        rc = fxp::scale_partials(x, 0, partials, &np, s);
+        return rc ? rc : fxp::scale_finish(partials, np, e_max, s);
+    }
+    return fxp::scale_and_map(x, rows, cols, e_max, q, qT, seed, stream_id, rounding, bits, partials, s);
 }
 
 static int check_desc(const fxp_map_desc* d, int rounding, int bits) {

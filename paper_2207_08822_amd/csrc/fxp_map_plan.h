@@ -1,6 +1,7 @@
 // How a map launch cuts a tensor up: host arithmetic only, so that it can be checked without a device.
 #pragma once
 #include <cstdint>
+#include <initializer_list>
 
 namespace fxp {
 
@@ -51,6 +52,56 @@ inline MapPlan plan_map(int64_t rows, int64_t cols, bool aligned16, bool transpo
 inline bool tiles_for_both(const MapPlan& a, int64_t cols_a, const MapPlan& b, int64_t cols_b) {
     auto full = [](const MapPlan& p, int64_t cols) { return 8 * cols >= 7 * ((cols + p.tc - 1) / p.tc * p.tc); };
     return a.tiles && b.tiles && a.tc == b.tc && !a.any && !b.any && (!a.flat || full(a, cols_a)) && (!b.flat || full(b, cols_b));
+}
+
+// ---- tiles of quads (fxp_map_rows.hip) ----
+constexpr uint32_t kRowsWidth = 128;                  // most columns of a window
+constexpr uint32_t kScanWidth = 32;                   // ... where every workgroup reads the whole tensor: small tiles, many of them
+constexpr int64_t kScanMaxElements = 65536;           // of a tensor whose scale every workgroup works out for itself
+
+struct RowsPlan {
+    int tr;                          // rows of a tile
+    uint32_t windows, width;         // of a row: windows of `width` columns, the last one perhaps of fewer
+    uint32_t quads, magic;           // most quads that a window meets in a row; id / quads = (id * magic) >> 32 for ids of a tile
+    int64_t blocks;
+};
+
+// `windows` of a size (of any tensor of fewer than 2^22 columns), none wider than the stage of the kernel that they are for
+inline RowsPlan plan_rows(int64_t rows, int64_t cols, int tr, int64_t windows) {
+    RowsPlan p;
+    p.tr = tr;
+    int64_t width = (cols + windows - 1) / windows;
+    if (cols % 4 == 0) width = (width + 3) / 4 * 4;               // whose quads then begin with them
+    p.windows = static_cast<uint32_t>((cols + width - 1) / width);
+    p.width = static_cast<uint32_t>(width);
+    p.quads = cols % 4 == 0 ? p.width / 4 : (p.width + 6) / 4;
+    if (p.quads < 2) p.quads = 2;                                 // (of one, the reciprocal has 33 bits)
+    p.magic = 0xffffffffu / p.quads + 1;
+    p.blocks = (rows + tr - 1) / tr * p.windows;
+    return p;
+}
+
+// Tall tiles write long runs of the transposed copy, but a few hundred of them leave CUs with one tile more than others: the
+// height whose tiles fill 256 CUs best, a halving counted as an eighth lost (both copies, us at 128 / 64 / 32 rows: 12608 x
+// 1001 22.4 / 24.0, 25000 x 301 16.1 / 15.1, 6000 x 1001 13.0 at 64 / 15.4, 18912 x 197 9.2 / 9.0); 32 rows below two tiles a CU.
+inline RowsPlan plan_rows(int64_t rows, int64_t cols) {
+    const int64_t windows = (cols + kRowsWidth - 1) / kRowsWidth;
+    RowsPlan best = plan_rows(rows, cols, 32, windows);
+    double best_score = 0.0, weight = 1.0;
+    for (int tr : {128, 64, 32}) {
+        const RowsPlan p = plan_rows(rows, cols, tr, windows);
+        const double score = weight * static_cast<double>(p.blocks) / static_cast<double>((p.blocks + 255) / 256 * 256);
+        if (p.blocks >= 512 && score > best_score) {
+            best = p;
+            best_score = score;
+        }
+        weight *= 0.87;
+    }
+    return best;
+}
+
+inline bool scale_by_scan(int64_t rows, int64_t cols) {
+    return rows > 0 && cols >= 16 && rows <= kScanMaxElements / cols;
 }
 
 }  // namespace fxp

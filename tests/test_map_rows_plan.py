@@ -1,0 +1,43 @@
+"""How tensors are cut into tiles of quads (csrc/fxp_map_plan.h), on the host: every element lies in one window, every quad that a
+window meets has a lane, the reciprocal divides exactly, and the addressing stays in 32 bits."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2207_08822_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = shutil.which("g++")
+    assert cxx, "g++ is part of the image"
+    exe = str(tmp_path_factory.mktemp("plan") / "map_rows_plan")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", CSRC, os.path.join(HERE, "helpers", "map_rows_plan.cpp"), "-o", exe], check=True)
+
+    def ask(cases):
+        out = subprocess.run([exe], input="".join("%d %d %d\n" % c for c in cases), capture_output=True, text=True, check=True).stdout
+        return [dict(zip(("tr", "windows", "width", "quads", "blocks", "exact", "scan"), map(int, l.split()))) for l in out.splitlines()]
+    return ask
+
+
+@pytest.mark.parametrize("rows", [1, 31, 129, 12608, 1 << 20])
+def test_every_element_has_one_lane(plan, rows):
+    cases = [(rows, c, tr) for c in list(range(4, 300)) + [1000, 1001, 3071, 3072, (1 << 22) - 4, (1 << 22) - 1] for tr in (0, -1, 64, 128)]
+    for (_, cols, tr), p in zip(cases, plan(cases)):
+        where = (rows, cols, tr, p)
+        assert p["exact"] and p["width"] <= (32 if tr < 0 else 128) and p["tr"] in (32, 64, 128), where
+        assert (p["windows"] - 1) * p["width"] < cols <= p["windows"] * p["width"], where
+        assert p["blocks"] == -(-rows // p["tr"]) * p["windows"], where
+        # the most quads that `width` columns meet: from any element where rows shift, from a quad's first where they do not
+        shifts = range(4) if cols % 4 else (0,)
+        assert all(p["width"] * w % 4 == 0 for w in range(p["windows"])) or cols % 4, where
+        assert p["quads"] >= max(-(-(s + min(p["width"], cols)) // 4) for s in shifts), where
+        assert p["tr"] * cols + 128 < 1 << 30, where                  # four-byte offsets of a tile's elements below 2^32
+
+
+def test_small_tensors(plan):
+    got = plan([(256, 256, -1), (1, 65536, -1), (4096, 16, -1), (4369, 15, -1), (257, 256, -1), (1, 65537, -1), (0, 16, -1)])
+    assert [p["scan"] for p in got] == [1, 1, 1, 0, 0, 0, 0]
