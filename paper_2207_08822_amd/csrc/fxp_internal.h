@@ -257,7 +257,9 @@ __device__ inline uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uin
 inline int scale_and_map(const float* x, int64_t rows, int64_t cols, int32_t* e, int8_t* q, int8_t* qT, uint64_t seed,
                          uint64_t sid, int rounding, int bits, uint32_t* partials, hipStream_t s) {
     int np = 0;
-    int rc = scale_partials(x, static_cast<size_t>(rows * cols), partials, &np, s);
+    int rc = scale_map_small_launch(MapTensor{x, rows, cols, nullptr, nullptr, 0, e, q, qT, sid}, nullptr, seed, rounding, bits, s);
+    if (rc != kNotApplicable) return rc;
+    rc = scale_partials(x, static_cast<size_t>(rows * cols), partials, &np, s);
     if (rc) return rc;
     const MapTensor t{x, rows, cols, nullptr, partials, np, e, q, qT, sid};
     return map_launch(t, seed, rounding, bits, s);
@@ -267,7 +269,9 @@ inline int scale_and_map(const float* x, int64_t rows, int64_t cols, int32_t* e,
 // reduction launch and one map launch cover both.  t.partials must point at kMaxPartials words each; e_in and
 // n_partials of the arguments are ignored.
 inline int scale_and_map2(MapTensor a, MapTensor b, uint64_t seed, int rounding, int bits, hipStream_t s) {
-    int rc = scale_partials2(a.x, static_cast<size_t>(a.rows * a.cols), const_cast<uint32_t*>(a.partials), &a.n_partials, b.x,
+    int rc = scale_map_small_launch(a, &b, seed, rounding, bits, s);
+    if (rc != kNotApplicable) return rc;
+    rc = scale_partials2(a.x, static_cast<size_t>(a.rows * a.cols), const_cast<uint32_t*>(a.partials), &a.n_partials, b.x,
                              static_cast<size_t>(b.rows * b.cols), const_cast<uint32_t*>(b.partials), &b.n_partials, s);
     if (rc) return rc;
     a.e_in = b.e_in = nullptr;
