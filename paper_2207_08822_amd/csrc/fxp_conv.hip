@@ -4,7 +4,8 @@
 //             scale+map W[Cout,KH,KW,C] (both orientations), int8 im2col -> col[M,K],
 //             Y[M,Cout] = unmap(col * Wq^T)                         M = N*Ho*Wo, K = KH*KW*C
 //   backward: scale+map dY[M,Cout] once (both orientations),
-//             dW[Cout,K] = unmap(dYqT * colT^T) with colT[K,M] rebuilt from the saved int8 X,
+//             dW[Cout,K] from dYq and the saved int8 X (fxp_conv_wgrad.hip; channels that are not whole 16-byte pieces, or
+//             very many weights: unmap(dYqT * colT^T) with colT[K,M] rebuilt from X),
 //             dX: for stride 1 it is itself a convolution - im2col of dYq (padded by K-1-pad) times the
 //             flipped weights WqF, inverse mapping fused in the GEMM; for other strides
 //             the same per class of input pixels (StrideClasses: stride 2), or
@@ -159,6 +160,12 @@ __device__ inline bool side_roles(const SideScale& side, unsigned tile_blocks, c
         return true;
     }
     return false;
+}
+
+// the side roles alone: where no transposed patches are written, the block maxima of the gradient and the flipped weights
+template <bool CLASSES>
+__global__ __launch_bounds__(256) void k_scale_flip(ConvGeo g, const int8_t* __restrict__ WqT, int8_t* __restrict__ WqF, SideScale side) {
+    side_roles<CLASSES>(side, 0u, WqT, g, WqF);
 }
 
 // colT[(tap*C + c)][m] for a tile of 128 consecutive m x TCH = 64 channels of one tap (128 bytes of a colT row: whole
@@ -510,6 +517,7 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     const bool strided = dX && !thin && dx_strided(g, dW != nullptr, area_bytes, &wc_at);
     const bool need_flip = dX && (dx_as_conv(g) || strided);
     int8_t* flipped = strided ? reinterpret_cast<int8_t*>(area + wc_at) : saved->WqF;
+    const bool direct = dW && !thin && conv_wgrad_fits(taps_of(g), g.KH, M, g.Cout, strided ? wc_at : area_bytes);
     ReduceRider pending;                 // the weight gradient's split-K reduction while it waits for a launch to ride in
     const unsigned flip_blocks = need_flip ? grid_for(K * flip_pieces(g)) : 0u;
     if (need_flip && (!dW || thin)) {
@@ -525,6 +533,16 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
         sum.eA = e_dY; sum.bitsA = bits;
         sum.eB = saved->eX; sum.bitsB = bits;
         if ((rc = splitk_reduce_launch(sum, s))) return rc;
+    } else if (dW && direct) {
+        hipLaunchKernelGGL(strided ? k_scale_flip<true> : k_scale_flip<false>, dim3(side.blocks + flip_blocks), dim3(256), 0, s, g,
+                           saved->WqT, flipped, side);
+        if ((rc = launch_status())) return rc;
+        const MapTensor tdY{dY, M, g.Cout, nullptr, side.partials, static_cast<int>(side.blocks), e_dY, dYq, dYqT,
+                            (step << 8) | FXP_TAG_DY};
+        if ((rc = map_launch(tdY, seed, rounding, bits, s))) return rc;
+        if ((rc = conv_wgrad_launch(taps_of(g), g.KH, M, g.Cout, saved->Xq, dYq, dW, e_dY, bits, saved->eX, bits, area, s,
+                                    need_flip ? &pending : nullptr)))
+            return rc;
     } else if (dW) {
         int8_t* colT = reinterpret_cast<int8_t*>(area);
         const bool quads = g.C % 4 == 0;                        // the dword kernel takes 128 output pixels per tile

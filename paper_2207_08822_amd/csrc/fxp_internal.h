@@ -146,6 +146,17 @@ int conv_thin_fwd_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, 
 bool conv_thin_wgrad_fits(const ConvTaps& ct, int KH, int64_t images, int64_t Cout, size_t part_bytes);
 int conv_thin_wgrad_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, int64_t Cout, const int8_t* Xq,
                            const int8_t* dYqT, void* parts, size_t part_bytes, ReduceRider* sum, hipStream_t s);
+// weight gradients without stored patches (fxp_conv_wgrad.hip); the sum of the slices is launched, or described in *defer
+struct WgradCut {
+    int bm, tiles_m, tiles_n, slices;
+    bool pairs;              // two workgroups per CU
+    int64_t per_slice;
+    size_t ws_bytes;
+};
+WgradCut plan_conv_wgrad(int64_t M, int64_t Cout, int64_t K);
+bool conv_wgrad_fits(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, size_t ws_bytes);
+int conv_wgrad_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* dYq, float* dW,
+                      const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, void* ws, hipStream_t s, ReduceRider* defer);
 int splitk_reduce_launch(ReduceRider r, hipStream_t s);      // chooses group and blocks itself
 size_t gemm_ws_worst(int64_t M, int64_t N, int64_t K);
 int transpose_i8_launch(const int8_t* src, int64_t rows, int64_t cols, int64_t ld, int8_t* dst, hipStream_t s);
