@@ -56,7 +56,8 @@ int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int r
 // scale + map of small tensors in one launch (fxp_map_rows.hip); b may be null, partials are not used
 int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s);
 // scale + map in one pass with the previous scale as a guess (fxp_map.hip)
-constexpr unsigned kGuessBlocks = 1008;            // workgroups of a guessing launch: their maxima and the guess fit one scratch area
+constexpr unsigned kGuessBlocks = 4080;            // workgroups of a guessing launch: their exponents and the guess fit one scratch area
+static_assert(kGuessBlocks % 16 == 0 && kGuessBlocks + sizeof(int32_t) <= kScaleWsBytes && kGuessBlocks <= 16 * 256, "one area");
 constexpr int64_t kGuessMinElements = int64_t{1} << 22;
 constexpr int kNoGuessPath = 2;
 constexpr int kGuessOneByOne = 3;

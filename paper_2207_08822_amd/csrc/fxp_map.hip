@@ -46,10 +46,12 @@ struct MapJob {
     int flat;               // row-major copy only: rows and columns do not matter (map_flat_body)
     unsigned blocks;
     unsigned xcd_blocks;    // leading workgroups whose tiles are numbered per XCD (see tile_of_workgroup)
-    // scale taken as a guess (see k_map_tile_guess): where the guess comes from, where the workgroup maxima of
-    // the guessing launch go, and the word that records which guess the tensor was mapped with (0 = none)
+    // scale taken as a guess (see k_map_tile_guess): where the guess comes from, where the largest exponents that the
+    // workgroups of the guessing launch met go, how many, and the word that records which guess the tensor was mapped with
+    // (0 = none)
     const int32_t* e_guess;
-    uint32_t* guess_partials;
+    uint8_t* guess_maxima;
+    int guess_blocks;
     int32_t* guess_used;
 };
 struct MapJobs {
@@ -93,7 +95,9 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     constexpr int RGP = kMapThreads / CG;         // groups of 4 rows per pass
     constexpr int TR = 4 * RGP * PASSES;          // rows of the tile
     constexpr int TS = RGP * PASSES + 1;          // dwords per staged column (TR row bytes + 4 pad)
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    // (in the loop over tiles: nothing that follows from the thread is kept from one tile to the next, which took 173 registers)
+    if (GUESS) asm volatile("" : "+v"(tid));
     const int cg = tid % CG;                      // group of 4 columns
     const int rgl = tid / CG;                     // group of 4 rows within a pass
     const uint32_t ucols = static_cast<uint32_t>(cols);
@@ -117,10 +121,11 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
         }
     };
     uint4 cur[4], nxt[4];
-    const uint32_t share = GUESS ? 0u : partials_share(J.partials, J.n_partials);
+    const bool given = GUESS || e_given != 0;
+    const uint32_t share = given ? 0u : partials_share(J.partials, J.n_partials);
     load_pass(0, cur);
     // the scale is resolved (block maxima re-read and reduced) while the first loads are in flight
-    const MapCfg cfg = make_cfg(GUESS ? e_given : resolve_scale(J.e_in, J.partials, share, J.e_out, red, publish), bits);
+    const MapCfg cfg = make_cfg(given ? e_given : resolve_scale(J.e_in, J.partials, share, J.e_out, red, publish), bits);
     const bool scale_ok = cfg.e_max >= 25 && cfg.e_max < 255;
     const uint32_t over_bits = ~cfg.sat;          // a fast-path result with any of these set needs saturation
     uint32_t seen = 0;                             // GUESS: largest magnitude bits this thread has loaded
@@ -207,6 +212,20 @@ __device__ inline void map_tile_body(const uint32_t* __restrict__ x, int64_t row
     }
 }
 
+// the scale that the guessing launch has seen: largest of at most kGuessBlocks exponents, sixteen a thread
+__device__ inline int scale_of_guess(const MapJob& J, uint32_t* red) {
+    uint32_t m = 0;
+    const int first = 16 * threadIdx.x;
+    if (first < J.guess_blocks) {
+        const uint4 v = reinterpret_cast<const uint4*>(J.guess_maxima)[threadIdx.x];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (first + k < J.guess_blocks) m = max(m, (w[k >> 2] >> (8 * (k & 3))) & 0xffu);
+    }
+    return max(1, static_cast<int>(block_max(m, red)));
+}
+
 // FLAT: a launch with a flat tensor in it.  (A parameter: with the flat body in every instantiation the tiles of an aligned
 // tensor ran at lower occupancy or spilled, 159744 x 208 both copies 39.1 -> 40.0 us.)
 template <bool STOCH, int PASSES, int TC, bool FLAT>
@@ -218,11 +237,13 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
     const bool second = blockIdx.x >= jobs.j[0].blocks;            // workgroup-uniform
     const MapJob& J = jobs.j[second ? 1 : 0];
     const unsigned bid = blockIdx.x - (second ? jobs.j[0].blocks : 0u);
+    int e_true = 0;
     if (J.guess_used != nullptr) {
         // this launch follows k_map_tile_guess: the tensor is already mapped if the guess was its scale - then
         // the scale is published and nothing else is left to do; otherwise the tile is mapped now
-        const int e = resolve_scale(nullptr, J.partials, partials_share(J.partials, J.n_partials), J.e_out, red, bid == 0);
-        if (J.guess_used[0] == e) return;
+        e_true = scale_of_guess(J, red);
+        if (bid == 0 && threadIdx.x == 0) J.e_out[0] = e_true;
+        if (J.guess_used[0] == e_true) return;
     }
     if (FLAT && J.flat) {
         const uint64_t first = static_cast<uint64_t>(bid) * (4 * kMapThreads * PASSES);
@@ -240,16 +261,16 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile(const MapJobs jobs, ui
     const int64_t r0 = static_cast<int64_t>(rb) * TR;
     const int64_t c0 = static_cast<int64_t>(cb) * TC;
     if (r0 + TR <= rows && c0 + TC <= cols)
-        map_tile_body<STOCH, false, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
+        map_tile_body<STOCH, false, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage, e_true);
     else
-        map_tile_body<STOCH, true, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage);
+        map_tile_body<STOCH, true, PASSES, TC>(x, rows, cols, J, bits, bid == 0, red, q, qT, key0, key1, J.sid0, J.sid1, r0, c0, stage, e_true);
 }
 
 // Scale and map in ONE pass over the tensor, for a caller that has a guess of the scale (the tensor's scale of
 // the previous training step: the largest exponent of a weight, an activation or a gradient tensor seldom moves
 // from one step to the next).  Every workgroup maps its tiles with the guess and keeps the largest magnitude it
-// saw; the launch leaves one maximum per workgroup (at most kGuessBlocks, so that the launch that follows can
-// reduce them like block maxima) and the guess it used.  The launch that follows (k_map_tile with guess_used
+// saw; the launch leaves one exponent per workgroup (at most kGuessBlocks: a tile a workgroup up to that many, each a byte)
+// and the guess it used.  The launch that follows (k_map_tile with guess_used
 // set) computes the true scale from the maxima: equal to the guess - the bytes written here are exactly what the
 // two-pass path writes, and that launch ends at once; different, or no usable guess (outside 1 .. 255) - it
 // maps the tensor again with the true scale.  4 B read + 2 B written per element instead of 8 + 2 on a hit.
@@ -259,39 +280,29 @@ __global__ __launch_bounds__(kMapThreads) void k_map_tile_guess(const MapJobs jo
     constexpr int TR = 4 * RGP * PASSES;
     __shared__ uint32_t stage[TC * (RGP * PASSES + 1)];
     __shared__ uint32_t red[kMapThreads / 64];
-    int guess[2];
-    uint32_t seen[2] = {0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        guess[j] = jobs.j[j].blocks != 0 ? jobs.j[j].e_guess[0] : 0;
-        if (guess[j] < 1 || guess[j] > 255) guess[j] = 0;
-        if (jobs.j[j].blocks != 0 && blockIdx.x == 0 && threadIdx.x == 0) jobs.j[j].guess_used[0] = guess[j];
-    }
-    const unsigned total = jobs.j[0].blocks + jobs.j[1].blocks;
-    for (unsigned tile = blockIdx.x; tile < total; tile += gridDim.x) {
-        const int which = tile >= jobs.j[0].blocks ? 1 : 0;       // workgroup-uniform
-        const MapJob& J = jobs.j[which];
-        const unsigned bid = tile - (which ? jobs.j[0].blocks : 0u);
+    const bool second = blockIdx.x >= static_cast<unsigned>(jobs.j[0].guess_blocks);       // workgroup-uniform
+    const MapJob& J = jobs.j[second ? 1 : 0];
+    const unsigned first = blockIdx.x - (second ? jobs.j[0].guess_blocks : 0), step = J.guess_blocks;
+    int guess = J.e_guess[0];
+    if (guess < 1 || guess > 255) guess = 0;
+    if (first == 0 && threadIdx.x == 0) J.guess_used[0] = guess;
+    uint32_t seen = 0;
+#pragma unroll 1
+    for (unsigned tile = first; tile < J.blocks; tile += step) {
+        if (tile != first) __syncthreads();      // the staging area is read by other threads than those that fill it for the next tile
         unsigned rb, cb;
-        tile_of_workgroup(J, bid, &rb, &cb);
+        tile_of_workgroup(J, tile, &rb, &cb);
         const int64_t r0 = static_cast<int64_t>(rb) * TR;
         const int64_t c0 = static_cast<int64_t>(cb) * TC;
-        uint32_t m = 0;
         if (r0 + TR <= J.rows && c0 + TC <= J.cols)
             map_tile_body<STOCH, false, PASSES, TC, true>(J.x, J.rows, J.cols, J, bits, false, red, J.q, J.qT, key0, key1, J.sid0,
-                                                          J.sid1, r0, c0, stage, guess[which], guess[which] != 0, &m);
+                                                          J.sid1, r0, c0, stage, guess, guess != 0, &seen);
         else
             map_tile_body<STOCH, true, PASSES, TC, true>(J.x, J.rows, J.cols, J, bits, false, red, J.q, J.qT, key0, key1, J.sid0,
-                                                         J.sid1, r0, c0, stage, guess[which], guess[which] != 0, &m);
-        seen[which] = max(seen[which], m);
-        __syncthreads();      // the staging area is read by other threads than those that fill it for the next tile
+                                                         J.sid1, r0, c0, stage, guess, guess != 0, &seen);
     }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        if (jobs.j[j].blocks == 0) continue;
-        const uint32_t m = block_max(seen[j], red);
-        if (threadIdx.x == 0) jobs.j[j].guess_partials[blockIdx.x] = m;
-    }
+    seen = block_max(seen, red);
+    if (threadIdx.x == 0) J.guess_maxima[first] = static_cast<uint8_t>(seen >> 23);
 }
 
 // One element per thread, any shape and alignment.
@@ -349,7 +360,8 @@ static MapJob make_job(const MapTensor& t, int tc, int passes, bool flat) {
     const bool shared_lines = j.tiles_c > 1 && t.cols % 128 != 0;
     j.xcd_blocks = shared_lines ? static_cast<unsigned>((t.rows + tr - 1) / tr / 8 * 8 * j.tiles_c) : 0u;
     j.e_guess = nullptr;
-    j.guess_partials = nullptr;
+    j.guess_maxima = nullptr;
+    j.guess_blocks = 0;
     j.guess_used = nullptr;
     return j;
 }
@@ -414,21 +426,27 @@ int scale_map_guess_launch(const MapTensor& a, const MapTensor* b, uint32_t* are
     // (tiles, whether or not an ordinary map would take the tensor flat)
     if (!pa.tiles || !pb.tiles || pa.any || pb.any) return kNoGuessPath;
     if (pa.tc != pb.tc) return kGuessOneByOne;        // different tile widths: no common launch, but each may guess alone
-    const int passes = na >= nb ? pa.passes : pb.passes;
+    int passes = na >= nb ? pa.passes : pb.passes;
+    // The body that also keeps the maximum holds 111 registers for two passes and 143 for four: two, where every workgroup then
+    // still has one tile (12608 x 2304 34.8 us for 36.4; 8192 x 8192, three tiles of two passes for two of four, step 1612 for 1600).
+    if (passes == 4 && std::max(make_job(a, pa.tc, 2, false).blocks, b ? make_job(*b, pa.tc, 2, false).blocks : 0u) <= kGuessBlocks) passes = 2;
     MapJobs jobs;
     jobs.j[0] = make_job(a, pa.tc, passes, false);
     if (b) jobs.j[1] = make_job(*b, pa.tc, passes, false);
     else { jobs.j[1] = jobs.j[0]; jobs.j[1].blocks = 0; }
     const uint64_t total = static_cast<uint64_t>(jobs.j[0].blocks) + jobs.j[1].blocks;
     if (total >= (uint64_t{1} << 31)) return kNoGuessPath;
-    const unsigned grid = static_cast<unsigned>(std::min<uint64_t>(total, kGuessBlocks));
+    unsigned grid = 0;
     uint32_t* areas[2] = {area_a, area_b};
     const MapTensor* ts[2] = {&a, b};
     for (int j = 0; j < 2; ++j) {
         if (jobs.j[j].blocks == 0) continue;
         jobs.j[j].e_guess = ts[j]->e_out;                                   // last step's scale, if the caller kept it
-        jobs.j[j].guess_partials = areas[j];
-        jobs.j[j].guess_used = reinterpret_cast<int32_t*>(areas[j] + kGuessBlocks);
+        jobs.j[j].guess_maxima = reinterpret_cast<uint8_t*>(areas[j]);
+        const unsigned per = (jobs.j[j].blocks + kGuessBlocks - 1) / kGuessBlocks;       // tiles of a workgroup
+        jobs.j[j].guess_blocks = static_cast<int>((jobs.j[j].blocks + per - 1) / per);
+        grid += jobs.j[j].guess_blocks;
+        jobs.j[j].guess_used = reinterpret_cast<int32_t*>(areas[j] + kGuessBlocks / 4);
         jobs.j[j].e_in = nullptr;
         jobs.j[j].partials = nullptr;
     }
@@ -437,12 +455,7 @@ int scale_map_guess_launch(const MapTensor& a, const MapTensor* b, uint32_t* are
     launch_tiles_guess(jobs, grid, pa.tc, passes, stoch, k0, k1, bits, s);
     int rc = launch_status();
     if (rc) return rc;
-    // the launch that verifies: an ordinary map launch that takes the workgroup maxima as block maxima
-    for (int j = 0; j < 2; ++j) {
-        if (jobs.j[j].blocks == 0) continue;
-        jobs.j[j].partials = areas[j];
-        jobs.j[j].n_partials = static_cast<int>(grid);
-    }
+    // the launch that verifies: an ordinary map launch whose workgroups look at the maxima first
     launch_tiles(jobs, pa.tc, passes, stoch, k0, k1, bits, s);
     return launch_status();
 }
@@ -474,8 +487,8 @@ int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStr
     return launch_status();
 }
 
-// Two tensors in one launch when both take the tiled kernel with the same tile width, or one of them is flat; the tile height is the
-// one the larger tensor would pick.  Otherwise one launch each.
+// Two tensors in one launch when both are tiled or flat; the tile height is the one the larger tensor would pick.  Otherwise one
+// launch each.
 int map_launch2(const MapTensor& a, const MapTensor& b, uint64_t seed, int rounding, int bits, hipStream_t s) {
     MapPlan pa = plan_map(a), pb = plan_map(b);
     if (tiles_for_both(pa, a.cols, pb, b.cols)) {
