@@ -106,9 +106,10 @@ int fxp_scale_map(const float* x, int64_t rows, int64_t cols, int32_t* e_max, in
 /* Two tensors per launch: what fxp_map / fxp_scale_map do for one tensor, done for two with one map launch
  * (and one reduction launch) instead of two each - the layer calls use this for the activation and the
  * weight of a forward pass, where the second tensor is often too small to fill the chip by itself.  Results
- * are identical to two separate calls.  One launch needs both tensors on the fast path of fxp_map and of the
- * same tile width (cols <= 64 or cols % 128 in 1..64 selects the narrow tile), or one of them wanted row-major only (which
- * needs no tiles, whatever its width); otherwise two launches are made. */
+ * are identical to two separate calls.  One launch needs both tensors tiled or flat (see fxp_map: rows of 16 columns or more,
+ * or row-major only, whatever the width); otherwise two launches are made.  Two small tensors have their scales found in the
+ * same launch.
+ */
 typedef struct fxp_map_desc {
     const float* x;      /* [rows, cols] fp32, device */
     int64_t rows, cols;
@@ -387,7 +388,8 @@ int fxp_clock_probe(uint64_t* out, uint32_t microseconds, void* stream);
  * elapsed microseconds and the tag of the later one (so an interval is the in-stream duration of that launch
  * behind the launch that really precedes it in the step; an FXP_TL_ENTRY interval is the idle time between two
  * calls); *count receives the number of intervals written (at most `capacity`).  Then the events are destroyed.
- * The two gradients of a small layer go out in one launch, FXP_TL_GEMM_GRADS in place of _DW and _DX.
+ * The two gradients of a small layer go out in one launch, FXP_TL_GEMM_GRADS in place of _DW and _DX; a small layer's
+ * scales are found in its map launches, and their FXP_TL_SCALE intervals are empty.
  * One timeline per process; not to be begun or ended while layer calls are running in other threads. */
 enum { FXP_TL_ENTRY = 0, FXP_TL_SCALE = 1, FXP_TL_MAP = 2, FXP_TL_GEMM_FWD = 3, FXP_TL_GEMM_DW = 4, FXP_TL_GEMM_DX = 5,
        FXP_TL_REDUCE = 6, FXP_TL_GEMM_GRADS = 7 };
