@@ -58,9 +58,10 @@ __device__ inline void tile_of_block(int b, int tiles_m, int tiles_n, int group_
 // the riders, the input gradient of a 32 x 28 x 28 x 128 3x3 layer took 14.0 us for 11.3).  64-bit sums ride like any other:
 // layer steps of 64 x 56 x 56 x 64 -> 64 3x3 145 us, with a launch of their own 151, one element a thread 176;
 // 262144 x 128 x 512 521 / 528 / 525; 200000 x 256 x 64 230 / 241 / 264.
-template <bool ALONE>
+// NT: threads of the workgroup, 256 alone, those of the host product when riding (blockDim would be a vector load).
+template <bool ALONE, unsigned NT>
 __device__ inline void splitk_reduce_body(const ReduceRider& r, unsigned b, unsigned nb) {
-    const unsigned nt = blockDim.x;                  // 256 stand-alone; the host product's workgroup size when riding
+    constexpr unsigned nt = NT;
     float m = 0.0f;
     int E = 0;
     if (r.fp32_out) E = lsb_exponent(r.eA[0], r.bitsA) + (r.eB ? lsb_exponent(r.eB[0], r.bitsB) : 0);
@@ -245,7 +246,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
         if (blockIdx.x >= first && blockIdx.x < first + rider.blocks) {
-            splitk_reduce_body<false>(rider, blockIdx.x - first, rider.blocks);
+            splitk_reduce_body<false, (BM / WM) * (BN / WN) * 64>(rider, blockIdx.x - first, rider.blocks);
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
@@ -413,7 +414,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
 template <int MODE>
 __global__ __launch_bounds__(256) void k_gemm_nt_direct(Product p0, Product p1, ReduceRider rider) {
     if (rider.blocks != 0 && blockIdx.x >= rider.tiles) {          // workgroup-uniform: the last workgroups
-        splitk_reduce_body<false>(rider, blockIdx.x - rider.tiles, rider.blocks);
+        splitk_reduce_body<false, 256>(rider, blockIdx.x - rider.tiles, rider.blocks);
         return;
     }
     const bool second = blockIdx.x >= p0.tiles;
@@ -520,7 +521,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt_dma(
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
         if (blockIdx.x >= first && blockIdx.x < first + rider.blocks) {
-            splitk_reduce_body<false>(rider, blockIdx.x - first, rider.blocks);
+            splitk_reduce_body<false, (BM / WM) * (BN / WN) * 64>(rider, blockIdx.x - first, rider.blocks);
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
@@ -792,7 +793,7 @@ __global__ __launch_bounds__((256 / WM) * (256 / WN) * 64) void k_gemm_nt_ring(
     if (rider.blocks != 0) {                                      // workgroup-uniform
         const unsigned first = rider.front ? 0u : rider.tiles;    // the riders are the first or the last workgroups
         if (blockIdx.x >= first && blockIdx.x < first + rider.blocks) {
-            splitk_reduce_body<false>(rider, blockIdx.x - first, rider.blocks);
+            splitk_reduce_body<false, (256 / WM) * (256 / WN) * 64>(rider, blockIdx.x - first, rider.blocks);
             return;
         }
         if (rider.front) tile_block -= static_cast<int>(rider.blocks);
@@ -1133,7 +1134,7 @@ static int launch_dma(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t 
     return launch_status();
 }
 
-__global__ __launch_bounds__(256) void k_splitk_reduce(ReduceRider r) { splitk_reduce_body<true>(r, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void k_splitk_reduce(ReduceRider r) { splitk_reduce_body<true, 256>(r, blockIdx.x, gridDim.x); }
 
 // workgroups of a reduction with `lanes` lanes per 16-byte piece of the output: 256 threads each, at most 2048
 static unsigned reduce_blocks(const ReduceRider& r, int lanes) {
@@ -1141,12 +1142,13 @@ static unsigned reduce_blocks(const ReduceRider& r, int lanes) {
     return static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (pieces * lanes + 255) / 256)));
 }
 
-// One lane a piece while the pieces alone fill the chip or the slices are few; else up to sixteen lanes, each with eight
-// slices or more (a 64 x 147 output of 126 slices: ten workgroups walked all slices in turn, 123 us; 256 slices now 9 us).
+// One lane a piece while the pieces alone fill the chip or the slices are few; else up to 32 lanes, each with eight slices - one
+// round of loads - or more (a 64 x 147 output of 126 slices: ten workgroups walked all slices in turn, 123 us; 256 slices with
+// sixteen lanes 8.7 us, with 32 lanes 6.3).
 int splitk_reduce_launch(ReduceRider r, hipStream_t s) {
     const int64_t pieces = static_cast<int64_t>(r.M) * r.N / 4;
     r.group = 1;
-    while (r.group < 16 && r.splits >= 16 * r.group && pieces * r.group < 65536) r.group *= 2;
+    while (r.group < 32 && r.splits >= 8 * r.group && pieces * r.group < 131072) r.group *= 2;
     r.blocks = reduce_blocks(r, r.group);
     hipLaunchKernelGGL(k_splitk_reduce, dim3(r.blocks), dim3(256), 0, s, r);
     return launch_status();
