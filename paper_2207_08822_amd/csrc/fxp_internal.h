@@ -181,14 +181,15 @@ __device__ inline uint32_t wave_max(uint32_t v) {
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
 }
 
-// max over a block of 256 threads; lds holds four words.  (The size is a constant: blockDim is a vector load from the dispatch's
-// arguments, waited for with all loads before it.)
+// max over a block of WAVES waves (a power of two); lds holds a word for each.  (The size is a constant: blockDim is a vector load
+// from the dispatch's arguments, waited for with all loads before it.)
+template <int WAVES = 4>
 __device__ inline uint32_t block_max(uint32_t v, uint32_t* lds) {
     v = wave_max(v);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane == 0) lds[wave] = v;
     __syncthreads();
-    uint32_t r = lds[lane & 3];
+    uint32_t r = lds[lane & (WAVES - 1)];
     r = wave_max(r);
     __syncthreads();
     return r;

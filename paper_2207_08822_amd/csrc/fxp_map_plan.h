@@ -57,7 +57,10 @@ inline bool tiles_for_both(const MapPlan& a, int64_t cols_a, const MapPlan& b, i
 // ---- tiles of quads (fxp_map_rows.hip) ----
 constexpr uint32_t kRowsWidth = 128;                  // most columns of a window
 constexpr uint32_t kScanWidth = 32;                   // ... where every workgroup reads the whole tensor: small tiles, many of them
-constexpr int64_t kScanMaxElements = 65536;           // of a tensor whose scale every workgroup works out for itself
+// Of a tensor whose scale every workgroup works out for itself: 64 bytes a clock from L2, so beyond some 100000 elements reading
+// it takes longer than a reduction launch (steps of n^3, two launches / scan in us: 256 30 / 21.0, 300 26.8 / 22.2, 330 28.0 / 25.5,
+// 362 29.8 / 31.0, 400 26.4 / 30.8).
+constexpr int64_t kScanMaxElements = 112 * 1024;
 
 struct RowsPlan {
     int tr;                          // rows of a tile

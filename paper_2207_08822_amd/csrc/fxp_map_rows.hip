@@ -43,10 +43,10 @@ __device__ inline unsigned tile_in_xcd_run(unsigned bid, unsigned blocks) {
     return xcd < more ? xcd * (per + 1) + at : more * (per + 1) + (xcd - more) * per + at;
 }
 
-// Largest magnitude bits of a whole tensor, by every workgroup for itself: sixteen 16-byte loads in flight a thread, each
-// workgroup from a chunk of its own on so that not all of them miss the same lines at once.
+// Largest magnitude bits of a whole tensor, by every workgroup for itself: sixteen 16-byte loads in flight a thread (eight where
+// they reach all of it), each workgroup from a chunk of its own on so that not all of them miss the same lines at once.
+constexpr int kScanThreads = 512;
 __device__ inline uint32_t scan_absmax(const uint32_t* __restrict__ x, uint32_t n, unsigned bid) {
-    constexpr uint32_t kChunk = 16 * kMapThreads;                // quads
     const uint32_t kAbs = 0x7fffffffu;
     const uint32_t mis = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(x) >> 2) & 3u;
     const uint32_t head = min(mis ? 4 - mis : 0u, n), nvec = (n - head) >> 2, tail0 = head + 4 * nvec;
@@ -54,15 +54,23 @@ __device__ inline uint32_t scan_absmax(const uint32_t* __restrict__ x, uint32_t 
     uint32_t m = 0;
     if (threadIdx.x < head) m = x[threadIdx.x] & kAbs;
     if (tail0 + threadIdx.x < n) m = max(m, x[tail0 + threadIdx.x] & kAbs);       // fewer than four
-    const uint32_t chunks = (nvec + kChunk - 1) / kChunk;
-    uint32_t at = chunks ? bid % chunks : 0;
-    for (uint32_t c = 0; c < chunks; ++c) {
-        uint4 v[16];
+    auto chunk = [&](uint32_t first, auto loads) {
+        constexpr uint32_t kLoads = decltype(loads)::value;
+        uint4 v[kLoads];
 #pragma unroll
-        for (uint32_t k = 0; k < 16; ++k) v[k] = xv[min(at * kChunk + k * kMapThreads + threadIdx.x, nvec - 1)];
+        for (uint32_t k = 0; k < kLoads; ++k) v[k] = xv[min(first + k * kScanThreads + threadIdx.x, nvec - 1)];
 #pragma unroll
-        for (uint32_t k = 0; k < 16; ++k) m = max(m, absmax4(v[k]));
-        if (++at == chunks) at = 0;
+        for (uint32_t k = 0; k < kLoads; ++k) m = max(m, absmax4(v[k]));
+    };
+    if (nvec != 0 && nvec <= 8 * kScanThreads) {
+        chunk(0u, std::integral_constant<uint32_t, 8>{});
+    } else if (nvec != 0) {
+        const uint32_t chunks = (nvec + 16 * kScanThreads - 1) / (16 * kScanThreads);
+        uint32_t at = bid % chunks;
+        for (uint32_t c = 0; c < chunks; ++c) {
+            chunk(at * 16 * kScanThreads, std::integral_constant<uint32_t, 16>{});
+            if (++at == chunks) at = 0;
+        }
     }
     return m;
 }
@@ -74,7 +82,8 @@ template <bool STOCH, int TR, bool SCAN>
 __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, uint32_t key1, unsigned bid, uint32_t* red,
                                      uint8_t* stage) {
     constexpr int TS = TR + 4;                    // bytes per staged column: an odd number of dwords
-    constexpr int U = 4;                          // quads in flight per thread
+    constexpr int NT = SCAN ? kScanThreads : kMapThreads;
+    constexpr int U = SCAN ? 1 : 4;               // quads in flight per thread
     constexpr uint32_t kOff = 0xffffffffu;        // offset of a lane without a quad
     const unsigned tile = tile_in_xcd_run(bid, J.blocks), rb = tile / J.windows, cb = tile - rb * J.windows;
     const int64_t r0 = static_cast<int64_t>(rb) * TR;
@@ -98,7 +107,7 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     };
     auto load = [&](uint32_t id, Quads& a) {
 #pragma unroll
-        for (int u = 0; u < U; ++u, id += kMapThreads) {
+        for (int u = 0; u < U; ++u, id += NT) {
             const uint32_t row = __umulhi(id, J.magic), off = lead0 + row * ucols;
             const uint32_t rel = (off & ~3u) + 4 * (id - row * J.quads);
             const int col = static_cast<int>(rel - off);
@@ -114,7 +123,7 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     if (total) load(id, cur);
     int e;
     if constexpr (SCAN) {
-        const uint32_t m = block_max(scan_absmax(J.x, static_cast<uint32_t>(n), bid), red);
+        const uint32_t m = block_max<kScanThreads / 64>(scan_absmax(J.x, static_cast<uint32_t>(n), bid), red);
         e = max(1, static_cast<int>(m >> 23));
         if (bid == 0 && threadIdx.x == 0) J.e_out[0] = e;
     } else {
@@ -122,9 +131,9 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     }
     const MapCfg cfg = make_cfg(e, bits);
     const bool scale_ok = cfg.e_max >= 25 && cfg.e_max < 255;
-    const uint32_t rounds = (total + U * kMapThreads - 1) / (U * kMapThreads);
+    const uint32_t rounds = (total + U * NT - 1) / (U * NT);
     for (uint32_t round = 0; round < rounds; ++round) {
-        if (round + 1 < rounds) load(id += U * kMapThreads, nxt);
+        if (round + 1 < rounds) load(id += U * NT, nxt);
         uint32_t o[U], q_or = 0;
         uint64_t bad = 0;                          // wave-uniform: any lane with an uncovered element
         auto words_of = [&](int u) {
@@ -166,7 +175,7 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     __syncthreads();
     int8_t* qTt = qT + static_cast<uint64_t>(c0) * J.rows + r0;
     constexpr uint32_t PIECES = TR / 16;
-    for (uint32_t p = threadIdx.x; p < static_cast<uint32_t>(w_here) * PIECES; p += kMapThreads) {
+    for (uint32_t p = threadIdx.x; p < static_cast<uint32_t>(w_here) * PIECES; p += NT) {
         const uint32_t c = p / PIECES, ch = p % PIECES;
         if (16 * ch >= rows_here) continue;
         const uint32_t* src = reinterpret_cast<const uint32_t*>(stage + (c + 3) * TS) + 4 * ch;
@@ -180,9 +189,9 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
 }
 
 template <bool STOCH, int TR, bool SCAN, bool FLAT>
-__global__ __launch_bounds__(kMapThreads) void k_map_rows(const RowsJobs jobs, uint32_t key0, uint32_t key1, int bits) {
+__global__ __launch_bounds__(SCAN ? kScanThreads : kMapThreads) void k_map_rows(const RowsJobs jobs, uint32_t key0, uint32_t key1, int bits) {
     __shared__ __align__(16) uint8_t stage[((SCAN ? kScanWidth : kRowsWidth) + 6) * (TR + 4)];
-    __shared__ uint32_t red[kMapThreads / 64];
+    __shared__ uint32_t red[kScanThreads / 64];
     const bool second = blockIdx.x >= jobs.j[0].blocks;            // workgroup-uniform
     const RowsJob& J = jobs.j[second ? 1 : 0];
     const unsigned bid = blockIdx.x - (second ? jobs.j[0].blocks : 0u);
@@ -221,7 +230,7 @@ static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat) {
 }
 
 static int launch_rows(const RowsJobs& jobs, int tr, bool scan, uint64_t seed, int rounding, int bits, hipStream_t s) {
-    const dim3 grid(jobs.j[0].blocks + jobs.j[1].blocks), block(kMapThreads);
+    const dim3 grid(jobs.j[0].blocks + jobs.j[1].blocks), block(scan ? kScanThreads : kMapThreads);
     const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
     const bool flat = jobs.j[0].flat || jobs.j[1].flat, stoch = rounding == FXP_ROUND_STOCHASTIC;
     auto pick = [&](auto st) {

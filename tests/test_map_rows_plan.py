@@ -39,5 +39,5 @@ def test_every_element_has_one_lane(plan, rows):
 
 
 def test_small_tensors(plan):
-    got = plan([(256, 256, -1), (1, 65536, -1), (4096, 16, -1), (4369, 15, -1), (257, 256, -1), (1, 65537, -1), (0, 16, -1)])
-    assert [p["scan"] for p in got] == [1, 1, 1, 0, 0, 0, 0]
+    got = plan([(256, 256, -1), (1, 114688, -1), (7168, 16, -1), (7645, 15, -1), (449, 256, -1), (448, 256, -1), (1, 114689, -1), (0, 16, -1)])
+    assert [p["scan"] for p in got] == [1, 1, 1, 0, 0, 1, 0, 0]
