@@ -321,13 +321,17 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
             if (k + b < ke) w[b >> 2] |= static_cast<uint32_t>(static_cast<uint8_t>(p[k + b])) << (8 * (b & 3));
         return make_uint4(w[0], w[1], w[2], w[3]);
     };
+    auto load_whole = [&](int it, uint4 (&va)[NA], uint4 (&vb)[NB]) {
+        const int kk = kb + it * BK;
+#pragma unroll
+        for (int j = 0; j < NA; ++j) va[j] = load16(pa[j] + kk + kc_a[j]);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) vb[j] = load16(pb[j] + kk + kc_b[j]);
+    };
     auto load_step = [&](int it, uint4 (&va)[NA], uint4 (&vb)[NB]) {
         const int kk = kb + it * BK;
         if (WIDE && kk + BK <= ke) {                              // workgroup-uniform
-#pragma unroll
-            for (int j = 0; j < NA; ++j) va[j] = load16(pa[j] + kk + kc_a[j]);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) vb[j] = load16(pb[j] + kk + kc_b[j]);
+            load_whole(it, va, vb);
         } else {
 #pragma unroll
             for (int j = 0; j < NA; ++j) va[j] = tail_piece(pa[j], kk + kc_a[j], true);
@@ -385,7 +389,24 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_nt(
         if (nk > 1) load_step(1, ra[1], rb[1]);
         if (nk > 0) store_step(0, ra[0], rb[0]);
         __syncthreads();
-        for (int it = 0; it < nk; it += 2) {
+        // While both steps to be requested are whole, without a branch: with one around the loads the compiler cannot count
+        // those in flight, and waits for the new ones where it parks the older (1379 x 768 x 1000 gradients
+        // 14.2 -> 11.6 us, 12608 x 768 x 1001 step 148.9 -> 137.8).
+        auto steady = [&](int it, auto buf_c) {
+            constexpr int buf = decltype(buf_c)::value;
+            load_whole(it + 2, ra[buf], rb[buf]);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(buf);
+            store_step(buf ^ 1, ra[buf ^ 1], rb[buf ^ 1]);
+            __syncthreads();
+        };
+        const int whole = (ke - kb) / BK;
+        int it = 0;
+        for (; it + 3 < whole; it += 2) {
+            steady(it, IC<0>{});
+            steady(it + 1, IC<1>{});
+        }
+        for (; it < nk; it += 2) {
             step(it, IC<0>{});
             if (it + 1 < nk) step(it + 1, IC<1>{});
         }
