@@ -188,8 +188,10 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     }
 }
 
+// Five waves per SIMD (96 registers) where that spills nothing: 98 leave four (49344 x 257 18.8 -> 17.8 us, 25000 x 301 13.9 -> 13.3,
+// 18912 x 197 8.4 -> 8.2; 8191 x 8191, bound by memory, 97 -> 100).
 template <bool STOCH, int TR, bool SCAN, bool FLAT>
-__global__ __launch_bounds__(SCAN ? kScanThreads : kMapThreads) void k_map_rows(const RowsJobs jobs, uint32_t key0, uint32_t key1, int bits) {
+__global__ __launch_bounds__(SCAN ? kScanThreads : kMapThreads, SCAN ? 1 : FLAT ? 4 : 5) void k_map_rows(const RowsJobs jobs, uint32_t key0, uint32_t key1, int bits) {
     __shared__ __align__(16) uint8_t stage[((SCAN ? kScanWidth : kRowsWidth) + 6) * (TR + 4)];
     __shared__ uint32_t red[kScanThreads / 64];
     const bool second = blockIdx.x >= jobs.j[0].blocks;            // workgroup-uniform
