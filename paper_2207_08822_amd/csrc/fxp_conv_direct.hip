@@ -60,7 +60,7 @@ __device__ inline v4i keep(v4i v, const int8_t* base, int64_t at, int64_t size, 
 
 // Y[m][co] = unmap(sum over filter rows kh of patch bytes * weights).  A wave owns tiles of 32 output pixels and all
 // 32 * FN output channels; the weights, laid out as MFMA operands, are shared through LDS.  Bound by the output, 103 MB
-// of the 113 MB that the 32 x 224 x 224 x 3 -> 64 stem moves: 32 us (3.5 TB/s; 118 with the patch matrix stored and read
+// of the 113 MB that the 32 x 224 x 224 x 3 -> 64 stem moves: 29 us (3.9 TB/s; 118 with the patch matrix stored and read
 // back, 57 with every load waited for before the next).
 template <int FN>
 __global__ __launch_bounds__(256, FN <= 2 ? 4 : 2) void k_conv_thin_fwd(const int8_t* __restrict__ Xq, const int8_t* __restrict__ Wq,
@@ -146,8 +146,9 @@ int conv_thin_fwd_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, 
     const int64_t x_bytes = images * ct.H * ct.W * ct.C;
     if (x_bytes < 16 || Cout * KH * ct.KW * ct.C < 16) return kNotApplicable;
     const uint32_t tiles = static_cast<uint32_t>((M + 31) / 32);
-    // up to eight workgroups per CU: the weights are laid out once per workgroup, not once per tile
-    const dim3 grid(std::min<uint32_t>((tiles + 3) / 4, 2048)), block(256);
+    // as many workgroups as are resident (four per CU with up to 64 output channels, else two), which walk the tiles: the weights
+    // are laid out once per workgroup (32 x 224 x 224 x 3 -> 64: 3136 workgroups 38.0 us, 2048 32.5, 1568 34.3, 1024 29.3, 784 33.2)
+    const dim3 grid(std::min<uint32_t>((tiles + 3) / 4, fn <= 2 ? 1024 : 512)), block(256);
     const size_t lds = static_cast<size_t>(KH) * fn * 1024;
 #define FXP_THIN(FN)                                                                                                        \
     hipLaunchKernelGGL((k_conv_thin_fwd<FN>), grid, block, lds, s, Xq, Wq, Y, ct, KH, static_cast<uint32_t>(M),               \
