@@ -11,14 +11,15 @@
 // One kernel per line: 8 B read + 4 B written per element, two Philox blocks per four elements.  The
 // scales of x and y arrive as block maxima (the kernel finishes the reduction, like the map kernel does), and
 // the kernel leaves the block maxima of z behind, so a chain of lines needs no scale pass for intermediates.
-// Bound by VALU issue, just above what the memory takes: per wave and quad 36 64-bit multiply-adds of 16 cycles for
-// the random words and about 160 instructions of 4 cycles.  A line over 11.7 M parameters: 29.4 us with the elements
-// handled as signed integers that are tested against their scale, 26.1 on magnitudes (5.4 TB/s).
+// Bound by memory, 140 MB a line at 5.3 TB/s for 11.7 M parameters; issue comes next: per wave and quad 36 64-bit multiply-adds
+// for the random words (full rate: a wave issues one in 4.5 cycles, measured) and about 200 other instructions, 17 us.  29.4 us
+// with the elements handled as signed integers that are tested against their scale, 26.1 on magnitudes.
 #include "fxp_internal.h"
 
 namespace fxp {
 
 constexpr int kAxpyThreads = 256;
+typedef float Float4 __attribute__((ext_vector_type(4)));
 template <bool V>
 struct IC {
     static constexpr bool value = V;
@@ -237,7 +238,9 @@ __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t
                         for (int k = 0; k < 4; ++k) zf[k] = axpy_one<STOCH>(xb[k], yb[k], wxy[k], wu[k], ex, ey, a_hat, al, Ex);
                     }
                 }
-                zv[q] = make_float4(zf[0], zf[1], zf[2], zf[3]);
+                // (the last line's result is not read again in the step: as an ordinary store it took 0.5 us of 27 from the others)
+                if (pz == nullptr) __builtin_nontemporal_store(Float4{zf[0], zf[1], zf[2], zf[3]}, reinterpret_cast<Float4*>(zv + q));
+                else zv[q] = make_float4(zf[0], zf[1], zf[2], zf[3]);
                 // (never NaN: the inverse mapping of integers)
                 fmax = fmaxf(fmaxf(fmax, fmaxf(fabsf(zf[0]), fabsf(zf[1]))), fmaxf(fabsf(zf[2]), fabsf(zf[3])));
                 xc = xn;
