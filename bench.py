@@ -181,8 +181,8 @@ def step_only_line(args, torch, dev, metric, unit, value, ms, dtype, workload):
 
 
 def bench_conv(args, torch, fxp, synth, dev):
-    """The c2 layer given as a convolution (channels-last): map the activation once, int8 im2col, GEMMs,
-    gather col2im.  Same integer work as c2 (3 x 2*M*K*Cout), far fewer fp32 bytes."""
+    """The c2 layer given as a convolution (channels-last): map the activation once, three products that read their patches
+    from the int8 images.  Same integer work as c2 (3 x 2*M*K*Cout), far fewer fp32 bytes."""
     X, Wt, dY, g = synth.conv_tensors()
     buf = fxp.ConvBuffers(g["N"], g["H"], g["W"], g["C"], g["Cout"], g["KH"], g["KW"], g["stride"], g["pad"], device=dev)
     Xd, Wd, dYd = (torch.from_numpy(a).to(dev) for a in (X, Wt, dY))
@@ -206,10 +206,10 @@ def bench_conv(args, torch, fxp, synth, dev):
                               "int8", "c2conv")
     nx, nw, ny = X.size, Wt.size, dY.size
     # algorithmic HBM bytes of every kernel of the step: scale + map of X (one
-    # copy), W and dY (both copies); forward GEMM reading the image and the weights; transposed patches of X and the
-    # weight flip; weight-gradient GEMM; input-gradient GEMM reading the gradient image and the flipped weights
+    # copy), W and dY (both copies); forward GEMM reading the image and the weights; the weight flip; weight-gradient GEMM
+    # reading the image and its gradient; input-gradient GEMM reading the gradient image and the flipped weights
     step_bytes = (4 * nx + 5 * nx) + (4 * nw + 6 * nw) + (nx + nw + 4 * ny) \
-        + (4 * ny + 6 * ny) + (nx + M * K) + 2 * nw + (M * K + ny + 4 * nw) + (ny + nw + 4 * nx)
+        + (4 * ny + 6 * ny) + 2 * nw + (nx + ny + 4 * nw) + (ny + nw + 4 * nx)
     gbs = step_bytes / (ms * 1e-3) / 1e9
     cpu = None
     if not args.no_cpu_baseline:
@@ -232,8 +232,7 @@ def bench_conv(args, torch, fxp, synth, dev):
         "scaling": "weak", "vs_baseline": None, "dtype": "int8", "data": "synthetic",
         "config": {"workload": "c2conv: the c2 ResNet-18 3x3 convolution as a channels-last convolution layer "
                                f"N={g['N']} H=W={g['H']} C={g['C']} Cout={g['Cout']} (M={M} K={K})",
-                   "pass": "scale+map X, W, dY; forward and input-gradient GEMMs read their patches from the int8 images; "
-                           "transposed int8 patches + GEMM for the weight gradient",
+                   "pass": "scale+map X, W, dY; all three GEMMs read their patches from the int8 images",
                    "rounding": "stochastic (Philox-4x32-10)", "bits": args.bits},
         "roofline": dict(bound="hbm", achieved=round(gbs, 1), peak=PEAK_HBM_GBS, unit="GB/s",
                          frac=round(gbs / PEAK_HBM_GBS, 4), kernel="whole step (7 launches, all HBM- or launch-bound)",
