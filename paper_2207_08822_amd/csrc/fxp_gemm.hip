@@ -1275,8 +1275,8 @@ static int launch_direct(const Product& p0, const Product& p1, bool fp32_out, hi
 }
 
 // Two independent products with fp32 outputs (the gradients of one layer, or of `batch` matrices each) in one launch, where
-// both take the same small-product kernel; kNotApplicable: one launch each.  Such launches wait for each other longer
-// than they run (a launch behind a launch takes 4.5 us), and neither fills the chip: the gradients of a 1379 x 768 x 1000
+// neither fills the chip; kNotApplicable: one launch each.  Such launches wait for each other longer
+// than they run (a launch behind a launch takes 4.5 us): the gradients of a 1379 x 768 x 1000
 // layer 13.7 + 8.7 -> 13.4 us, of 256 x 256 x 256 4.7 + 4.6 -> 4.9, the second pair of 96 x (197 x 64 x 197) 6.5 + 6.9 -> 7.9.
 int gemm_nt_pair_launch(const GemmArgs& a, const GemmArgs& b, int64_t batch, hipStream_t s) {
     auto product = [](const GemmArgs& g, int tile) {
@@ -1286,13 +1286,22 @@ int gemm_nt_pair_launch(const GemmArgs& a, const GemmArgs& b, int64_t batch, hip
     };
     if (batch == 1 && direct_fits(a.M, a.N, a.K) && direct_fits(b.M, b.N, b.K))
         return launch_direct(product(a, 32), product(b, 32), true, s);
+    // Where one of them lies off the 16-byte grid the staged kernel is its own; products that the direct-to-LDS kernels would take
+    // gain by the common launch while their large tiles, of which each CU would have one or none, are fewer than two per CU together
+    // (layer steps, two launches / one: 1024^3 40.0 / 31.8, 1376 x 768 x 1000 47.9 / 36.7, 2032 x 768 x 768 51.4 / 37.7, 640 x 1024 x
+    // 640 36.9 / 30.1, 1600^3 - 338 large tiles - 57.4 / 55.3, 2001 x 1600 x 1600 - 377 - 71.1 / 66.9, 2001 x 2032 x 3072 - 640 - 123.2 /
+    // 124.1).  Not in batches, which fill the chip (60 x 250 x 250 81.2 / 82.8).
+    bool aligned_one = false;
     auto staged = [&](const GemmArgs& g) {
         const bool vec = aligned(g.A, 16) && aligned(g.B, 16) && g.lda % 16 == 0 && g.ldb % 16 == 0 && g.K % 16 == 0 &&
                          (batch == 1 || (g.strideA % 16 == 0 && g.strideB % 16 == 0));
-        return !(vec && g.K >= 64) && g.K >= 16 && g.K <= kMaxContraction && small_tiles(g.M, g.N, batch) &&
+        if (vec && g.K >= 64) aligned_one = true;
+        return g.K >= 16 && g.K <= kMaxContraction && small_tiles(g.M, g.N, batch) &&
                (batch > 1 || (plan_gemm(g.M, g.N, g.K).splits == 1 && !direct_fits(g.M, g.N, g.K)));
     };
     if (!staged(a) || !staged(b)) return kNotApplicable;
+    auto large_tiles = [](const GemmArgs& g) { return ((g.M + 127) / 128) * ((g.N + 127) / 128); };
+    if (aligned_one && (batch > 1 || large_tiles(a) + large_tiles(b) >= 512)) return kNotApplicable;
     const Product two = product(b, 64);
     Batch bt;
     bt.count = static_cast<unsigned>(batch);
