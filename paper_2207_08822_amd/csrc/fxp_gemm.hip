@@ -1275,9 +1275,8 @@ static int launch_direct(const Product& p0, const Product& p1, bool fp32_out, hi
 }
 
 // Two independent products with fp32 outputs (the gradients of one layer, or of `batch` matrices each) in one launch, where
-// neither fills the chip; kNotApplicable: one launch each.  Such launches wait for each other longer
-// than they run (a launch behind a launch takes 4.5 us): the gradients of a 1379 x 768 x 1000
-// layer 13.7 + 8.7 -> 13.4 us, of 256 x 256 x 256 4.7 + 4.6 -> 4.9, the second pair of 96 x (197 x 64 x 197) 6.5 + 6.9 -> 7.9.
+// neither fills the chip; kNotApplicable: one launch each.  Such launches wait for each other longer than they run (a launch
+// behind a launch takes 4.5 us): the gradients of a 1379 x 768 x 1000 layer 13.7 + 8.7 -> 13.4 us, of 256 x 256 x 256 4.7 + 4.6 -> 4.9, the second pair of 96 x (197 x 64 x 197) 6.5 + 6.9 -> 7.9.
 int gemm_nt_pair_launch(const GemmArgs& a, const GemmArgs& b, int64_t batch, hipStream_t s) {
     auto product = [](const GemmArgs& g, int tile) {
         Product p = make_product(g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.eA, g.bitsA, g.eB, g.bitsB, nullptr, tile);
@@ -1431,6 +1430,13 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         rc = launch_dma<128, 256, 64, 64, 64, 3>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
     else if (use256)
         rc = launch_dma<256, 256, 64, 64, 128, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
+    // At most 128 large tiles, unsplit: half the CUs or more would have none.  A quarter the size, as for convolutions (the product
+    // alone, 128 x 128 / 64 x 64 tiles: 1024^3 7.9 / 6.0 us, 512 x 768 x 3072 - 96 tiles - 7.6 / 6.6, 300 x 2000 x 1000 15.2 / 8.1; the call
+    // 2000 x 1920 x 960 - 128 tiles - 25.9 / 24.9)
+    else if (splits == 1 && ((M + 127) / 128) * ((N + 127) / 128) <= 128 && K % 128 == 0)
+        rc = launch_dma<64, 64, 128, 32, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, 1, eA, bitsA, eB, bitsB, s, 0, nullptr, one, amax1, ride);
+    else if (splits == 1 && ((M + 127) / 128) * ((N + 127) / 128) <= 128)
+        rc = launch_dma<64, 64, 64, 32, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, 1, eA, bitsA, eB, bitsB, s, 0, nullptr, one, amax1, ride);
     else if (K % 128 == 0)
         rc = launch_dma<128, 128, 128, 64, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
     else
