@@ -56,10 +56,10 @@ inline bool tiles_for_both(const MapPlan& a, int64_t cols_a, const MapPlan& b, i
 
 // ---- tiles of quads (fxp_map_rows.hip) ----
 constexpr uint32_t kRowsWidth = 128;                  // most columns of a window
-constexpr uint32_t kScanWidth = 32;                   // ... where every workgroup reads the whole tensor: small tiles, many of them
-// Of a tensor whose scale every workgroup works out for itself: 64 bytes a clock from L2, so beyond some 100000 elements reading
-// it takes longer than a reduction launch (steps of n^3, two launches / scan in us: 256 30 / 21.0, 300 26.8 / 22.2, 330 28.0 / 25.5,
-// 362 29.8 / 31.0, 400 26.4 / 30.8).
+// A tensor whose scale every workgroup works out for itself, 64 bytes a clock from L2: small tiles, many of them, but no more
+// workgroups than CUs if it can be, since each CU reads the tensor once per workgroup.  Beyond some 100000 elements a CU that takes
+// longer than a reduction launch (steps of n^3, two launches / scan in us: 256 30 / 21.0, 300 26.8 / 22.2, 330 28.0 / 25.5, 362
+// 29.8 / 31.0, 400 26.4 / 30.8).
 constexpr int64_t kScanMaxElements = 112 * 1024;
 
 struct RowsPlan {
@@ -103,8 +103,18 @@ inline RowsPlan plan_rows(int64_t rows, int64_t cols) {
     return best;
 }
 
-inline bool scale_by_scan(int64_t rows, int64_t cols) {
-    return rows > 0 && cols >= 16 && rows <= kScanMaxElements / cols;
+// Tiles of about 1024 elements, so that a tensor of the limit is 112 of them: 32 rows, and columns to match where there are fewer
+// (scale + map in us, two launches / scan with 32 columns / so: 8 x 12288 6.6 / 9.3 / 6.2, 4 x 16384 6.4 / 7.5 / 5.1, 1 x 32768
+// 6.3 / 8.8 / 4.3).
+inline RowsPlan plan_scan(int64_t rows, int64_t cols) {
+    const int64_t width = rows > 16 ? 32 : rows > 8 ? 64 : kRowsWidth;
+    return plan_rows(rows, cols, 32, (cols + width - 1) / width);
 }
+
+// Whether `blocks` workgroups together, each for the scale of a tensor of at most `elements`, read little enough: what a CU reads is
+// what bounds them (scan of 1 x 114688 by 3584 workgroups 55.8 us, two launches 8.4; 2 x 50257, 1571 workgroups, 29.5 / 9.6; 8 x 12288,
+// 384 workgroups, 9.3 / 6.6).
+inline bool scan_pays(int64_t elements, int64_t blocks) { return (blocks + 255) / 256 * elements <= kScanMaxElements; }
+inline bool scan_takes(int64_t rows, int64_t cols) { return rows > 0 && cols >= 16 && rows <= kScanMaxElements / cols; }
 
 }  // namespace fxp

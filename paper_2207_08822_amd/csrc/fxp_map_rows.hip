@@ -192,7 +192,7 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
 // 18912 x 197 8.4 -> 8.2; 8191 x 8191, bound by memory, 97 -> 100).
 template <bool STOCH, int TR, bool SCAN, bool FLAT>
 __global__ __launch_bounds__(SCAN ? kScanThreads : kMapThreads, SCAN ? 1 : FLAT ? 4 : 5) void k_map_rows(const RowsJobs jobs, uint32_t key0, uint32_t key1, int bits) {
-    __shared__ __align__(16) uint8_t stage[((SCAN ? kScanWidth : kRowsWidth) + 6) * (TR + 4)];
+    __shared__ __align__(16) uint8_t stage[(kRowsWidth + 6) * (TR + 4)];
     __shared__ uint32_t red[kScanThreads / 64];
     const bool second = blockIdx.x >= jobs.j[0].blocks;            // workgroup-uniform
     const RowsJob& J = jobs.j[second ? 1 : 0];
@@ -271,11 +271,15 @@ int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int r
 int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s) {
     const MapTensor* ts[2] = {&a, b};
     RowsJobs jobs{};
+    int64_t elements = 0, blocks = 0;
     for (int j = 0; j < (b ? 2 : 1); ++j) {
         const MapTensor& t = *ts[j];
-        if (!scale_by_scan(t.rows, t.cols)) return kNotApplicable;
-        jobs.j[j] = make_rows_job(t, plan_rows(t.rows, t.cols, 32, (t.cols + kScanWidth - 1) / kScanWidth), false);
+        if (!scan_takes(t.rows, t.cols)) return kNotApplicable;
+        jobs.j[j] = make_rows_job(t, plan_scan(t.rows, t.cols), false);
+        elements = std::max(elements, t.rows * t.cols);
+        blocks += jobs.j[j].blocks;
     }
+    if (!scan_pays(elements, blocks)) return kNotApplicable;
     return launch_rows(jobs, 32, true, seed, rounding, bits, s);
 }
 

@@ -28,7 +28,7 @@ def test_every_element_has_one_lane(plan, rows):
     cases = [(rows, c, tr) for c in list(range(4, 300)) + [1000, 1001, 3071, 3072, (1 << 22) - 4, (1 << 22) - 1] for tr in (0, -1, 64, 128)]
     for (_, cols, tr), p in zip(cases, plan(cases)):
         where = (rows, cols, tr, p)
-        assert p["exact"] and p["width"] <= (32 if tr < 0 else 128) and p["tr"] in (32, 64, 128), where
+        assert p["exact"] and p["width"] <= (32 if tr < 0 and rows > 16 else 128) and p["tr"] in (32, 64, 128), where
         assert (p["windows"] - 1) * p["width"] < cols <= p["windows"] * p["width"], where
         assert p["blocks"] == -(-rows // p["tr"]) * p["windows"], where
         # the most quads that `width` columns meet: from any element where rows shift, from a quad's first where they do not
@@ -40,4 +40,17 @@ def test_every_element_has_one_lane(plan, rows):
 
 def test_small_tensors(plan):
     got = plan([(256, 256, -1), (1, 114688, -1), (7168, 16, -1), (7645, 15, -1), (449, 256, -1), (448, 256, -1), (1, 114689, -1), (0, 16, -1)])
-    assert [p["scan"] for p in got] == [1, 1, 1, 0, 0, 1, 0, 0]
+    assert [p["scan"] for p in got] == [1, 0, 1, 0, 0, 1, 0, 0]
+
+
+def test_scan_of_few_rows(plan):
+    """What a CU reads of a tensor whose scale every workgroup finds for itself stays within what one workgroup reads of the largest,
+    whatever the shape: few rows are many windows."""
+    sizes = [1000, 16384, 32768, 50257, 65536, 98304, 100352, 114688]
+    cases = [(r, n // r, -1) for n in sizes for r in (1, 2, 3, 4, 8, 9, 16, 17, 24, 31, 32, 33, 64, 256) if n // r >= 16]
+    for (rows, cols, _), p in zip(cases, plan(cases)):
+        reads = -(-p["blocks"] // 256) * rows * cols
+        assert p["scan"] == (reads <= 112 * 1024), (rows, cols, p)
+        assert rows < 8 or p["blocks"] <= 256, (rows, cols, p)          # eight rows and more: never more workgroups than CUs
+    shapes = [(1, 114688, -1), (2, 50257, -1), (1, 65536, -1), (4, 25088, -1), (8, 10000, -1), (1, 32768, -1)]
+    assert [p["scan"] for p in plan(shapes)] == [0, 0, 0, 1, 1, 1]
