@@ -57,9 +57,9 @@ inline bool tiles_for_both(const MapPlan& a, int64_t cols_a, const MapPlan& b, i
 // ---- tiles of quads (fxp_map_rows.hip) ----
 constexpr uint32_t kRowsWidth = 128;                  // most columns of a window
 // A tensor whose scale every workgroup works out for itself, 64 bytes a clock from L2: small tiles, many of them, but no more
-// workgroups than CUs if it can be, since each CU reads the tensor once per workgroup.  Beyond some 100000 elements a CU that takes
-// longer than a reduction launch (steps of n^3, two launches / scan in us: 256 30 / 21.0, 300 26.8 / 22.2, 330 28.0 / 25.5, 362
-// 29.8 / 31.0, 400 26.4 / 30.8).
+// workgroups than CUs if it can be, since each CU reads the tensor once per workgroup.  Beyond some 100000 elements that takes longer
+// than a reduction launch (steps of n^3 launched one by one, two launches / scan in us: 256 30 / 21.0, 300 26.8 / 22.2, 330 28.0 / 25.5,
+// 362 29.8 / 31.0, 400 26.4 / 30.8; replayed from a graph: 300 22.0 / 20.7, 320 20.6 / 21.0, 336 20.6 / 21.4).
 constexpr int64_t kScanMaxElements = 112 * 1024;
 
 struct RowsPlan {

@@ -43,8 +43,10 @@ __device__ inline unsigned tile_in_xcd_run(unsigned bid, unsigned blocks) {
     return xcd < more ? xcd * (per + 1) + at : more * (per + 1) + (xcd - more) * per + at;
 }
 
-// Largest magnitude bits of a whole tensor, by every workgroup for itself: sixteen 16-byte loads in flight a thread (eight where
-// they reach all of it), each workgroup from a chunk of its own on so that not all of them miss the same lines at once.
+// Largest magnitude bits of a whole tensor, by every workgroup for itself, bound by what a CU reads from L2: in chunks of sixteen
+// 16-byte loads a thread, each workgroup from a chunk of its own on so that not all of them miss the same lines at once, and eight
+// for a rest of half a chunk or less (256 x 448 6.8 -> 6.4 us).  The compiler keeps nine to ten in flight; all sixteen, held together
+// by a scheduling barrier, are slower (256 x 256 4.9 -> 5.1, 256 x 384 5.8 -> 6.2).
 constexpr int kScanThreads = 512;
 __device__ inline uint32_t scan_absmax(const uint32_t* __restrict__ x, uint32_t n, unsigned bid) {
     const uint32_t kAbs = 0x7fffffffu;
@@ -62,16 +64,15 @@ __device__ inline uint32_t scan_absmax(const uint32_t* __restrict__ x, uint32_t 
 #pragma unroll
         for (uint32_t k = 0; k < kLoads; ++k) m = max(m, absmax4(v[k]));
     };
-    if (nvec != 0 && nvec <= 8 * kScanThreads) {
-        chunk(0u, std::integral_constant<uint32_t, 8>{});
-    } else if (nvec != 0) {
-        const uint32_t chunks = (nvec + 16 * kScanThreads - 1) / (16 * kScanThreads);
-        uint32_t at = bid % chunks;
-        for (uint32_t c = 0; c < chunks; ++c) {
-            chunk(at * 16 * kScanThreads, std::integral_constant<uint32_t, 16>{});
-            if (++at == chunks) at = 0;
-        }
+    constexpr uint32_t kChunk = 16 * kScanThreads;
+    if (nvec == 0) return m;
+    const uint32_t chunks = (nvec + kChunk / 2 - 1) / kChunk;                    // and half of one, or less
+    uint32_t at = chunks ? bid % chunks : 0;
+    for (uint32_t c = 0; c < chunks; ++c) {
+        chunk(at * kChunk, std::integral_constant<uint32_t, 16>{});
+        if (++at == chunks) at = 0;
     }
+    if (nvec > chunks * kChunk) chunk(chunks * kChunk, std::integral_constant<uint32_t, 8>{});
     return m;
 }
 

@@ -56,8 +56,9 @@ def test_map_tiles_of_quads(fxp, rows, cols, offset, rounding):
         assert (a[:at] == 77).all() and (a[at + n:] == 77).all()
 
 
-# 114688 elements and one more, one round of eight loads (16384) and beyond, the narrowest rows and narrower ones, one row
-@pytest.mark.parametrize("rows,cols", [(256, 256), (7168, 16), (1, 114688), (1, 16), (2, 15), (255, 257), (448, 257), (1, 114689), (1, 1154), (128, 128), (129, 127),
+# 114688 elements and one more, one round of eight loads (16384) and beyond, sixteen and eight (49152) and beyond, the narrowest rows
+# and narrower ones, one row
+@pytest.mark.parametrize("rows,cols", [(256, 256), (7168, 16), (1, 114688), (1, 16), (2, 15), (255, 257), (448, 257), (1, 114689), (1, 1154), (128, 128), (129, 127), (192, 256), (4, 12289), (9, 12288),
                                        (200, 100), (33, 31)])
 @pytest.mark.parametrize("kind", ["plain", "special", "zero"])
 def test_scale_and_map_of_small_tensors(fxp, rows, cols, kind):
