@@ -54,6 +54,7 @@ struct MapTensor {
 int map_launch(const MapTensor& t, uint64_t seed, int rounding, int bits, hipStream_t s);
 int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s);
 // scale + map of small tensors in one launch (fxp_map_rows.hip); b may be null, partials are not used
+bool scale_map_small_fits(const MapTensor& a, const MapTensor* b);
 int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s);
 // scale + map in one pass with the previous scale as a guess (fxp_map.hip)
 constexpr unsigned kGuessBlocks = 4080;            // workgroups of a guessing launch: their exponents and the guess fit one scratch area
@@ -269,12 +270,10 @@ __device__ inline uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uin
 // scale + map of one tensor: block maxima, then the map kernel finishes the reduction and publishes *e
 inline int scale_and_map(const float* x, int64_t rows, int64_t cols, int32_t* e, int8_t* q, int8_t* qT, uint64_t seed,
                          uint64_t sid, int rounding, int bits, uint32_t* partials, hipStream_t s) {
-    int np = 0;
-    int rc = scale_map_small_launch(MapTensor{x, rows, cols, nullptr, nullptr, 0, e, q, qT, sid}, nullptr, seed, rounding, bits, s);
-    if (rc != kNotApplicable) return rc;
-    rc = scale_partials(x, static_cast<size_t>(rows * cols), partials, &np, s);
+    MapTensor t{x, rows, cols, nullptr, partials, 0, e, q, qT, sid};
+    if (scale_map_small_fits(t, nullptr)) return scale_map_small_launch(t, nullptr, seed, rounding, bits, s);
+    const int rc = scale_partials(x, static_cast<size_t>(rows * cols), partials, &t.n_partials, s);
     if (rc) return rc;
-    const MapTensor t{x, rows, cols, nullptr, partials, np, e, q, qT, sid};
     return map_launch(t, seed, rounding, bits, s);
 }
 
@@ -282,9 +281,8 @@ inline int scale_and_map(const float* x, int64_t rows, int64_t cols, int32_t* e,
 // reduction launch and one map launch cover both.  t.partials must point at kMaxPartials words each; e_in and
 // n_partials of the arguments are ignored.
 inline int scale_and_map2(MapTensor a, MapTensor b, uint64_t seed, int rounding, int bits, hipStream_t s) {
-    int rc = scale_map_small_launch(a, &b, seed, rounding, bits, s);
-    if (rc != kNotApplicable) return rc;
-    rc = scale_partials2(a.x, static_cast<size_t>(a.rows * a.cols), const_cast<uint32_t*>(a.partials), &a.n_partials, b.x,
+    if (scale_map_small_fits(a, &b)) return scale_map_small_launch(a, &b, seed, rounding, bits, s);
+    const int rc = scale_partials2(a.x, static_cast<size_t>(a.rows * a.cols), const_cast<uint32_t*>(a.partials), &a.n_partials, b.x,
                              static_cast<size_t>(b.rows * b.cols), const_cast<uint32_t*>(b.partials), &b.n_partials, s);
     if (rc) return rc;
     a.e_in = b.e_in = nullptr;

@@ -129,12 +129,10 @@ static int linear_fwd_run(const float* X, const float* W, int64_t M, int64_t K, 
     // with the scales of the last step as guesses: one pass that maps and finds the maxima, one launch that verifies
     int rc = guess ? scale_map_guess_launch(tX, &tW, pX, pW, seed, rounding, bits, s) : kNoGuessPath;
     if (rc == kGuessOneByOne) rc = scale_map_operands(tX, tW, pX, pW, seed, rounding, bits, s, true);
-    if (rc == kNoGuessPath) {
-        // small operands: scale and map in one launch, whose time is the map's
+    if (rc == kNoGuessPath && scale_map_small_fits(tX, &tW)) {
+        timeline_mark(s, FXP_TL_SCALE);                  // small operands: scale and map in one launch, whose time is the map's
         rc = scale_map_small_launch(tX, &tW, seed, rounding, bits, s);
-        if (rc == FXP_OK) timeline_mark(s, FXP_TL_SCALE);
-    }
-    if (rc == kNotApplicable) {
+    } else if (rc == kNoGuessPath) {
         // scale + map of both operands in two launches: one reduction launch and one map launch cover both tensors
         rc = scale_partials2(X, static_cast<size_t>(M * K), pX, &tX.n_partials, W, static_cast<size_t>(K * N), pW, &tW.n_partials, s);
         if (rc) return rc;
@@ -225,11 +223,10 @@ static int linear_bwd_impl(const float* dY, const fxp_saved* saved, int64_t M, i
     {
         MapTensor t{dY, M, N, nullptr, static_cast<uint32_t*>(ws), 0, e_dY, dYq, dYqT, (step << 8) | FXP_TAG_DY};
         rc = guess ? scale_map_guess_launch(t, nullptr, static_cast<uint32_t*>(ws), nullptr, seed, rounding, bits, s) : kNoGuessPath;
-        if (rc == kNoGuessPath) {
+        if (rc == kNoGuessPath && scale_map_small_fits(t, nullptr)) {
+            timeline_mark(s, FXP_TL_SCALE);
             rc = scale_map_small_launch(t, nullptr, seed, rounding, bits, s);
-            if (rc == FXP_OK) timeline_mark(s, FXP_TL_SCALE);
-        }
-        if (rc == kNotApplicable) {
+        } else if (rc == kNoGuessPath) {
             if ((rc = scale_partials(dY, static_cast<size_t>(M * N), static_cast<uint32_t*>(ws), &t.n_partials, s))) return rc;
             timeline_mark(s, FXP_TL_SCALE);
             rc = map_launch(t, seed, rounding, bits, s);

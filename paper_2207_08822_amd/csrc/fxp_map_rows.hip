@@ -268,19 +268,17 @@ int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int r
     return launch_rows(jobs, tr, false, seed, rounding, bits, s);
 }
 
-// Scale and map of one tensor or two (b may be null) in one launch; kNotApplicable: not small enough.
+// Scale and map of one tensor or two (b may be null) in one launch: whether they are small enough, and the launch.
+bool scale_map_small_fits(const MapTensor& a, const MapTensor* b) {
+    if (!scan_takes(a.rows, a.cols) || (b && !scan_takes(b->rows, b->cols))) return false;
+    const int64_t elements = std::max(a.rows * a.cols, b ? b->rows * b->cols : 0);
+    return scan_pays(elements, plan_scan(a.rows, a.cols).blocks + (b ? plan_scan(b->rows, b->cols).blocks : 0));
+}
+
 int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s) {
-    const MapTensor* ts[2] = {&a, b};
     RowsJobs jobs{};
-    int64_t elements = 0, blocks = 0;
-    for (int j = 0; j < (b ? 2 : 1); ++j) {
-        const MapTensor& t = *ts[j];
-        if (!scan_takes(t.rows, t.cols)) return kNotApplicable;
-        jobs.j[j] = make_rows_job(t, plan_scan(t.rows, t.cols), false);
-        elements = std::max(elements, t.rows * t.cols);
-        blocks += jobs.j[j].blocks;
-    }
-    if (!scan_pays(elements, blocks)) return kNotApplicable;
+    jobs.j[0] = make_rows_job(a, plan_scan(a.rows, a.cols), false);
+    if (b) jobs.j[1] = make_rows_job(*b, plan_scan(b->rows, b->cols), false);
     return launch_rows(jobs, 32, true, seed, rounding, bits, s);
 }
 

@@ -42,6 +42,18 @@ def test_rows_follow_the_intervals(paired):
     assert sum(g["ops"] for g in gemms) == total["ops"] and sum(g["bytes"] for g in gemms) == total["bytes"]
 
 
+@pytest.mark.parametrize("sizes,joint", [([(256, 256, 256)], True), ([(256, 256, 256), (25088, 1152, 128)], False)])
+def test_small_layers_have_no_scale_row(sizes, joint):
+    layers = [types.SimpleNamespace(M=M, K=K, N=N) for M, K, N in sizes]
+    rows = {r: dict(kernel=r, t=t, tmin=t, launches=2, bytes=b, ops=0.0) for r, t, b in (("map", 6e-6, 600.0), ("scale", 2e-6, 400.0))}
+    in_step = {(li, r): us for li in range(len(layers)) for r, us in (("map", 50.0), ("scale", 10.0))}
+    bench.join_small_scales(rows, layers, in_step)
+    bench.set_in_step_times(rows, [], in_step, 10)
+    assert set(rows) == ({"map"} if joint else {"map", "scale"})
+    assert rows["map"]["t"] == pytest.approx(5e-6 * len(layers)) and (joint or rows["scale"]["t"] == pytest.approx(1e-6 * len(layers)))
+    assert sum(r["t_loop"] for r in rows.values()) == pytest.approx(8e-6) and rows["map"]["bytes"] == 600.0
+
+
 def test_tags_of_the_header():
     import os
     import re

@@ -598,6 +598,25 @@ def test_timeline_tags_both_gradients_of_one_launch(fxp, M, K, N, grads):
     assert all(us[i] > 0.0 for i in range(n.value))
 
 
+def test_timeline_gives_a_small_layers_launch_to_the_map(fxp):
+    """Scale and map of small tensors are one launch, and its time is the map's: the scale's interval is the gap before it."""
+    import ctypes
+    say("timeline of scale and map in one launch")
+    L = fxp.lib()
+    X, W, dY = (torch.randn(256, 256, device="cuda") for _ in range(3))
+    buf = fxp.LayerBuffers(256, 256, 256)
+    us, tags, n = (ctypes.c_float * 256)(), (ctypes.c_int * 256)(), ctypes.c_int(0)
+    for warm in (True, False):
+        assert L.fxp_timeline_begin(256) == 0
+        for _ in range(20):
+            fxp.linear_fwd(X, W, buf, 5, 2)
+            fxp.linear_bwd(dY, buf, 5, 2)
+        assert L.fxp_timeline_end(us, tags, 256, ctypes.byref(n)) == 0
+    scale, mapped = (sorted(us[i] for i in range(n.value) if tags[i] == t) for t in (1, 2))
+    assert len(scale) == len(mapped) == 40
+    assert scale[20] < mapped[20], (scale, mapped)
+
+
 def test_timeline_and_clock_probe_measure_without_changing_results(fxp):
     """The measurement helpers: the events recorded inside the layer calls come back as one interval per launch,
     in launch order, and the outputs are the ones an undisturbed call gives; the clock probe reports a plausible
