@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "fxp_gemm_device.h"
+#include "fxp_gemm_plan.h"
 #include "fxp_internal.h"
 
 namespace fxp {
@@ -1163,13 +1164,8 @@ static unsigned reduce_blocks(const ReduceRider& r, int lanes) {
     return static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (pieces * lanes + 255) / 256)));
 }
 
-// One lane a piece while the pieces alone fill the chip or the slices are few; else up to 32 lanes, each with eight slices - one
-// round of loads - or more (a 64 x 147 output of 126 slices: ten workgroups walked all slices in turn, 123 us; 256 slices with
-// sixteen lanes 8.7 us, with 32 lanes 6.3).
 int splitk_reduce_launch(ReduceRider r, hipStream_t s) {
-    const int64_t pieces = static_cast<int64_t>(r.M) * r.N / 4;
-    r.group = 1;
-    while (r.group < 32 && r.splits >= 8 * r.group && pieces * r.group < 131072) r.group *= 2;
+    r.group = reduce_lanes(static_cast<int64_t>(r.M) * r.N / 4, r.splits);
     r.blocks = reduce_blocks(r, r.group);
     hipLaunchKernelGGL(k_splitk_reduce, dim3(r.blocks), dim3(256), 0, s, r);
     return launch_status();
