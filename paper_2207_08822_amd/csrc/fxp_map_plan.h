@@ -103,6 +103,10 @@ inline RowsPlan plan_rows(int64_t rows, int64_t cols) {
     return best;
 }
 
+// ... and what a flat run beside them has in place of rows, 32 a pass, is for as many workgroups as its own plan wants (the image
+// of 4 x 224 x 224 x 3 beside the weights of its layer, as 37 workgroups of 16384 elements 9.5 us, as 147 5.0).
+inline int rows_height(const MapPlan& p, int64_t rows, int64_t cols) { return p.flat ? 32 * p.passes : plan_rows(rows, cols).tr; }
+
 // Tiles of about 1024 elements, so that a tensor of the limit is 112 of them: 32 rows, and columns to match where there are fewer
 // (scale + map in us, two launches / scan with 32 columns / so: 8 x 12288 6.6 / 9.3 / 6.2, 4 x 16384 6.4 / 7.5 / 5.1, 1 x 32768
 // 6.3 / 8.8 / 4.3).

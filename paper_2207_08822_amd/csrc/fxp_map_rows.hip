@@ -250,15 +250,19 @@ static int launch_rows(const RowsJobs& jobs, int tr, bool scan, uint64_t seed, i
 
 // One tensor or two (b may be null), planned as tiles or flat by plan_map.
 int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s) {
-    const int64_t na = a.rows * a.cols, nb = b ? b->rows * b->cols : 0;
-    const int tr = na >= nb ? plan_rows(a.rows, a.cols).tr : plan_rows(b->rows, b->cols).tr;      // the larger tensor's
     const MapTensor* ts[2] = {&a, b};
+    MapPlan plans[2] = {};
+    for (int j = 0; j < (b ? 2 : 1); ++j) {
+        const MapTensor& t = *ts[j];
+        plans[j] = plan_map(t.rows, t.cols, aligned(t.x, 16) && aligned(t.q, 16) && aligned(t.qT, 16), t.qT != nullptr);
+    }
+    const int larger = b && b->rows * b->cols > a.rows * a.cols ? 1 : 0;
+    const int tr = rows_height(plans[larger], ts[larger]->rows, ts[larger]->cols);
     RowsJobs jobs{};
     uint64_t blocks = 0;
     for (int j = 0; j < (b ? 2 : 1); ++j) {
         const MapTensor& t = *ts[j];
-        const bool flat = plan_map(t.rows, t.cols, aligned(t.x, 16) && aligned(t.q, 16) && aligned(t.qT, 16), t.qT != nullptr).flat;
-        jobs.j[j] = make_rows_job(t, plan_rows(t.rows, t.cols, tr, (t.cols + kRowsWidth - 1) / kRowsWidth), flat);
+        jobs.j[j] = make_rows_job(t, plan_rows(t.rows, t.cols, tr, (t.cols + kRowsWidth - 1) / kRowsWidth), plans[j].flat);
         blocks += jobs.j[j].blocks;
     }
     if (b && blocks >= (uint64_t{1} << 31)) {

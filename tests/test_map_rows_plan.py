@@ -19,7 +19,7 @@ def plan(tmp_path_factory):
 
     def ask(cases):
         out = subprocess.run([exe], input="".join("%d %d %d\n" % c for c in cases), capture_output=True, text=True, check=True).stdout
-        return [dict(zip(("tr", "windows", "width", "quads", "blocks", "exact", "scan"), map(int, l.split()))) for l in out.splitlines()]
+        return [dict(zip(("tr", "windows", "width", "quads", "blocks", "exact", "scan", "flat"), map(int, l.split()))) for l in out.splitlines()]
     return ask
 
 
@@ -54,3 +54,15 @@ def test_scan_of_few_rows(plan):
         assert rows < 8 or p["blocks"] <= 256, (rows, cols, p)          # eight rows and more: never more workgroups than CUs
     shapes = [(1, 114688, -1), (2, 50257, -1), (1, 65536, -1), (4, 25088, -1), (8, 10000, -1), (1, 32768, -1)]
     assert [p["scan"] for p in plan(shapes)] == [0, 0, 0, 1, 1, 1]
+
+
+@pytest.mark.parametrize("cols", [1, 3, 17, 131])
+def test_flat_run_beside_tiles_fills_the_chip(plan, cols):
+    """A flat tensor's workgroups in a launch with tiles of quads: 4096 elements for every 32 rows of height, a thousand workgroups if
+    the tensor has them, and no smaller than that takes."""
+    rows = [10, 1000, 50176, 200704, 401408, 1605632, 10 ** 7]
+    for (r, _, _), p in zip([(r, cols, 0) for r in rows], plan([(r, cols, 0) for r in rows])):
+        n = r * cols
+        blocks = -(-n // (4096 * p["flat"] // 32))
+        assert p["flat"] in (32, 64, 128) and blocks >= min(1024, -(-n // 4096)), (r, cols, p, blocks)
+        assert p["flat"] == 128 or -(-n // (4096 * p["flat"] // 16)) < 1024, (r, cols, p, blocks)
