@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include "fxp_gemm_device.h"
+#include "fxp_gemm_plan.h"
 #include "fxp_internal.h"
 
 namespace fxp {
@@ -36,7 +37,7 @@ struct WgradArgs {
     int step_n, step_h, step_w;      // how far kStep pixels lead: images, rows, columns
 };
 
-constexpr int kStep = 128;    // pixels of a stage
+constexpr int kStep = kWgradStep;    // pixels of a stage
 
 // Half a wave of a transposing read meets eight rows of 32 bytes: pairs of 16-byte pieces are exchanged so that these fall into
 // all 64 banks once (single pieces exchanged as in the other product kernels: two-way conflicts, half of the LDS's time).
@@ -280,42 +281,11 @@ int conv_wgrad_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const
     r.fp32_out = 1;
     r.eA = eA; r.bitsA = bitsA; r.eB = eB; r.bitsB = bitsB;
     r.wide = M > kMaxContraction ? 1 : 0;
-    if (defer == nullptr) return splitk_reduce_launch(r, s);
+    // (a rider takes a lane a piece: more slices than that are summed by several, in a launch of their own)
+    if (defer == nullptr || p.slices > 64) return splitk_reduce_launch(r, s);
     r.blocks = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(2048, (Cout * K / 4 + 255) / 256)));
     *defer = r;
     return FXP_OK;
-}
-
-WgradCut plan_conv_wgrad(int64_t M, int64_t Cout, int64_t K) {
-    WgradCut p;
-    p.bm = Cout <= 64 ? 64 : 128;
-    p.tiles_m = static_cast<int>((Cout + p.bm - 1) / p.bm);
-    p.tiles_n = static_cast<int>((K + 127) / 128);
-    const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
-    // The number of slices whose rounds take least: eight waves and four stages, one workgroup per CU, 0.75 us a step (0.58 with 64
-    // channels), or four waves of 64 x 64 and two stages, two workgroups per CU, 1.25 us a step of both; 4.5 us around the steps; the
-    // slices written and read again at 4.5 TB/s, partly under the product that their sum rides with.
-    int64_t splits = 1;
-    double best = 0.0;
-    p.pairs = false;
-    for (int pairs = 0; pairs <= (p.bm == 128 ? 1 : 0); ++pairs)
-        for (int64_t n = 1; n == 1 || (n <= 64 && n <= M / 512); ++n) {
-            if (pairs && tiles * n <= 256) continue;
-            const int64_t slots = pairs ? 512 : 256, steps = (M + n * kStep - 1) / (n * kStep);
-            const double step_us = pairs ? 1.25 : p.bm == 128 ? 0.75 : 0.58;
-            const double us = static_cast<double>((tiles * n + slots - 1) / slots) * (step_us * static_cast<double>(steps) + 4.5) +
-                              (n > 1 ? 1.0 + 1.2 * 4.0 * static_cast<double>(n * Cout * K) / 4.5e6 : 0.0);
-            if (best == 0.0 || us < best) {
-                best = us;
-                splits = n;
-                p.pairs = pairs != 0;
-            }
-        }
-    if (M > kMaxContraction) splits = std::max<int64_t>(splits, (M + kMaxSlice - 1) / kMaxSlice);
-    p.per_slice = ((M + splits - 1) / splits + kStep - 1) / kStep * kStep;
-    p.slices = static_cast<int>((M + p.per_slice - 1) / p.per_slice);
-    p.ws_bytes = p.slices > 1 ? static_cast<size_t>(p.slices) * ((Cout * K + 3) / 4 * 4) * sizeof(int32_t) : 0;
-    return p;
 }
 
 // Channels in whole 16-byte pieces, 32-bit pixel numbers and offsets in a slice's images, room for the slices; not more tiles than

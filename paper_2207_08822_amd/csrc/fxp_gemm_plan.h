@@ -1,8 +1,16 @@
-// How sums of slices are cut up: host arithmetic only, so that it can be checked without a device.
+// How products are cut into slices and sums of slices among lanes: host arithmetic only, so that it can be checked without a device.
 #pragma once
+#include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 namespace fxp {
+
+constexpr int64_t kMaxContraction = 133144;   // 127^2 * K < 2^31: the longest contraction one int32 sum can hold
+// Longer contractions (a weight gradient over more rows than that) run as slices of at most kMaxSlice terms (a
+// multiple of every K step), each summed exactly in int32 into its workspace slice; the slices are added in 64
+// bits and the inverse mapping rounds that sum once.
+constexpr int64_t kMaxSlice = 133120;
 
 // Lanes of a wave that share a 16-byte piece of the output in a sum of slices that is a launch of its own.  One while the pieces alone
 // fill the chip or the slices are few; else up to 32, each with eight slices - one round of loads - or more (a 64 x 147 output of 126
@@ -13,6 +21,50 @@ inline int reduce_lanes(int64_t pieces, int64_t splits) {
     int lanes = 1;
     while (lanes < 32 && splits >= 16 * lanes && pieces * lanes < 65536) lanes *= 2;
     return lanes;
+}
+
+// ---- weight gradients of convolutions without stored patches (fxp_conv_wgrad.hip) ----
+constexpr int kWgradStep = 128;                       // pixels of a stage
+struct WgradCut {
+    int bm, tiles_m, tiles_n, slices;
+    bool pairs;              // two workgroups per CU
+    int64_t per_slice;
+    size_t ws_bytes;
+};
+
+inline WgradCut plan_conv_wgrad(int64_t M, int64_t Cout, int64_t K) {
+    WgradCut p;
+    p.bm = Cout <= 64 ? 64 : 128;
+    p.tiles_m = static_cast<int>((Cout + p.bm - 1) / p.bm);
+    p.tiles_n = static_cast<int>((K + 127) / 128);
+    const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
+    // The number of slices whose rounds take least: eight waves and four stages, one workgroup per CU, 0.75 us a step (0.58 with 64
+    // channels), or four waves of 64 x 64 and two stages, two workgroups per CU, 1.25 us a step of both; 4.5 us around the steps; the
+    // slices written and read again at 4.5 TB/s, partly under the product that their sum rides with.  More than 64 slices only where
+    // they are no more bytes than stored patches would be: few weights, many pixels, and with 64 workgroups at work one tile took
+    // longer than patches and their product (steps in us, stored / 64 slices at most / so: 256 x 56 x 56 x 16 -> 96 1x1 273 / 335 / 268,
+    // 16 -> 16 151 / 172 / 140, 64 x 56 x 56 x 64 -> 64 1x1 83 / 85 / 76).
+    int64_t splits = 1;
+    double best = 0.0;
+    p.pairs = false;
+    for (int pairs = 0; pairs <= (p.bm == 128 ? 1 : 0); ++pairs)
+        for (int64_t n = 1; n == 1 || (n <= M / 512 && (n <= 64 || (n <= 512 && 4 * n * Cout <= M))); n += n < 64 ? 1 : 32) {
+            if (pairs && tiles * n <= 256) continue;
+            const int64_t slots = pairs ? 512 : 256, steps = (M + n * kWgradStep - 1) / (n * kWgradStep);
+            const double step_us = pairs ? 1.25 : p.bm == 128 ? 0.75 : 0.58;
+            const double us = static_cast<double>((tiles * n + slots - 1) / slots) * (step_us * static_cast<double>(steps) + 4.5) +
+                              (n > 1 ? 1.0 + 1.2 * 4.0 * static_cast<double>(n * Cout * K) / 4.5e6 : 0.0);
+            if (best == 0.0 || us < best) {
+                best = us;
+                splits = n;
+                p.pairs = pairs != 0;
+            }
+        }
+    if (M > kMaxContraction) splits = std::max<int64_t>(splits, (M + kMaxSlice - 1) / kMaxSlice);
+    p.per_slice = ((M + splits - 1) / splits + kWgradStep - 1) / kWgradStep * kWgradStep;
+    p.slices = static_cast<int>((M + p.per_slice - 1) / p.per_slice);
+    p.ws_bytes = p.slices > 1 ? static_cast<size_t>(p.slices) * ((Cout * K + 3) / 4 * 4) * sizeof(int32_t) : 0;
+    return p;
 }
 
 }  // namespace fxp

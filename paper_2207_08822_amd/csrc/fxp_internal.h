@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "../../include/fxp.h"
+#include "fxp_gemm_plan.h"
 
 namespace fxp {
 
@@ -17,11 +18,6 @@ constexpr int kMaxPartials = 1024;        // capacity of a block-maxima scratch 
 constexpr int kScaleBlocks = 256;
 constexpr int kScaleThreads = 256;
 constexpr size_t kScaleWsBytes = kMaxPartials * sizeof(uint32_t);
-constexpr int64_t kMaxContraction = 133144;   // 127^2 * K < 2^31: the longest contraction one int32 sum can hold
-// Longer contractions (a weight gradient over more rows than that) run as slices of at most kMaxSlice terms (a
-// multiple of every K step), each summed exactly in int32 into its workspace slice; the slices are added in 64
-// bits and the inverse mapping rounds that sum once.
-constexpr int64_t kMaxSlice = 133120;
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? FXP_OK : FXP_ERR_LAUNCH; }
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
@@ -149,13 +145,6 @@ bool conv_thin_wgrad_fits(const ConvTaps& ct, int KH, int64_t images, int64_t Co
 int conv_thin_wgrad_launch(const ConvTaps& ct, int KH, int64_t images, int64_t M, int64_t Cout, const int8_t* Xq,
                            const int8_t* dYqT, void* parts, size_t part_bytes, ReduceRider* sum, hipStream_t s);
 // weight gradients without stored patches (fxp_conv_wgrad.hip); the sum of the slices is launched, or described in *defer
-struct WgradCut {
-    int bm, tiles_m, tiles_n, slices;
-    bool pairs;              // two workgroups per CU
-    int64_t per_slice;
-    size_t ws_bytes;
-};
-WgradCut plan_conv_wgrad(int64_t M, int64_t Cout, int64_t K);
 bool conv_wgrad_fits(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, size_t ws_bytes);
 int conv_wgrad_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const int8_t* Xq, const int8_t* dYq, float* dW,
                       const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, void* ws, hipStream_t s, ReduceRider* defer);

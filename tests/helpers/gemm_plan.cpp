@@ -1,4 +1,5 @@
-// gemm_plan: for "reduce pieces splits" lines on standard input the lanes that share a piece in a sum of slices.
+// gemm_plan: for "reduce pieces splits 0" lines on standard input the lanes that share a piece in a sum of slices, for "wgrad M Cout K"
+// lines the cut of a convolution's weight gradient: pairs, tile rows, tiles, slices, pixels of a slice, bytes of the slices.
 #include <cstdio>
 #include <cstring>
 
@@ -6,6 +7,14 @@
 
 int main() {
     char what[16];
-    long long a, b;
-    while (std::scanf("%15s %lld %lld", what, &a, &b) == 3) std::printf("%d\n", fxp::reduce_lanes(a, b));
+    long long a, b, c;
+    while (std::scanf("%15s %lld %lld %lld", what, &a, &b, &c) == 4) {
+        if (std::strcmp(what, "reduce") == 0) {
+            std::printf("%d\n", fxp::reduce_lanes(a, b));
+            continue;
+        }
+        const fxp::WgradCut p = fxp::plan_conv_wgrad(a, b, c);
+        std::printf("%d %d %d %d %lld %lld\n", p.pairs, p.bm, p.tiles_m * p.tiles_n, p.slices, static_cast<long long>(p.per_slice),
+                    static_cast<long long>(p.ws_bytes));
+    }
 }

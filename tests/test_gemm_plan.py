@@ -1,4 +1,4 @@
-"""How sums of slices are cut up (csrc/fxp_gemm_plan.h), on the host."""
+"""How products are cut into slices and sums of slices among lanes (csrc/fxp_gemm_plan.h), on the host."""
 import os
 import shutil
 import subprocess
@@ -25,9 +25,35 @@ def ask(tmp_path_factory):
 @pytest.mark.parametrize("pieces", [1, 1024, 2352, 4096, 16384, 65535, 65536, 1 << 20])
 def test_a_lane_of_a_shared_piece_has_a_round_of_slices(ask, pieces):
     splits = list(range(1, 600))
-    lanes = [l[0] for l in ask([("reduce", pieces, s) for s in splits])]
+    lanes = [l[0] for l in ask([("reduce", pieces, s, 0) for s in splits])]
     for s, l in zip(splits, lanes):
         assert l in (1, 2, 4, 8, 16, 32), (pieces, s, l)
         assert l == 1 or s // l >= 8, (pieces, s, l)               # eight loads in flight, all of them slices
         assert l == 1 or pieces * l // 2 < 65536, (pieces, s, l)   # and only while half as many lanes leave CUs idle
     assert lanes == sorted(lanes) and (lanes[255] == 32 or pieces * 16 >= 65536)
+
+
+SIZES = [1, 16, 49, 784, 6272, 25088, 100352, 133144, 133145, 200704, 802816, 1 << 22]
+
+
+@pytest.mark.parametrize("Cout", [16, 64, 80, 128, 512, 1024])
+def test_weight_gradient_cuts(ask, Cout):
+    """Every pixel in one slice, none longer than an int32 sum holds, slices within their workspace; the chip full where there are
+    pixels enough for it; many slices only where they are no more bytes than stored patches."""
+    cases = [(M, Cout, K) for M in SIZES for K in (16, 64, 144, 576, 1152, 4608)]
+    for (M, _, K), (pairs, bm, tiles, slices, per, ws) in zip(cases, ask([("wgrad",) + c for c in cases])):
+        where = (M, Cout, K, pairs, bm, tiles, slices, per, ws)
+        assert bm == (64 if Cout <= 64 else 128) and tiles == -(-Cout // bm) * -(-K // 128) and not (pairs and bm == 64), where
+        assert per % 128 == 0 and (slices - 1) * per < M <= slices * per, where
+        assert per <= 133120 or M <= 133144, where
+        assert ws == (4 * slices * Cout * K if slices > 1 else 0), where
+        assert slices <= 64 or ws <= M * K, where
+        most = min(M // 512, max(64, min(512, M // (4 * Cout))))
+        assert tiles * slices >= 100 or slices * 1.5 >= min(most, 128 / tiles), where
+
+
+def test_weight_gradient_cuts_of_the_gpu_tests(ask):
+    """What the shapes of tests/test_gpu_conv_wgrad.py are there for: (pairs, slices, steps of a slice)."""
+    cases = {(200704, 16, 16): (0, 224, 7), (99910, 32, 16): (0, 157, 5)}
+    for got, (case, want) in zip(ask([("wgrad",) + c for c in cases]), cases.items()):
+        assert (got[0], got[3], got[4] // 128) == want, (case, got)
