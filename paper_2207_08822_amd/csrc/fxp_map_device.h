@@ -105,7 +105,8 @@ __device__ inline MapCfg make_cfg(int e_max, int bits) {
     return c;
 }
 
-// What this thread sees of the block maxima: loaded before the elements, so that their reduction runs while those are in flight.
+// What this thread sees of the block maxima: loaded before the elements, so that their reduction can run while those are in flight (in
+// k_map_tile; tiles of quads wait for both).
 __device__ inline uint32_t partials_share(const uint32_t* partials, int n_partials) {
     if (partials == nullptr) return 0u;
     uint32_t m = static_cast<int>(threadIdx.x) < n_partials ? partials[threadIdx.x] : 0u;

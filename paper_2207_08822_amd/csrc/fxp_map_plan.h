@@ -84,19 +84,33 @@ inline RowsPlan plan_rows(int64_t rows, int64_t cols, int tr, int64_t windows) {
     return p;
 }
 
-// Tall tiles write long runs of the transposed copy, but a few hundred of them leave CUs with one tile more than others: the
-// height whose tiles fill 256 CUs best, a halving counted as an eighth lost (both copies, us at 128 / 64 / 32 rows: 12608 x
-// 1001 22.4 / 24.0, 25000 x 301 16.1 / 15.1, 6000 x 1001 13.0 at 64 / 15.4, 18912 x 197 9.2 / 9.0); 32 rows below two tiles a CU.
+// Windows of a row: 128 columns, or 125 where rows are not whole quads - the most that meet no more than 32 quads, so that 32 rows are
+// one round of four quads a thread (with 33 every height took a round more for next to nothing, both copies: 12608 x 1001 21.8 -> 19.4
+// us, 6000 x 1001 12.1 -> 11.1, 64 x 50257 10.6 -> 7.5, 1379 x 1001 6.6 -> 5.1).
+inline int64_t rows_windows(int64_t cols) {
+    const int64_t most = cols % 4 == 0 ? kRowsWidth : kRowsWidth - 3;
+    return (cols + most - 1) / most;
+}
+
+// Tall tiles write long runs of the transposed copy, but a few hundred of them leave CUs with one tile more than others, and rounds of
+// 1024 quads that the rows of a window do not fill leave lanes without one: the height and the windows - up to two more than need be -
+// whose tiles fill 256 CUs and their rounds best, a halving counted as an eighth lost (both copies, heights and windows by the CUs alone
+// / so, in us: 12608 x 1001 19.2 / 17.9, 25000 x 301 13.1 / 12.0, 28800 x 150 10.1 / 8.8, 70001 x 17 7.0 / 5.6, 6000 x 1001 11.0 / 12.1;
+// rounding to nearest 28800 x 150 7.3 / 6.7, 9456 x 257 5.2 / 4.7); 32 rows and no window more below two tiles a CU.
 inline RowsPlan plan_rows(int64_t rows, int64_t cols) {
-    const int64_t windows = (cols + kRowsWidth - 1) / kRowsWidth;
+    const int64_t windows = rows_windows(cols);
     RowsPlan best = plan_rows(rows, cols, 32, windows);
+    const int64_t most = windows + (best.blocks < 512 ? 0 : 2);
     double best_score = 0.0, weight = 1.0;
     for (int tr : {128, 64, 32}) {
-        const RowsPlan p = plan_rows(rows, cols, tr, windows);
-        const double score = weight * static_cast<double>(p.blocks) / static_cast<double>((p.blocks + 255) / 256 * 256);
-        if (p.blocks >= 512 && score > best_score) {
-            best = p;
-            best_score = score;
+        for (int64_t w = windows; w <= most && (w == windows || cols >= 16 * w); ++w) {
+            const RowsPlan p = plan_rows(rows, cols, tr, w);
+            const int64_t lanes = (static_cast<int64_t>(tr) * p.quads + 1023) / 1024 * 1024 * ((p.blocks + 255) / 256 * 256);
+            const double score = weight * static_cast<double>(rows * cols / 4) / static_cast<double>(lanes);
+            if (p.blocks >= 512 && score > best_score) {
+                best = p;
+                best_score = score;
+            }
         }
         weight *= 0.87;
     }

@@ -11,7 +11,7 @@ int main() {
     while (std::scanf("%lld %lld %d", &rows, &cols, &tr) == 3) {
         const fxp::RowsPlan p = tr < 0    ? fxp::plan_scan(rows, cols)
                                 : tr == 0 ? fxp::plan_rows(rows, cols)
-                                          : fxp::plan_rows(rows, cols, tr, (cols + fxp::kRowsWidth - 1) / fxp::kRowsWidth);
+                                          : fxp::plan_rows(rows, cols, tr, fxp::rows_windows(cols));
         int exact = 1;
         for (uint32_t id = 0; id < p.tr * p.quads + 4096; ++id) exact &= static_cast<uint32_t>((uint64_t{id} * p.magic) >> 32) == id / p.quads;
         std::printf("%d %u %u %u %lld %d %d %d\n", p.tr, p.windows, p.width, p.quads, static_cast<long long>(p.blocks), exact,

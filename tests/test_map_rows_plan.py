@@ -38,6 +38,21 @@ def test_every_element_has_one_lane(plan, rows):
         assert p["tr"] * cols + 128 < 1 << 30, where                  # four-byte offsets of a tile's elements below 2^32
 
 
+@pytest.mark.parametrize("rows", [40, 64, 1379, 12608, 28800, 1 << 20])
+def test_rounds_are_filled(plan, rows):
+    """No window meets more quads than the lanes of a round have rows for; where there are tiles for every CU, the chosen height and
+    windows leave no more lanes idle than the plainest cut of that height."""
+    cols = list(range(16, 400)) + [1000, 1001, 3071, 3072, 50257]
+    best, plain = (plan([(rows, c, tr) for c in cols]) for tr in (0, 32))
+
+    def busy(p, c):
+        rounds = -(-p["tr"] * p["quads"] // 1024)
+        return rows * c / 4 / (rounds * 1024 * (-(-p["blocks"] // 256) * 256))
+    for c, p, q in zip(cols, best, plain):
+        assert p["quads"] <= 32 and q["quads"] <= 32, (rows, c, p, q)
+        assert q["blocks"] < 512 and p == q or p["blocks"] >= 512 and busy(p, c) >= 0.87 ** 2 * busy(q, c), (rows, c, p, q)
+
+
 def test_small_tensors(plan):
     got = plan([(256, 256, -1), (1, 114688, -1), (7168, 16, -1), (7645, 15, -1), (449, 256, -1), (448, 256, -1), (1, 114689, -1), (0, 16, -1)])
     assert [p["scan"] for p in got] == [1, 0, 1, 0, 0, 1, 0, 0]
