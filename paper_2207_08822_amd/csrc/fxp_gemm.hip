@@ -1353,7 +1353,7 @@ int gemm_nt_batched_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int
 //     kernel (k_gemm_nt: whole 16-byte loads at any byte address), 64 x 64 x 128 tiles below 512 large ones
 //     (small_tiles), else 128 x 128 x 64;
 //   * enough 256 x 256 tiles to fill the chip -> the ring kernel (K % 128 == 0) or the
-//     four-stage 256 x 256 x 64 kernel; otherwise 128 x 128 tiles;
+//     four-stage 256 x 256 x 64 kernel; otherwise 128 x 128 tiles, or 64 x 64 (quarter_tiles);
 //   * output-bound products (below the ridge, wide and large output or a very short contraction) -> 128-row tiles
 //     of 64 or 96 KiB of LDS, so that two workgroups are resident per CU and one stores while the other multiplies;
 //   * long contraction and a small output (the weight gradient) -> split K over grid.y.
@@ -1426,12 +1426,9 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         rc = launch_dma<128, 256, 64, 64, 64, 3>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
     else if (use256)
         rc = launch_dma<256, 256, 64, 64, 128, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
-    // At most 128 large tiles, unsplit: half the CUs or more would have none.  A quarter the size, as for convolutions (the product
-    // alone, 128 x 128 / 64 x 64 tiles: 1024^3 7.9 / 6.0 us, 512 x 768 x 3072 - 96 tiles - 7.6 / 6.6, 300 x 2000 x 1000 15.2 / 8.1; the call
-    // 2000 x 1920 x 960 - 128 tiles - 25.9 / 24.9)
-    else if (splits == 1 && ((M + 127) / 128) * ((N + 127) / 128) <= 128 && K % 128 == 0)
+    else if (splits == 1 && K % 128 == 0 && quarter_tiles(M, N, K))
         rc = launch_dma<64, 64, 128, 32, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, 1, eA, bitsA, eB, bitsB, s, 0, nullptr, one, amax1, ride);
-    else if (splits == 1 && ((M + 127) / 128) * ((N + 127) / 128) <= 128)
+    else if (splits == 1 && quarter_tiles(M, N, K))
         rc = launch_dma<64, 64, 64, 32, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, 1, eA, bitsA, eB, bitsB, s, 0, nullptr, one, amax1, ride);
     else if (K % 128 == 0)
         rc = launch_dma<128, 128, 128, 64, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);

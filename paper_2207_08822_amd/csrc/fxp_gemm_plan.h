@@ -23,6 +23,21 @@ inline int reduce_lanes(int64_t pieces, int64_t splits) {
     return lanes;
 }
 
+// Unsplit direct-to-LDS products of at most 128 large tiles, whatever they are for: half the CUs or more would have none, so tiles a
+// quarter the size (the product alone, 128 x 128 / 64 x 64 tiles in us: 1024^3 7.3 / 5.5, M x N x K 512 x 3072 x 768 - 96 tiles - 7.6 /
+// 6.6, 300 x 1000 x 2000 15.2 / 8.1, 16384 x 16 x 3072 14.9 / 10.9; also where large tiles would be padded by
+// small ones, 1300 x 1400 x 2000 12.8 / 11.5).  Close to two small tiles a CU
+// the gain is small, and it is lost where every row starts off the 64-byte grid and the contraction is long (480 and 512 small tiles:
+// 1024 x 1920 x 2000 11.5 / 11.8, 1024 x 2048 x 2000 11.6 / 12.0, x 1520 9.6 / 9.9 but 1000 x 2000 x 1520 10.0 / 9.6; 448 small tiles
+// 1024 x 1792 x 2000 11.4 / 11.2; at most 128 rows, whose operand all CUs share, 128 x 16384 x 2000 16.4 / 14.9), and in whole steps
+// of 128 along a very long one (128 x 16384 x 4096 17.7 / 17.5, x 5120 21.7 / 22.7, x 8192 31.0 / 32.4, x 12288 43.6 / 46.7).
+inline bool quarter_tiles(int64_t M, int64_t N, int64_t K) {
+    const int64_t large = ((M + 127) / 128) * ((N + 127) / 128), small = ((M + 63) / 64) * ((N + 63) / 64);
+    if (large > 128) return false;
+    if (small <= 448 || small < 4 * large) return true;
+    return K % 128 == 0 ? K <= 4096 : K % 64 == 0 || K <= 1536 || std::min(M, N) <= 128;
+}
+
 // ---- weight gradients of convolutions without stored patches (fxp_conv_wgrad.hip) ----
 constexpr int kWgradStep = 128;                       // pixels of a stage
 struct WgradCut {

@@ -33,6 +33,14 @@ def test_a_lane_of_a_shared_piece_has_a_round_of_slices(ask, pieces):
     assert lanes == sorted(lanes) and (lanes[255] == 32 or pieces * 16 >= 65536)
 
 
+def test_tiles_of_products(ask):
+    """Small tiles where they leave CUs with one each; near two each, not off the 64-byte grid or along very long contractions."""
+    want = {(1024, 1024, 1024): 1, (1024, 2048, 1024): 1, (1024, 2048, 1984): 1, (1024, 2048, 2000): 0, (2048, 1024, 1776): 0, (1000, 2000, 2032): 0,
+            (1024, 1920, 2000): 0, (1024, 1792, 2000): 1, (1024, 2048, 1040): 1, (1300, 1400, 2000): 1, (128, 16384, 2000): 1, (16384, 100, 2032): 1,
+            (128, 16384, 4096): 1, (128, 16384, 5120): 0, (64, 16384, 8192): 1, (100, 16384, 12288): 0, (2048, 2048, 1024): 0, (129, 16384, 512): 0}
+    assert [g[0] for g in ask([("tiles",) + c for c in want])] == list(want.values())
+
+
 SIZES = [1, 16, 49, 784, 6272, 25088, 100352, 133144, 133145, 200704, 802816, 1 << 22]
 
 
