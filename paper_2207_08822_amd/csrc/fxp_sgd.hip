@@ -119,6 +119,13 @@ __device__ inline float axpy_one(uint32_t xb, uint32_t yb, uint32_t wxy, uint32_
 
 __device__ inline uint32_t word_of(const uint4& r, uint32_t k) { return k == 0 ? r.x : k == 1 ? r.y : k == 2 ? r.z : r.w; }
 
+// Which results go out non-temporally (stream_z): the last line's of a step, whose weights nothing in the step reads again and whose
+// place in the caches is better spent on what the lines do (11.7 M parameters 101.6 -> 100.2 us, and 111.3 -> 109.8 with a reduction
+// over the new weights behind it); of a line by itself, whose result the caller is likely to read next, only where x, y and z together
+// are more than the 256 MB Infinity Cache holds (a line and a reduction over its result, ordinary / non-temporal in us: 65536 elements
+// 13.0 / 14.0, 589824 15.6 / 16.5, 20 M 77.9 / 79.8, 25 M 107 / 99, 33.6 M 145 / 130, 67 M 293 / 274).
+constexpr uint64_t kStreamElements = (uint64_t{1} << 28) / 12;
+
 // VEC: x, y, z are 16-byte aligned; a thread owns whole quads of four consecutive elements (16-byte loads and
 // stores, both Philox blocks of the quad used in full) and block 0 finishes the n % 4 tail.  Otherwise one
 // element per thread and iteration.
@@ -127,9 +134,9 @@ template <bool STOCH, bool VEC>
 __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t* x, const uint32_t* y, uint32_t a_bits,
                                                                   uint64_t n, float* z, const uint32_t* __restrict__ px,
                                                                   int npx, const uint32_t* __restrict__ py, int npy,
-                                                                  uint32_t* __restrict__ pz, int32_t* __restrict__ e_out,
-                                                                  uint32_t key0, uint32_t key1, uint64_t step, unsigned bid,
-                                                                  unsigned nblocks, uint32_t* red) {
+                                                                  uint32_t* __restrict__ pz, bool stream_z,
+                                                                  int32_t* __restrict__ e_out, uint32_t key0, uint32_t key1,
+                                                                  uint64_t step, unsigned bid, unsigned nblocks, uint32_t* red) {
     // scales of the two tensors from their block maxima, the scalar's from its own exponent
     uint32_t mx = 0, my = 0;
     for (int i = threadIdx.x; i < npx; i += kAxpyThreads) mx = max(mx, px[i]);
@@ -238,8 +245,7 @@ __device__ __attribute__((always_inline)) inline void axpy16_body(const uint32_t
                         for (int k = 0; k < 4; ++k) zf[k] = axpy_one<STOCH>(xb[k], yb[k], wxy[k], wu[k], ex, ey, a_hat, al, Ex);
                     }
                 }
-                // (the last line's result is not read again in the step: as an ordinary store it took 0.5 us of 27 from the others)
-                if (pz == nullptr) __builtin_nontemporal_store(Float4{zf[0], zf[1], zf[2], zf[3]}, reinterpret_cast<Float4*>(zv + q));
+                if (stream_z) __builtin_nontemporal_store(Float4{zf[0], zf[1], zf[2], zf[3]}, reinterpret_cast<Float4*>(zv + q));
                 else zv[q] = make_float4(zf[0], zf[1], zf[2], zf[3]);
                 // (never NaN: the inverse mapping of integers)
                 fmax = fmaxf(fmaxf(fmax, fmaxf(fabsf(zf[0]), fabsf(zf[1]))), fmaxf(fabsf(zf[2]), fabsf(zf[3])));
@@ -276,10 +282,11 @@ template <bool STOCH, bool VEC>
 __global__ __launch_bounds__(kAxpyThreads) void k_axpy16(const uint32_t* x, const uint32_t* y, uint32_t a_bits, uint64_t n,
                                                          float* z, const uint32_t* __restrict__ px, int npx,
                                                          const uint32_t* __restrict__ py, int npy,
-                                                         uint32_t* __restrict__ pz, int32_t* __restrict__ e_out,
+                                                         uint32_t* __restrict__ pz, int stream_z, int32_t* __restrict__ e_out,
                                                          uint32_t key0, uint32_t key1, uint64_t step) {
     __shared__ uint32_t red[kAxpyThreads / 64];
-    axpy16_body<STOCH, VEC>(x, y, a_bits, n, z, px, npx, py, npy, pz, e_out, key0, key1, step, blockIdx.x, gridDim.x, red);
+    axpy16_body<STOCH, VEC>(x, y, a_bits, n, z, px, npx, py, npy, pz, stream_z != 0, e_out, key0, key1, step, blockIdx.x,
+                             gridDim.x, red);
 }
 
 // ---- many parameter tensors per launch ------------------------------------------------------------------
@@ -343,10 +350,10 @@ __global__ __launch_bounds__(kAxpyThreads) void k_axpy16_multi(const SgdJobs job
     const uint32_t* yb = reinterpret_cast<const uint32_t*>(y);
     uint32_t* pzt = pz ? pz + J.block0 : nullptr;
     if (vec)
-        axpy16_body<STOCH, true>(xb, yb, a_bits, J.n, z, px + J.block0, J.blocks, py + J.block0, J.blocks, pzt, nullptr, key0, key1,
+        axpy16_body<STOCH, true>(xb, yb, a_bits, J.n, z, px + J.block0, J.blocks, py + J.block0, J.blocks, pzt, pz == nullptr, nullptr, key0, key1,
                                  line_step, bid, J.blocks, red);
     else
-        axpy16_body<STOCH, false>(xb, yb, a_bits, J.n, z, px + J.block0, J.blocks, py + J.block0, J.blocks, pzt, nullptr, key0, key1,
+        axpy16_body<STOCH, false>(xb, yb, a_bits, J.n, z, px + J.block0, J.blocks, py + J.block0, J.blocks, pzt, pz == nullptr, nullptr, key0, key1,
                                   line_step, bid, J.blocks, red);
 }
 
@@ -362,7 +369,7 @@ static int axpy_grid(uint64_t n) {
 
 // one line; px / py: block maxima of x / y (npx / npy of them); pz receives axpy_grid(n) block maxima of z
 static int axpy16_launch(const float* x, const float* y, float a, uint64_t n, float* z, const uint32_t* px, int npx,
-                         const uint32_t* py, int npy, uint32_t* pz, int32_t* e_out, uint64_t seed, uint64_t step,
+                         const uint32_t* py, int npy, uint32_t* pz, bool stream_z, int32_t* e_out, uint64_t seed, uint64_t step,
                          int rounding, hipStream_t s) {
     uint32_t a_bits;
     __builtin_memcpy(&a_bits, &a, sizeof a_bits);
@@ -372,7 +379,7 @@ static int axpy16_launch(const float* x, const float* y, float a, uint64_t n, fl
     const uint32_t* xb = reinterpret_cast<const uint32_t*>(x);
     const uint32_t* yb = reinterpret_cast<const uint32_t*>(y);
 #define FXP_AXPY_LAUNCH(STOCH, VEC) \
-    hipLaunchKernelGGL((k_axpy16<STOCH, VEC>), grid, block, 0, s, xb, yb, a_bits, n, z, px, npx, py, npy, pz, e_out, k0, k1, step)
+    hipLaunchKernelGGL((k_axpy16<STOCH, VEC>), grid, block, 0, s, xb, yb, a_bits, n, z, px, npx, py, npy, pz, stream_z ? 1 : 0, e_out, k0, k1, step)
     if (rounding == FXP_ROUND_STOCHASTIC) {
         if (vec) FXP_AXPY_LAUNCH(true, true);
         else FXP_AXPY_LAUNCH(true, false);
@@ -410,7 +417,7 @@ extern "C" int fxp_axpy16(const float* x, const float* y, float a, size_t n, flo
     int npx = 0, npy = 0;
     if ((rc = scale_partials(x, n, px, &npx, s))) return rc;
     if ((rc = scale_partials(y, n, py, &npy, s))) return rc;
-    return axpy16_launch(x, y, a, n, z, px, npx, py, npy, nullptr, e_out, seed, step, rounding, s);
+    return axpy16_launch(x, y, a, n, z, px, npx, py, npy, nullptr, n > kStreamElements, e_out, seed, step, rounding, s);
 }
 
 extern "C" int fxp_sgd16_step(float* w, const float* g, float* v, size_t n, float lr, float momentum, float weight_decay,
@@ -437,7 +444,7 @@ extern "C" int fxp_sgd16_step(float* w, const float* g, float* v, size_t n, floa
     const uint32_t* pg1 = pg;
     int npg1 = npg;
     if (weight_decay != 0.0f) {           // g1 = g + wd * w
-        if ((rc = axpy16_launch(g, w, weight_decay, n, tmp, pg, npg, pw, npw, pt, nullptr, seed, 3 * step, rounding, s)))
+        if ((rc = axpy16_launch(g, w, weight_decay, n, tmp, pg, npg, pw, npw, pt, false, nullptr, seed, 3 * step, rounding, s)))
             return rc;
         g1 = tmp; pg1 = pt; npg1 = npz;
     }
@@ -446,12 +453,12 @@ extern "C" int fxp_sgd16_step(float* w, const float* g, float* v, size_t n, floa
     int npd = npg1;
     if (momentum != 0.0f) {               // v = g1 + momentum * v
         if ((rc = scale_partials(v, n, pv, &npv, s))) return rc;
-        if ((rc = axpy16_launch(g1, v, momentum, n, v, pg1, npg1, pv, npv, pn, nullptr, seed, 3 * step + 1, rounding, s)))
+        if ((rc = axpy16_launch(g1, v, momentum, n, v, pg1, npg1, pv, npv, pn, false, nullptr, seed, 3 * step + 1, rounding, s)))
             return rc;
         d = v; pd = pn; npd = npz;
     }
     // w = w + (-lr) * d
-    return axpy16_launch(w, d, -lr, n, w, pw, npw, pd, npd, nullptr, nullptr, seed, 3 * step + 2, rounding, s);
+    return axpy16_launch(w, d, -lr, n, w, pw, npw, pd, npd, nullptr, true, nullptr, seed, 3 * step + 2, rounding, s);
 }
 
 namespace fxp {

@@ -39,6 +39,16 @@ def test_axpy16(fxp, n, a):
     assert same_bits(host(z), zo)
 
 
+@pytest.mark.parametrize("n", [22369621, 22369623])              # x, y and z of 256 MB together, and beyond: stores that pass the caches
+def test_axpy16_at_the_size_of_the_cache(fxp, n):
+    say("axpy16 in and beyond the cache", n)
+    w, g, _ = tensors(n % 97, n)
+    wd = dev(w)
+    fxp.axpy16(wd, dev(g), -0.1, out=wd, seed=5, step=7)
+    zo, _ = oracle.axpy16(w, g, -0.1, seed=5, step=7)
+    assert int(fxp.scale(wd)[0]) == oracle.scale(zo) and same_bits(host(wd), zo)
+
+
 @pytest.mark.parametrize("rounding", [0, 1])
 def test_axpy16_special_values_in_place_and_unaligned(fxp, rounding):
     say("axpy16 special", rounding)
