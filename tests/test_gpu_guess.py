@@ -111,3 +111,24 @@ def test_guessed_scales_batched_products(fxp):
             assert np.array_equal(host(buf.AqT), sv["Aq"].reshape(batch * M, K).T), (name, step)
             assert np.array_equal(host(buf.dYq), aux["dYq"]), (name, step)
             assert same_bits(Y, Yo) and same_bits(host(dA), dAo) and same_bits(host(dB), dBo), (name, step)
+
+
+@pytest.mark.parametrize("M,K,N", [(66852, 1024, 128), (348300, 192, 64)], ids=["tiles-of-128", "tiles-of-64"])
+def test_guess_with_several_tiles_a_workgroup(fxp, M, K, N):
+    """More tiles than the guessing launch has workgroups (4080): some take a second tile, with what they keep of the first.  Mapped
+    copies and scale byte for byte: guess missing, right, too small and too large, with the largest element in the last tile."""
+    tc = 128 if K % 128 == 0 else 64
+    assert -(-M // (16384 // tc)) * (K // tc) > 4080
+    rng = np.random.default_rng(M)
+    X = rng.standard_normal((M, K)).astype(np.float32)
+    Wd = dev((rng.standard_normal((K, N)) * 0.05).astype(np.float32))
+    buf = fxp.LayerBuffers(M, K, N)
+    for step, (what, factor) in enumerate([("no guess", 1.0), ("right", 1.0), ("too small", 64.0), ("too large", 0.5)]):
+        say("guess, several tiles a workgroup", (M, K, N), what)
+        x = X * np.float32(factor)
+        x[-1, -1] = 7.0 * factor
+        fxp.linear_fwd(dev(x), Wd, buf, 7, step, guess=True)
+        e = oracle.scale(x)
+        assert int(buf.e[0]) == e, what
+        want = oracle.map(x, e, seed=7, stream_id=step << 8)
+        assert np.array_equal(host(buf.Xq), want) and np.array_equal(host(buf.XqT), want.T), what
