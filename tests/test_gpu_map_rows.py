@@ -30,9 +30,11 @@ def tensor(rows, cols, special):
 
 
 # windows of a quad and of its parts, a last window that begins in the tensor's short last quad (1154 = 36 x 32 + 2, 3 x 1025),
-# one to four tiles of rows, remainders of 1, 2, 3 elements, tiles of 64 and 128 rows (the last four)
+# one to eight row blocks of a window side by side and more of them, remainders of 1, 2, 3 elements, tiles of 64 and of 128 rows (the
+# last five)
 SHAPES = [(1, 16), (1, 17), (3, 19), (1, 1154), (3, 1025), (31, 130), (33, 127), (64, 129), (65, 257), (127, 66), (95, 33), (129, 99),
-          (5000, 51), (12001, 197), (33000, 35), (70001, 17)]
+          (250, 99), (5000, 51), (12001, 197), (25200, 149), (33000, 35), (70001, 17),
+          (12608, 1001)]
 
 
 @pytest.mark.parametrize("rows,cols", SHAPES)

@@ -53,6 +53,13 @@ def test_rounds_are_filled(plan, rows):
         assert q["blocks"] < 512 and p == q or p["blocks"] >= 512 and busy(p, c) >= 0.87 ** 2 * busy(q, c), (rows, c, p, q)
 
 
+def test_heights_of_the_gpu_tests(plan):
+    """The heights (and windows) that shapes of tests/test_gpu_map_rows.py are there for."""
+    want = {(5000, 51): (32, 1), (12001, 197): (64, 4), (25200, 149): (64, 3), (33000, 35): (128, 2), (70001, 17): (128, 1), (12608, 1001): (128, 11)}
+    got = plan([(r, c, 0) for r, c in want])
+    assert [(p["tr"], p["windows"]) for p in got] == list(want.values())
+
+
 def test_small_tensors(plan):
     got = plan([(256, 256, -1), (1, 114688, -1), (7168, 16, -1), (7645, 15, -1), (449, 256, -1), (448, 256, -1), (1, 114689, -1), (0, 16, -1)])
     assert [p["scan"] for p in got] == [1, 0, 1, 0, 0, 1, 0, 0]
