@@ -62,6 +62,7 @@ def test_weight_gradient_cuts(ask, Cout):
 
 def test_weight_gradient_cuts_of_the_gpu_tests(ask):
     """What the shapes of tests/test_gpu_conv_wgrad.py are there for: (pairs, slices, steps of a slice)."""
-    cases = {(200704, 16, 16): (0, 224, 7), (99910, 32, 16): (0, 157, 5)}
+    cases = {(784, 1024, 4608): (1, 1, 7), (12544, 512, 2304): (1, 7, 14), (560, 1040, 4752): (1, 1, 5), (200704, 16, 16): (0, 224, 7),
+             (99910, 32, 16): (0, 157, 5)}
     for got, (case, want) in zip(ask([("wgrad",) + c for c in cases]), cases.items()):
         assert (got[0], got[3], got[4] // 128) == want, (case, got)

@@ -1,6 +1,6 @@
 """Weight gradients read straight from the gradient and the image: edges of the tiles (16 to 144 channels, weights around 128),
 pixels below, at and beyond a stage, lines and images passed several times in one stage, padding and stride, one slice and many,
-both tile shapes, more slices than ride (of 64-bit sums too), and the shapes left to stored patches.  Bit for bit against the CPU oracle."""
+both tile shapes, two workgroups a CU with several stages and with slices, more slices than ride (of 64-bit sums too), and the shapes left to stored patches.  Bit for bit against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (300, 2, 2, 16, 16, 2, 2, 1, 1), (7, 5, 3, 64, 128, 3, 3, 1, 2), (2, 17, 19, 112, 144, 3, 3, 2, 0), (3, 30, 29, 80, 64, 5, 4, 3, 2),
     (11, 14, 14, 128, 128, 3, 3, 1, 1), (12, 28, 28, 64, 64, 3, 3, 1, 1), (40, 28, 27, 16, 32, 3, 3, 1, 1), (9, 40, 1, 144, 272, 3, 1, 1, 1),
     (1, 8, 8, 512, 1024, 3, 3, 2, 1), (3, 5, 5, 512, 496, 3, 3, 1, 1), (1, 2, 2, 1024, 1024, 3, 3, 1, 1),
+    (16, 7, 7, 512, 1024, 3, 3, 1, 1), (64, 14, 14, 256, 512, 3, 3, 1, 1), (4, 10, 14, 528, 1040, 3, 3, 1, 1),
     (16, 112, 112, 16, 16, 1, 1, 1, 0), (10, 103, 97, 16, 32, 1, 1, 1, 0),
     (1, 9, 9, 24, 64, 3, 3, 1, 1), (2, 9, 9, 32, 40, 3, 3, 2, 1)])
 def test_weight_gradient(fxp, N, H, W, C, Cout, KH, KW, stride, pad):  # noqa: F811

@@ -36,12 +36,13 @@ def test_linear(fxp, M, K, N, need_dX, offset):  # noqa: F811
     assert not host(room[:offset]).any() and not host(room[offset + K * N:]).any()
 
 
-# stored patches with the sum in a launch of its own, and riding in an implicit input gradient of stride 1 and of stride 2;
-# a 1x1 layer
-@pytest.mark.parametrize("N,H,W,C,Cout,KH,stride,pad", [(3, 212, 212, 16, 16, 3, 1, 1), (3, 211, 212, 20, 64, 3, 1, 1), (2, 519, 520, 32, 64, 3, 2, 1),
-                                                        (43, 56, 56, 64, 64, 1, 1, 0)])
-def test_conv(fxp, N, H, W, C, Cout, KH, stride, pad):  # noqa: F811
-    say("conv, long sums", (N, H, W, C, Cout, KH, stride, pad))
+# the gradient read from the image (C and Cout multiples of 16), of stride 1 and 2, and of a 1x1 layer; stored patches (C = 20 and 36)
+# with the sum riding in an implicit input gradient of stride 1 and of stride 2, launched before one of stored patches, and alone
+@pytest.mark.parametrize("N,H,W,C,Cout,KH,stride,pad,need_dX", [
+    (3, 212, 212, 16, 16, 3, 1, 1, True), (3, 211, 212, 20, 64, 3, 1, 1, True), (2, 519, 520, 32, 64, 3, 2, 1, True), (43, 56, 56, 64, 64, 1, 1, 0, True),
+    (2, 519, 520, 20, 64, 3, 2, 1, True), (3, 211, 212, 36, 24, 3, 1, 1, True), (3, 211, 212, 20, 64, 3, 1, 1, False), (2, 519, 520, 36, 64, 3, 2, 1, False)])
+def test_conv(fxp, N, H, W, C, Cout, KH, stride, pad, need_dX):  # noqa: F811
+    say("conv, long sums", (N, H, W, C, Cout, KH, stride, pad), "dX" if need_dX else "no dX")
     rng = np.random.default_rng(H + C)
     X = np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0).clip(0, 3.9)
     Wt = rng.standard_normal((Cout, KH, KH, C), dtype=np.float32) * np.float32(0.1)
@@ -49,4 +50,4 @@ def test_conv(fxp, N, H, W, C, Cout, KH, stride, pad):  # noqa: F811
     assert N * Ho * Wo > 133144
     dY = rng.uniform(-1e-3, 1e-3, (N, Ho, Wo, Cout)).astype(np.float32)
     X[..., 0], dY[..., 0] = 127 / 32, 127 * 2.0 ** -16
-    check_conv(fxp, X, Wt, dY, stride, pad)
+    check_conv(fxp, X, Wt, dY, stride, pad, need_dX=need_dX)
