@@ -388,8 +388,8 @@ int fxp_clock_probe(uint64_t* out, uint32_t microseconds, void* stream);
  * elapsed microseconds and the tag of the later one (so an interval is the in-stream duration of that launch
  * behind the launch that really precedes it in the step; an FXP_TL_ENTRY interval is the idle time between two
  * calls); *count receives the number of intervals written (at most `capacity`).  Then the events are destroyed.
- * The two gradients of a small layer go out in one launch, FXP_TL_GEMM_GRADS in place of _DW and _DX; a small layer's
- * scales are found in its map launches, and their FXP_TL_SCALE intervals are empty.
+ * The two gradients of a small or medium layer go out in one launch, FXP_TL_GEMM_GRADS in place of _DW and _DX; a small
+ * layer's scales are found in its map launches, and their FXP_TL_SCALE intervals hold no launch, only the gap before it.
  * One timeline per process; not to be begun or ended while layer calls are running in other threads. */
 enum { FXP_TL_ENTRY = 0, FXP_TL_SCALE = 1, FXP_TL_MAP = 2, FXP_TL_GEMM_FWD = 3, FXP_TL_GEMM_DW = 4, FXP_TL_GEMM_DX = 5,
        FXP_TL_REDUCE = 6, FXP_TL_GEMM_GRADS = 7 };

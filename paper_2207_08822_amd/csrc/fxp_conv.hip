@@ -417,6 +417,8 @@ static size_t conv_ws_fwd(const ConvGeo& g) {
            gemm_split_ws_bytes(g.M(), g.Cout, g.K());
 }
 
+// (Room for stored patches whatever the layer: which paths need them depends on the gradients that are asked for and on measured lines,
+// and a caller's workspace outlives both.)
 static size_t conv_ws_bwd(const ConvGeo& g) {
     const size_t dw = round_up(static_cast<size_t>(g.K()) * g.M(), 256) + gemm_split_ws_bytes(g.Cout, g.K(), g.M());
     size_t dx;
@@ -499,10 +501,11 @@ extern "C" int fxp_conv2d_bwd(const float* dY, const fxp_conv_saved* saved, cons
     uint8_t* area = w8 + round_up(kScaleWsBytes, 256);
     const size_t area_bytes = ws_bytes - round_up(kScaleWsBytes, 256);
     const int64_t M = g.M(), K = g.K();
-    // a thin image's weight gradient reads the image itself; any other writes transposed patches first
+    // The weight gradient of a thin image reads that image and the transposed gradient (thin); one of channels in 16-byte pieces reads
+    // image and gradient as they lie (direct, below); any other writes transposed patches first.
     const bool thin = dW && conv_thin_wgrad_fits(taps_of(g), g.KH, g.N, g.Cout, area_bytes);
-    // With transposed patches to write, the block maxima of dY are reduced by that launch (below) and the map of dY
-    // follows it; otherwise the usual pair of launches.
+    // Where the weight gradient is not thin's, the block maxima of dY are reduced by the launch that writes the transposed patches, or
+    // flips the weights alone, and the map of dY follows it; otherwise the usual pair of launches.
     SideScale side;
     if (dW && !thin) {
         side.x = reinterpret_cast<const uint32_t*>(dY);
