@@ -288,13 +288,15 @@ int conv_wgrad_launch(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, const
     return FXP_OK;
 }
 
-// Channels in whole 16-byte pieces, 32-bit pixel numbers and offsets in a slice's images, room for the slices; up to 512 tiles, which
-// is what is resident at once of the two-per-CU kernel: beyond, the larger tiles of the product of stored patches are ahead where
-// there are pixels enough (stored / from the image in us: 576 tiles, 16 x 14 x 14 x 1024 3x3 127 / 146, 64 x 7 x 7 127 / 146, but
-// 16 x 7 x 7 86 / 81; 567, 16 x 14 x 14 x 896 -> 1152 122 / 143; 441, 896 -> 896 119 / 100).  The kernels with one workgroup a CU
-// gain up to there as well, in two rounds (432 tiles, 32 x 14 x 14 x 6144 -> 64 549 / 420; 270, 64 x 14 x 14 x 640 -> 768 239 / 205).
+// Channels in whole 16-byte pieces, 32-bit pixel numbers and offsets in a slice's images, room for the slices, no 1x1 layer of few
+// pixels (one_tap_patches); up to 512 tiles, which is what is resident at once of the two-per-CU kernel: beyond, the larger tiles of the
+// product of stored patches are ahead where there are pixels enough (stored / from the image in us: 576 tiles, 16 x 14 x 14 x 1024
+// 3x3 127 / 146, 64 x 7 x 7 127 / 146, but 16 x 7 x 7 86 / 81; 567, 16 x 14 x 14 x 896 -> 1152 122 / 143; 441, 896 -> 896 119 / 100).
+// The kernels with one workgroup a CU gain up to there as well, in two rounds (432 tiles, 32 x 14 x 14 x 6144 -> 64 549 / 420; 270,
+// 64 x 14 x 14 x 640 -> 768 239 / 205).
 bool conv_wgrad_fits(const ConvTaps& ct, int KH, int64_t M, int64_t Cout, size_t ws_bytes) {
     if (ct.C % 16 != 0 || Cout % 16 != 0 || M >= (int64_t{1} << 30)) return false;
+    if (KH == 1 && ct.KW == 1 && one_tap_patches(M, Cout, ct.C)) return false;
     const WgradCut p = plan_conv_wgrad(M, Cout, static_cast<int64_t>(KH) * ct.KW * ct.C);
     return static_cast<int64_t>(p.tiles_m) * p.tiles_n <= 512 && p.ws_bytes <= ws_bytes &&
            (p.per_slice / (static_cast<int64_t>(ct.Ho) * ct.Wo) + 4) * ct.H * ct.W * ct.C < (int64_t{1} << 31);

@@ -1235,14 +1235,6 @@ static bool small_tiles(int64_t M, int64_t N, int64_t count) {
     return ((M + 127) / 128) * ((N + 127) / 128) * count < 512;
 }
 
-// Products that k_gemm_nt_direct takes: at most one 32 x 32 tile per CU, at most one round of loads per wave.  Measured
-// with a launch behind a launch against the LDS-staged kernels: 197 x 768 x 768 5.1 us for 6.5, 1 x 3072 x 768 4.6 for
-// 6.5, 512 x 512 x 512 5.2 for 5.6; but 197 x 3072 x 768 7.8 for 6.8 and 197 x 768 x 3072 (three rounds) 11.5 for 11.1:
-// every load instruction touches 32 rows.
-static bool direct_fits(int64_t M, int64_t N, int64_t K) {
-    return K >= 16 && K <= 1024 && ((M + 63) / 64) * ((N + 63) / 64) <= 64;
-}
-
 static Product make_product(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda, const int8_t* B, int64_t ldb, void* C,
                             int64_t ldc, const int32_t* eA, int bitsA, const int32_t* eB, int bitsB, uint32_t* amax, int tile) {
     Product p;

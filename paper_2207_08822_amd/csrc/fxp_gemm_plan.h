@@ -38,6 +38,14 @@ inline bool quarter_tiles(int64_t M, int64_t N, int64_t K) {
     return K % 128 == 0 ? K <= 4096 : K % 64 == 0 || K <= 1536 || std::min(M, N) <= 128;
 }
 
+// Products that k_gemm_nt_direct takes: at most one 32 x 32 tile per CU, at most one round of loads per wave.  Measured
+// with a launch behind a launch against the LDS-staged kernels: 197 x 768 x 768 5.1 us for 6.5, 1 x 3072 x 768 4.6 for
+// 6.5, 512 x 512 x 512 5.2 for 5.6; but 197 x 3072 x 768 7.8 for 6.8 and 197 x 768 x 3072 (three rounds) 11.5 for 11.1:
+// every load instruction touches 32 rows.
+inline bool direct_fits(int64_t M, int64_t N, int64_t K) {
+    return K >= 16 && K <= 1024 && ((M + 63) / 64) * ((N + 63) / 64) <= 64;
+}
+
 // ---- weight gradients of convolutions without stored patches (fxp_conv_wgrad.hip) ----
 constexpr int kWgradStep = 128;                       // pixels of a stage
 struct WgradCut {
@@ -80,6 +88,22 @@ inline WgradCut plan_conv_wgrad(int64_t M, int64_t Cout, int64_t K) {
     p.slices = static_cast<int>((M + p.per_slice - 1) / p.per_slice);
     p.ws_bytes = p.slices > 1 ? static_cast<size_t>(p.slices) * ((Cout * K + 3) / 4 * 4) * sizeof(int32_t) : 0;
     return p;
+}
+
+// Weight gradients of 1x1 layers that go through stored patches all the same, which are one transposed copy of the image: some 500 to
+// 1000 pixels are one slice of five to eight stages, one after the other, but one round of loads of k_gemm_nt_direct (backward
+// passes for dW alone, replayed from a graph, stored / from the image in us: 784 pixels 272 -> 400 13.0 / 16.4, 16 -> 32 11.8 / 12.5;
+// 960 pixels 512 -> 512 13.2 / 15.7; 576 pixels 128 -> 256 12.3 / 12.6, 256 -> 64 12.1 / 11.5; 512 pixels 128 -> 256 12.5 / 11.9).  Off
+// the 16-byte grid that product and the map of dY are slower, and outputs of up to 64 channels stay: whole quads are ahead later the
+// more channels there are (700 pixels 16 -> 512 13.2 / 15.3, 128 -> 512 14.7 / 14.5; 900 pixels 128 -> 512 15.3 / 15.5, both gradients
+// 512 -> 400 21.9 / 20.6; 980 pixels 512 -> 128 14.3 / 15.5), other counts with the fewest (961 pixels 16 -> 480 15.2 / 16.7, 512 ->
+// 256 17.3 / 15.7).
+inline bool one_tap_patches(int64_t M, int64_t Cout, int64_t C) {
+    if (!direct_fits(Cout, C, M)) return false;
+    if (M % 16 == 0) return M > (Cout > 64 ? 512 : 640);
+    if (Cout <= 64) return false;
+    if (M % 4 == 0) return M > (C <= 32 ? 512 : C <= 256 ? 768 : 960);
+    return C == 16 && M > 768;
 }
 
 }  // namespace fxp

@@ -1,5 +1,5 @@
 // gemm_plan: for "reduce pieces splits 0" lines on standard input the lanes that share a piece in a sum of slices, for "tiles M N K" lines
-// whether a product takes tiles of 64 x 64, for "wgrad M Cout K" lines the cut of a convolution's weight gradient: pairs, tile rows, tiles, slices, pixels of a slice, bytes of the slices.
+// whether a product takes tiles of 64 x 64, for "patches M Cout C" lines whether a 1x1 layer's weight gradient goes through stored patches, for "wgrad M Cout K" lines the cut of a convolution's weight gradient: pairs, tile rows, tiles, slices, pixels of a slice, bytes of the slices.
 #include <cstdio>
 #include <cstring>
 
@@ -11,6 +11,10 @@ int main() {
     while (std::scanf("%15s %lld %lld %lld", what, &a, &b, &c) == 4) {
         if (std::strcmp(what, "reduce") == 0) {
             std::printf("%d\n", fxp::reduce_lanes(a, b));
+            continue;
+        }
+        if (std::strcmp(what, "patches") == 0) {
+            std::printf("%d\n", fxp::one_tap_patches(a, b, c));
             continue;
         }
         if (std::strcmp(what, "tiles") == 0) {

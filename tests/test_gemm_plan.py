@@ -60,6 +60,15 @@ def test_weight_gradient_cuts(ask, Cout):
         assert tiles * slices >= 100 or slices * 1.5 >= min(most, 128 / tiles), where
 
 
+def test_one_tap_layers_of_few_pixels(ask):
+    """1x1 layers whose weight gradient one round of loads of the direct product beats a slice of five to eight stages."""
+    want = {(784, 400, 272): 1, (784, 32, 16): 1, (960, 32, 64): 1, (1024, 1024, 16): 1, (576, 256, 128): 1, (512, 256, 128): 0, (576, 64, 256): 0,
+            (640, 64, 64): 0, (656, 64, 64): 1, (1040, 128, 128): 0, (784, 800, 384): 0, (980, 256, 64): 1, (980, 256, 272): 1, (940, 256, 272): 0, (980, 64, 64): 0,
+            (756, 256, 64): 0, (588, 128, 32): 1, (980, 128, 512): 1, (900, 400, 512): 0, (961, 512, 256): 0, (961, 480, 16): 1, (675, 480, 16): 0,
+            (392, 192, 16): 0}
+    assert [g[0] for g in ask([("patches",) + c for c in want])] == list(want.values())
+
+
 def test_weight_gradient_cuts_of_the_gpu_tests(ask):
     """What the shapes of tests/test_gpu_conv_wgrad.py are there for: (pairs, slices, steps of a slice)."""
     cases = {(784, 1024, 4608): (1, 1, 7), (12544, 512, 2304): (1, 7, 14), (560, 1040, 4752): (1, 1, 5), (200704, 16, 16): (0, 224, 7),
