@@ -1418,9 +1418,9 @@ int gemm_nt_launch(int64_t M, int64_t N, int64_t K, const int8_t* A, int64_t lda
         rc = launch_dma<128, 256, 64, 64, 64, 3>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
     else if (use256)
         rc = launch_dma<256, 256, 64, 64, 128, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);
-    else if (splits == 1 && K % 128 == 0 && quarter_tiles(M, N, K))
+    else if (splits == 1 && K % 128 == 0 && quarter_tiles(M, N, K, amax != nullptr))
         rc = launch_dma<64, 64, 128, 32, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, 1, eA, bitsA, eB, bitsB, s, 0, nullptr, one, amax1, ride);
-    else if (splits == 1 && quarter_tiles(M, N, K))
+    else if (splits == 1 && quarter_tiles(M, N, K, amax != nullptr))
         rc = launch_dma<64, 64, 64, 32, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, 1, eA, bitsA, eB, bitsB, s, 0, nullptr, one, amax1, ride);
     else if (K % 128 == 0)
         rc = launch_dma<128, 128, 128, 64, 32, 4>(M, N, K, A, lda, B, ldb, dst, dst_ld, first_mode, splits, eA, bitsA, eB, bitsB, s, split_stride, &slices, one, amax1, ride);

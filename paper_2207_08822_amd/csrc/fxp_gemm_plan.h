@@ -31,9 +31,13 @@ inline int reduce_lanes(int64_t pieces, int64_t splits) {
 // 1024 x 1920 x 2000 11.5 / 11.8, 1024 x 2048 x 2000 11.6 / 12.0, x 1520 9.6 / 9.9 but 1000 x 2000 x 1520 10.0 / 9.6; 448 small tiles
 // 1024 x 1792 x 2000 11.4 / 11.2; at most 128 rows, whose operand all CUs share, 128 x 16384 x 2000 16.4 / 14.9), and in whole steps
 // of 128 along a very long one (128 x 16384 x 4096 17.7 / 17.5, x 5120 21.7 / 22.7, x 8192 31.0 / 32.4, x 12288 43.6 / 46.7).
-inline bool quarter_tiles(int64_t M, int64_t N, int64_t K) {
+// Products that publish their largest magnitude do so once a wave, four times as often with small tiles: where many of them come to an
+// end within a short contraction large ones are ahead (that product, large / small in us: 14848 x 128 x 128 6.2 / 6.6, 8000 x 256 x 128
+// 6.3 / 6.8, 256 x 7232 x 256 6.5 / 6.8, 14976 x 128 x 448 7.0 / 7.1; 284 small tiles 9088 x 128 x 256 6.1 / 5.9, 452 of 256 x 7232 x 768
+// 8.4 / 7.9).
+inline bool quarter_tiles(int64_t M, int64_t N, int64_t K, bool absmax) {
     const int64_t large = ((M + 127) / 128) * ((N + 127) / 128), small = ((M + 63) / 64) * ((N + 63) / 64);
-    if (large > 128) return false;
+    if (large > 128 || (absmax && small > 340 && K <= 448)) return false;
     if (small <= 448 || small < 4 * large) return true;
     return K % 128 == 0 ? K <= 4096 : K % 64 == 0 || K <= 1536 || std::min(M, N) <= 128;
 }

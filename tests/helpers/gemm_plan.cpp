@@ -1,5 +1,5 @@
 // gemm_plan: for "reduce pieces splits 0" lines on standard input the lanes that share a piece in a sum of slices, for "tiles M N K" lines
-// whether a product takes tiles of 64 x 64, for "patches M Cout C" lines whether a 1x1 layer's weight gradient goes through stored patches, for "wgrad M Cout K" lines the cut of a convolution's weight gradient: pairs, tile rows, tiles, slices, pixels of a slice, bytes of the slices.
+// whether a product takes tiles of 64 x 64, without and with its largest magnitude, for "patches M Cout C" lines whether a 1x1 layer's weight gradient goes through stored patches, for "wgrad M Cout K" lines the cut of a convolution's weight gradient: pairs, tile rows, tiles, slices, pixels of a slice, bytes of the slices.
 #include <cstdio>
 #include <cstring>
 
@@ -18,7 +18,7 @@ int main() {
             continue;
         }
         if (std::strcmp(what, "tiles") == 0) {
-            std::printf("%d\n", fxp::quarter_tiles(a, b, c));
+            std::printf("%d %d\n", fxp::quarter_tiles(a, b, c, false), fxp::quarter_tiles(a, b, c, true));
             continue;
         }
         const fxp::WgradCut p = fxp::plan_conv_wgrad(a, b, c);

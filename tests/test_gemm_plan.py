@@ -34,11 +34,14 @@ def test_a_lane_of_a_shared_piece_has_a_round_of_slices(ask, pieces):
 
 
 def test_tiles_of_products(ask):
-    """Small tiles where they leave CUs with one each; near two each, not off the 64-byte grid or along very long contractions."""
+    """Small tiles where they leave CUs with one each; near two each, not off the 64-byte grid or along very long contractions,
+    nor many of a short one that publish their largest magnitude."""
     want = {(1024, 1024, 1024): 1, (1024, 2048, 1024): 1, (1024, 2048, 1984): 1, (1024, 2048, 2000): 0, (2048, 1024, 1776): 0, (1000, 2000, 2032): 0,
             (1024, 1920, 2000): 0, (1024, 1792, 2000): 1, (1024, 2048, 1040): 1, (1300, 1400, 2000): 1, (128, 16384, 2000): 1, (16384, 100, 2032): 1,
             (128, 16384, 4096): 1, (128, 16384, 5120): 0, (64, 16384, 8192): 1, (100, 16384, 12288): 0, (2048, 2048, 1024): 0, (129, 16384, 512): 0}
     assert [g[0] for g in ask([("tiles",) + c for c in want])] == list(want.values())
+    short = {(14848, 128, 128): [1, 0], (256, 7232, 256): [1, 0], (9088, 128, 256): [1, 1], (256, 7232, 768): [1, 1], (2048, 2048, 256): [0, 0]}
+    assert ask([("tiles",) + c for c in short]) == list(short.values())
 
 
 SIZES = [1, 16, 49, 784, 6272, 25088, 100352, 133144, 133145, 200704, 802816, 1 << 22]

@@ -414,14 +414,14 @@ def test_layer_with_more_input_features_than_one_int32_sum_holds(fxp):
     assert float(host(buf.Y)[5, 7]) == float(np.float32(-16129.0 * K * 2.0 ** -12))
 
 
-ABSMAX_SHAPES = [(2560, 2560, 256), (4096, 1536, 128), (300, 200, 160), (100, 90, 50), (256, 128, 8192), (17, 5, 7)]
+ABSMAX_SHAPES = [(2560, 2560, 256), (4096, 1536, 128), (1100, 700, 192), (768, 896, 256), (3776, 400, 128), (300, 200, 160), (100, 90, 50), (256, 128, 8192), (17, 5, 7)]
 
 
 @pytest.mark.parametrize("M,N,K", ABSMAX_SHAPES)
 def test_product_leaves_its_absmax_for_the_next_map(fxp, M, N, K):
     """fxp_gemm_unmap_absmax: same output as fxp_gemm_unmap, and the word it raises is the bit pattern of the
     largest |C|, from which fxp_map_absmax takes the scale the reduction pass would have found (every kernel
-    family: 256-tiles, output-streaming tile, 128-tiles, element-wise loader, split along K with and without
+    family: 256-tiles, output-streaming tile, 128-tiles, 64-tiles, element-wise loader, split along K with and without
     workspace)."""
     say("gemm absmax", M, N, K)
     rng = np.random.default_rng(M + N + K)
