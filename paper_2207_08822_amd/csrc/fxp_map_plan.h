@@ -59,7 +59,9 @@ constexpr uint32_t kRowsWidth = 128;                  // most columns of a windo
 // A tensor whose scale every workgroup works out for itself, 64 bytes a clock from L2: small tiles, many of them, but no more
 // workgroups than CUs if it can be, since each CU reads the tensor once per workgroup.  Beyond some 100000 elements that takes longer
 // than a reduction launch (steps of n^3 launched one by one, two launches / scan in us: 256 30 / 21.0, 300 26.8 / 22.2, 330 28.0 / 25.5,
-// 362 29.8 / 31.0, 400 26.4 / 30.8; replayed from a graph: 300 22.0 / 20.7, 320 20.6 / 21.0, 336 20.6 / 21.4).
+// 362 29.8 / 31.0, 400 26.4 / 30.8; replayed from a graph: 300 22.0 / 20.7, 320 20.6 / 21.0, 336 20.6 / 21.4).  A single
+// tensor wanted row-major only loses from 80 K elements on in a graph (133 x 858 6.2 / 6.9) what it gains launched by itself (115 x
+// 968 14.3 / 11.4).
 constexpr int64_t kScanMaxElements = 112 * 1024;
 
 struct RowsPlan {

@@ -8,7 +8,9 @@
 // bytes go to LDS one by one, [column][row] with room for three columns on either side, and leave it as 16-byte pieces along
 // the rows of qT.
 // (18912 x 197, both copies, 18.6 MB read and written: 14.8 us as tiles of 4 x 4 elements, which need five blocks of random
-// words per 16 elements and element-wise loads at their edges.)
+// words per 16 elements and element-wise loads at their edges.  Those were ahead in one place: tall tensors of 64 or 128 columns
+// whose base is off the grid, which they cut into whole tiles with longer runs of qT - 262144 x 64 27.7 / 30.8 us to nearest and
+// 30.5 / 33.0, 65536 x 128 16.7 / 18.0 and 19.5 / 20.3; 96 columns 68.1 / 55.1, 192 59.1 / 55.3.)
 #include <algorithm>
 
 #include "fxp_internal.h"
