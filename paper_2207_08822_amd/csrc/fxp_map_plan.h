@@ -126,15 +126,33 @@ inline int rows_height(const MapPlan& p, int64_t rows, int64_t cols) { return p.
 // Tiles of about 1024 elements, so that a tensor of the limit is 112 of them: 32 rows, and columns to match where there are fewer
 // (scale + map in us, two launches / scan with 32 columns / so: 8 x 12288 6.6 / 9.3 / 6.2, 4 x 16384 6.4 / 7.5 / 5.1, 1 x 32768
 // 6.3 / 8.8 / 4.3).
+inline int scan_width_log2(int64_t rows) { return rows > 16 ? 5 : rows > 8 ? 6 : 7; }
 inline RowsPlan plan_scan(int64_t rows, int64_t cols) {
-    const int64_t width = rows > 16 ? 32 : rows > 8 ? 64 : kRowsWidth;
-    return plan_rows(rows, cols, 32, (cols + width - 1) / width);
+    const int shift = scan_width_log2(rows);
+    return plan_rows(rows, cols, 32, (cols + (1 << shift) - 1) >> shift);
 }
 
 // Whether `blocks` workgroups together, each for the scale of a tensor of at most `elements`, read little enough: what a CU reads is
 // what bounds them (scan of 1 x 114688 by 3584 workgroups 55.8 us, two launches 8.4; 2 x 50257, 1571 workgroups, 29.5 / 9.6; 8 x 12288,
 // 384 workgroups, 9.3 / 6.6).
 inline bool scan_pays(int64_t elements, int64_t blocks) { return (blocks + 255) / 256 * elements <= kScanMaxElements; }
-inline bool scan_takes(int64_t rows, int64_t cols) { return rows > 0 && cols >= 16 && rows <= kScanMaxElements / cols; }
+inline bool scan_takes(int64_t rows, int64_t cols) {
+    return rows > 0 && cols >= 16 && rows <= kScanMaxElements && cols <= kScanMaxElements && rows * cols <= kScanMaxElements;
+}
+
+// One tensor or two in a launch.  (Asked before every call's maps: no division where the widest windows already are one round.)
+struct ScanSize {
+    int64_t rows, cols;
+};
+inline bool scan_fits(ScanSize a, const ScanSize* b) {
+    if (!scan_takes(a.rows, a.cols) || (b && !scan_takes(b->rows, b->cols))) return false;
+    auto at_most = [](const ScanSize& t) {
+        const int shift = scan_width_log2(t.rows);
+        return ((t.rows + 31) >> 5) * ((t.cols + (1 << shift) - 1) >> shift);
+    };
+    if (at_most(a) + (b ? at_most(*b) : 0) <= 256) return true;
+    const int64_t na = a.rows * a.cols, nb = b ? b->rows * b->cols : 0;
+    return scan_pays(na > nb ? na : nb, plan_scan(a.rows, a.cols).blocks + (b ? plan_scan(b->rows, b->cols).blocks : 0));
+}
 
 }  // namespace fxp

@@ -42,7 +42,8 @@ struct RowsJobs {
 // Workgroup bid of `blocks` works on tile number ...: one run of tiles per XCD, so that the lines which neighbouring windows
 // (and, in the transposed copy, neighbouring row blocks) share are met in one L2.  Of up to eight row blocks, whose tiles of one window
 // write lines of the transposed copy between them, these are neighbours; else the windows of a row block (1000 x 50257 75.7 -> 67.3 us,
-// 64 x 50257 7.5 -> 7.2, rounding to nearest 6.0 -> 5.6).
+// 64 x 50257 7.5 -> 7.2, rounding to nearest 6.0 -> 5.6); a small tensor's tiles are all in L2, and the choice between the two took
+// 0.1 us of its launch (256^3 forward pass 9.95 -> 9.84).
 __device__ inline unsigned tile_in_xcd_run(unsigned bid, unsigned blocks) {
     const unsigned per = blocks / 8u, more = blocks % 8u, xcd = bid % 8u, at = bid / 8u;
     return xcd < more ? xcd * (per + 1) + at : more * (per + 1) + (xcd - more) * per + at;
@@ -92,7 +93,7 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     constexpr int U = SCAN ? 1 : 4;               // quads in flight per thread
     constexpr uint32_t kOff = 0xffffffffu;        // offset of a lane without a quad
     const unsigned tile = tile_in_xcd_run(bid, J.blocks), outer = tile / J.inner, inner = tile - outer * J.inner;
-    const unsigned rb = J.down ? inner : outer, cb = J.down ? outer : inner;
+    const unsigned rb = !SCAN && J.down ? inner : outer, cb = !SCAN && J.down ? outer : inner;
     const int64_t r0 = static_cast<int64_t>(rb) * TR;
     const uint32_t c0 = cb * J.width, ucols = static_cast<uint32_t>(J.cols);
     const uint32_t rows_here = static_cast<uint32_t>(min<int64_t>(TR, J.rows - r0));
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(SCAN ? kScanThreads : kMapThreads, SCAN ? 1 : FLAT 
     map_rows_body<STOCH, TR, SCAN>(J, bits, key0, key1, bid, red, stage);
 }
 
-static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat) {
+static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat, bool scan) {
     RowsJob j;
     j.x = reinterpret_cast<const uint32_t*>(t.x);
     j.rows = t.rows;
@@ -232,7 +233,7 @@ static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat) {
     j.quads = p.quads;
     j.magic = p.magic;
     const int64_t high = p.blocks / p.windows;
-    j.down = high <= 8 ? 1 : 0;
+    j.down = !scan && high <= 8 ? 1 : 0;
     j.inner = j.down ? static_cast<uint32_t>(high) : p.windows;
     j.flat = flat ? 1 : 0;
     j.blocks = static_cast<unsigned>(flat ? (t.rows * t.cols + kFlatTileElements * p.tr / 32 - 1) / (kFlatTileElements * p.tr / 32)
@@ -271,7 +272,7 @@ int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int r
     for (int j = 0; j < (b ? 2 : 1); ++j) {
         const MapTensor& t = *ts[j];
         const RowsPlan p = j == larger && !plans[j].flat ? plan_rows(t.rows, t.cols) : plan_rows(t.rows, t.cols, tr, rows_windows(t.cols));
-        jobs.j[j] = make_rows_job(t, p, plans[j].flat);
+        jobs.j[j] = make_rows_job(t, p, plans[j].flat, false);
         blocks += jobs.j[j].blocks;
     }
     if (b && blocks >= (uint64_t{1} << 31)) {
@@ -283,15 +284,14 @@ int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int r
 
 // Scale and map of one tensor or two (b may be null) in one launch: whether they are small enough, and the launch.
 bool scale_map_small_fits(const MapTensor& a, const MapTensor* b) {
-    if (!scan_takes(a.rows, a.cols) || (b && !scan_takes(b->rows, b->cols))) return false;
-    const int64_t elements = std::max(a.rows * a.cols, b ? b->rows * b->cols : 0);
-    return scan_pays(elements, plan_scan(a.rows, a.cols).blocks + (b ? plan_scan(b->rows, b->cols).blocks : 0));
+    const ScanSize sb{b ? b->rows : 0, b ? b->cols : 0};
+    return scan_fits(ScanSize{a.rows, a.cols}, b ? &sb : nullptr);
 }
 
 int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s) {
     RowsJobs jobs{};
-    jobs.j[0] = make_rows_job(a, plan_scan(a.rows, a.cols), false);
-    if (b) jobs.j[1] = make_rows_job(*b, plan_scan(b->rows, b->cols), false);
+    jobs.j[0] = make_rows_job(a, plan_scan(a.rows, a.cols), false, true);
+    if (b) jobs.j[1] = make_rows_job(*b, plan_scan(b->rows, b->cols), false, true);
     return launch_rows(jobs, 32, true, seed, rounding, bits, s);
 }
 

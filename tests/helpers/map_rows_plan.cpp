@@ -15,7 +15,7 @@ int main() {
         int exact = 1;
         for (uint32_t id = 0; id < p.tr * p.quads + 4096; ++id) exact &= static_cast<uint32_t>((uint64_t{id} * p.magic) >> 32) == id / p.quads;
         std::printf("%d %u %u %u %lld %d %d %d\n", p.tr, p.windows, p.width, p.quads, static_cast<long long>(p.blocks), exact,
-                    fxp::scan_takes(rows, cols) && fxp::scan_pays(rows * cols, p.blocks),
+                    fxp::scan_fits({rows, cols}, nullptr),
                     fxp::rows_height(fxp::plan_map(rows, cols, false, false), rows, cols));
     }
 }
