@@ -42,8 +42,7 @@ struct RowsJobs {
 // Workgroup bid of `blocks` works on tile number ...: one run of tiles per XCD, so that the lines which neighbouring windows
 // (and, in the transposed copy, neighbouring row blocks) share are met in one L2.  Of up to eight row blocks, whose tiles of one window
 // write lines of the transposed copy between them, these are neighbours; else the windows of a row block (1000 x 50257 75.7 -> 67.3 us,
-// 64 x 50257 7.5 -> 7.2, rounding to nearest 6.0 -> 5.6); a small tensor's tiles are all in L2, and the choice between the two took
-// 0.1 us of its launch (256^3 forward pass 9.95 -> 9.84).
+// 64 x 50257 7.5 -> 7.2, rounding to nearest 6.0 -> 5.6).
 __device__ inline unsigned tile_in_xcd_run(unsigned bid, unsigned blocks) {
     const unsigned per = blocks / 8u, more = blocks % 8u, xcd = bid % 8u, at = bid / 8u;
     return xcd < more ? xcd * (per + 1) + at : more * (per + 1) + (xcd - more) * per + at;
@@ -93,7 +92,7 @@ __device__ inline void map_rows_body(const RowsJob& J, int bits, uint32_t key0, 
     constexpr int U = SCAN ? 1 : 4;               // quads in flight per thread
     constexpr uint32_t kOff = 0xffffffffu;        // offset of a lane without a quad
     const unsigned tile = tile_in_xcd_run(bid, J.blocks), outer = tile / J.inner, inner = tile - outer * J.inner;
-    const unsigned rb = !SCAN && J.down ? inner : outer, cb = !SCAN && J.down ? outer : inner;
+    const unsigned rb = J.down ? inner : outer, cb = J.down ? outer : inner;
     const int64_t r0 = static_cast<int64_t>(rb) * TR;
     const uint32_t c0 = cb * J.width, ucols = static_cast<uint32_t>(J.cols);
     const uint32_t rows_here = static_cast<uint32_t>(min<int64_t>(TR, J.rows - r0));
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(SCAN ? kScanThreads : kMapThreads, SCAN ? 1 : FLAT 
     map_rows_body<STOCH, TR, SCAN>(J, bits, key0, key1, bid, red, stage);
 }
 
-static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat, bool scan) {
+static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat) {
     RowsJob j;
     j.x = reinterpret_cast<const uint32_t*>(t.x);
     j.rows = t.rows;
@@ -233,7 +232,7 @@ static RowsJob make_rows_job(const MapTensor& t, const RowsPlan& p, bool flat, b
     j.quads = p.quads;
     j.magic = p.magic;
     const int64_t high = p.blocks / p.windows;
-    j.down = !scan && high <= 8 ? 1 : 0;
+    j.down = high <= 8 ? 1 : 0;
     j.inner = j.down ? static_cast<uint32_t>(high) : p.windows;
     j.flat = flat ? 1 : 0;
     j.blocks = static_cast<unsigned>(flat ? (t.rows * t.cols + kFlatTileElements * p.tr / 32 - 1) / (kFlatTileElements * p.tr / 32)
@@ -272,7 +271,7 @@ int map_rows_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int r
     for (int j = 0; j < (b ? 2 : 1); ++j) {
         const MapTensor& t = *ts[j];
         const RowsPlan p = j == larger && !plans[j].flat ? plan_rows(t.rows, t.cols) : plan_rows(t.rows, t.cols, tr, rows_windows(t.cols));
-        jobs.j[j] = make_rows_job(t, p, plans[j].flat, false);
+        jobs.j[j] = make_rows_job(t, p, plans[j].flat);
         blocks += jobs.j[j].blocks;
     }
     if (b && blocks >= (uint64_t{1} << 31)) {
@@ -290,8 +289,8 @@ bool scale_map_small_fits(const MapTensor& a, const MapTensor* b) {
 
 int scale_map_small_launch(const MapTensor& a, const MapTensor* b, uint64_t seed, int rounding, int bits, hipStream_t s) {
     RowsJobs jobs{};
-    jobs.j[0] = make_rows_job(a, plan_scan(a.rows, a.cols), false, true);
-    if (b) jobs.j[1] = make_rows_job(*b, plan_scan(b->rows, b->cols), false, true);
+    jobs.j[0] = make_rows_job(a, plan_scan(a.rows, a.cols), false);
+    if (b) jobs.j[1] = make_rows_job(*b, plan_scan(b->rows, b->cols), false);
     return launch_rows(jobs, 32, true, seed, rounding, bits, s);
 }
 
